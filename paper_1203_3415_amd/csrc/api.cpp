@@ -106,6 +106,19 @@ int32_t init_device_locked(int dev) {
     d.tables.mult[k] = (const uint8_t*)mult;
     d.tables.und_of[k] = (const int16_t*)und;
   }
+  for (int k = 3; k <= 4; ++k) {
+    const SubgraphInverse inv = subgraph_inverse(k);
+    const std::vector<int32_t>* part[3] = {&inv.off, &inv.cls, &inv.coef};
+    const int32_t** dst[3] = {&d.tables.inv[k].off, &d.tables.inv[k].cls, &d.tables.inv[k].coef};
+    for (int i = 0; i < 3; ++i) {
+      void* b = nullptr;
+      const size_t bytes = part[i]->size() * sizeof(int32_t);
+      if (hipMalloc(&b, bytes) != hipSuccess) return MOTIF_ENOMEM;
+      d.owned.push_back(b);
+      if (hipMemcpy(b, part[i]->data(), bytes, hipMemcpyHostToDevice) != hipSuccess) return MOTIF_EDEVICE;
+      *dst[i] = (const int32_t*)b;
+    }
+  }
   // the allocation-free entry point's workspace: this device's copy of the
   // array, and a pinned word block its status is read back into
   void* sp = nullptr;
@@ -429,17 +442,23 @@ int32_t run_census_multi_enqueue(Pipeline& p, const BuildInput& in, int32_t nk, 
   for (int32_t i = 0; i < nk; ++i) profile_mark(ks[i], 0, false, s);
   if (pre_on_side && hipStreamWaitEvent(s, p.ev_pre, 0) != hipSuccess) return device_error();
   uint64_t* acc[3] = {};  // nk <= 3 (checked by the entry point)
-  acc[top] = p.arena.take<uint64_t>((size_t)in.ngraphs * motif_num_classes(ks[top]));
+  for (int32_t i = 0; i < nk; ++i) acc[i] = p.arena.take<uint64_t>((size_t)in.ngraphs * motif_num_classes(ks[i]));
+  // the triangles that k = 4 lists are all that k = 3 needs: one pass for both
+  int32_t i3 = -1, i4 = -1;
+  for (int32_t i = 0; i < nk; ++i) {
+    if (ks[i] == 3) i3 = i;
+    if (ks[i] == 4 && by_copies(4, p.tune.k[4])) i4 = i;
+  }
+  uint64_t* acc3 = i3 >= 0 && i4 >= 0 ? acc[i3] : nullptr;
   // the second stream starts once the largest census has done the clears
   // and small kernels of its set-up (G* and N+ are complete by then)
   bool side_ok = true;
   enqueue_census(p, g, ks[top], acc[top], fork ? nullptr : hists[top], s, true, fork ? p.ev_fork : nullptr,
-                 &side_ok, fork ? &pre : nullptr);
+                 &side_ok, fork ? &pre : nullptr, top == i4 ? acc3 : nullptr);
   if (fork && (!side_ok || hipStreamWaitEvent(p.side, p.ev_fork, 0) != hipSuccess)) return device_error();
   for (int32_t i = 0; i < nk; ++i) {
-    if (i == top) continue;
-    acc[i] = p.arena.take<uint64_t>((size_t)in.ngraphs * motif_num_classes(ks[i]));
-    enqueue_census(p, g, ks[i], acc[i], nullptr, p.side, false);
+    if (i == top || (acc3 && i == i3)) continue;
+    enqueue_census(p, g, ks[i], acc[i], nullptr, p.side, false, nullptr, nullptr, nullptr, i == i4 ? acc3 : nullptr);
   }
   if (!fork) return read_status(p, s);
   // after the smaller sizes: the check then runs beside the largest census

@@ -36,54 +36,13 @@
 // side's sums and are corrected per lighter side.
 #include <hip/hip_runtime.h>
 
+#include "codes.h"
 #include "internal.h"
 #include "scan.h"
 
 namespace motif {
 
 namespace {
-
-// Bit of the arc i -> j (i != j) in the adjacency codes that index the
-// device class tables.  Row-major with the diagonal left out, except for
-// k = 5, where the two arcs between slots 3 and 4 (the members of a pair in
-// the closed forms) are moved to bits 0 and 1 and the rest keep their order
-// above them: a code without that edge and its three variants with it are
-// then four consecutive entries of the 2 MB table, one aligned 8-byte read
-// (lut_quad) instead of two.  (For k = 4 the table sits in LDS, and the same
-// order measured slightly slower.)  The host table keeps row-major order;
-// device_lut_order writes the device copy in this one.
-template <int K>
-__host__ __device__ constexpr int cbit(int i, int j) {
-  const int n = i * (K - 1) + (j < i ? j : j - 1);
-  if (K != 5) return n;
-  const int a = (K - 2) * K, b = (K - 1) * (K - 1) + K - 2;  // row-major bits of (3, 4) and (4, 3)
-  return n == a ? 0 : n == b ? 1 : n < a ? n + 2 : n < b ? n + 1 : n;
-}
-static_assert(cbit<5>(3, 4) == 0 && cbit<5>(4, 3) == 1 && cbit<5>(0, 1) == 2 && cbit<5>(4, 2) == 19 &&
-                  cbit<5>(3, 2) == 16 && cbit<5>(4, 0) == 17,
-              "k = 5 order");
-
-// Code bits of a neighbour placed in slot S whose types towards the anchor
-// vertices 0..K-3 are packed 2 bits each in L (1 = arc anchor->x, 2 = arc
-// x->anchor, 3 = both).
-template <int K, int S>
-__device__ __forceinline__ uint32_t slot_code(uint32_t L) {
-  uint32_t c = 0;
-#pragma unroll
-  for (int i = 0; i < K - 2; ++i) {
-    const uint32_t t = (L >> (2 * i)) & 3u;
-    c |= (t & 1u) ? (1u << cbit<K>(i, S)) : 0u;
-    c |= (t & 2u) ? (1u << cbit<K>(S, i)) : 0u;
-  }
-  return c;
-}
-
-// Code bits of the edge between slot K-2 (x) and slot K-1 (y); t = type of y
-// relative to x.
-template <int K>
-__device__ __forceinline__ uint32_t rel_code(uint32_t t) {
-  return ((t & 1u) ? (1u << cbit<K>(K - 2, K - 1)) : 0u) | ((t & 2u) ? (1u << cbit<K>(K - 1, K - 2)) : 0u);
-}
 
 // k = 5: the classes of code c0 (no edge between slots 3 and 4) and of c0
 // with that edge of each type, in one read; entry r of the word is the class
@@ -94,8 +53,6 @@ __device__ __forceinline__ uint64_t lut_quad(const uint16_t* lut, uint32_t c0) {
 }
 __device__ __forceinline__ uint32_t quad_at(uint64_t q, uint32_t r) { return (uint32_t)(q >> (16u * r)) & 0xFFFFu; }
 
-__device__ __forceinline__ uint32_t flip(uint32_t t) { return ((t & 1u) << 1) | ((t & 2u) >> 1); }
-
 // k = 4: slot of the label pair (a, b), 1 <= a <= b <= 15, among the 120 such
 // pairs (row-major upper triangle).
 constexpr int kPairs4 = 120;
@@ -103,8 +60,6 @@ __device__ __forceinline__ uint32_t pair_slot4(uint32_t a, uint32_t b) {
   const uint32_t a0 = a - 1u;
   return a0 * 15u - (a0 * (a0 - 1u)) / 2u + (b - a);
 }
-
-constexpr int num_classes(int k) { return k == 3 ? 13 : k == 4 ? 199 : 9364; }
 
 constexpr int kMaxHubs = 512;  // rows of the per-core W table in LDS
 constexpr int kMaxBig = 64;          // cores whose W / M tables are built once per call
@@ -146,16 +101,6 @@ __device__ __forceinline__ uint32_t hash_slot(int32_t y) {
   return ((uint32_t)y * 2654435761u) >> (32 - kWaveHashBits);  // Fibonacci hashing
 }
 
-// Ordering point for LDS traffic inside one wave: LDS operations of a wave
-// complete in issue order, so only the compiler has to be kept from moving
-// accesses across it.
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-using u64 = unsigned long long;
 constexpr u64 kMinusOne = ~0ull;
 
 template <int C, int BLOCK>
@@ -227,179 +172,6 @@ __device__ __forceinline__ int32_t find_row(const int32_t* off, int32_t lo, int3
     if (off[mid] <= j) lo = mid; else hi = mid - 1;
   }
   return lo;
-}
-
-// ================================================================== k = 3 ==
-//
-// Anchor = vertex v (Definition "v-Patterns").  Closed form per vertex: the
-// six pair counts n_a n_b, n_a n_c, n_b n_c, C(n_a,2), C(n_b,2), C(n_c,2)
-// (Figure "star").  Edges between two neighbours of v are exactly the
-// triangles at v (Algorithm "alternative"), listed once each as
-// u -> w -> x in rank order: x in N+(u) and in N+(w).  For each corner the
-// pair of the other two corners leaves its open class, and the triangle class
-// gains one occurrence per corner (the division by 3 removes the repetition).
-//
-// One wave per vertex u, vertices handed out in chunks from a device counter
-// so that every wave of the chip stays busy and a heavy vertex delays only
-// its own wave.  The wave counts the types of u's row with ballots (a hub's
-// row is read 64 entries at a time), adds the six closed forms, puts N+(u)
-// into a wave-private LDS hash (vertex -> type), lays the N+ rows of its
-// members end to end over the lanes and looks every entry x up: a hit is a
-// triangle.  A u with more than kTriHash / 2 higher-ranked neighbours
-// binary-searches N+(u) instead of the hash.  Counts go to a per-wave LDS
-// histogram, flushed when the wave's vertex moves to another graph of a batch.
-constexpr int kTriHashBits = 10;
-constexpr int kTriHash = 1 << kTriHashBits;
-
-template <int BLOCK>
-__global__ __launch_bounds__(BLOCK) void k3_kernel(DevGraph G, const uint16_t* __restrict__ lut_g,
-                                                   uint64_t* __restrict__ acc, const int32_t* st,
-                                                   int32_t* __restrict__ queue, int32_t chunk) {
-  constexpr int K = 3, C = 13, NW = BLOCK / 64;
-  __shared__ u64 whist[NW * 16];
-  __shared__ uint16_t lut[64];
-  __shared__ uint32_t th[NW * kTriHash];
-  __shared__ uint16_t tslot[NW * (kTriHash / 2)];  // slot of each key of N+(u), to empty exactly those
-  if (st[kStatus] != 0) return;
-  for (int i = threadIdx.x; i < 64; i += BLOCK) lut[i] = lut_g[i];
-  for (int i = threadIdx.x; i < NW * 16; i += BLOCK) whist[i] = 0;
-  for (int i = threadIdx.x; i < NW * kTriHash; i += BLOCK) th[i] = kEmptySlot;
-  __syncthreads();
-  const int32_t lane = (int32_t)(threadIdx.x & 63u);
-  uint32_t* H = th + (threadIdx.x >> 6) * kTriHash;
-  uint16_t* HS = tslot + (threadIdx.x >> 6) * (kTriHash / 2);
-  u64* hist = whist + (threadIdx.x >> 6) * 16;
-  auto tri = [&](uint32_t tuw, uint32_t tux, uint32_t twx) {
-    const uint32_t full = slot_code<K, 1>(tuw) | slot_code<K, 2>(tux) | rel_code<K>(twx);
-    atomicAdd(&hist[lut[full]], 3ull);
-    atomicAdd(&hist[lut[slot_code<K, 1>(tuw) | slot_code<K, 2>(tux)]], kMinusOne);
-    atomicAdd(&hist[lut[slot_code<K, 1>(flip(tuw)) | slot_code<K, 2>(twx)]], kMinusOne);
-    atomicAdd(&hist[lut[slot_code<K, 1>(flip(tux)) | slot_code<K, 2>(flip(twx))]], kMinusOne);
-  };
-  auto flush = [&](int32_t g) {  // this wave's counts to graph g's accumulator
-    wave_sync();
-    if (g >= 0 && lane < C) {
-      const u64 v = hist[lane];
-      if (v) atomicAdd((u64*)&acc[(int64_t)g * C + lane], v);
-    }
-    if (lane < C) hist[lane] = 0;
-    wave_sync();
-  };
-  const int32_t n = G.n;
-  int32_t cur_g = -1;
-  for (;;) {
-    int32_t v0 = 0;
-    if (lane == 0) v0 = atomicAdd(queue, chunk);
-    v0 = __shfl(v0, 0);
-    if (v0 >= n) break;
-    const int32_t v1 = min(n, v0 + chunk);
-    for (int32_t u = v0; u < v1; ++u) {
-      const int32_t g = G.gid ? G.gid[u] : 0;
-      if (g != cur_g) {
-        flush(cur_g);
-        cur_g = g;
-      }
-      // type counts of u's row: 1 = B, 2 = C, 3 = A
-      const int32_t ra = G.gs_off[u], rb = G.gs_off[u + 1];
-      uint32_t nb = 0, nc = 0, na = 0;
-      for (int32_t j0 = ra; j0 < rb; j0 += 64) {
-        const int32_t j = j0 + lane;
-        const uint32_t t = j < rb ? G.gs_idx[j] >> kTypeShift : 0u;
-        nb += (uint32_t)__popcll(__ballot(t == 1u));
-        nc += (uint32_t)__popcll(__ballot(t == 2u));
-        na += (uint32_t)__popcll(__ballot(t == 3u));
-      }
-      if (lane < 6) {
-        const uint32_t ta = lane < 2 ? 3u : lane == 2 ? 1u : lane == 3 ? 3u : lane == 4 ? 1u : 2u;
-        const uint32_t tb = lane == 0 ? 1u : lane == 1 ? 2u : lane == 2 ? 2u : lane == 3 ? 3u : lane == 4 ? 1u : 2u;
-        const u64 x = lane == 0 ? (u64)na * nb : lane == 1 ? (u64)na * nc : lane == 2 ? (u64)nb * nc
-                    : lane == 3 ? (u64)na * (na - (na > 0)) / 2 : lane == 4 ? (u64)nb * (nb - (nb > 0)) / 2
-                                                                : (u64)nc * (nc - (nc > 0)) / 2;
-        if (x) atomicAdd(&hist[lut[slot_code<K, 1>(ta) | slot_code<K, 2>(tb)]], x);
-      }
-      // triangles u -> w -> x
-      const int32_t ua = G.np_off[u], du = G.np_off[u + 1] - ua;
-      if (du < 2) continue;
-      const bool hashed = du <= kTriHash / 2;
-      if (hashed) {
-        for (int32_t i = lane; i < du; i += 64) {
-          const uint32_t e = G.np_idx[ua + i];
-          uint32_t h = ((e & kIdMask) * 2654435761u) >> (32 - kTriHashBits);
-          const uint32_t ent = ((e & kIdMask) << 2) | (e >> kTypeShift);  // id < 2^30 - 1: never kEmptySlot
-          while (atomicCAS(&H[h], kEmptySlot, ent) != kEmptySlot) h = (h + 1) & (kTriHash - 1);
-          HS[i] = (uint16_t)h;  // du <= kTriHash / 2: i in range
-        }
-        wave_sync();
-      }
-      for (int32_t i0 = 0; i0 < du; i0 += 64) {
-        // lanes take members w of N+(u); their rows are laid end to end
-        const int32_t i = i0 + lane;
-        int32_t len = 0, rb2 = 0;
-        uint32_t tuw = 0;
-        if (i < du) {
-          const uint32_t e = G.np_idx[ua + i];
-          const int32_t w = (int32_t)(e & kIdMask);
-          tuw = e >> kTypeShift;
-          rb2 = G.np_off[w];
-          len = G.np_off[w + 1] - rb2;
-        }
-        int32_t inc = len;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-          const int32_t tt = __shfl_up(inc, d);
-          if (lane >= d) inc += tt;
-        }
-        const int32_t tot = __shfl(inc, 63);
-        const int32_t rs = rb2 - (inc - len);
-        for (int32_t jb = 0; jb < tot; jb += 64 * kUnroll) {
-          uint32_t fs[kUnroll], ts[kUnroll];
-#pragma unroll
-          for (int uu = 0; uu < kUnroll; ++uu) {
-            const int32_t j = jb + uu * 64 + lane;
-            int32_t sl = 0;
-#pragma unroll
-            for (int st2 = 32; st2; st2 >>= 1)
-              if (__shfl(inc, sl + st2 - 1) <= j) sl += st2;
-            ts[uu] = (uint32_t)__shfl((int32_t)tuw, sl);
-            const int32_t srs = __shfl(rs, sl);
-            fs[uu] = j < tot ? G.np_idx[srs + j] : 0u;
-          }
-#pragma unroll
-          for (int uu = 0; uu < kUnroll; ++uu) {
-            if (jb + uu * 64 + lane >= tot) continue;
-            const uint32_t f = fs[uu], x = f & kIdMask;
-            uint32_t tux = 0;
-            if (hashed) {
-              uint32_t h = (x * 2654435761u) >> (32 - kTriHashBits);
-              for (;;) {
-                const uint32_t e = H[h];
-                if (e == kEmptySlot) break;
-                if ((e >> 2) == x) {
-                  tux = e & 3u;
-                  break;
-                }
-                h = (h + 1) & (kTriHash - 1);
-              }
-            } else {
-              int32_t lo = ua, hi = ua + du;
-              while (lo < hi) {
-                const int32_t mid = (lo + hi) >> 1;
-                if ((G.np_idx[mid] & kIdMask) < x) lo = mid + 1; else hi = mid;
-              }
-              if (lo < ua + du && (G.np_idx[lo] & kIdMask) == x) tux = G.np_idx[lo] >> kTypeShift;
-            }
-            if (tux) tri(ts[uu], tux, f >> kTypeShift);
-          }
-        }
-      }
-      if (hashed) {
-        wave_sync();
-        for (int32_t i = lane; i < du; i += 64) H[HS[i]] = kEmptySlot;  // the slots this vertex filled
-        wave_sync();
-      }
-    }
-  }
-  flush(cur_g);
 }
 
 // Closed form over the non-empty neighbour sets of one anchor: pairs within a
@@ -2310,7 +2082,8 @@ size_t pipeline_bytes(int64_t N, int64_t M, int32_t G, bool batch, int k, int nu
                       const Tuning& t) {
   auto al = [](size_t b) { return (b + 255) & ~size_t(255); };
   size_t b = build_bytes(N, M, G, batch);
-  const bool reuse = (k == 4 || k == 5) && t.heavy == 1;
+  const bool reuse = k == 5 && t.heavy == 1;
+  if (by_copies(k, t)) b += count_bytes(N, M, maxn > 0 ? maxn : N, k == 4);
   if (reuse)
     b += al(sizeof(int32_t) * (N + 1)) + al(64 * sizeof(int32_t)) +
          al(sizeof(uint32_t) * kBigRow * (size_t)(maxn > 0 ? maxn : N) * grid_size(t, num_cus));
@@ -2324,7 +2097,7 @@ size_t pipeline_bytes(int64_t N, int64_t M, int32_t G, bool batch, int k, int nu
            al(sizeof(uint32_t) * (size_t)nb * big_label_words(mn)) + al(sizeof(uint32_t) * (size_t)nb * kBigRow * mn) +
            al(sizeof(uint32_t) * 32 * kMaxBig);
   }
-  b += 2 * al(sizeof(uint64_t) * (size_t)G * num_classes(k));  // accumulators (+ output staging)
+  b += 3 * al(sizeof(uint64_t) * (size_t)G * num_classes(k));  // accumulators, the last step, output staging
   b += al(64 * sizeof(int32_t));                               // queue counters
   // labels are indexed within one graph: room for the largest one
   const int32_t ln = (int32_t)(maxn > 0 ? maxn : N);
@@ -2344,13 +2117,13 @@ size_t pipeline_bytes(int64_t N, int64_t M, int32_t G, bool batch, int k, int nu
                      glabels, lw, t.tile)
 
 size_t w_slice_bytes(int k, int64_t maxn, const Tuning& t, int num_cus) {
-  if (!((k == 4 || k == 5) && t.heavy == 1)) return 0;
+  if (!(k == 5 && t.heavy == 1)) return 0;
   return sizeof(uint32_t) * kBigRow * (size_t)(maxn > 0 ? maxn : 1) * (size_t)grid_size(t, num_cus);
 }
 
 BigTables take_big_tables(Pipeline& p, int k, int32_t n, int64_t maxn, const Tuning& t, ZeroBatch& z) {
   BigTables b;
-  const bool reuse = (k == 4 || k == 5) && t.heavy == 1;
+  const bool reuse = k == 5 && t.heavy == 1;
   b.nbig = reuse && n > 0 ? big_slots(maxn) : 0;
   if (b.nbig == 0) return b;
   const int64_t lstride = big_label_words(maxn), wstride = (int64_t)kBigRow * maxn;
@@ -2366,7 +2139,7 @@ BigTables take_big_tables(Pipeline& p, int k, int32_t n, int64_t maxn, const Tun
 }
 
 void enqueue_census(Pipeline& p, const DevGraph& g, int k, uint64_t* acc, uint64_t* out, hipStream_t s,
-                    bool use_wpool, hipEvent_t side_start, bool* side_ok, const BigTables* pre) {
+                    bool use_wpool, hipEvent_t side_start, bool* side_ok, const BigTables* pre, uint64_t* acc3) {
   bool forked = side_start == nullptr;
   auto fork_side = [&] {
     if (forked) return;
@@ -2388,15 +2161,17 @@ void enqueue_census(Pipeline& p, const DevGraph& g, int k, uint64_t* acc, uint64
                    std::min(t.light5, kLight5Max)};
   bool marked = false;  // the profiling events bracket the main census kernel only
   if (g.n > 0) {
-    if (k == 3) {
+    if (by_copies(k, t)) {
+      z.add(acc3, acc3 ? sizeof(uint64_t) * (int64_t)g.ngraphs * num_classes(3) : 0);
       enqueue_zero_batch(z, s);
       fork_side();
       profile_mark(k, 1, true, s);
+      if (acc3) profile_mark(3, 1, true, s);
       marked = true;
-      hipLaunchKernelGGL((k3_kernel<256>), dim3(grid), dim3(256), 0, s, g, T.lut[3], acc, p.status, queue,
-                         std::max(1, t.tile));
+      enqueue_counts(p, g, k == 3 ? acc : acc3, k == 4 ? acc : nullptr, queue, s);
+      if (acc3) profile_mark(3, 1, false, s);
     } else {
-      const bool reuse = t.heavy == 1;
+      const bool reuse = k == 5 && t.heavy == 1;
       // labels are indexed within one graph (Labels::base): room for the largest
       const int32_t ln = g.max_graph_n > 0 ? g.max_graph_n : g.n;
       const int cap = k == 4 ? label_cap_k4(ln) : label_cap_k5(ln);
@@ -2438,10 +2213,7 @@ void enqueue_census(Pipeline& p, const DevGraph& g, int k, uint64_t* acc, uint64
         hipLaunchKernelGGL(k_assign_hubs, dim3(blocks_for(g.n, 256)), dim3(256), 0, s, g.gs_off, g.n, hs, hub_id,
                            nbig, big_id, big_list, p.status);
         const int32_t cmax = cost_cap(g.gs_cap);
-        if (k == 4)
-          enqueue_scan1(sc_cost, cost, UnitCost4{g, cmax, lim.light}, p.status, s);
-        else
-          enqueue_scan1(sc_cost, cost, UnitCost5{g, cmax}, p.status, s);
+        enqueue_scan1(sc_cost, cost, UnitCost5{g, cmax}, p.status, s);
         if (nbig > 0)
           hipLaunchKernelGGL(k_big_labels, dim3(16, nbig), dim3(256), 0, s, g, hs, big_list, lbig, lstride, p.status);
         fork_side();
@@ -2454,15 +2226,7 @@ void enqueue_census(Pipeline& p, const DevGraph& g, int k, uint64_t* acc, uint64
       fork_side();
       profile_mark(k, 1, true, s);
       marked = true;
-      if (k == 4 && reuse) {
-        if (t.block == 512) {
-          if (cap == 8192) LAUNCH_KR(4, 512, 8192); else if (cap == 65536) LAUNCH_KR(4, 512, 65536); else LAUNCH_KR(4, 512, 0);
-        } else if (t.block == 1024) {
-          if (cap == 8192) LAUNCH_KR(4, 1024, 8192); else if (cap == 65536) LAUNCH_KR(4, 1024, 65536); else LAUNCH_KR(4, 1024, 0);
-        } else {
-          if (cap == 8192) LAUNCH_KR(4, 256, 8192); else if (cap == 65536) LAUNCH_KR(4, 256, 65536); else LAUNCH_KR(4, 256, 0);
-        }
-      } else if (k == 4) {
+      if (k == 4) {
         if (t.block == 512) {
           if (cap == 8192) LAUNCH_K4(512, 8192); else if (cap == 65536) LAUNCH_K4(512, 65536); else LAUNCH_K4(512, 0);
         } else if (t.block == 1024) {
@@ -2494,7 +2258,10 @@ void enqueue_census(Pipeline& p, const DevGraph& g, int k, uint64_t* acc, uint64
 
 void enqueue_finalise(Pipeline& p, int k, int32_t ngraphs, const uint64_t* acc, uint64_t* out, hipStream_t s) {
   const int C = num_classes(k);
-  enqueue_divide(acc, dev_tables().mult[k], C, (int64_t)ngraphs * C, out, p.status, s);
+  if (by_copies(k, p.tune.k[k]))
+    enqueue_solve(k, acc, p.arena.take<uint64_t>((size_t)ngraphs * C), out, ngraphs, p.status, s);
+  else
+    enqueue_divide(acc, dev_tables().mult[k], C, (int64_t)ngraphs * C, out, p.status, s);
 }
 
 void enqueue_divide(const uint64_t* acc, const uint8_t* mult, int32_t C, int64_t total, uint64_t* out,

@@ -17,6 +17,7 @@
 #include "classes.h"
 
 #include <algorithm>
+#include <map>
 #include <mutex>
 
 namespace motif {
@@ -166,6 +167,38 @@ const ClassTable* class_table(int k) {
   if (k < 3 || k > 5) return nullptr;
   std::call_once(g_once[k - 3], [k] { g_tables[k - 3] = build(k); });
   return &g_tables[k - 3];
+}
+
+SubgraphInverse subgraph_inverse(int k) {
+  const ClassTable* t = class_table(k);
+  const int C = (int)t->canon.size();
+  std::vector<std::map<int32_t, int32_t>> rows(C);
+  for (int c = 0; c < C; ++c) {
+    const uint32_t x = t->canon[c];
+    uint32_t pair[10];
+    int e = 0;
+    for (int i = 0; i < k; ++i)
+      for (int j = i + 1; j < k; ++j) {
+        const uint32_t bits = x & (1u << code_bit(k, i, j) | 1u << code_bit(k, j, i));
+        if (bits) pair[e++] = bits;
+      }
+    for (uint32_t out = 0; out < 1u << e; ++out) {
+      uint32_t y = x;
+      for (uint32_t r = out; r; r &= r - 1) y &= ~pair[__builtin_ctz(r)];
+      const uint16_t sub = t->lut[y];
+      if (sub != 0xFFFF) rows[sub][c] += __builtin_popcount(out) & 1 ? -1 : 1;
+    }
+  }
+  SubgraphInverse m;
+  m.off.push_back(0);
+  for (int r = 0; r < C; ++r) {
+    for (const auto& kv : rows[r]) {
+      m.cls.push_back(kv.first);
+      m.coef.push_back(kv.second);
+    }
+    m.off.push_back((int32_t)m.cls.size());
+  }
+  return m;
 }
 
 }  // namespace motif

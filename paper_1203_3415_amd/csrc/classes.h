@@ -21,6 +21,16 @@ struct ClassTable {
 // Built once per k and cached (thread-safe).  k in {3,4,5}; nullptr otherwise.
 const ClassTable* class_table(int k);
 
+// Inclusion and exclusion over the edges left out: induced count of class r =
+// sum over its entries of coef * N(cls), N(c) the number of copies of class c
+// as a subgraph (a vertex set with a subset of its edges, types kept).  Row r
+// holds the classes with a spanning subgraph of class r; coef = (-1)^(edges
+// left out) times the number of such subgraphs in one set.
+struct SubgraphInverse {
+  std::vector<int32_t> off, cls, coef;  // rows in CSR form
+};
+SubgraphInverse subgraph_inverse(int k);
+
 // Bit of the arc i -> j in a k-vertex code.
 inline int code_bit(int k, int i, int j) { return i * (k - 1) + (j < i ? j : j - 1); }
 

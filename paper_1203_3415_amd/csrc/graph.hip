@@ -482,15 +482,33 @@ struct EntryFlag {
   }
 };
 
-// gs_off[v] = position of row v's first half-edge in the scanned flags;
-// with deg given, also the row's length.
+// N+ offsets (the scanned flags at the row starts) and the types of every
+// vertex's neighbours: its half-edges are one per one-way neighbour and two
+// per reciprocated one, so their number less d* is the number of reciprocated
+// neighbours, and the out-degree then gives the two one-way numbers.
+__global__ void k_gather_plus(const int32_t* pos, const int32_t* gs_off, const int32_t* hoff, const int32_t* out_off,
+                              int32_t n, int32_t* np_off, uint4* dt, const int32_t* st) {
+  if (st[kStatus] != 0) return;
+  for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v <= n; v += (int64_t)gridDim.x * blockDim.x) {
+    np_off[v] = pos[gs_off[v]];
+    if (v < n) {
+      const uint32_t d = (uint32_t)(gs_off[v + 1] - gs_off[v]);
+      const uint32_t both = (uint32_t)(hoff[v + 1] - hoff[v]) - d;
+      const uint32_t out = (uint32_t)(out_off[v + 1] - out_off[v]) - both;
+      dt[v] = make_uint4(out, d - both - out, both, d);
+    }
+  }
+}
+
+// gs_off[v] = position of row v's first half-edge in the scanned flags, and
+// the row's length.
 __global__ void k_gather_off(const int32_t* pos, const int32_t* hoff, int32_t n, int32_t* gs_off, int32_t* deg,
                              const int32_t* st) {
   if (st[kStatus] != 0) return;
   for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v <= n; v += (int64_t)gridDim.x * blockDim.x) {
     const int32_t a = pos[hoff[v]];
     gs_off[v] = a;
-    if (deg && v < n) deg[v] = pos[hoff[v + 1]] - a;
+    if (v < n) deg[v] = pos[hoff[v + 1]] - a;
   }
 }
 
@@ -525,16 +543,24 @@ struct PlusFlag {
   }
 };
 
+// N+ rows with the row of each entry, and N- rows: entry j of G* has
+// flag_pos[j] entries of N+ before it, so j - flag_pos[j] of N-.
 __global__ void k_write_plus(const uint32_t* gs_idx, const int32_t* flag_pos, const int32_t* gs_row,
-                             const int32_t* deg, const int32_t* gs_off, int32_t n, uint32_t* np_idx,
-                             const int32_t* st) {
+                             const int32_t* deg, const int32_t* gs_off, int32_t n, uint32_t* np_idx, int32_t* np_row,
+                             uint32_t* nm_idx, const int32_t* st) {
   if (st[kStatus] != 0) return;
   const int64_t e = gs_off[n];
   for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < e; j += (int64_t)gridDim.x * blockDim.x) {
     const int32_t v = gs_row[j];
     const uint32_t x = gs_idx[j];
     const int32_t w = (int32_t)(x & kIdMask);
-    if (rank_less(deg[v], v, deg[w], w)) np_idx[flag_pos[j]] = x;
+    const int32_t pos = flag_pos[j];
+    if (rank_less(deg[v], v, deg[w], w)) {
+      np_idx[pos] = x;
+      np_row[pos] = v;
+    } else {
+      nm_idx[j - pos] = x;
+    }
   }
 }
 
@@ -704,12 +730,20 @@ namespace {
 // (bidirected), so the directed census of the result is the census of the
 // undirected version G* with each edge read as a pair of arcs.
 __global__ void k_all_bidirected(const int32_t* gs_off, uint32_t* gs_idx, const int32_t* np_off, uint32_t* np_idx,
-                                 int32_t n, const int32_t* st) {
+                                 uint32_t* nm_idx, uint4* dt, int32_t n, const int32_t* st) {
   if (st[kStatus] != 0) return;
   const int64_t ng = gs_off[n], nn = np_off[n];
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < ng; i += (int64_t)gridDim.x * blockDim.x) {
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x, t0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  for (int64_t i = t0; i < ng; i += stride) {
     gs_idx[i] |= 3u << kTypeShift;
-    if (i < nn) np_idx[i] |= 3u << kTypeShift;
+    if (i < nn) {  // N+ and N- hold every edge once each
+      np_idx[i] |= 3u << kTypeShift;
+      nm_idx[i] |= 3u << kTypeShift;
+    }
+  }
+  for (int64_t v = t0; v < n; v += stride) {
+    const uint32_t d = dt[v].w;
+    dt[v] = make_uint4(0u, 0u, d, d);
   }
 }
 
@@ -741,7 +775,8 @@ __global__ void k_project_undirected(const uint64_t* dir, const int16_t* und_of,
 
 void enqueue_all_bidirected(const DevGraph& g, hipStream_t s, const int32_t* st) {
   hipLaunchKernelGGL(k_all_bidirected, dim3(grid_for(g.gs_cap)), dim3(kB), 0, s, g.gs_off,
-                     const_cast<uint32_t*>(g.gs_idx), g.np_off, const_cast<uint32_t*>(g.np_idx), g.n, st);
+                     const_cast<uint32_t*>(g.gs_idx), g.np_off, const_cast<uint32_t*>(g.np_idx),
+                     const_cast<uint32_t*>(g.nm_idx), const_cast<uint4*>(g.dt), g.n, st);
 }
 
 void enqueue_project_undirected(const uint64_t* dir, const int16_t* und_of, int32_t C, int32_t U, uint64_t* out,
@@ -835,6 +870,13 @@ DevGraph enqueue_build(Pipeline& p, const BuildInput& in, hipStream_t s, hipEven
   const int64_t bm_words = (2 * (int64_t)n + 31) / 32 + 1;
   uint32_t* bitmaps = A.take<uint32_t>(kBigSlots * bm_words);
   uint32_t* marks = A.take<uint32_t>((2 * m + 31) / 32 + 1);
+  // written once the sorts and the merge are done with these regions: N- and
+  // the rows of N+ (m* <= m entries each) in the half-edge keys, the neighbour
+  // types (4 n words) from the sort queues to the end of the bitmaps (2 (n +
+  // 1) + 32 bm_words words and more, bm_words > 2 n / 32)
+  uint32_t* nm_idx = keys;
+  int32_t* np_row = reinterpret_cast<int32_t*>(keys + m);
+  uint4* dt = reinterpret_cast<uint4*>(midq);
   ZeroBatch z;
   z.add(in_cnt, sizeof(int32_t) * (n + 1));
   z.add(fill, sizeof(int32_t) * (n + 1));
@@ -854,6 +896,10 @@ DevGraph enqueue_build(Pipeline& p, const BuildInput& in, hipStream_t s, hipEven
   g.max_graph_n = in.gid ? in.max_graph_n : n;
   g.gs_row = gs_row;
   g.gs_cap = 2 * m + 1;
+  g.np_row = np_row;
+  g.nm_idx = nm_idx;
+  g.dt = dt;
+  g.tmp_n = fill;
   if (n == 0) {
     if (graph_ready) *ready_ok = hipEventRecord(graph_ready, s) == hipSuccess;
     return g;
@@ -899,9 +945,10 @@ DevGraph enqueue_build(Pipeline& p, const BuildInput& in, hipStream_t s, hipEven
                      gs_row, st);
   // oriented rows N+: flags over the G* entries (at most 2m of them), scanned
   enqueue_scan1(sc_plus, flags, PlusFlag{gs_idx, gs_row, deg, gs_off, n}, st, s);
-  hipLaunchKernelGGL(k_gather_off, dim3(grid_for(n + 1)), dim3(kB), 0, s, flags, gs_off, n, np_off, nullptr, st);
+  hipLaunchKernelGGL(k_gather_plus, dim3(grid_for(n + 1)), dim3(kB), 0, s, flags, gs_off, hoff, in.out_off, n, np_off,
+                     dt, st);
   hipLaunchKernelGGL(k_write_plus, dim3(grid_for(2 * m)), dim3(kB), 0, s, gs_idx, flags, gs_row, deg, gs_off, n,
-                     np_idx, st);
+                     np_idx, np_row, nm_idx, st);
   // G* and N+ are complete here; the in-CSR check below only compares
   if (graph_ready) *ready_ok = hipEventRecord(graph_ready, s) == hipSuccess;
   InCheck c{in_cnt, marks, from_in};

@@ -45,11 +45,24 @@ struct DevGraph {
   int32_t ngraphs = 1;
   int32_t max_graph_n = 0;          // largest vertex count of one graph
   const int32_t* gs_row = nullptr;  // [2m*] row (vertex) of each G* entry
+  const int32_t* np_row = nullptr;  // [m*] row of each N+ entry
+  const uint32_t* nm_idx = nullptr; // [m*] N-(v): neighbours of lower rank, row v at gs_off[v] - np_off[v]
+  const uint4* dt = nullptr;        // [n] neighbours of type 1, 2 and 3, and d*
+  int32_t* tmp_n = nullptr;         // [n+1] scratch, free once the graph is built
   int64_t gs_cap = 0;               // 2m + 1 >= entries of G* + 1
+};
+
+// Rows of the matrix that takes subgraph-copy counts to induced counts
+// (subgraph_inverse in classes.h), in CSR form on the device.
+struct SubInverse {
+  const int32_t* off = nullptr;   // [C + 1]
+  const int32_t* cls = nullptr;
+  const int32_t* coef = nullptr;
 };
 
 // Device class tables uploaded by motif_init.
 struct DevTables {
+  SubInverse inv[6];
   const uint16_t* lut[6] = {};   // index k
   const uint8_t* mult[6] = {};
   const int16_t* und_of[6] = {};  // undirected class of each directed class, -1 if an arc is one-way
@@ -203,11 +216,25 @@ BigTables take_big_tables(Pipeline& p, int k, int32_t n, int64_t maxn, const Tun
 // on a second stream that waits for it then runs beside the rest of this
 // census instead of crowding those steps.  pre (optional): big-core tables
 // taken before the build and already cleared in stream order.
+// acc3 (optional, k = 4 by copies): the k = 3 totals of the same graph are
+// accumulated there as well (zeroed here).
 void enqueue_census(Pipeline& p, const DevGraph& g, int k, uint64_t* acc, uint64_t* out, hipStream_t s,
                     bool use_wpool, hipEvent_t side_start = nullptr, bool* side_ok = nullptr,
-                    const BigTables* pre = nullptr);
-// The exact division alone: out[i] = acc[i] / multiplicity, after a check
-// that every remainder is zero (Fact "correction").
+                    const BigTables* pre = nullptr, uint64_t* acc3 = nullptr);
+// The k = 3, 4 censuses by subgraph copies (counts.hip): copies of every class
+// into a3[ngraphs * 13] and / or a4[ngraphs * 199] (null: not wanted; both and
+// the 64 queue words zeroed by the caller), then the induced counts into out
+// through tmp (same size), written only if none is negative.
+size_t count_bytes(int64_t n, int64_t m, int64_t maxn, bool k4);
+void enqueue_counts(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_t* a4, int32_t* queue, hipStream_t s);
+void enqueue_solve(int k, const uint64_t* acc, uint64_t* tmp, uint64_t* out, int64_t ngraphs, int32_t* status,
+                   hipStream_t s);
+// Whether k's census under tuning t counts subgraph copies.
+inline bool by_copies(int k, const Tuning& t) { return k == 3 || (k == 4 && t.heavy == 1); }
+
+// The last step alone: subgraph copies to induced counts, or (per-anchor
+// totals) out[i] = acc[i] / multiplicity, after a check that every remainder
+// is zero (Fact "correction").
 void enqueue_finalise(Pipeline& p, int k, int32_t ngraphs, const uint64_t* acc, uint64_t* out, hipStream_t s);
 // The same for any table: out[i] = acc[i] / mult[i % C], i < total.
 void enqueue_divide(const uint64_t* acc, const uint8_t* mult, int32_t C, int64_t total, uint64_t* out,
