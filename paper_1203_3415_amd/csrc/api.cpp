@@ -379,7 +379,7 @@ int32_t run_census_on(Pipeline& p, const BuildInput& in, int32_t k, uint64_t* hi
     profile_mark(k, 0, true, s);
     DevGraph g = enqueue_build(p, in, s);
     profile_mark(k, 0, false, s);
-    uint64_t* acc = p.arena.take<uint64_t>((size_t)in.ngraphs * C);
+    uint64_t* acc = p.arena.take<uint64_t>(acc_words(k, in.ngraphs, p.tune.k[k]));
     enqueue_census(p, g, k, acc, hist, s, true);
   } catch (const WorkspaceError&) {
     return drain_after_error(p, s);
@@ -442,7 +442,7 @@ int32_t run_census_multi_enqueue(Pipeline& p, const BuildInput& in, int32_t nk, 
   for (int32_t i = 0; i < nk; ++i) profile_mark(ks[i], 0, false, s);
   if (pre_on_side && hipStreamWaitEvent(s, p.ev_pre, 0) != hipSuccess) return device_error();
   uint64_t* acc[3] = {};  // nk <= 3 (checked by the entry point)
-  for (int32_t i = 0; i < nk; ++i) acc[i] = p.arena.take<uint64_t>((size_t)in.ngraphs * motif_num_classes(ks[i]));
+  for (int32_t i = 0; i < nk; ++i) acc[i] = p.arena.take<uint64_t>(acc_words(ks[i], in.ngraphs, p.tune.k[ks[i]]));
   // the triangles that k = 4 lists are all that k = 3 needs: one pass for both
   int32_t i3 = -1, i4 = -1;
   for (int32_t i = 0; i < nk; ++i) {
@@ -530,7 +530,7 @@ int32_t census_batch_with(const motif_graph_t* graphs, int32_t count, int32_t k,
     }
     DevGraph g = enqueue_build(*p, in, s);
     profile_mark(k, 0, false, s);
-    uint64_t* acc = p->arena.take<uint64_t>((size_t)count * C);
+    uint64_t* acc = p->arena.take<uint64_t>(acc_words(k, count, p->tune.k[k]));
     enqueue_census(*p, g, k, acc, hists, s, true);
   } catch (const WorkspaceError&) {
     return drain_after_error(*p, s);
@@ -834,7 +834,7 @@ int32_t motif_census_async(const int32_t* out_off, const int32_t* out_idx, const
       profile_mark(k, 0, true, s);
       DevGraph g = enqueue_build(*p, in, s);
       profile_mark(k, 0, false, s);
-      uint64_t* acc = p->arena.take<uint64_t>((size_t)motif_num_classes(k));
+      uint64_t* acc = p->arena.take<uint64_t>(acc_words(k, 1, p->tune.k[k]));
       enqueue_census(*p, g, k, acc, hist, s, true);
     }
     enqueue_status_out(status, p->status, s);
@@ -935,7 +935,7 @@ int32_t motif_census_undirected(const int32_t* out_off, const int32_t* out_idx, 
     DevGraph g = enqueue_build(*p, in, s);
     enqueue_all_bidirected(g, s, p->status);
     profile_mark(k, 0, false, s);
-    uint64_t* acc = p->arena.take<uint64_t>((size_t)C);
+    uint64_t* acc = p->arena.take<uint64_t>(acc_words(k, 1, p->tune.k[k]));
     uint64_t* dir = p->arena.take<uint64_t>((size_t)C);
     enqueue_census(*p, g, k, acc, dir, s, true);
     enqueue_project_undirected(dir, dev_tables().und_of[k], C, U, hist, p->status, s);
@@ -1315,7 +1315,7 @@ bool enqueue_plan(motif_batch_plan* b) {
     enqueue_zero(b->p.status, sizeof(int32_t) * kStatusWords, b->stream);
     BuildInput in = enqueue_pack(b->p, b->graphs, b->count, b->voff, b->aoff, b->stream);
     DevGraph g = enqueue_build(b->p, in, b->stream);
-    uint64_t* acc = b->p.arena.take<uint64_t>((size_t)b->count * C);
+    uint64_t* acc = b->p.arena.take<uint64_t>(acc_words(b->k, b->count, b->p.tune.k[b->k]));
     enqueue_census(b->p, g, b->k, acc, b->hists, b->stream, false);
     return !in.copy_error;
   } catch (const WorkspaceError&) {

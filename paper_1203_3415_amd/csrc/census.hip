@@ -2097,13 +2097,14 @@ size_t pipeline_bytes(int64_t N, int64_t M, int32_t G, bool batch, int k, int nu
            al(sizeof(uint32_t) * (size_t)nb * big_label_words(mn)) + al(sizeof(uint32_t) * (size_t)nb * kBigRow * mn) +
            al(sizeof(uint32_t) * 32 * kMaxBig);
   }
-  b += 3 * al(sizeof(uint64_t) * (size_t)G * num_classes(k));  // accumulators, the last step, output staging
+  b += al(sizeof(uint64_t) * acc_words(k, G, t)) +             // accumulators, the last step, output staging
+       2 * al(sizeof(uint64_t) * (size_t)G * num_classes(k));
   b += al(64 * sizeof(int32_t));                               // queue counters
   // labels are indexed within one graph: room for the largest one
   const int32_t ln = (int32_t)(maxn > 0 ? maxn : N);
   const int cap = k == 4 ? label_cap_k4(ln) : k == 5 ? label_cap_k5(ln) : 1;
   if (cap == 0) b += al(sizeof(uint32_t) * (size_t)label_words(k, ln) * grid_size(t, num_cus));
-  return b + 4096;
+  return b + 2048;
 }
 
 #define LAUNCH_K4(BLOCK, CAP)                                                                                   \
@@ -2152,7 +2153,7 @@ void enqueue_census(Pipeline& p, const DevGraph& g, int k, uint64_t* acc, uint64
   // every region the set-up needs cleared goes into one batch, launched
   // before the first kernel that reads any of them
   ZeroBatch z;
-  z.add(acc, sizeof(uint64_t) * total);
+  z.add(acc, sizeof(uint64_t) * acc_words(k, g.ngraphs, p.tune.k[k]));
   int32_t* queue = p.arena.take<int32_t>(64);
   z.add(queue, 64 * sizeof(int32_t));
   const Tuning& t = p.tune.k[k];
@@ -2162,7 +2163,7 @@ void enqueue_census(Pipeline& p, const DevGraph& g, int k, uint64_t* acc, uint64
   bool marked = false;  // the profiling events bracket the main census kernel only
   if (g.n > 0) {
     if (by_copies(k, t)) {
-      z.add(acc3, acc3 ? sizeof(uint64_t) * (int64_t)g.ngraphs * num_classes(3) : 0);
+      z.add(acc3, acc3 ? sizeof(uint64_t) * acc_words(3, g.ngraphs, t) : 0);
       enqueue_zero_batch(z, s);
       fork_side();
       profile_mark(k, 1, true, s);

@@ -26,6 +26,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "codes.h"
 #include "internal.h"
@@ -35,20 +36,31 @@ namespace motif {
 namespace {
 
 constexpr uint32_t kNone = 0xFFFFFFFFu;
-constexpr u64 kNeg = ~0ull;
 
-// Counters in the zeroed queue words of a census (64 int32).
-enum QueueSlot : int { kQTri = 0, kQTriBig = 1, kQWedge = 2, kQWedgeMid = 3, kQWedgeTop = 4, kQEdges = 6,
-                       kNTriBig = 8, kNWedgeMid = 9, kNWedgeTop = 10 };
-
-// Chunks of vertices handed out in batches: a workgroup works on one graph at
-// a time, so that its LDS counters can be added to that graph's totals.
-constexpr int kBatchChunk = 256;
+// Lists of vertices by the work they bring, counted in the zeroed queue words
+// of a census (64 int32).  Units are dealt out by position, not pulled from a
+// counter: a pull is an atomic on one address, about 25 ns each however many
+// waves wait for it, which was most of these kernels' time on 10^4 vertices.
+enum ListId : int { kTri16 = 0, kTri64 = 1, kTriBig = 2, kWedge16 = 3, kWedge64 = 4, kWedge256 = 5, kWedgeTop = 6,
+                    kLists = 7 };
+struct Lists {
+  int32_t* v[kLists];
+};
+constexpr int kCap16 = 96, kCap64 = 384, kCap256 = 3072;  // visits of a vertex in the three wedge hashes
 
 __device__ __forceinline__ uint32_t hash_mul(uint32_t x, int bits) { return (x * 2654435761u) >> (32 - bits); }
 
 __device__ __forceinline__ void gadd(uint64_t* a, u64 v) {
   if (v) atomicAdd(reinterpret_cast<u64*>(a), v);
+}
+
+// The totals of graph g that this workgroup adds to.  A single graph has R
+// copies of its totals, summed by k_solve_one: additions to one address (and
+// one 128-byte line) queue up, and a thousand workgroups ending together on
+// the same 199 counters took longer than their counting.
+template <int C, int R>
+__device__ __forceinline__ uint64_t* totals(const DevGraph& G, uint64_t* a, int32_t g) {
+  return a + (int64_t)(G.gid ? g : (int32_t)blockIdx.x & (R - 1)) * C;
 }
 
 __device__ __forceinline__ uint32_t typ(const uint4& d, uint32_t t) { return t == 1u ? d.x : t == 2u ? d.y : d.z; }
@@ -62,38 +74,39 @@ __device__ __forceinline__ uint32_t typ(const uint4& d, uint32_t t) { return t =
 // q], p, q the types of the third vertex seen from the lower and the higher
 // end, less one) and one bit per type in a 64 x 64 adjacency of N+(x), from
 // which the K4s above x are read off as the common bits of two rows.
-// One wave per x with at most kTriD higher neighbours (sixteen lanes per row);
-// the others go to k_tri_big.
-constexpr int kTriD = 64;
-constexpr int kTriHB = 8;
-constexpr int kTriH = 1 << kTriHB;
+// Sixteen lanes per x with at most 16 higher neighbours (four x per wave: the
+// chain of loads before the first row is the bulk of a small x), one wave up
+// to 64 (k_tri), one workgroup beyond (k_tri_big).
 
-// Workgroup counters of the triangle kernels and their flush to one graph.
+// Workgroup counters of the triangle kernels and their flush to one graph: by
+// class in LDS first, so that a workgroup makes one global addition per class.
 template <bool K4>
 struct TriBins {
   u64* tri;   // [27] typed triangles (xy, xz, yz)
   u64* paw;   // [27][3 corners][3 types] sums of the corner's typed degree
-  u64* kh;    // [199] K4 classes
+  u64* kh;    // [199] classes (K4s while counting)
+  u64* h3;    // [13] k = 3 classes, zero outside flush
   __device__ __forceinline__ void clear(int t, int nt) const {
     for (int i = t; i < 27; i += nt) tri[i] = 0;
+    for (int i = t; i < 13; i += nt) h3[i] = 0;
     if constexpr (K4) {
       for (int i = t; i < 243; i += nt) paw[i] = 0;
       for (int i = t; i < 199; i += nt) kh[i] = 0;
     }
   }
-  // Adds everything to graph g's totals and clears (between barriers).
-  __device__ __forceinline__ void flush(int32_t g, const uint16_t* lut3, const uint16_t* lut4, uint64_t* a3,
-                                        uint64_t* a4, int t, int nt) const {
+  // Adds everything to one graph's totals and clears (every thread; the
+  // counters are settled before and usable after).
+  __device__ __forceinline__ void flush(const uint16_t* lut3, const uint16_t* lut4, uint64_t* a3, uint64_t* a4, int t,
+                                        int nt) const {
     for (int i = t; i < 27; i += nt) {
       const u64 c = tri[i];
       if (!c) continue;
       const uint32_t xy = (uint32_t)i / 9 + 1, xz = ((uint32_t)i / 3) % 3 + 1, yz = (uint32_t)i % 3 + 1;
-      if (a3) gadd(&a3[(int64_t)g * 13 + lut3[edge_code<3>(0, 1, xy) | edge_code<3>(0, 2, xz) | edge_code<3>(1, 2, yz)]], c);
+      atomicAdd(&h3[lut3[edge_code<3>(0, 1, xy) | edge_code<3>(0, 2, xz) | edge_code<3>(1, 2, yz)]], c);
       if constexpr (K4) {
         // the paths of three edges whose ends are one vertex
-        uint64_t* a = a4 + (int64_t)g * 199;
         auto p4 = [&](uint32_t mid, uint32_t p, uint32_t q) {
-          gadd(&a[lut4[edge_code<4>(0, 1, mid) | edge_code<4>(0, 2, p) | edge_code<4>(1, 3, q)]], 0 - c);
+          atomicAdd(&kh[lut4[edge_code<4>(0, 1, mid) | edge_code<4>(0, 2, p) | edge_code<4>(1, 3, q)]], 0 - c);
         };
         p4(xy, xz, yz);
         p4(xz, xy, flip(yz));
@@ -101,7 +114,6 @@ struct TriBins {
       }
     }
     if constexpr (K4) {
-      uint64_t* a = a4 + (int64_t)g * 199;
       for (int i = t; i < 243; i += nt) {
         const int tau = i / 9, corner = (i / 3) % 3;
         const u64 c = tri[tau];
@@ -112,11 +124,18 @@ struct TriBins {
         const uint32_t t1 = corner == 0 ? xy : corner == 1 ? flip(xy) : flip(xz);
         const uint32_t t2 = corner == 0 ? xz : corner == 1 ? yz : flip(yz);
         const u64 w = paw[i] - c * (u64)((t1 == s) + (t2 == s));
-        gadd(&a[lut4[edge_code<4>(0, 1, xy) | edge_code<4>(0, 2, xz) | edge_code<4>(1, 2, yz) |
-                     edge_code<4>(corner, 3, s)]], w);
+        atomicAdd(&kh[lut4[edge_code<4>(0, 1, xy) | edge_code<4>(0, 2, xz) | edge_code<4>(1, 2, yz) |
+                           edge_code<4>(corner, 3, s)]], w);
       }
-      for (int i = t; i < 199; i += nt) gadd(&a[i], kh[i]);
     }
+    __syncthreads();
+    if (a3)
+      for (int i = t; i < 13; i += nt) gadd(&a3[i], h3[i]);
+    if constexpr (K4)
+      for (int i = t; i < 199; i += nt) gadd(&a4[i], kh[i]);
+    __syncthreads();
+    clear(t, nt);
+    __syncthreads();
   }
 };
 
@@ -133,87 +152,182 @@ __device__ __forceinline__ void tri_add(const TriBins<K4>& b, uint32_t tau, cons
   }
 }
 
+// body(i, p[i]) for i = r, r + step, r + 2 step, r + 3 step below m, the four
+// loads issued together.
+template <class F>
+__device__ __forceinline__ void each4(const uint32_t* p, int32_t r, int32_t step, int32_t m, F&& body) {
+  uint32_t f[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) f[k] = p[min(r + k * step, m - 1)];
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    if (r + k * step < m) body(r + k * step, f[k]);
+}
+
+// Calls one(v) for the listed vertices, `groups` of them at a time per
+// workgroup (this thread's group: `my`), and flush(g) with every thread of the
+// workgroup, between barriers, when all of a graph's vertices that this
+// workgroup takes are done and at the end.  A single graph's list is dealt out
+// entry by entry; a batch's in one segment per workgroup, cut into runs of one
+// graph, so that a flush comes once per graph and segment or so.
+template <int NT, class One, class Flush>
+__device__ __forceinline__ void for_listed(const DevGraph& G, const int32_t* list, int32_t count, int groups, int my,
+                                           One&& one, Flush&& flush) {
+  if (!G.gid) {
+    for (int32_t i = (int32_t)blockIdx.x * groups + my; i < count; i += (int32_t)gridDim.x * groups) one(list[i]);
+    __syncthreads();
+    flush(0);
+    return;
+  }
+  __shared__ int32_t sh_run;
+  const int32_t s1 = (int32_t)((int64_t)count * (blockIdx.x + 1) / gridDim.x);
+  int32_t cur = -1;
+  for (int32_t s0 = (int32_t)((int64_t)count * blockIdx.x / gridDim.x); s0 < s1;) {
+    const int32_t g = G.gid[list[s0]];
+    __syncthreads();
+    if (threadIdx.x == 0) sh_run = NT;
+    __syncthreads();
+    const int32_t i = s0 + (int32_t)threadIdx.x;
+    if (i >= s1 || G.gid[list[i]] != g) atomicMin(&sh_run, (int32_t)threadIdx.x);
+    __syncthreads();
+    const int32_t e = s0 + sh_run;  // at least one entry
+    if (g != cur) {
+      if (cur >= 0) flush(cur);
+      __syncthreads();
+      cur = g;
+    }
+    for (int32_t k = s0 + my; k < e; k += groups) one(list[k]);
+    s0 = e;
+  }
+  __syncthreads();
+  if (cur >= 0) flush(cur);
+}
+
+// Sorts the vertices into the lists: higher neighbours for the triangles,
+// lower neighbours and visits for the wedges (k = 4).  Eight lanes per vertex;
+// one counter update per list and workgroup.
+constexpr int kClassify = 2048;  // most vertices of a workgroup (places fit in 12 bits)
 template <bool K4>
+__global__ __launch_bounds__(256) void k_classify(DevGraph G, Lists L, int32_t* __restrict__ nlist,
+                                                  const int32_t* st) {
+  __shared__ int32_t cnt[kLists], base[kLists];
+  __shared__ uint32_t where[kClassify];
+  if (st[kStatus] != 0) return;
+  const int l8 = threadIdx.x & 7;
+  const int64_t per = ((int64_t)G.n + gridDim.x - 1) / gridDim.x;  // vertices of this workgroup, at most kClassify
+  const int64_t v0 = (int64_t)blockIdx.x * per, v1 = min((int64_t)G.n, v0 + per);
+  if (v0 >= v1) return;
+  if (threadIdx.x < kLists) cnt[threadIdx.x] = 0;
+  __syncthreads();
+  for (int64_t v = v0 + (threadIdx.x >> 3); v < v1; v += 32) {
+    int lt = 15, lw = 15;
+    const int32_t pa = G.np_off[v], pb = G.np_off[v + 1], d = pb - pa;
+    if (d >= 2) lt = d <= 16 ? kTri16 : d <= 64 ? kTri64 : kTriBig;
+    if (K4) {
+      const int32_t ma = G.gs_off[v] - pa, dm = G.gs_off[v + 1] - pb - ma;
+      if (dm > 127) {
+        lw = kWedgeTop;
+      } else if (dm >= 2) {
+        int32_t vis = 0;
+        for (int32_t i = l8; i < dm; i += 8) {
+          const uint32_t w = G.nm_idx[ma + i] & kIdMask;
+          vis += min(G.gs_off[w + 1] - G.gs_off[w], kCap256 + 1);
+        }
+#pragma unroll
+        for (int o = 4; o; o >>= 1) vis += __shfl_xor(vis, o);
+        lw = vis <= kCap16 ? kWedge16 : vis <= kCap64 ? kWedge64 : vis <= kCap256 ? kWedge256 : kWedgeTop;
+      }
+    }
+    if (l8 == 0) {  // lists of v (15: none) and its places in this workgroup's parts of them
+      const int at = lt < kLists ? atomicAdd(&cnt[lt], 1) : 0, aw = lw < kLists ? atomicAdd(&cnt[lw], 1) : 0;
+      where[v - v0] = (uint32_t)lt | (uint32_t)lw << 4 | (uint32_t)at << 8 | (uint32_t)aw << 20;
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x < kLists && cnt[threadIdx.x]) base[threadIdx.x] = atomicAdd(&nlist[threadIdx.x], cnt[threadIdx.x]);
+  __syncthreads();
+  for (int64_t v = v0 + threadIdx.x; v < v1; v += 256) {
+    const uint32_t w = where[v - v0], lt = w & 15u, lw = (w >> 4) & 15u;
+    if (lt < kLists) L.v[lt][base[lt] + (int32_t)((w >> 8) & 4095u)] = (int32_t)v;
+    if (lw < kLists) L.v[lw][base[lw] + (int32_t)(w >> 20)] = (int32_t)v;
+  }
+}
+
+template <int GS, bool K4>
 __global__ __launch_bounds__(256) void k_tri(DevGraph G, const uint16_t* __restrict__ lut3,
                                              const uint16_t* __restrict__ lut4, uint64_t* __restrict__ a3,
                                              uint64_t* __restrict__ a4, uint32_t* __restrict__ T, const int32_t* st,
-                                             int32_t* __restrict__ queue, int32_t chunk, int32_t* __restrict__ big) {
-  constexpr int NW = 4;
-  __shared__ u64 s_tri[27], s_paw[K4 ? 243 : 1], s_kh[K4 ? 199 : 1];
+                                             const int32_t* __restrict__ nlist, const int32_t* __restrict__ vlist) {
+  constexpr int NGR = 256 / GS, H = 4 * GS, HB = GS == 16 ? 6 : 8, LPR = GS / 4;  // groups, hash, lanes per row
+  __shared__ u64 s_tri[27], s_paw[K4 ? 243 : 1], s_kh[K4 ? 199 : 1], s_h3[13];
   __shared__ uint16_t lut[K4 ? 4096 : 1];
-  __shared__ uint32_t s_key[NW][kTriH];
-  __shared__ uint8_t s_at[NW][kTriH];
-  __shared__ uint32_t s_list[NW][kTriD];
-  __shared__ u64 s_T[K4 ? NW : 1][kTriD];                          // nine 7-bit counters per member of N+(x)
-  __shared__ u64 s_a1[K4 ? NW : 1][kTriD], s_a2[K4 ? NW : 1][kTriD];  // adjacency of N+(x), a bit plane per arc
-  __shared__ int32_t sh_v;
+  __shared__ uint32_t s_key[NGR][H];
+  __shared__ uint8_t s_at[NGR][H];
+  __shared__ uint32_t s_list[NGR][GS];
+  __shared__ u64 s_T[K4 ? NGR : 1][GS];                            // nine 7-bit counters per member of N+(x)
+  __shared__ u64 s_a1[K4 ? NGR : 1][GS], s_a2[K4 ? NGR : 1][GS];  // adjacency of N+(x), a bit plane per arc
   if (st[kStatus] != 0) return;
-  const TriBins<K4> bins{s_tri, s_paw, s_kh};
-  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int32_t count = nlist[GS == 16 ? kTri16 : kTri64];
+  if ((int64_t)blockIdx.x * (G.gid ? 1 : NGR) >= count) return;
+  const TriBins<K4> bins{s_tri, s_paw, s_kh, s_h3};
+  const int gr = threadIdx.x / GS, lane = threadIdx.x % GS, lane0 = (threadIdx.x & 63) - lane;
   bins.clear(threadIdx.x, 256);
   if (K4)
     for (int i = threadIdx.x; i < 4096; i += 256) lut[i] = lut4[i];
-  for (int i = lane; i < kTriH; i += 64) s_key[wv][i] = kNone;
+  for (int i = lane; i < H; i += GS) s_key[gr][i] = kNone;
   if (K4) {
-    s_T[wv][lane] = 0;
-    s_a1[wv][lane] = 0;
-    s_a2[wv][lane] = 0;
+    s_T[gr][lane] = 0;
+    s_a1[gr][lane] = 0;
+    s_a2[gr][lane] = 0;
   }
   __syncthreads();
-  uint32_t* key = s_key[wv];
-  uint8_t* at = s_at[wv];
-  uint32_t* list = s_list[wv];
-  u64 *Tl = s_T[K4 ? wv : 0], *A1 = s_a1[K4 ? wv : 0], *A2 = s_a2[K4 ? wv : 0];
-  const int32_t n = G.n;
+  uint32_t* key = s_key[gr];
+  uint8_t* at = s_at[gr];
+  uint32_t* list = s_list[gr];
+  u64 *Tl = s_T[K4 ? gr : 0], *A1 = s_a1[K4 ? gr : 0], *A2 = s_a2[K4 ? gr : 0];
 
-  auto one = [&](int32_t x) {  // uniform over the wave
-    const int32_t xa = G.np_off[x], d = G.np_off[x + 1] - xa;
-    if (d < 2) return;
-    if (d > kTriD) {
-      if (lane == 0) big[atomicAdd(&queue[kNTriBig], 1)] = x;
-      return;
-    }
+  auto one = [&](int32_t x) {  // the same x on the GS lanes of a group
+    const int32_t xa = G.np_off[x], d = G.np_off[x + 1] - xa;  // 2 .. GS
     // member `lane` of N+(x): entry, hash slot, row
     uint32_t e = 0, hs = 0;
     int32_t ra = 0, len = 0;
-    uint4 dy = make_uint4(0, 0, 0, 0);
     if (lane < d) {
       e = G.np_idx[xa + lane];
       const uint32_t y = e & kIdMask;
       list[lane] = e;
-      hs = hash_mul(y, kTriHB);
-      while (atomicCAS(&key[hs], kNone, y) != kNone) hs = (hs + 1) & (kTriH - 1);
+      hs = hash_mul(y, HB);
+      while (atomicCAS(&key[hs], kNone, y) != kNone) hs = (hs + 1) & (H - 1);
       at[hs] = (uint8_t)lane;
       ra = G.np_off[y];
       len = G.np_off[y + 1] - ra;
-      if (K4) dy = G.dt[y];
     }
     const uint4 dx = K4 ? G.dt[x] : make_uint4(0, 0, 0, 0);
     wave_sync();
-    const int32_t sub = lane >> 4, l16 = lane & 15;
+    const int32_t sub = lane / LPR, lr = lane % LPR;
     for (int32_t j0 = 0; j0 < d; j0 += 4) {
       const int32_t j = j0 + sub;
-      const int32_t a = __shfl(ra, j), mj = __shfl(len, j), m = j < d ? mj : 0;
-      for (int32_t t = l16; t < m; t += 16) {
-        const uint32_t f = G.np_idx[a + t], z = f & kIdMask;
-        uint32_t h = hash_mul(z, kTriHB), kk;
-        while ((kk = key[h]) != z && kk != kNone) h = (h + 1) & (kTriH - 1);
-        if (kk != z) continue;
+      const int32_t a = __shfl(ra, lane0 + j), mj = __shfl(len, lane0 + j), m = j < d ? mj : 0;
+      auto entry = [&](int32_t t, uint32_t f) {
+        const uint32_t z = f & kIdMask;
+        uint32_t h = hash_mul(z, HB), kk;
+        while ((kk = key[h]) != z && kk != kNone) h = (h + 1) & (H - 1);
+        if (kk != z) return;
         const int32_t k = at[h];
         const uint32_t ey = list[j], ez = list[k];
         const uint32_t xy = ey >> kTypeShift, xz = ez >> kTypeShift, yz = f >> kTypeShift;
         const uint32_t tau = (xy - 1) * 9 + (xz - 1) * 3 + (yz - 1);
         if constexpr (K4) {
+          atomicAdd(&T[(int64_t)(a + t) * 9 + (flip(xy) - 1) * 3 + (flip(xz) - 1)], 1u);
           tri_add<true>(bins, tau, dx, G.dt[ey & kIdMask], G.dt[z]);
           atomicAdd(&Tl[j], 1ull << (7 * ((xz - 1) * 3 + (yz - 1))));
           atomicAdd(&Tl[k], 1ull << (7 * ((xy - 1) * 3 + (flip(yz) - 1))));
-          atomicAdd(&T[(int64_t)(a + t) * 9 + (flip(xy) - 1) * 3 + (flip(xz) - 1)], 1u);
           if (yz & 1u) atomicOr(&A1[j], 1ull << k);
           if (yz & 2u) atomicOr(&A2[j], 1ull << k);
         } else {
           atomicAdd(&bins.tri[tau], 1ull);
         }
-      }
+      };
+      for (int32_t t = lr; t < m; t += 4 * LPR) each4(G.np_idx + a, t, LPR, m, entry);
     }
     wave_sync();
     if constexpr (K4) {
@@ -252,91 +366,58 @@ __global__ __launch_bounds__(256) void k_tri(DevGraph G, const uint16_t* __restr
     if (lane < d) key[hs] = kNone;
     wave_sync();
   };
-
-  if (!G.gid) {
-    for (;;) {
-      int32_t v0 = 0;
-      if (lane == 0) v0 = atomicAdd(&queue[kQTri], chunk);
-      v0 = __shfl(v0, 0);
-      if (v0 >= n) break;
-      const int32_t v1 = min(n, v0 + chunk);
-      for (int32_t x = v0; x < v1; ++x) one(x);
-    }
-    __syncthreads();
-    bins.flush(0, lut3, K4 ? lut : lut4, a3, a4, threadIdx.x, 256);
-    return;
-  }
-  int32_t cur = -1;
-  for (;;) {
-    __syncthreads();
-    if (threadIdx.x == 0) sh_v = atomicAdd(&queue[kQTri], kBatchChunk);
-    __syncthreads();
-    const int32_t v0 = sh_v;
-    if (v0 >= n) break;
-    const int32_t v1 = min(n, v0 + kBatchChunk);
-    for (int32_t a = v0; a < v1;) {
-      const int32_t g = G.gid[a];
-      const int32_t b = (int32_t)min((int64_t)v1, G.voff[g + 1]);
-      if (g != cur) {
-        __syncthreads();
-        if (cur >= 0) bins.flush(cur, lut3, K4 ? lut : lut4, a3, a4, threadIdx.x, 256);
-        __syncthreads();
-        bins.clear(threadIdx.x, 256);
-        __syncthreads();
-        cur = g;
-      }
-      for (int32_t x = a + wv; x < b; x += NW) one(x);
-      a = b;
-    }
-  }
-  if (cur >= 0) bins.flush(cur, lut3, K4 ? lut : lut4, a3, a4, threadIdx.x, 256);
+  for_listed<256>(G, vlist, count, NGR, gr, one, [&](int32_t g) {
+    bins.flush(lut3, K4 ? lut : lut4, a3 ? totals<13, kRep3>(G, a3, g) : nullptr,
+               K4 ? totals<199, kRep4>(G, a4, g) : nullptr, threadIdx.x, 256);
+  });
 }
 
-// The x with more than kTriD higher neighbours, one workgroup each: N+(x) in
-// an LDS hash of up to kBigH / 2 members (beyond that a binary search in the
+// The x with more than 64 higher neighbours, one workgroup each: N+(x) in an
+// LDS hash of up to kBigH / 2 members (beyond that a binary search in the
 // id-sorted row), T by global atomics, and for k = 4 the two adjacency bit
-// planes of N+(x) in the workgroup's slice of global memory (2 D rows of
-// `words` words, D >= any d+).  d+ is at most sqrt(2 m), so a slice is a few
-// hundred KB on 10^6 arcs; few x are here on sparse graphs (553 of 96,632 on
-// the n = 10^5 graph).
+// planes of N+(x), in LDS up to kPlaneD members and else in the workgroup's
+// slice of global memory (2 D rows of `words` words, D >= any d+).  d+ is at
+// most sqrt(2 m), so few x are here on sparse graphs (553 of 96,632 on the n =
+// 10^5 graph, none above 98).
 constexpr int kBigHB = 13;
 constexpr int kBigH = 1 << kBigHB;
+constexpr int kPlaneD = 256;
 
 template <bool K4>
 __global__ __launch_bounds__(512) void k_tri_big(DevGraph G, const uint16_t* __restrict__ lut3,
                                                  const uint16_t* __restrict__ lut4, uint64_t* __restrict__ a3,
                                                  uint64_t* __restrict__ a4, uint32_t* __restrict__ T,
-                                                 const int32_t* st, int32_t* __restrict__ queue,
-                                                 const int32_t* __restrict__ big, u64* __restrict__ planes, int64_t D,
+                                                 const int32_t* st, const int32_t* __restrict__ nlist,
+                                                 const int32_t* __restrict__ vlist, u64* __restrict__ planes, int64_t D,
                                                  int64_t words) {
   constexpr int NT = 512, NW = NT / 64;
-  __shared__ u64 s_tri[27], s_paw[K4 ? 243 : 1], s_kh[K4 ? 199 : 1];
+  __shared__ u64 s_tri[27], s_paw[K4 ? 243 : 1], s_kh[K4 ? 199 : 1], s_h3[13];
   __shared__ uint32_t key[kBigH];
   __shared__ uint16_t at[kBigH];
-  __shared__ int32_t sh_i;
+  __shared__ u64 lplane[K4 ? 2 * kPlaneD * kPlaneD / 64 : 1];
+  __shared__ uint16_t lut[K4 ? 4096 : 1];
   if (st[kStatus] != 0) return;
-  const int32_t nbig = queue[kNTriBig];
-  if (nbig == 0) return;
-  const TriBins<K4> bins{s_tri, s_paw, s_kh};
+  const int32_t count = nlist[kTriBig];
+  if ((int32_t)blockIdx.x >= count) return;
+  const TriBins<K4> bins{s_tri, s_paw, s_kh, s_h3};
   bins.clear(threadIdx.x, NT);
   for (int i = threadIdx.x; i < kBigH; i += NT) key[i] = kNone;
-  u64* P1 = K4 ? planes + (int64_t)blockIdx.x * 2 * D * words : nullptr;
-  u64* P2 = K4 ? P1 + D * words : nullptr;
+  if (K4)
+    for (int i = threadIdx.x; i < 4096; i += NT) lut[i] = lut4[i];
+  __syncthreads();
   const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  int32_t cur = -1;
-  for (;;) {
-    __syncthreads();
-    if (threadIdx.x == 0) sh_i = atomicAdd(&queue[kQTriBig], 1);
-    __syncthreads();
-    if (sh_i >= nbig) break;
-    const int32_t x = big[sh_i];
-    const int32_t g = G.gid ? G.gid[x] : 0;
-    if (g != cur) {
-      if (cur >= 0) bins.flush(cur, lut3, lut4, a3, a4, threadIdx.x, NT);
-      __syncthreads();
-      bins.clear(threadIdx.x, NT);
-      cur = g;
-    }
+  // rows of the adjacency: LDS planes plainly, global ones by accesses in L2
+  // (where their bits are set by atomics)
+  auto work = [&](int32_t x, auto in_lds, u64* P1, u64* P2) {
+    constexpr bool L = decltype(in_lds)::value;
+    auto put = [&](u64* p, u64 v) {
+      if constexpr (L) *p = v;
+      else __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    auto word = [&](const u64* p, int64_t i) {
+      if constexpr (L) return p[i];
+      else return __hip_atomic_load(p + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
     const int32_t xa = G.np_off[x], d = G.np_off[x + 1] - xa;
     const int32_t W = (d + 63) / 64;  // <= words: d <= D
     const bool hashed = d <= kBigH / 2;
@@ -349,8 +430,8 @@ __global__ __launch_bounds__(512) void k_tri_big(DevGraph G, const uint16_t* __r
       }
     if (K4)
       for (int64_t i = threadIdx.x; i < (int64_t)d * W; i += NT) {
-        __hip_atomic_store(&P1[i], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(&P2[i], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        put(&P1[i], 0ull);
+        put(&P2[i], 0ull);
       }
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
@@ -393,28 +474,33 @@ __global__ __launch_bounds__(512) void k_tri_big(DevGraph G, const uint16_t* __r
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     if constexpr (K4) {
-      auto word = [&](const u64* p, int64_t i) {  // set by atomics in L2
-        return __hip_atomic_load(p + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      // common bits of rows j and k: a lane per k of row j while a row is a
+      // few words, else a lane per word
+      auto edge = [&](int32_t j, int32_t k, uint32_t bx, uint32_t yz, int32_t l0, int32_t ls) {
+        const uint32_t bk = bx | edge_code<4>(0, 2, G.np_idx[xa + k] >> kTypeShift) | edge_code<4>(1, 2, yz);
+        for (int32_t lw = l0; lw < W; lw += ls) {
+          const u64 r1 = word(P1, (int64_t)j * W + lw), r2 = word(P2, (int64_t)j * W + lw);
+          const u64 q1 = word(P1, (int64_t)k * W + lw), q2 = word(P2, (int64_t)k * W + lw);
+          for (u64 com = (r1 | r2) & (q1 | q2); com; com &= com - 1ull) {
+            const int l = __builtin_ctzll(com);
+            const uint32_t code = bk | edge_code<4>(0, 3, G.np_idx[xa + lw * 64 + l] >> kTypeShift) |
+                                  edge_code<4>(1, 3, (uint32_t)((r1 >> l) & 1) | (uint32_t)((r2 >> l) & 1) << 1) |
+                                  edge_code<4>(2, 3, (uint32_t)((q1 >> l) & 1) | (uint32_t)((q2 >> l) & 1) << 1);
+            atomicAdd(&bins.kh[lut[code]], 1ull);
+          }
+        }
       };
       for (int32_t j = wv; j < d; j += NW) {
         const uint32_t bx = edge_code<4>(0, 1, G.np_idx[xa + j] >> kTypeShift);
         for (int32_t kw = 0; kw < W; ++kw) {
           const u64 p1 = word(P1, (int64_t)j * W + kw), p2 = word(P2, (int64_t)j * W + kw);
-          for (u64 r = p1 | p2; r; r &= r - 1ull) {  // the same on every lane
-            const int b = __builtin_ctzll(r);
-            const int32_t k = kw * 64 + b;
-            const uint32_t bk = bx | edge_code<4>(0, 2, G.np_idx[xa + k] >> kTypeShift) |
-                                edge_code<4>(1, 2, (uint32_t)((p1 >> b) & 1) | (uint32_t)((p2 >> b) & 1) << 1);
-            for (int32_t lw = lane; lw < W; lw += 64) {
-              const u64 r1 = word(P1, (int64_t)j * W + lw), r2 = word(P2, (int64_t)j * W + lw);
-              const u64 q1 = word(P1, (int64_t)k * W + lw), q2 = word(P2, (int64_t)k * W + lw);
-              for (u64 com = (r1 | r2) & (q1 | q2); com; com &= com - 1ull) {
-                const int l = __builtin_ctzll(com);
-                const uint32_t code = bk | edge_code<4>(0, 3, G.np_idx[xa + lw * 64 + l] >> kTypeShift) |
-                                      edge_code<4>(1, 3, (uint32_t)((r1 >> l) & 1) | (uint32_t)((r2 >> l) & 1) << 1) |
-                                      edge_code<4>(2, 3, (uint32_t)((q1 >> l) & 1) | (uint32_t)((q2 >> l) & 1) << 1);
-                atomicAdd(&bins.kh[lut4[code]], 1ull);
-              }
+          if constexpr (L) {
+            const uint32_t yz = (uint32_t)((p1 >> lane) & 1) | (uint32_t)((p2 >> lane) & 1) << 1;
+            if (yz) edge(j, kw * 64 + lane, bx, yz, 0, 1);
+          } else {
+            for (u64 r = p1 | p2; r; r &= r - 1ull) {  // the same on every lane
+              const int b = __builtin_ctzll(r);
+              edge(j, kw * 64 + b, bx, (uint32_t)((p1 >> b) & 1) | (uint32_t)((p2 >> b) & 1) << 1, lane, 64);
             }
           }
         }
@@ -423,9 +509,20 @@ __global__ __launch_bounds__(512) void k_tri_big(DevGraph G, const uint16_t* __r
     }
     if (hashed)
       for (int i = threadIdx.x; i < kBigH; i += NT) key[i] = kNone;
-  }
-  __syncthreads();
-  if (cur >= 0) bins.flush(cur, lut3, lut4, a3, a4, threadIdx.x, NT);
+    __syncthreads();
+  };
+  u64* const gp = K4 ? planes + (int64_t)blockIdx.x * 2 * D * words : nullptr;
+  for_listed<NT>(
+      G, vlist, count, 1, 0,
+      [&](int32_t x) {
+        const int32_t d = G.np_off[x + 1] - G.np_off[x];
+        if (!K4 || d <= kPlaneD) work(x, std::true_type{}, lplane, lplane + kPlaneD * kPlaneD / 64);
+        else work(x, std::false_type{}, gp, gp + D * words);
+      },
+      [&](int32_t g) {
+        bins.flush(lut3, K4 ? lut : lut4, a3 ? totals<13, kRep3>(G, a3, g) : nullptr,
+                   K4 ? totals<199, kRep4>(G, a4, g) : nullptr, threadIdx.x, NT);
+      });
 }
 
 // ================================================================ wedges ==
@@ -435,13 +532,22 @@ __global__ __launch_bounds__(512) void k_tri_big(DevGraph G, const uint16_t* __r
 // and of w seen from v.  Two wedges to the same w of lower rank are a C4
 // u - v - w - v'.  A count is at most min(d-(u), d(w)), which bounds the width
 // of its field: nine fields of 7 bits share one 64-bit word while d-(u) <= 127.
-//   k_wedge<64, 8>    one wave per u with at most 192 visits (a hash of w)
-//   k_wedge<256, 12>  one workgroup per u with at most 3,072 visits
-//   k_wedge_top       the rest: a direct table over one block of vertex ids at
-//                     a time, the work unit being (u, block)
+//   k_wedge<16, 7>, <64, 9>, <256, 12>   that many threads per u and a hash of
+//                    w, for u with at most 96, 384 and 3,072 visits
+//   k_wedge_top      the rest: a direct table over one block of vertex ids at a
+//                    time, the work unit being (u, block)
 __device__ __forceinline__ bool ranked_below(const DevGraph& G, uint32_t dw, int32_t w, uint32_t du, int32_t u) {
   return dw < du || (dw == du && w < u);
 }
+
+// A word of packed counters that holds one single wedge: one bit set, at the
+// foot of a field (ones: the feet).
+template <class W>
+__device__ __forceinline__ bool one_wedge(W c, W ones) {
+  return (c & (c - 1)) == 0 && (c & ones) != 0;
+}
+constexpr u64 kOnes7 = 1ull | 1ull << 7 | 1ull << 14 | 1ull << 21 | 1ull << 28 | 1ull << 35 | 1ull << 42 | 1ull << 49 |
+                       1ull << 56;
 
 // Pairs of wedges to one w, by the types of both, into bins[9 i + j], i <= j.
 __device__ __forceinline__ void c4_pairs(const uint32_t (&c)[9], u64* bins) {
@@ -467,25 +573,20 @@ __device__ __forceinline__ void c4_flush(const u64* bins, const uint16_t* lut4, 
   }
 }
 
-constexpr int kMidVisits = 3072;
-
-// NT threads per u, a hash of 2^HB slots (at most 3/4 full).  NT = 64: every
-// vertex, those with more visits go to `mid`; NT = 256: the vertices of `mid`.
 template <int NT, int HB>
 __global__ __launch_bounds__(256) void k_wedge(DevGraph G, const uint16_t* __restrict__ lut4,
                                                uint64_t* __restrict__ a4, const int32_t* st,
-                                               int32_t* __restrict__ queue, int32_t chunk, int32_t* __restrict__ mid,
-                                               int32_t* __restrict__ top) {
+                                               const int32_t* __restrict__ nlist, const int32_t* __restrict__ vlist) {
   constexpr int NU = 256 / NT, H = 1 << HB;
-  constexpr bool WAVE = NT == 64;
-  constexpr int kCap = WAVE ? 192 : kMidVisits;
-  static_assert(kCap <= H * 3 / 4, "hash load");
+  constexpr int LPR = NT == 16 ? 4 : 8;  // lanes per row
+  static_assert((NT == 16 ? kCap16 : NT == 64 ? kCap64 : kCap256) <= H * 3 / 4, "hash load");
   __shared__ uint32_t s_key[NU][H];
   __shared__ u64 s_cnt[NU][H];
   __shared__ u64 bins[81];
-  __shared__ int32_t sh_v;
   if (st[kStatus] != 0) return;
-  const int un = threadIdx.x / NT, t = threadIdx.x % NT, lane = threadIdx.x & 63;
+  const int32_t count = nlist[NT == 16 ? kWedge16 : NT == 64 ? kWedge64 : kWedge256];
+  if ((int64_t)blockIdx.x * (G.gid ? 1 : NU) >= count) return;
+  const int un = threadIdx.x / NT, t = threadIdx.x % NT;
   uint32_t* key = s_key[un];
   u64* cnt = s_cnt[un];
   for (int i = t; i < H; i += NT) {
@@ -495,39 +596,19 @@ __global__ __launch_bounds__(256) void k_wedge(DevGraph G, const uint16_t* __res
   for (int i = threadIdx.x; i < 81; i += 256) bins[i] = 0;
   __syncthreads();
   auto sync = [] {
-    if constexpr (WAVE) wave_sync();
+    if constexpr (NT <= 64) wave_sync();
     else __syncthreads();
   };
-  auto one = [&](int32_t u) {  // uniform over the NT threads
-    const int32_t ma = G.gs_off[u] - G.np_off[u];
-    const int32_t dm = G.gs_off[u + 1] - G.np_off[u + 1] - ma;
-    if (dm < 2) return;
-    if constexpr (WAVE) {
-      int32_t vis = kMidVisits + 1;
-      if (dm <= 127) {
-        vis = 0;
-        for (int32_t i = lane; i < dm; i += 64) {
-          const uint32_t v = G.nm_idx[ma + i] & kIdMask;
-          vis += min(G.gs_off[v + 1] - G.gs_off[v], kMidVisits + 1);
-        }
-#pragma unroll
-        for (int o = 32; o; o >>= 1) vis += __shfl_xor(vis, o);
-      }
-      if (vis > kCap) {
-        if (lane == 0) {
-          if (vis <= kMidVisits) mid[atomicAdd(&queue[kNWedgeMid], 1)] = u;
-          else top[atomicAdd(&queue[kNWedgeTop], 1)] = u;
-        }
-        return;
-      }
-    }
-    for (int32_t i = t >> 3; i < dm; i += NT / 8) {  // eight lanes per row
+  auto one = [&](int32_t u) {  // the same u on the NT threads
+    const int32_t ua = G.gs_off[u], ub = G.gs_off[u + 1];
+    const int32_t ma = ua - G.np_off[u], dm = ub - G.np_off[u + 1] - ma;
+    for (int32_t i = t / LPR; i < dm; i += NT / LPR) {
       const uint32_t ev = G.nm_idx[ma + i], v = ev & kIdMask;
       const int32_t ra = G.gs_off[v], rb = G.gs_off[v + 1];
       const int p7 = 21 * (int)((ev >> kTypeShift) - 1u);
-      for (int32_t r = ra + (t & 7); r < rb; r += 8) {
-        const uint32_t f = G.gs_idx[r], w = f & kIdMask;
-        if ((int32_t)w == u) continue;
+      auto entry = [&](int32_t, uint32_t f) {
+        const uint32_t w = f & kIdMask;
+        if ((int32_t)w == u) return;
         uint32_t h = hash_mul(w, HB);
         for (;;) {
           const uint32_t old = atomicCAS(&key[h], kNone, w);
@@ -535,20 +616,18 @@ __global__ __launch_bounds__(256) void k_wedge(DevGraph G, const uint16_t* __res
           h = (h + 1) & (H - 1);
         }
         atomicAdd(&cnt[h], 1ull << (p7 + 7 * (int)((f >> kTypeShift) - 1u)));
-      }
+      };
+      for (int32_t r = t % LPR; r < rb - ra; r += 4 * LPR) each4(G.gs_idx + ra, r, LPR, rb - ra, entry);
     }
     sync();
-    const uint32_t du = (uint32_t)(G.gs_off[u + 1] - G.gs_off[u]);
+    const uint32_t du = (uint32_t)(ub - ua);
     for (int i = t; i < H; i += NT) {
       const u64 c = cnt[i];
       if (!c) continue;
       cnt[i] = 0;
       const uint32_t w = key[i];
       key[i] = kNone;
-      // a single wedge: one field, equal to one
-      constexpr u64 kOnes = 1ull | 1ull << 7 | 1ull << 14 | 1ull << 21 | 1ull << 28 | 1ull << 35 | 1ull << 42 |
-                            1ull << 49 | 1ull << 56;
-      if ((c & (c - 1ull)) == 0 && (c & kOnes)) continue;
+      if (one_wedge(c, kOnes7)) continue;
       if (!ranked_below(G, (uint32_t)(G.gs_off[w + 1] - G.gs_off[w]), (int32_t)w, du, u)) continue;
       uint32_t f[9];
 #pragma unroll
@@ -557,244 +636,299 @@ __global__ __launch_bounds__(256) void k_wedge(DevGraph G, const uint16_t* __res
     }
     sync();
   };
-  const int32_t n = G.n;
-  if constexpr (!WAVE) {
-    const int32_t nmid = queue[kNWedgeMid];
-    int32_t cur = -1;
-    for (;;) {
-      if (threadIdx.x == 0) sh_v = atomicAdd(&queue[kQWedgeMid], 1);
-      __syncthreads();
-      const int32_t i = sh_v;
-      __syncthreads();
-      if (i >= nmid) break;
-      const int32_t u = mid[i], g = G.gid ? G.gid[u] : 0;
-      if (g != cur) {
-        if (cur >= 0) c4_flush(bins, lut4, a4 + (int64_t)cur * 199, threadIdx.x, 256);
-        __syncthreads();
-        if (threadIdx.x < 81) bins[threadIdx.x] = 0;
-        __syncthreads();
-        cur = g;
-      }
-      one(u);
-    }
-    if (cur >= 0) c4_flush(bins, lut4, a4 + (int64_t)cur * 199, threadIdx.x, 256);
-  } else if (!G.gid) {
-    for (;;) {
-      int32_t v0 = 0;
-      if (lane == 0) v0 = atomicAdd(&queue[kQWedge], chunk);
-      v0 = __shfl(v0, 0);
-      if (v0 >= n) break;
-      const int32_t v1 = min(n, v0 + chunk);
-      for (int32_t u = v0; u < v1; ++u) one(u);
-    }
+  for_listed<256>(G, vlist, count, NU, un, one, [&](int32_t g) {
+    c4_flush(bins, lut4, totals<199, kRep4>(G, a4, g), threadIdx.x, 256);
     __syncthreads();
-    c4_flush(bins, lut4, a4, threadIdx.x, 256);
-  } else {
-    int32_t cur = -1;
-    for (;;) {
-      __syncthreads();
-      if (threadIdx.x == 0) sh_v = atomicAdd(&queue[kQWedge], kBatchChunk);
-      __syncthreads();
-      const int32_t v0 = sh_v;
-      if (v0 >= n) break;
-      const int32_t v1 = min(n, v0 + kBatchChunk);
-      for (int32_t a = v0; a < v1;) {
-        const int32_t g = G.gid[a];
-        const int32_t b = (int32_t)min((int64_t)v1, G.voff[g + 1]);
-        if (g != cur) {
-          __syncthreads();
-          if (cur >= 0) c4_flush(bins, lut4, a4 + (int64_t)cur * 199, threadIdx.x, 256);
-          __syncthreads();
-          if (threadIdx.x < 81) bins[threadIdx.x] = 0;
-          __syncthreads();
-          cur = g;
-        }
-        for (int32_t u = a + un; u < b; u += NU) one(u);
-        a = b;
-      }
-    }
-    if (cur >= 0) c4_flush(bins, lut4, a4 + (int64_t)cur * 199, threadIdx.x, 256);
-  }
+    if (threadIdx.x < 81) bins[threadIdx.x] = 0;
+  });
 }
 
-// Vertex u of many visits: (u, block of w) is a work unit of one workgroup.
-// The wedge counts of the block's vertices sit in a direct LDS table, the
-// widest block that the bound of u allows: nine 7-bit fields in 8 bytes for
-// d-(u) <= 127, 3 x three 10-bit fields in 12 for d-(u) <= 1,023, else 3 x
-// three 21-bit fields in 24 (WIDE, for graphs with degrees of 2^21 and more:
-// nine words of 36 bytes).  split holds the start of every granule of ids in
-// every row, so a unit reads just its part of each row N(v) (null: binary
-// search).  Parts of more than kLongPart entries are listed and taken by whole
-// waves, the others by eight lanes.
-constexpr int kTopTable = 147456;  // bytes: 6,144 vertices of 24 bytes, 4,096 of 36
+// Vertex u of many visits: (u, block of kBlock ids) is a work unit of one
+// workgroup.  The sum over w of the products of two of its nine wedge counts is
+// a 9 x 9 Gram matrix, taken by the matrix cores: the counts sit in LDS as
+// bytes, one row of the block per field, so that a lane reads sixteen of its
+// field's counts at once, and 64 w are one v_mfma_i32_16x16x64_i8 with the same
+// register as both operands (row 9 holds ones: the plain sums, for the pairs
+// within a field).  Counts stay below 128 where d-(u) or d(w) does; the w of
+// degree over 127 (hubs), when d-(u) is too, have 32-bit counts instead, kHubs
+// of them at a time, multiplied digit by digit (ND digits of 7 bits).  The
+// pairs as 45 products per w summed in LDS took 1,300 us on the n = 10^5 graph,
+// where every wave's 45 additions meet on the same 45 words.
+//
+// split holds the first entry of every block in every row, so that a unit
+// reads its part of each row N(v) only (null: binary search).  The parts are
+// listed in LDS first, empty ones left out, kParts rows at a time, so that the
+// loads that find them are one short chain for many rows; eight lanes then
+// read a part, whole waves those of more than kLongPart entries.
+constexpr int kBlock = 12288;
+constexpr int kByteRow = kBlock + 64;  // bytes of a field's row: four fields on distinct banks
+constexpr int kHubs = 1024;
 constexpr int kLongPart = 64;
-constexpr int kLongCap = 128;
 constexpr int kTopThreads = 1024;
+constexpr int kParts = 896;
+constexpr int kGramRun = 1024;  // products of 64 w between flushes: 64 * 127^2 * 1024 < 2^31
 
-template <bool WIDE>
-constexpr int top_granule() { return WIDE ? 4096 : 6144; }
+typedef int v4i __attribute__((ext_vector_type(4)));
 
-template <bool WIDE>
+// Gram sums of one wave over ND digits: acc[a (a + 1) / 2 + b] = digit a
+// (rows) by digit b <= a (columns), 16 x 16 spread over the lanes: register r
+// of lane l is row (l / 16) * 4 + r, column l % 16.
+template <int ND>
+struct Gram {
+  static constexpr int N = ND * (ND + 1) / 2;
+  v4i acc[N];
+  int run = 0;
+  __device__ __forceinline__ void clear() {
+#pragma unroll
+    for (int i = 0; i < N; ++i) acc[i] = v4i{0, 0, 0, 0};
+    run = 0;
+  }
+  // Into bins[9 i + j], i <= j: sums of n_i n_j; bins[81 + i]: sums of n_i.
+  __device__ __forceinline__ void flush(u64* bins) {
+    if (run == 0) return;
+    const int lane = threadIdx.x & 63, j = lane & 15;
+#pragma unroll
+    for (int a = 0; a < ND; ++a)
+#pragma unroll
+      for (int b = 0; b <= a; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int i = (lane >> 4) * 4 + r;
+          const u64 v = (u64)(uint32_t)acc[a * (a + 1) / 2 + b][r] << (7 * (a + b));
+          if (!v || i > 8 || j > 9) continue;
+          if (j == 9) {
+            if (b == 0) atomicAdd(&bins[81 + i], v);
+          } else if (a == b) {
+            if (i <= j) atomicAdd(&bins[9 * i + j], v);
+          } else {
+            atomicAdd(&bins[9 * min(i, j) + max(i, j)], i == j ? 2 * v : v);
+          }
+        }
+    clear();
+  }
+};
+
+template <int ND>
 __global__ __launch_bounds__(kTopThreads) void k_wedge_top(DevGraph G, const uint16_t* __restrict__ lut4,
                                                            uint64_t* __restrict__ a4, const int32_t* st,
-                                                           int32_t* __restrict__ queue,
+                                                           const int32_t* __restrict__ nlist,
                                                            const int32_t* __restrict__ top,
-                                                           const int32_t* __restrict__ split, int32_t ngran) {
-  constexpr int NT = kTopThreads, GR = top_granule<WIDE>();
-  constexpr int kMaxBlock = WIDE ? 4096 : 18432;
-  __shared__ __align__(16) uint32_t tab[kTopTable / 4];
-  __shared__ u64 bins[81];
-  __shared__ int32_t l_a[kLongCap], l_b[kLongCap], l_p[kLongCap], nlong;
-  __shared__ u64 sh_i;
-  __shared__ uint16_t act[4096];  // vertices with two wedges or more
-  __shared__ int32_t nact;
+                                                           const int32_t* __restrict__ split, int32_t nblk) {
+  constexpr int NT = kTopThreads, NW = NT / 64, NQ = kBlock / 64;
+  __shared__ __align__(16) uint32_t bytes[9 * kByteRow / 4];
+  __shared__ __align__(16) uint32_t wide[9 * kHubs];
+  __shared__ int32_t pt_a[kParts], pt_n[kParts], pt_p[kParts];
+  __shared__ u64 mlow[NQ], mhub[NQ];  // of the block's ids: of lower rank than u, of degree over 127
+  __shared__ uint16_t hpre[NQ];       // hubs before each word of mhub
+  __shared__ u64 bins[90];
+  __shared__ int32_t nshort, nlong, nhub;
   if (st[kStatus] != 0) return;
-  const int32_t ntop = queue[kNWedgeTop];
-  if (ntop == 0) return;
+  const int64_t units = (int64_t)nlist[kWedgeTop] * nblk;
+  if ((int64_t)blockIdx.x >= units) return;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  for (int i = threadIdx.x; i < 81; i += NT) bins[i] = 0;
-  u64* const t64 = reinterpret_cast<u64*>(tab);
-  const int64_t units = (int64_t)ntop * ngran;
+  for (int i = threadIdx.x; i < 90; i += NT) bins[i] = 0;
+  if (threadIdx.x == 0) nshort = nlong = nhub = 0;
+  Gram<1> low;   // byte counts
+  Gram<ND> hub;  // hub counts
+  low.clear();
+  hub.clear();
   int32_t cur = -1;
-  for (;;) {
+  auto give = [&](int32_t g) {  // every wave's sums to graph g
+    low.flush(bins);
+    hub.flush(bins);
     __syncthreads();
-    if (threadIdx.x == 0) {
-      sh_i = atomicAdd(reinterpret_cast<u64*>(&queue[kQWedgeTop]), 1ull);  // two words: units may pass 2^31
-      nlong = 0;
-      nact = 0;
+    if (threadIdx.x < 9) {  // pairs within a field: (sum of squares - sum) / 2
+      u64& d = bins[10 * threadIdx.x];
+      d = (d - bins[81 + threadIdx.x]) / 2;
     }
     __syncthreads();
-    const int64_t unit = (int64_t)sh_i;
-    if (unit >= units) break;
-    const int32_t u = top[unit / ngran];
+    c4_flush(bins, lut4, totals<199, kRep4>(G, a4, g), threadIdx.x, NT);
+    __syncthreads();
+    for (int i = threadIdx.x; i < 90; i += NT) bins[i] = 0;
+    __syncthreads();
+  };
+  const v4i ones = v4i{0x01010101, 0x01010101, 0x01010101, 0x01010101}, none = v4i{0, 0, 0, 0};
+  const int fld = lane & 15, kb = lane >> 4;
+  __syncthreads();
+  for (int64_t unit = blockIdx.x; unit < units; unit += gridDim.x) {
+    const int32_t u = top[unit / nblk], blk = (int32_t)(unit % nblk);
     const int32_t g = G.gid ? G.gid[u] : 0;
     const int32_t base = G.voff ? (int32_t)G.voff[g] : 0;
     const int32_t ng = G.voff ? (int32_t)(G.voff[g + 1] - G.voff[g]) : G.n;
-    const int32_t ma = G.gs_off[u] - G.np_off[u];
-    const int32_t dm = G.gs_off[u + 1] - G.np_off[u + 1] - ma;
-    // format: 0 = 8 bytes, 1 = 12, 2 = 24, 3 = 36; granules per block
-    const int fmt = WIDE ? 3 : dm <= 127 ? 0 : dm <= 1023 ? 1 : 2;
-    const int32_t per = WIDE ? 1 : fmt == 0 ? 3 : fmt == 1 ? 2 : 1;
-    const int32_t blk = (int32_t)(unit % ngran);
-    const int32_t g0 = blk * per;                 // first granule
-    if ((int64_t)g0 * GR >= ng) continue;         // uniform over the workgroup
-    const int32_t g1 = min(g0 + per, (ng + GR - 1) / GR);
-    const int32_t w0 = base + g0 * GR, w1 = min(base + ng, base + g1 * GR);
-    const int32_t nw = w1 - w0;                   // <= kMaxBlock
-    const int32_t BS = per * GR;                  // table stride of the formats with three or nine arrays
+    if ((int64_t)blk * kBlock >= ng) continue;  // uniform over the workgroup
+    const int32_t ua = G.gs_off[u], ub = G.gs_off[u + 1], du = ub - ua;
+    const int32_t ma = ua - G.np_off[u], dm = ub - G.np_off[u + 1] - ma;
+    const int32_t w0 = base + blk * kBlock, nw = min(kBlock, ng - blk * kBlock), nq = (nw + 63) / 64;
+    const bool divert = dm > 127;
     if (g != cur) {
-      if (cur >= 0) c4_flush(bins, lut4, a4 + (int64_t)cur * 199, threadIdx.x, NT);
-      __syncthreads();
-      for (int i = threadIdx.x; i < 81; i += NT) bins[i] = 0;
+      if (cur >= 0) give(cur);
       cur = g;
     }
-    for (int i = threadIdx.x; i < kTopTable / 16; i += NT) reinterpret_cast<uint4*>(tab)[i] = make_uint4(0, 0, 0, 0);
-    __syncthreads();
-    auto add = [&](uint32_t p, uint32_t f) {  // p, type less one
-      const int32_t w = (int32_t)(f & kIdMask) - w0;
-      const uint32_t q = (f >> kTypeShift) - 1u;
-      if (fmt == 0) atomicAdd(&t64[w], 1ull << (21 * p + 7 * q));
-      else if (fmt == 1) atomicAdd(&tab[p * BS + w], 1u << (10 * q));
-      else if (fmt == 2) atomicAdd(&t64[p * BS + w], 1ull << (21 * q));
-      else atomicAdd(&tab[(3 * p + q) * BS + w], 1u);
-    };
-    for (int32_t i = threadIdx.x >> 3; i < dm; i += NT / 8) {
-      const uint32_t ev = G.nm_idx[ma + i], p = (ev >> kTypeShift) - 1u;
-      const int32_t v = (int32_t)(ev & kIdMask);
-      int32_t a, b;
-      if (split) {
-        const int32_t* sp = split + (int64_t)v * (ngran + 1);
-        a = sp[g0];
-        b = sp[g1];
-      } else {
-        auto first = [&](int32_t id) {
-          int32_t lo = G.gs_off[v], hi = G.gs_off[v + 1];
-          while (lo < hi) {
-            const int32_t mid = (lo + hi) >> 1;
-            if ((int32_t)(G.gs_idx[mid] & kIdMask) < id) lo = mid + 1; else hi = mid;
-          }
-          return lo;
-        };
-        a = first(w0);
-        b = first(w1);
+    for (int k = 0; k < 9; ++k) {
+      uint4* t16 = reinterpret_cast<uint4*>(bytes) + k * (kByteRow / 16);
+      for (int32_t i = threadIdx.x; i < nq * 4; i += NT) t16[i] = make_uint4(0, 0, 0, 0);
+    }
+    for (int32_t q = wv; q < nq; q += NW) {
+      const int32_t w = q * 64 + lane, id = w0 + w;
+      const int32_t d = w < nw ? G.deg[id] : 0;
+      const u64 lo = __ballot(w < nw && (d < du || (d == du && id < u))), hb = __ballot(d > 127);
+      if (lane == 0) {
+        mlow[q] = lo;
+        mhub[q] = hb;
       }
-      if (b - a > kLongPart) {
-        int32_t s = kLongCap;
-        if ((threadIdx.x & 7) == 0) s = atomicAdd(&nlong, 1);
-        s = __shfl(s, lane & 56);
-        if (s < kLongCap) {
-          if ((threadIdx.x & 7) == 0) {
-            l_a[s] = a;
-            l_b[s] = b;
-            l_p[s] = (int32_t)p;
+    }
+    __syncthreads();
+    int32_t nh = 0;
+    if (divert) {
+      if (wv == 0) {
+        int32_t run = 0;
+        for (int32_t q0 = 0; q0 < nq; q0 += 64) {
+          const int32_t q = q0 + lane, c = q < nq ? __popcll(mhub[q]) : 0;
+          int32_t inc = c;
+#pragma unroll
+          for (int o = 1; o < 64; o <<= 1) {
+            const int32_t y = __shfl_up(inc, o);
+            if (lane >= o) inc += y;
           }
-          continue;
+          if (q < nq) hpre[q] = (uint16_t)(run + inc - c);
+          run += __shfl(inc, 63);
+        }
+        if (lane == 0) nhub = run;
+      }
+      __syncthreads();
+      nh = nhub;
+    }
+    for (int32_t h0 = 0; h0 == 0 || h0 < nh; h0 += kHubs) {
+      const int32_t nhc = min(kHubs, nh - h0);  // hubs of this pass
+      if (nhc > 0) {
+        for (int32_t i = threadIdx.x; i < 9 * kHubs / 4; i += NT)
+          reinterpret_cast<uint4*>(wide)[i] = make_uint4(0, 0, 0, 0);
+        __syncthreads();
+      }
+      auto hub_at = [&](int32_t w) {  // index of hub w in this pass (any value of kHubs or more: not in it)
+        const u64 m = mhub[w >> 6];
+        return (uint32_t)((int32_t)hpre[w >> 6] + __popcll(m & ((1ull << (w & 63)) - 1ull)) - h0);
+      };
+      auto add = [&](uint32_t p, uint32_t f) {  // p, type less one
+        const int32_t w = (int32_t)(f & kIdMask) - w0;
+        const uint32_t k = 3 * p + (f >> kTypeShift) - 1u;
+        if (divert) {
+          if ((mhub[w >> 6] >> (w & 63)) & 1ull) {
+            const uint32_t h = hub_at(w);
+            if (h < (uint32_t)kHubs) atomicAdd(&wide[k * kHubs + h], 1u);
+            return;
+          }
+          if (h0) return;
+        }
+        atomicAdd(&bytes[(k * kByteRow + (uint32_t)w) >> 2], 1u << (8 * (w & 3)));
+      };
+      for (int32_t i0 = 0; i0 < dm; i0 += kParts) {
+        const int32_t i = i0 + (int32_t)threadIdx.x;
+        if (threadIdx.x < kParts && i < dm) {
+          const uint32_t ev = G.nm_idx[ma + i];
+          const int32_t v = (int32_t)(ev & kIdMask);
+          int32_t a, b;
+          if (split) {
+            const int32_t* sp = split + (int64_t)v * (nblk + 1) + blk;
+            a = sp[0];
+            b = sp[1];
+          } else {
+            auto first = [&](int64_t id) {
+              int32_t lo = G.gs_off[v], hi = G.gs_off[v + 1];
+              while (lo < hi) {
+                const int32_t mid = (lo + hi) >> 1;
+                if ((int64_t)(G.gs_idx[mid] & kIdMask) < id) lo = mid + 1; else hi = mid;
+              }
+              return lo;
+            };
+            a = first(w0);
+            b = first((int64_t)w0 + nw);
+          }
+          if (b > a) {  // short parts from the front, long ones from the back
+            const int32_t s = b - a > kLongPart ? kParts - 1 - atomicAdd(&nlong, 1) : atomicAdd(&nshort, 1);
+            pt_a[s] = a;
+            pt_n[s] = b - a;
+            pt_p[s] = (int32_t)(ev >> kTypeShift) - 1;
+          }
+        }
+        __syncthreads();
+        const int32_t ns = nshort, nl = nlong;
+        for (int32_t k = threadIdx.x >> 3; k < ns; k += NT / 8) {
+          const int32_t a = pt_a[k], m = pt_n[k];
+          const uint32_t p = (uint32_t)pt_p[k];
+          for (int32_t r = threadIdx.x & 7; r < m; r += 32)
+            each4(G.gs_idx + a, r, 8, m, [&](int32_t, uint32_t f) { add(p, f); });
+        }
+        for (int32_t k = wv; k < nl; k += NW) {
+          const int32_t s = kParts - 1 - k, a = pt_a[s], m = pt_n[s];
+          const uint32_t p = (uint32_t)pt_p[s];
+          for (int32_t r = lane; r < m; r += 256)
+            each4(G.gs_idx + a, r, 64, m, [&](int32_t, uint32_t f) { add(p, f); });
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) nshort = nlong = 0;
+        __syncthreads();
+      }
+      // w of higher rank, and u itself (in every row N(v)), do not count
+      for (int32_t q = wv; q < nq; q += NW) {
+        const int32_t w = q * 64 + lane;
+        if (w >= nw || (mlow[q] >> lane) & 1ull) continue;
+        if (divert && (mhub[q] >> lane) & 1ull) {
+          const uint32_t h = hub_at(w);
+          if (h < (uint32_t)kHubs)
+            for (int k = 0; k < 9; ++k) wide[k * kHubs + h] = 0u;
+        } else if (h0 == 0) {
+          for (int k = 0; k < 9; ++k) reinterpret_cast<uint8_t*>(bytes)[k * kByteRow + w] = 0;
         }
       }
-      for (int32_t r = a + (threadIdx.x & 7); r < b; r += 8) add(p, G.gs_idx[r]);
-    }
-    __syncthreads();
-    const int32_t nl = min(nlong, kLongCap);
-    for (int32_t i = wv; i < nl; i += NT / 64) {
-      const int32_t b = l_b[i];
-      const uint32_t p = (uint32_t)l_p[i];
-      for (int32_t r = l_a[i] + lane; r < b; r += 64) add(p, G.gs_idx[r]);
-    }
-    __syncthreads();
-    // u itself is in every row N(v): its counts are no wedges
-    const uint32_t du = (uint32_t)(G.gs_off[u + 1] - G.gs_off[u]);
-    auto fields = [&](int32_t w, uint32_t (&c)[9]) {
-#pragma unroll
-      for (int k = 0; k < 9; ++k) {
-        const int p = k / 3, q = k % 3;
-        c[k] = fmt == 0 ? (uint32_t)(t64[w] >> (7 * k)) & 127u
-             : fmt == 1 ? (tab[p * BS + w] >> (10 * q)) & 1023u
-             : fmt == 2 ? (uint32_t)(t64[p * BS + w] >> (21 * q)) & 0x1FFFFFu
-                        : tab[k * BS + w];
-      }
-    };
-    auto many = [&](int32_t w) {  // two wedges or more
-      uint32_t c[9], s = 0;
-      fields(w, c);
-#pragma unroll
-      for (int k = 0; k < 9; ++k) s |= c[k] > 1u ? 2u : s ? (c[k] ? 2u : 0u) : c[k];
-      return s >= 2u;
-    };
-    // the vertices that count are listed first: few of a block do, and the
-    // pair loop then runs on full waves
-    for (int32_t b0 = 0; b0 < nw; b0 += 4096) {
-      for (int32_t w = b0 + (int32_t)threadIdx.x; w < min(nw, b0 + 4096); w += NT) {
-        if (!many(w)) continue;
-        const int32_t id = w0 + w;
-        if (id == u || !ranked_below(G, (uint32_t)(G.gs_off[id + 1] - G.gs_off[id]), id, du, u)) continue;
-        act[atomicAdd(&nact, 1)] = (uint16_t)w;
-      }
       __syncthreads();
-      const int32_t na = nact;
-      for (int32_t i = threadIdx.x; i < na; i += NT) {
-        uint32_t c[9];
-        fields((int32_t)act[i], c);
-        c4_pairs(c, bins);
+      if (h0 == 0) {
+        for (int32_t q = wv; q < nq; q += NW) {
+          v4i x = fld == 9 ? ones : none;
+          if (fld < 9) x = *reinterpret_cast<const v4i*>(bytes + (fld * kByteRow + q * 64 + kb * 16) / 4);
+          low.acc[0] = __builtin_amdgcn_mfma_i32_16x16x64_i8(x, x, low.acc[0], 0, 0, 0);
+          if (++low.run == kGramRun) low.flush(bins);
+        }
       }
-      __syncthreads();
-      if (threadIdx.x == 0) nact = 0;
+      for (int32_t q = wv; q < (nhc + 63) / 64; q += NW) {
+        v4i x[ND];
+#pragma unroll
+        for (int a = 0; a < ND; ++a) x[a] = fld == 9 && a == 0 ? ones : none;
+        if (fld < 9) {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const uint4 c = *reinterpret_cast<const uint4*>(wide + fld * kHubs + q * 64 + kb * 16 + 4 * k);
+#pragma unroll
+            for (int a = 0; a < ND; ++a)
+              x[a][k] = (int)(((c.x >> (7 * a)) & 127u) | ((c.y >> (7 * a)) & 127u) << 8 |
+                              ((c.z >> (7 * a)) & 127u) << 16 | ((c.w >> (7 * a)) & 127u) << 24);
+          }
+        }
+#pragma unroll
+        for (int a = 0; a < ND; ++a)
+#pragma unroll
+          for (int b = 0; b <= a; ++b)
+            hub.acc[a * (a + 1) / 2 + b] =
+                __builtin_amdgcn_mfma_i32_16x16x64_i8(x[a], x[b], hub.acc[a * (a + 1) / 2 + b], 0, 0, 0);
+        if (++hub.run == kGramRun) hub.flush(bins);
+      }
       __syncthreads();
     }
   }
   __syncthreads();
-  if (cur >= 0) c4_flush(bins, lut4, a4 + (int64_t)cur * 199, threadIdx.x, NT);
+  if (cur >= 0) give(cur);
 }
 
-// split[v * (ngran + 1) + i] = first entry of row v with id >= the start of
-// granule i of its graph (i = ngran: the row's end).
-__global__ void k_split(DevGraph G, int32_t gran, int32_t ngran, int32_t* __restrict__ split, const int32_t* st) {
+// split[v * (nblk + 1) + i] = first entry of row v with id >= the start of
+// block i of its graph (i = nblk: the row's end).
+__global__ void k_split(DevGraph G, int32_t nblk, int32_t* __restrict__ split, const int32_t* st) {
   if (st[kStatus] != 0) return;
-  const int64_t cols = ngran + 1, total = (int64_t)G.n * cols;
+  const int64_t cols = nblk + 1, total = (int64_t)G.n * cols;
   for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < total; k += (int64_t)gridDim.x * blockDim.x) {
     const int32_t v = (int32_t)(k / cols), i = (int32_t)(k % cols);
-    const int64_t id = (G.voff ? G.voff[G.gid[v]] : 0) + (int64_t)i * gran;
+    const int64_t id = (G.voff ? G.voff[G.gid[v]] : 0) + (int64_t)i * kBlock;
     int32_t lo = G.gs_off[v], hi = G.gs_off[v + 1];
-    if (i == ngran) {
+    if (i == nblk) {
       lo = hi;
     } else {
       while (lo < hi) {
@@ -811,103 +945,114 @@ __global__ void k_split(DevGraph G, int32_t gran, int32_t ngran, int32_t* __rest
 // Wedges and claws from the typed degrees of each vertex; P4s from those of
 // each edge's ends (the paths whose two ends coincide are taken off with the
 // triangles); diamonds from each edge's typed triangle counts.
+// Sums stay in registers (a wave's LDS atomics would all hit a handful of
+// addresses) and are added up at the end of a graph.
 template <bool K3, bool K4>
 __global__ __launch_bounds__(256) void k_local(DevGraph G, const uint16_t* __restrict__ lut3,
                                                const uint16_t* __restrict__ lut4, uint64_t* __restrict__ a3,
                                                uint64_t* __restrict__ a4, const uint32_t* __restrict__ T,
-                                               const int32_t* st, int32_t* __restrict__ queue, int32_t chunk) {
-  __shared__ u64 w3[6], w4[10], p4[27], h4[K4 ? 199 : 1];
+                                               const int32_t* st) {
+  constexpr int NT = 256, NS = (K3 ? 6 : 0) + (K4 ? 37 : 0), O4 = K3 ? 6 : 0;  // wedges, then claws and P4s
+  __shared__ u64 sums[NS], h4[K4 ? 199 : 1];
   __shared__ uint16_t lut[K4 ? 4096 : 1];
-  __shared__ int32_t sh_v;
   if (st[kStatus] != 0) return;
-  const int nt = 256;
-  auto clear = [&] {
-    for (int i = threadIdx.x; i < 27; i += nt) {
-      p4[i] = 0;
-      if (i < 6) w3[i] = 0;
-      if (i < 10) w4[i] = 0;
-    }
-    if (K4)
-      for (int i = threadIdx.x; i < 199; i += nt) h4[i] = 0;
-  };
-  clear();
-  if (K4)
-    for (int i = threadIdx.x; i < 4096; i += nt) lut[i] = lut4[i];
+  const int32_t n = G.n;
+  const int64_t items = (int64_t)n + (K4 ? G.np_off[n] : 0);
+  const int64_t chunk = (items + gridDim.x - 1) / gridDim.x;  // batch: one run of items per workgroup
+  if ((G.gid ? (int64_t)blockIdx.x * chunk : (int64_t)blockIdx.x * NT) >= items) return;
+  for (int i = threadIdx.x; i < NS; i += NT) sums[i] = 0;
+  if (K4) {
+    for (int i = threadIdx.x; i < 199; i += NT) h4[i] = 0;
+    for (int i = threadIdx.x; i < 4096; i += NT) lut[i] = lut4[i];
+  }
   __syncthreads();
-  auto flush = [&](int32_t g) {
-    if (K3 && threadIdx.x < 6) {
-      // pairs (a, b), a <= b, row-major
-      const int i = threadIdx.x, a = i < 3 ? 1 : i < 5 ? 2 : 3, b = i < 3 ? i + 1 : i < 5 ? i - 1 : 3;
-      gadd(&a3[(int64_t)g * 13 + lut3[edge_code<3>(0, 1, a) | edge_code<3>(0, 2, b)]], w3[i]);
+  u64 acc[NS];
+#pragma unroll
+  for (int i = 0; i < NS; ++i) acc[i] = 0;
+  auto flush = [&](int32_t g) {  // every thread
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+      u64 v = acc[i];
+#pragma unroll
+      for (int o = 32; o; o >>= 1) v += __shfl_xor(v, o);
+      if ((threadIdx.x & 63) == 0 && v) atomicAdd(&sums[i], v);
+      acc[i] = 0;
+    }
+    __syncthreads();
+    const int i = threadIdx.x;
+    if (K3 && i < 6) {  // pairs (a, b), a <= b, row-major
+      const int a = i < 3 ? 1 : i < 5 ? 2 : 3, b = i < 3 ? i + 1 : i < 5 ? i - 1 : 3;
+      gadd(&totals<13, kRep3>(G, a3, g)[lut3[edge_code<3>(0, 1, a) | edge_code<3>(0, 2, b)]], sums[i]);
     }
     if constexpr (K4) {
-      uint64_t* A = a4 + (int64_t)g * 199;
-      if (threadIdx.x < 10) {
-        int k = threadIdx.x, a = 1, b = 1, c = 1;
+      if (i < 10) {
+        int k = i, a = 1, b = 1, c = 1;
         for (; k; --k) {  // the k-th triple a <= b <= c
           if (c < 3) ++c;
           else if (b < 3) c = ++b;
           else a = b = c = a + 1;
         }
-        gadd(&A[lut[edge_code<4>(0, 1, a) | edge_code<4>(0, 2, b) | edge_code<4>(0, 3, c)]], w4[threadIdx.x]);
+        atomicAdd(&h4[lut[edge_code<4>(0, 1, a) | edge_code<4>(0, 2, b) | edge_code<4>(0, 3, c)]], sums[O4 + i]);
+      } else if (i < 37) {
+        const int e = i - 10;
+        atomicAdd(&h4[lut[edge_code<4>(0, 1, e / 9 + 1) | edge_code<4>(0, 2, (e / 3) % 3 + 1) |
+                          edge_code<4>(1, 3, e % 3 + 1)]], sums[O4 + i]);
       }
-      for (int i = threadIdx.x; i < 27; i += nt)
-        gadd(&A[lut[edge_code<4>(0, 1, i / 9 + 1) | edge_code<4>(0, 2, (i / 3) % 3 + 1) |
-                    edge_code<4>(1, 3, i % 3 + 1)]], p4[i]);
-      for (int i = threadIdx.x; i < 199; i += nt) gadd(&A[i], h4[i]);
+      __syncthreads();
+      for (int k = i; k < 199; k += NT) {
+        gadd(&totals<199, kRep4>(G, a4, g)[k], h4[k]);
+        h4[k] = 0;
+      }
     }
+    __syncthreads();
+    if (i < NS) sums[i] = 0;
+    __syncthreads();
   };
   auto vertex = [&](int32_t v) {
     const uint4 D = G.dt[v];
     const u64 d[4] = {0, D.x, D.y, D.z};
+    auto c2 = [](u64 x) { return x * (x - (x > 0)) / 2; };
     if constexpr (K3) {
       int k = 0;
 #pragma unroll
       for (int a = 1; a <= 3; ++a)
 #pragma unroll
-        for (int b = a; b <= 3; ++b, ++k) {
-          const u64 w = a == b ? d[a] * (d[a] - (d[a] > 0)) / 2 : d[a] * d[b];
-          if (w) atomicAdd(&w3[k], w);
-        }
+        for (int b = a; b <= 3; ++b, ++k) acc[k] += a == b ? c2(d[a]) : d[a] * d[b];
     }
     if constexpr (K4) {
-      auto c2 = [](u64 x) { return x * (x - (x > 0)) / 2; };
-      auto c3 = [](u64 x) {  // x (x - 1) (x - 2) / 6, x < 2^30: the division comes before the last product
+      auto c3 = [](u64 x) {  // x (x - 1) (x - 2) / 6, x < 2^30: divided before the last product
         if (x < 3) return (u64)0;
         const u64 y = x * (x - 1) / 2;
         return y % 3 == 0 ? y / 3 * (x - 2) : y * ((x - 2) / 3);
       };
-      int k = 0;
+      int k = O4;
 #pragma unroll
       for (int a = 1; a <= 3; ++a)
 #pragma unroll
         for (int b = a; b <= 3; ++b)
 #pragma unroll
-          for (int c = b; c <= 3; ++c, ++k) {
-            const u64 w = a == b && b == c ? c3(d[a]) : a == b ? c2(d[a]) * d[c] : b == c ? d[a] * c2(d[b])
-                                                                                         : d[a] * d[b] * d[c];
-            if (w) atomicAdd(&w4[k], w);
-          }
+          for (int c = b; c <= 3; ++c, ++k)
+            acc[k] += a == b && b == c ? c3(d[a]) : a == b ? c2(d[a]) * d[c] : b == c ? d[a] * c2(d[b])
+                                                                                       : d[a] * d[b] * d[c];
     }
   };
   auto edge = [&](int64_t e) {
     const uint32_t f = G.np_idx[e], t = f >> kTypeShift, tf = flip(t);
     const uint4 X = G.dt[G.np_row[e]], Y = G.dt[f & kIdMask];
-#pragma unroll
-    for (uint32_t p = 1; p <= 3; ++p) {
-      const u64 dx = typ(X, p) - (p == t);
-#pragma unroll
-      for (uint32_t q = 1; q <= 3; ++q) {
-        const u64 w = dx * (u64)(typ(Y, q) - (q == tf));
-        if (w) atomicAdd(&p4[(t - 1) * 9 + (p - 1) * 3 + (q - 1)], w);
-      }
-    }
     uint32_t c[9], s = 0;
 #pragma unroll
     for (int i = 0; i < 9; ++i) {
       c[i] = T[e * 9 + i];
       s += c[i];
     }
+#pragma unroll
+    for (uint32_t p = 1; p <= 3; ++p)
+#pragma unroll
+      for (uint32_t q = 1; q <= 3; ++q) {
+        const u64 w = (u64)(typ(X, p) - (p == t)) * (u64)(typ(Y, q) - (q == tf));
+#pragma unroll
+        for (uint32_t r = 1; r <= 3; ++r) acc[O4 + 10 + (r - 1) * 9 + (p - 1) * 3 + (q - 1)] += r == t ? w : 0ull;
+      }
     if (s < 2) return;
     const uint32_t base = edge_code<4>(0, 1, t);
 #pragma unroll
@@ -921,57 +1066,88 @@ __global__ __launch_bounds__(256) void k_local(DevGraph G, const uint16_t* __res
       }
     }
   };
-  const int32_t n = G.n;
-  const int64_t items = (int64_t)n + (K4 ? G.np_off[n] : 0);
-  int32_t cur = G.gid ? -1 : 0;
-  for (;;) {
-    __syncthreads();
-    if (threadIdx.x == 0) sh_v = atomicAdd(&queue[kQEdges], 1);
-    __syncthreads();
-    const int64_t i0 = (int64_t)sh_v * chunk;
-    if (i0 >= items) break;
-    const int64_t i1 = min(items, i0 + chunk);
-    for (int64_t a = i0; a < i1;) {
-      int64_t b = i1;
-      if (a < n && b > n) b = n;
-      if (G.gid) {  // up to the end of the graph
-        const int32_t g = G.gid[a < n ? a : (int64_t)G.np_row[a - n]];
-        const int64_t end = a < n ? G.voff[g + 1] : (int64_t)n + G.np_off[G.voff[g + 1]];
-        b = min(b, end);
-        if (g != cur) {
-          __syncthreads();
-          if (cur >= 0) flush(cur);
-          __syncthreads();
-          clear();
-          __syncthreads();
-          cur = g;
-        }
-      }
-      for (int64_t i = a + threadIdx.x; i < b; i += nt) {
-        if (i < n) vertex((int32_t)i);
-        else if constexpr (K4) edge(i - n);
-      }
-      a = b;
-    }
+  auto item = [&](int64_t i) {
+    if (i < n) vertex((int32_t)i);
+    else if constexpr (K4) edge(i - n);
+  };
+  if (!G.gid) {
+    for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i < items; i += (int64_t)gridDim.x * NT) item(i);
+    flush(0);
+    return;
   }
-  __syncthreads();
-  if (cur >= 0) flush(cur);
+  const int64_t i1 = min(items, (int64_t)(blockIdx.x + 1) * chunk);
+  int32_t cur = -1;
+  for (int64_t a = (int64_t)blockIdx.x * chunk; a < i1;) {  // up to the end of a graph's vertices or edges
+    const int32_t g = G.gid[a < n ? a : (int64_t)G.np_row[a - n]];
+    const int64_t b = min(i1, a < n ? G.voff[g + 1] : (int64_t)n + G.np_off[G.voff[g + 1]]);
+    if (g != cur) {
+      if (cur >= 0) flush(cur);
+      cur = g;
+    }
+    for (int64_t i = a + threadIdx.x; i < b; i += NT) item(i);
+    a = b;
+  }
+  flush(cur);
 }
 
 // ================================================================= solve ==
-// out[c] = sum of coef * N over row c of the inverse (in CSR form), one
-// workgroup per graph and block of classes.  A negative count is a failed
-// self-check; nothing is written by k_solve_write then.
+// out[c] = sum of coef * N over row c of the inverse (in CSR form), eight lanes
+// per class.  A negative count is a failed self-check, and nothing is written
+// then.  One graph: one workgroup computes, checks and writes.
+constexpr int kSolve1 = 1024;
+template <class P>
+__device__ __forceinline__ int64_t solve_row(const P* acc, const SubInverse& M, int32_t c, int l8) {
+  int64_t s = 0;
+  for (int32_t k = M.off[c] + l8, e = M.off[c + 1]; k < e; k += 8) s += (int64_t)M.coef[k] * (int64_t)acc[M.cls[k]];
+#pragma unroll
+  for (int o = 4; o; o >>= 1) s += __shfl_xor(s, o);
+  return s;
+}
+__global__ __launch_bounds__(kSolve1) void k_solve_one(const uint64_t* __restrict__ acc, int32_t copies,
+                                                       const SubInverse M, uint64_t* __restrict__ out, int32_t C,
+                                                       int32_t* st) {
+  constexpr int kRows = 2;  // classes per eight lanes: C <= kSolve1 / 8 * kRows
+  __shared__ u64 sum[256];
+  if (st[kStatus] != 0) return;
+  if (threadIdx.x < 256) sum[threadIdx.x] = 0;
+  __syncthreads();
+  const int32_t c0 = threadIdx.x & 255;
+  if (c0 < C) {
+    u64 t = 0;
+    for (int32_t r = threadIdx.x >> 8; r < copies; r += kSolve1 / 256) t += acc[(int64_t)r * C + c0];
+    if (t) atomicAdd(&sum[c0], t);
+  }
+  __syncthreads();
+  const int l8 = threadIdx.x & 7;
+  int64_t v[kRows];
+  bool bad = false;
+#pragma unroll
+  for (int i = 0; i < kRows; ++i) {
+    const int32_t c = (int32_t)(threadIdx.x >> 3) + i * (kSolve1 / 8);
+    v[i] = c < C ? solve_row(sum, M, c, l8) : 0;
+    bad |= v[i] < 0;
+  }
+  if (__syncthreads_or(bad)) {
+    if (threadIdx.x == 0) atomicMin(&st[kStatus], MOTIF_EINTERNAL);
+    return;
+  }
+#pragma unroll
+  for (int i = 0; i < kRows; ++i) {
+    const int32_t c = (int32_t)(threadIdx.x >> 3) + i * (kSolve1 / 8);
+    if (c < C && l8 == 0) out[c] = (uint64_t)v[i];
+  }
+}
 __global__ __launch_bounds__(256) void k_solve(const uint64_t* __restrict__ acc, const SubInverse M,
                                                uint64_t* __restrict__ out, int32_t C, int64_t total, int32_t* st) {
   if (st[kStatus] != 0) return;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
+  const int64_t stride = (int64_t)gridDim.x * 32;
+  for (int64_t i = blockIdx.x * (int64_t)32 + (threadIdx.x >> 3); i < total; i += stride) {
     const int32_t c = (int32_t)(i % C);
-    const uint64_t* a = acc + (i - c);
-    int64_t s = 0;
-    for (int32_t k = M.off[c], e = M.off[c + 1]; k < e; ++k) s += (int64_t)M.coef[k] * (int64_t)a[M.cls[k]];
-    if (s < 0) atomicMin(&st[kStatus], MOTIF_EINTERNAL);
-    out[i] = (uint64_t)s;
+    const int64_t s = solve_row(acc + (i - c), M, c, threadIdx.x & 7);
+    if ((threadIdx.x & 7) == 0) {
+      if (s < 0) atomicMin(&st[kStatus], MOTIF_EINTERNAL);
+      out[i] = (uint64_t)s;
+    }
   }
 }
 
@@ -993,28 +1169,25 @@ constexpr size_t kPlaneBytes = size_t(64) << 20;  // adjacency slices of k_tri_b
 
 struct CountPlan {
   bool wide;                 // degrees may reach 2^21
-  int32_t gran, ngran;
+  int32_t nblk;              // blocks of ids of k_wedge_top
   bool split;
   int64_t D, words;          // bound on d+ and the words of an adjacency row
-  int slices;                // workgroups of k_tri_big
-  bool top;                  // some u may have more visits than a wave takes
+  int slices;                // adjacency slices of k_tri_big in global memory (0: none can be needed)
 };
 
 CountPlan count_plan(int64_t n, int64_t m, int64_t maxn) {
   CountPlan c{};
   const int64_t mg = maxn > 0 ? maxn : n;
   c.wide = std::min(mg - 1, m) >= (int64_t(1) << 21);
-  c.gran = c.wide ? top_granule<true>() : top_granule<false>();
-  c.ngran = (int32_t)std::max<int64_t>(1, (mg + c.gran - 1) / c.gran);
-  c.split = n * (c.ngran + 1) <= kSplitCap;
+  c.nblk = (int32_t)std::max<int64_t>(1, (mg + kBlock - 1) / kBlock);
+  c.split = n * (c.nblk + 1) <= kSplitCap;
   // N+(x) has at most sqrt(2 m*) entries: its members all have degree d(x) or more
   int64_t r = 1;
   while (r * r <= 2 * m) ++r;
   c.D = std::max<int64_t>(1, std::min(mg, r));
   c.words = (c.D + 63) / 64;
   const size_t per = (size_t)c.D * (size_t)c.words * 16;
-  c.slices = c.D > kTriD ? (int)std::max<size_t>(1, std::min<size_t>(256, kPlaneBytes / per)) : 0;
-  c.top = 2 * m > 192;
+  c.slices = c.D > kPlaneD ? (int)std::max<size_t>(1, std::min<size_t>(256, kPlaneBytes / per)) : 0;
   return c;
 }
 
@@ -1024,8 +1197,8 @@ size_t count_bytes(int64_t n, int64_t m, int64_t maxn, bool k4) {
   auto al = [](size_t b) { return (b + 255) & ~size_t(255); };
   if (!k4) return 0;
   const CountPlan c = count_plan(n, m, maxn);
-  size_t b = al(sizeof(uint32_t) * 9 * (size_t)(m + 1)) + 2 * al(sizeof(int32_t) * (size_t)(n + 1));
-  if (c.split) b += al(sizeof(int32_t) * (size_t)n * (c.ngran + 1));
+  size_t b = al(sizeof(uint32_t) * 9 * (size_t)(m + 1)) + 4 * al(sizeof(int32_t) * (size_t)(n + 1));
+  if (c.split) b += al(sizeof(int32_t) * (size_t)n * (c.nblk + 1));
   b += al((size_t)c.slices * (size_t)c.D * (size_t)c.words * 16 + 16);
   return b;
 }
@@ -1036,62 +1209,85 @@ void enqueue_counts(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_t* a4, 
   const int64_t n = g.n, m = (g.gs_cap - 1) / 2;
   if (n == 0) return;
   const int cus = p.num_cus;
-  int32_t* big = g.tmp_n;
-  // enough chunks that every wave of the chip gets several, at most 16 vertices
-  const int32_t chunk = (int32_t)std::max<int64_t>(1, std::min<int64_t>(16, n / (cus * 32)));
-  const unsigned tri_grid = grid_of(n, g.gid ? kBatchChunk : 4 * chunk, cus * 6);
+  const CountPlan c = count_plan(n, m, g.max_graph_n);
+  // lists in words that the build is done with (at most 2 m / 17 and 2 m / 65
+  // vertices have a degree of 17 or 65)
+  Lists L{};
+  L.v[kTri16] = g.tmp_n;
+  L.v[kTri64] = g.tmp_n2;
+  L.v[kTriBig] = g.tmp_n3;
+  const unsigned cgrid = std::max(grid_of(n, 64, cus * 4), grid_of(n, kClassify, 1 << 20));
+  // workgroups for a list of at most `most` vertices, `per` at a time
+  auto list_grid = [&](int64_t most, int per, int wgs) { return dim3(grid_of(most, per, (int64_t)cus * wgs)); };
+  // a vertex of tier d has at least d higher neighbours of at least its degree
+  const int64_t n16 = std::min(n, m), n64 = std::min(n, 2 * m / 17), nbig = c.D > 64 ? std::min(n, 2 * m / 65) : 0;
   if (!a4) {
-    hipLaunchKernelGGL((k_tri<false>), dim3(grid_of(n, g.gid ? kBatchChunk : 4 * chunk, cus * 8)), dim3(256), 0, s, g,
-                       T.lut[3], T.lut[4], a3, nullptr, nullptr, p.status, queue, chunk, big);
-    hipLaunchKernelGGL((k_tri_big<false>), dim3(cus), dim3(512), 0, s, g, T.lut[3], T.lut[4], a3, nullptr, nullptr,
-                       p.status, queue, big, nullptr, 0, 0);
+    hipLaunchKernelGGL((k_classify<false>), dim3(cgrid), dim3(256), 0, s, g, L, queue, p.status);
+    hipLaunchKernelGGL((k_tri<16, false>), list_grid(n16, 16, 8), dim3(256), 0, s, g, T.lut[3], T.lut[4], a3, nullptr,
+                       nullptr, p.status, queue, L.v[kTri16]);
+    if (c.D > 16)
+      hipLaunchKernelGGL((k_tri<64, false>), list_grid(n64, 4, 8), dim3(256), 0, s, g, T.lut[3], T.lut[4], a3, nullptr,
+                         nullptr, p.status, queue, L.v[kTri64]);
+    if (nbig > 0)
+      hipLaunchKernelGGL((k_tri_big<false>), list_grid(nbig, 1, 3), dim3(512), 0, s, g, T.lut[3], T.lut[4], a3,
+                         nullptr, nullptr, p.status, queue, L.v[kTriBig], nullptr, 0, 0);
     hipLaunchKernelGGL((k_local<true, false>), dim3(grid_of(n, 256, cus * 4)), dim3(256), 0, s, g, T.lut[3], T.lut[4],
-                       a3, nullptr, nullptr, p.status, queue, 256);
+                       a3, nullptr, nullptr, p.status);
     return;
   }
-  const CountPlan c = count_plan(n, m, g.max_graph_n);
   uint32_t* Te = p.arena.take<uint32_t>(9 * (size_t)(m + 1));
-  int32_t* mid = p.arena.take<int32_t>((size_t)n + 1);
-  int32_t* top = p.arena.take<int32_t>((size_t)n + 1);
-  int32_t* split = c.split ? p.arena.take<int32_t>((size_t)n * (c.ngran + 1)) : nullptr;
+  for (int l : {kWedge16, kWedge64, kWedge256, kWedgeTop}) L.v[l] = p.arena.take<int32_t>((size_t)n + 1);
+  int32_t* split = c.split ? p.arena.take<int32_t>((size_t)n * (c.nblk + 1)) : nullptr;
   u64* planes = p.arena.take<u64>((size_t)c.slices * (size_t)c.D * (size_t)c.words * 2 + 1);
   enqueue_zero(Te, sizeof(uint32_t) * 9 * (size_t)(m + 1), s);
-  hipLaunchKernelGGL((k_tri<true>), dim3(tri_grid), dim3(256), 0, s, g, T.lut[3], T.lut[4], a3, a4, Te, p.status,
-                     queue, chunk, big);
-  if (c.slices > 0)
-    hipLaunchKernelGGL((k_tri_big<true>), dim3(std::min(c.slices, cus)), dim3(512), 0, s, g, T.lut[3], T.lut[4], a3,
-                       a4, Te, p.status, queue, big, planes, c.D, c.words);
-  hipLaunchKernelGGL((k_wedge<64, 8>), dim3(grid_of(n, g.gid ? kBatchChunk : 4 * chunk, cus * 8)), dim3(256), 0, s, g,
-                     T.lut[4], a4, p.status, queue, chunk, mid, top);
-  if (c.top) {
-    hipLaunchKernelGGL((k_wedge<256, 12>), dim3(cus * 3), dim3(256), 0, s, g, T.lut[4], a4, p.status, queue, 1, mid,
-                       top);
+  hipLaunchKernelGGL((k_classify<true>), dim3(cgrid), dim3(256), 0, s, g, L, queue, p.status);
+  hipLaunchKernelGGL((k_tri<16, true>), list_grid(n16, 16, 6), dim3(256), 0, s, g, T.lut[3], T.lut[4], a3, a4, Te,
+                     p.status, queue, L.v[kTri16]);
+  if (c.D > 16)
+    hipLaunchKernelGGL((k_tri<64, true>), list_grid(n64, 4, 6), dim3(256), 0, s, g, T.lut[3], T.lut[4], a3, a4, Te,
+                       p.status, queue, L.v[kTri64]);
+  if (nbig > 0)  // a workgroup whose x need a global slice has its own
+    hipLaunchKernelGGL((k_tri_big<true>), dim3(std::min<unsigned>(c.slices ? c.slices : 512, grid_of(nbig, 1, cus * 2))),
+                       dim3(512), 0, s, g, T.lut[3], T.lut[4], a3, a4, Te, p.status, queue, L.v[kTriBig], planes, c.D,
+                       c.words);
+  hipLaunchKernelGGL((k_wedge<16, 7>), list_grid(n16, 16, 6), dim3(256), 0, s, g, T.lut[4], a4, p.status, queue,
+                     L.v[kWedge16]);
+  if (2 * m > kCap16)
+    hipLaunchKernelGGL((k_wedge<64, 9>), list_grid(n16, 4, 6), dim3(256), 0, s, g, T.lut[4], a4, p.status, queue,
+                       L.v[kWedge64]);
+  if (2 * m > kCap64)
+    hipLaunchKernelGGL((k_wedge<256, 12>), list_grid(n16, 1, 3), dim3(256), 0, s, g, T.lut[4], a4, p.status, queue,
+                       L.v[kWedge256]);
+  if (m > 127) {  // over 127 lower neighbours, or over kCap256 visits
     if (split)
-      hipLaunchKernelGGL(k_split, dim3(grid_of(n * (c.ngran + 1), 256, 65536)), dim3(256), 0, s, g, c.gran, c.ngran,
-                         split, p.status);
+      hipLaunchKernelGGL(k_split, dim3(grid_of(n * (c.nblk + 1), 256, 65536)), dim3(256), 0, s, g, c.nblk, split,
+                         p.status);
+    const dim3 tg = list_grid(n * c.nblk, 1, 1);
     if (c.wide)
-      hipLaunchKernelGGL((k_wedge_top<true>), dim3(cus), dim3(kTopThreads), 0, s, g, T.lut[4], a4, p.status, queue,
-                         top, split, c.ngran);
+      hipLaunchKernelGGL((k_wedge_top<5>), tg, dim3(kTopThreads), 0, s, g, T.lut[4], a4, p.status, queue,
+                         L.v[kWedgeTop], split, c.nblk);
     else
-      hipLaunchKernelGGL((k_wedge_top<false>), dim3(cus), dim3(kTopThreads), 0, s, g, T.lut[4], a4, p.status, queue,
-                         top, split, c.ngran);
+      hipLaunchKernelGGL((k_wedge_top<3>), tg, dim3(kTopThreads), 0, s, g, T.lut[4], a4, p.status, queue,
+                         L.v[kWedgeTop], split, c.nblk);
   }
-  const int32_t lchunk = 1024;
-  const dim3 lgrid(grid_of(n + m, lchunk, cus * 8));
+  const dim3 lgrid(grid_of(n + m, 256, cus * 4));
   if (a3)
-    hipLaunchKernelGGL((k_local<true, true>), lgrid, dim3(256), 0, s, g, T.lut[3], T.lut[4], a3, a4, Te, p.status,
-                       queue, lchunk);
+    hipLaunchKernelGGL((k_local<true, true>), lgrid, dim3(256), 0, s, g, T.lut[3], T.lut[4], a3, a4, Te, p.status);
   else
-    hipLaunchKernelGGL((k_local<false, true>), lgrid, dim3(256), 0, s, g, T.lut[3], T.lut[4], a3, a4, Te, p.status,
-                       queue, lchunk);
+    hipLaunchKernelGGL((k_local<false, true>), lgrid, dim3(256), 0, s, g, T.lut[3], T.lut[4], a3, a4, Te, p.status);
 }
 
 void enqueue_solve(int k, const uint64_t* acc, uint64_t* tmp, uint64_t* out, int64_t ngraphs, int32_t* status,
                    hipStream_t s) {
   const int C = num_classes(k);
   const int64_t total = ngraphs * C;
-  hipLaunchKernelGGL(k_solve, dim3(grid_of(total, 256, 65536)), dim3(256), 0, s, acc, dev_tables().inv[k], tmp, C,
-                     total, status);
+  if (ngraphs == 1) {
+    hipLaunchKernelGGL(k_solve_one, dim3(1), dim3(kSolve1), 0, s, acc, k == 3 ? kRep3 : kRep4,
+                       dev_tables().inv[k], out, C, status);
+    return;
+  }
+  hipLaunchKernelGGL(k_solve, dim3(grid_of(total, 32, 65536)), dim3(256), 0, s, acc, dev_tables().inv[k], tmp, C, total,
+                     status);
   hipLaunchKernelGGL(k_solve_write, dim3(grid_of(total, 256, 65536)), dim3(256), 0, s, tmp, out, total, status);
 }
 

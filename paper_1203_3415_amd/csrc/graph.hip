@@ -899,7 +899,10 @@ DevGraph enqueue_build(Pipeline& p, const BuildInput& in, hipStream_t s, hipEven
   g.np_row = np_row;
   g.nm_idx = nm_idx;
   g.dt = dt;
+  g.deg = deg;
   g.tmp_n = fill;
+  g.tmp_n2 = flags;
+  g.tmp_n3 = hrow;
   if (n == 0) {
     if (graph_ready) *ready_ok = hipEventRecord(graph_ready, s) == hipSuccess;
     return g;

@@ -48,7 +48,9 @@ struct DevGraph {
   const int32_t* np_row = nullptr;  // [m*] row of each N+ entry
   const uint32_t* nm_idx = nullptr; // [m*] N-(v): neighbours of lower rank, row v at gs_off[v] - np_off[v]
   const uint4* dt = nullptr;        // [n] neighbours of type 1, 2 and 3, and d*
-  int32_t* tmp_n = nullptr;         // [n+1] scratch, free once the graph is built
+  const int32_t* deg = nullptr;     // [n] d*
+  // scratch, free once the graph is built: n + 1, 2 m + 1 and 2 m + 1 words
+  int32_t *tmp_n = nullptr, *tmp_n2 = nullptr, *tmp_n3 = nullptr;
   int64_t gs_cap = 0;               // 2m + 1 >= entries of G* + 1
 };
 
@@ -222,8 +224,8 @@ void enqueue_census(Pipeline& p, const DevGraph& g, int k, uint64_t* acc, uint64
                     bool use_wpool, hipEvent_t side_start = nullptr, bool* side_ok = nullptr,
                     const BigTables* pre = nullptr, uint64_t* acc3 = nullptr);
 // The k = 3, 4 censuses by subgraph copies (counts.hip): copies of every class
-// into a3[ngraphs * 13] and / or a4[ngraphs * 199] (null: not wanted; both and
-// the 64 queue words zeroed by the caller), then the induced counts into out
+// into a3 and / or a4 (acc_words each; null: not wanted; both and the 64 queue
+// words zeroed by the caller), then the induced counts into out
 // through tmp (same size), written only if none is negative.
 size_t count_bytes(int64_t n, int64_t m, int64_t maxn, bool k4);
 void enqueue_counts(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_t* a4, int32_t* queue, hipStream_t s);
@@ -231,6 +233,13 @@ void enqueue_solve(int k, const uint64_t* acc, uint64_t* tmp, uint64_t* out, int
                    hipStream_t s);
 // Whether k's census under tuning t counts subgraph copies.
 inline bool by_copies(int k, const Tuning& t) { return k == 3 || (k == 4 && t.heavy == 1); }
+// Copies of a single graph's totals (a workgroup adds to one of them).
+constexpr int kRep3 = 16, kRep4 = 64;
+// Words of the accumulators of a census of k over ngraphs graphs.
+inline size_t acc_words(int k, int64_t ngraphs, const Tuning& t) {
+  const int64_t C = k == 3 ? 13 : k == 4 ? 199 : 9364;
+  return (size_t)(C * (by_copies(k, t) && ngraphs == 1 ? (k == 3 ? kRep3 : kRep4) : ngraphs));
+}
 
 // The last step alone: subgraph copies to induced counts, or (per-anchor
 // totals) out[i] = acc[i] / multiplicity, after a check that every remainder
