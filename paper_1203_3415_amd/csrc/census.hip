@@ -2083,7 +2083,7 @@ size_t pipeline_bytes(int64_t N, int64_t M, int32_t G, bool batch, int k, int nu
   auto al = [](size_t b) { return (b + 255) & ~size_t(255); };
   size_t b = build_bytes(N, M, G, batch);
   const bool reuse = k == 5 && t.heavy == 1;
-  if (by_copies(k, t)) b += count_bytes(N, M, maxn > 0 ? maxn : N, k == 4);
+  if (by_copies(k, t)) b += count_bytes(N, M, maxn > 0 ? maxn : N, batch, k == 4);
   if (reuse)
     b += al(sizeof(int32_t) * (N + 1)) + al(64 * sizeof(int32_t)) +
          al(sizeof(uint32_t) * kBigRow * (size_t)(maxn > 0 ? maxn : N) * grid_size(t, num_cus));

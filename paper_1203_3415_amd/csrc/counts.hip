@@ -41,11 +41,12 @@ constexpr uint32_t kNone = 0xFFFFFFFFu;
 // of a census (64 int32).  Units are dealt out by position, not pulled from a
 // counter: a pull is an atomic on one address, about 25 ns each however many
 // waves wait for it, which was most of these kernels' time on 10^4 vertices.
-enum ListId : int { kTri16 = 0, kTri64 = 1, kTriBig = 2, kWedge16 = 3, kWedge64 = 4, kWedge256 = 5, kWedgeTop = 6,
-                    kLists = 7 };
+enum ListId : int { kTri16 = 0, kTri64 = 1, kTri128 = 2, kTriBig = 3, kWedge16 = 4, kWedge64 = 5, kWedge256 = 6,
+                    kWedgeTop = 7, kWedgeHuge = 8, kLists = 9 };
 struct Lists {
   int32_t* v[kLists];
 };
+constexpr int kHugeD = 1000;  // lower neighbours from which a vertex's wedges are cut by row entries too
 constexpr int kCap16 = 96, kCap64 = 384, kCap256 = 3072;  // visits of a vertex in the three wedge hashes
 
 __device__ __forceinline__ uint32_t hash_mul(uint32_t x, int bits) { return (x * 2654435761u) >> (32 - bits); }
@@ -72,11 +73,11 @@ __device__ __forceinline__ uint32_t typ(const uint4& d, uint32_t t) { return t =
 // count per typed triangle (27), and for k = 4 the typed degrees of its three
 // corners (paws), the typed triangle counts T of its three edges (T[e][3 p +
 // q], p, q the types of the third vertex seen from the lower and the higher
-// end, less one) and one bit per type in a 64 x 64 adjacency of N+(x), from
+// end, less one) and one bit per type in an adjacency matrix of N+(x), from
 // which the K4s above x are read off as the common bits of two rows.
 // Sixteen lanes per x with at most 16 higher neighbours (four x per wave: the
 // chain of loads before the first row is the bulk of a small x), one wave up
-// to 64 (k_tri), one workgroup beyond (k_tri_big).
+// to 64 and up to 128 (k_tri), one workgroup beyond (k_tri_big).
 
 // Workgroup counters of the triangle kernels and their flush to one graph: by
 // class in LDS first, so that a workgroup makes one global addition per class.
@@ -169,12 +170,16 @@ __device__ __forceinline__ void each4(const uint32_t* p, int32_t r, int32_t step
 // workgroup, between barriers, when all of a graph's vertices that this
 // workgroup takes are done and at the end.  A single graph's list is dealt out
 // entry by entry; a batch's in one segment per workgroup, cut into runs of one
-// graph, so that a flush comes once per graph and segment or so.
-template <int NT, class One, class Flush>
+// graph, so that a flush comes once per graph and segment or so.  WHOLE: a wave
+// holds several groups and one() needs all of it: groups past the end of the
+// list join in with one(-1).
+template <int NT, bool WHOLE, class One, class Flush>
 __device__ __forceinline__ void for_listed(const DevGraph& G, const int32_t* list, int32_t count, int groups, int my,
                                            One&& one, Flush&& flush) {
   if (!G.gid) {
-    for (int32_t i = (int32_t)blockIdx.x * groups + my; i < count; i += (int32_t)gridDim.x * groups) one(list[i]);
+    const int32_t step = (int32_t)gridDim.x * groups;
+    for (int32_t i = (int32_t)blockIdx.x * groups + my; WHOLE ? __ballot(i < count) != 0ull : i < count; i += step)
+      one(!WHOLE || i < count ? list[i] : -1);
     __syncthreads();
     flush(0);
     return;
@@ -196,7 +201,8 @@ __device__ __forceinline__ void for_listed(const DevGraph& G, const int32_t* lis
       __syncthreads();
       cur = g;
     }
-    for (int32_t k = s0 + my; k < e; k += groups) one(list[k]);
+    for (int32_t k = s0 + my; WHOLE ? __ballot(k < e) != 0ull : k < e; k += groups)
+      one(!WHOLE || k < e ? list[k] : -1);
     s0 = e;
   }
   __syncthreads();
@@ -222,16 +228,22 @@ __global__ __launch_bounds__(256) void k_classify(DevGraph G, Lists L, int32_t* 
   for (int64_t v = v0 + (threadIdx.x >> 3); v < v1; v += 32) {
     int lt = 15, lw = 15;
     const int32_t pa = G.np_off[v], pb = G.np_off[v + 1], d = pb - pa;
-    if (d >= 2) lt = d <= 16 ? kTri16 : d <= 64 ? kTri64 : kTriBig;
+    if (d >= 2) lt = d <= 16 ? kTri16 : d <= 64 ? kTri64 : d <= 128 ? kTri128 : kTriBig;
     if (K4) {
       const int32_t ma = G.gs_off[v] - pa, dm = G.gs_off[v + 1] - pb - ma;
       if (dm > 127) {
-        lw = kWedgeTop;
+        lw = dm > kHugeD ? kWedgeHuge : kWedgeTop;
       } else if (dm >= 2) {
         int32_t vis = 0;
-        for (int32_t i = l8; i < dm; i += 8) {
-          const uint32_t w = G.nm_idx[ma + i] & kIdMask;
-          vis += min(G.gs_off[w + 1] - G.gs_off[w], kCap256 + 1);
+        for (int32_t i = l8; i < dm; i += 32) {  // (past the end: the last one, not counted)
+          uint32_t w[4];
+#pragma unroll
+          for (int k = 0; k < 4; ++k) w[k] = G.nm_idx[ma + min(i + 8 * k, dm - 1)] & kIdMask;
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const int32_t dw = min(G.deg[w[k]], kCap256 + 1);
+            vis += i + 8 * k < dm ? dw : 0;
+          }
         }
 #pragma unroll
         for (int o = 4; o; o >>= 1) vis += __shfl_xor(vis, o);
@@ -253,132 +265,207 @@ __global__ __launch_bounds__(256) void k_classify(DevGraph G, Lists L, int32_t* 
   }
 }
 
-template <int GS, bool K4>
+// GS lanes per x of at most D higher neighbours.  The triangles found are
+// queued per wave and worked off by full waves: a pass over 64 entries finds
+// one or two, and counting those on the spot kept 62 lanes waiting each time
+// (n = 10^5 graph, k = 4: 343 us for the x of at most 64 neighbours).
+template <int GS, int D, bool K4>
 __global__ __launch_bounds__(256) void k_tri(DevGraph G, const uint16_t* __restrict__ lut3,
                                              const uint16_t* __restrict__ lut4, uint64_t* __restrict__ a3,
                                              uint64_t* __restrict__ a4, uint32_t* __restrict__ T, const int32_t* st,
                                              const int32_t* __restrict__ nlist, const int32_t* __restrict__ vlist) {
-  constexpr int NGR = 256 / GS, H = 4 * GS, HB = GS == 16 ? 6 : 8, LPR = GS / 4;  // groups, hash, lanes per row
+  constexpr int NGR = 256 / GS, HB = D == 16 ? 6 : D == 64 ? 8 : 9, H = 1 << HB, LPR = GS / 4;  // groups, hash, lanes per row
+  constexpr int DM = (D + GS - 1) / GS, W = (D + 63) / 64;  // members per lane, words of an adjacency row
+  constexpr int QC = 192;                                   // queued triangles per wave
+  static_assert(H == 4 * D && D <= 128, "hash load; seven bits per count");
   __shared__ u64 s_tri[27], s_paw[K4 ? 243 : 1], s_kh[K4 ? 199 : 1], s_h3[13];
   __shared__ uint16_t lut[K4 ? 4096 : 1];
   __shared__ uint32_t s_key[NGR][H];
   __shared__ uint8_t s_at[NGR][H];
-  __shared__ uint32_t s_list[NGR][GS];
-  __shared__ u64 s_T[K4 ? NGR : 1][GS];                            // nine 7-bit counters per member of N+(x)
-  __shared__ u64 s_a1[K4 ? NGR : 1][GS], s_a2[K4 ? NGR : 1][GS];  // adjacency of N+(x), a bit plane per arc
+  __shared__ uint32_t s_list[NGR][D];
+  __shared__ u64 s_T[K4 ? NGR : 1][D];                                     // nine 7-bit counters per member of N+(x)
+  __shared__ u64 s_a1[K4 ? NGR : 1][D * W], s_a2[K4 ? NGR : 1][D * W];     // adjacency of N+(x), a bit plane per arc
+  __shared__ int32_t s_x[NGR];
+  __shared__ uint32_t s_q[K4 ? 4 : 1][QC];
+  __shared__ int32_t s_qt[K4 ? 4 : 1][QC];
   if (st[kStatus] != 0) return;
-  const int32_t count = nlist[GS == 16 ? kTri16 : kTri64];
+  const int32_t count = nlist[D == 16 ? kTri16 : D == 64 ? kTri64 : kTri128];
   if ((int64_t)blockIdx.x * (G.gid ? 1 : NGR) >= count) return;
   const TriBins<K4> bins{s_tri, s_paw, s_kh, s_h3};
-  const int gr = threadIdx.x / GS, lane = threadIdx.x % GS, lane0 = (threadIdx.x & 63) - lane;
+  const int wv = threadIdx.x >> 6, wl = threadIdx.x & 63;
+  const int gr = threadIdx.x / GS, lane = threadIdx.x % GS, lane0 = wl - lane;
   bins.clear(threadIdx.x, 256);
   if (K4)
     for (int i = threadIdx.x; i < 4096; i += 256) lut[i] = lut4[i];
   for (int i = lane; i < H; i += GS) s_key[gr][i] = kNone;
-  if (K4) {
-    s_T[gr][lane] = 0;
-    s_a1[gr][lane] = 0;
-    s_a2[gr][lane] = 0;
-  }
+  if (K4)
+    for (int i = lane; i < D; i += GS) {
+      s_T[gr][i] = 0;
+      for (int w = 0; w < W; ++w) s_a1[gr][i * W + w] = s_a2[gr][i * W + w] = 0;
+    }
   __syncthreads();
   uint32_t* key = s_key[gr];
   uint8_t* at = s_at[gr];
   uint32_t* list = s_list[gr];
   u64 *Tl = s_T[K4 ? gr : 0], *A1 = s_a1[K4 ? gr : 0], *A2 = s_a2[K4 ? gr : 0];
-
-  auto one = [&](int32_t x) {  // the same x on the GS lanes of a group
-    const int32_t xa = G.np_off[x], d = G.np_off[x + 1] - xa;  // 2 .. GS
-    // member `lane` of N+(x): entry, hash slot, row
-    uint32_t e = 0, hs = 0;
-    int32_t ra = 0, len = 0;
-    if (lane < d) {
-      e = G.np_idx[xa + lane];
-      const uint32_t y = e & kIdMask;
-      list[lane] = e;
-      hs = hash_mul(y, HB);
-      while (atomicCAS(&key[hs], kNone, y) != kNone) hs = (hs + 1) & (H - 1);
-      at[hs] = (uint8_t)lane;
-      ra = G.np_off[y];
-      len = G.np_off[y + 1] - ra;
+  int qn = 0;  // the same on every lane of the wave
+  // queue entry: group of the wave, j, k (members y and z), type of z seen
+  // from y; and the place of z in N+(y)
+  auto drain = [&] {
+    if constexpr (K4) {
+      wave_sync();
+      for (int i = wl; i < qn; i += 64) {
+        const uint32_t q = s_q[wv][i];
+        const int g = wv * (64 / GS) + (int)(q >> 16), j = (int)(q & 127u), k = (int)((q >> 7) & 127u);
+        const uint32_t yz = (q >> 14) & 3u, ey = s_list[g][j], ez = s_list[g][k];
+        const uint32_t xy = ey >> kTypeShift, xz = ez >> kTypeShift;
+        atomicAdd(&T[(int64_t)s_qt[wv][i] * 9 + (flip(xy) - 1) * 3 + (flip(xz) - 1)], 1u);
+        tri_add<true>(bins, (xy - 1) * 9 + (xz - 1) * 3 + (yz - 1), G.dt[s_x[g]], G.dt[ey & kIdMask],
+                      G.dt[ez & kIdMask]);
+        atomicAdd(&s_T[g][j], 1ull << (7 * ((xz - 1) * 3 + (yz - 1))));
+        atomicAdd(&s_T[g][k], 1ull << (7 * ((xy - 1) * 3 + (flip(yz) - 1))));
+        if (yz & 1u) atomicOr(&s_a1[g][j * W + (k >> 6)], 1ull << (k & 63));
+        if (yz & 2u) atomicOr(&s_a2[g][j * W + (k >> 6)], 1ull << (k & 63));
+      }
+      wave_sync();
     }
-    const uint4 dx = K4 ? G.dt[x] : make_uint4(0, 0, 0, 0);
+    qn = 0;
+  };
+
+  auto one = [&](int32_t x) {  // the same x on the GS lanes of a group; x < 0: none.  Called by whole waves.
+    int32_t xa = 0, d = 0;
+    if (x >= 0) {
+      xa = G.np_off[x];
+      d = G.np_off[x + 1] - xa;  // 2 .. D
+      if (K4 && lane == 0) s_x[gr] = x;
+    }
+    // members lane, lane + GS .. of N+(x): entry, hash slot, row
+    uint32_t e[DM], hs[DM];
+    int32_t ra[DM], len[DM];
+#pragma unroll
+    for (int u = 0; u < DM; ++u) {
+      const int32_t i = lane + u * GS;
+      e[u] = hs[u] = 0;
+      ra[u] = len[u] = 0;
+      if (i < d) {
+        e[u] = G.np_idx[xa + i];
+        const uint32_t y = e[u] & kIdMask;
+        list[i] = e[u];
+        hs[u] = hash_mul(y, HB);
+        while (atomicCAS(&key[hs[u]], kNone, y) != kNone) hs[u] = (hs[u] + 1) & (H - 1);
+        at[hs[u]] = (uint8_t)i;
+        ra[u] = G.np_off[y];
+        len[u] = G.np_off[y + 1] - ra[u];
+      }
+    }
     wave_sync();
     const int32_t sub = lane / LPR, lr = lane % LPR;
-    for (int32_t j0 = 0; j0 < d; j0 += 4) {
+    for (int32_t j0 = 0; __ballot(j0 < d) != 0ull; j0 += 4) {
       const int32_t j = j0 + sub;
-      const int32_t a = __shfl(ra, lane0 + j), mj = __shfl(len, lane0 + j), m = j < d ? mj : 0;
-      auto entry = [&](int32_t t, uint32_t f) {
-        const uint32_t z = f & kIdMask;
-        uint32_t h = hash_mul(z, HB), kk;
-        while ((kk = key[h]) != z && kk != kNone) h = (h + 1) & (H - 1);
-        if (kk != z) return;
-        const int32_t k = at[h];
-        const uint32_t ey = list[j], ez = list[k];
-        const uint32_t xy = ey >> kTypeShift, xz = ez >> kTypeShift, yz = f >> kTypeShift;
-        const uint32_t tau = (xy - 1) * 9 + (xz - 1) * 3 + (yz - 1);
-        if constexpr (K4) {
-          atomicAdd(&T[(int64_t)(a + t) * 9 + (flip(xy) - 1) * 3 + (flip(xz) - 1)], 1u);
-          tri_add<true>(bins, tau, dx, G.dt[ey & kIdMask], G.dt[z]);
-          atomicAdd(&Tl[j], 1ull << (7 * ((xz - 1) * 3 + (yz - 1))));
-          atomicAdd(&Tl[k], 1ull << (7 * ((xy - 1) * 3 + (flip(yz) - 1))));
-          if (yz & 1u) atomicOr(&A1[j], 1ull << k);
-          if (yz & 2u) atomicOr(&A2[j], 1ull << k);
-        } else {
-          atomicAdd(&bins.tri[tau], 1ull);
+      int32_t a = __shfl(ra[0], lane0 + (j & (GS - 1))), m = __shfl(len[0], lane0 + (j & (GS - 1)));
+      if constexpr (DM > 1) {
+        const int32_t a1 = __shfl(ra[DM - 1], lane0 + (j & (GS - 1))), m1 = __shfl(len[DM - 1], lane0 + (j & (GS - 1)));
+        if (j >= GS) {
+          a = a1;
+          m = m1;
         }
-      };
-      for (int32_t t = lr; t < m; t += 4 * LPR) each4(G.np_idx + a, t, LPR, m, entry);
-    }
-    wave_sync();
-    if constexpr (K4) {
-      if (lane < d) {
-        const u64 p1 = A1[lane], p2 = A2[lane];
-        const uint32_t bx = edge_code<4>(0, 1, e >> kTypeShift);
-        for (u64 r = p1 | p2; r; r &= r - 1ull) {  // edge lane -> k above x
-          const int k = __builtin_ctzll(r);
-          const u64 q1 = A1[k], q2 = A2[k];
-          u64 com = (p1 | p2) & (q1 | q2);
-          if (!com) continue;
-          const uint32_t bk = bx | edge_code<4>(0, 2, list[k] >> kTypeShift) |
-                              edge_code<4>(1, 2, (uint32_t)((p1 >> k) & 1) | (uint32_t)((p2 >> k) & 1) << 1);
-          for (; com; com &= com - 1ull) {
-            const int l = __builtin_ctzll(com);
-            const uint32_t code = bk | edge_code<4>(0, 3, list[l] >> kTypeShift) |
-                                  edge_code<4>(1, 3, (uint32_t)((p1 >> l) & 1) | (uint32_t)((p2 >> l) & 1) << 1) |
-                                  edge_code<4>(2, 3, (uint32_t)((q1 >> l) & 1) | (uint32_t)((q2 >> l) & 1) << 1);
-            atomicAdd(&bins.kh[lut[code]], 1ull);
+      }
+      if (j >= d) m = 0;
+      for (int32_t t0 = 0; __ballot(t0 + lr < m) != 0ull; t0 += 4 * LPR) {
+        uint32_t f[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) f[u] = m > 0 ? G.np_idx[a + min(t0 + lr + u * LPR, m - 1)] : 0u;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int32_t t = t0 + lr + u * LPR;
+          int32_t k = -1;
+          if (t < m) {
+            const uint32_t z = f[u] & kIdMask;
+            uint32_t h = hash_mul(z, HB), kk;
+            while ((kk = key[h]) != z && kk != kNone) h = (h + 1) & (H - 1);
+            if (kk == z) k = at[h];
+          }
+          if constexpr (K4) {
+            const u64 hit = __ballot(k >= 0);
+            if (!hit) continue;
+            if (k >= 0) {
+              const int s = qn + __popcll(hit & ((1ull << wl) - 1ull));
+              s_q[wv][s] = (uint32_t)(gr % (64 / GS)) << 16 | (f[u] >> kTypeShift) << 14 | (uint32_t)k << 7 | (uint32_t)j;
+              s_qt[wv][s] = a + t;
+            }
+            qn += __popcll(hit);
+            if (qn > QC - 64) drain();
+          } else if (k >= 0) {
+            atomicAdd(&bins.tri[((list[j] >> kTypeShift) - 1) * 9 + ((list[k] >> kTypeShift) - 1) * 3 +
+                                ((f[u] >> kTypeShift) - 1)], 1ull);
           }
         }
-        const u64 c = Tl[lane];
+      }
+    }
+    if (K4 && qn) drain();
+    wave_sync();
+    if constexpr (K4) {
+#pragma unroll
+      for (int u = 0; u < DM; ++u) {
+        const int32_t i = lane + u * GS;
+        if (i >= d) continue;
+        const uint32_t bx = edge_code<4>(0, 1, e[u] >> kTypeShift);
+        for (int w = 0; w < W; ++w) {
+          const u64 p1 = A1[i * W + w], p2 = A2[i * W + w];
+          for (u64 r = p1 | p2; r; r &= r - 1ull) {  // edge i -> k above x
+            const int b = __builtin_ctzll(r), k = w * 64 + b;
+            uint32_t bk = 0;
+            for (int v = 0; v < W; ++v) {
+              const u64 r1 = A1[i * W + v], r2 = A2[i * W + v], q1 = A1[k * W + v], q2 = A2[k * W + v];
+              u64 com = (r1 | r2) & (q1 | q2);
+              if (!com) continue;
+              if (!bk)
+                bk = bx | edge_code<4>(0, 2, list[k] >> kTypeShift) |
+                     edge_code<4>(1, 2, (uint32_t)((p1 >> b) & 1) | (uint32_t)((p2 >> b) & 1) << 1);
+              for (; com; com &= com - 1ull) {
+                const int l = __builtin_ctzll(com);
+                const uint32_t code = bk | edge_code<4>(0, 3, list[v * 64 + l] >> kTypeShift) |
+                                      edge_code<4>(1, 3, (uint32_t)((r1 >> l) & 1) | (uint32_t)((r2 >> l) & 1) << 1) |
+                                      edge_code<4>(2, 3, (uint32_t)((q1 >> l) & 1) | (uint32_t)((q2 >> l) & 1) << 1);
+                atomicAdd(&bins.kh[lut[code]], 1ull);
+              }
+            }
+          }
+        }
+        const u64 c = Tl[i];
         if (c)
-          for (int i = 0; i < 9; ++i) {
-            const uint32_t v = (uint32_t)(c >> (7 * i)) & 127u;
-            if (v) atomicAdd(&T[(int64_t)(xa + lane) * 9 + i], v);
+          for (int f = 0; f < 9; ++f) {
+            const uint32_t v = (uint32_t)(c >> (7 * f)) & 127u;
+            if (v) atomicAdd(&T[(int64_t)(xa + i) * 9 + f], v);
           }
       }
       wave_sync();
-      if (lane < d) {
-        Tl[lane] = 0;
-        A1[lane] = 0;
-        A2[lane] = 0;
+#pragma unroll
+      for (int u = 0; u < DM; ++u) {
+        const int32_t i = lane + u * GS;
+        if (i >= d) continue;
+        Tl[i] = 0;
+        for (int w = 0; w < W; ++w) A1[i * W + w] = A2[i * W + w] = 0;
       }
     }
-    if (lane < d) key[hs] = kNone;
+#pragma unroll
+    for (int u = 0; u < DM; ++u)
+      if (lane + u * GS < d) key[hs[u]] = kNone;
     wave_sync();
   };
-  for_listed<256>(G, vlist, count, NGR, gr, one, [&](int32_t g) {
+  for_listed<256, GS < 64>(G, vlist, count, NGR, gr, one, [&](int32_t g) {
     bins.flush(lut3, K4 ? lut : lut4, a3 ? totals<13, kRep3>(G, a3, g) : nullptr,
                K4 ? totals<199, kRep4>(G, a4, g) : nullptr, threadIdx.x, 256);
   });
 }
 
-// The x with more than 64 higher neighbours, one workgroup each: N+(x) in an
+// The x with more than 128 higher neighbours, one workgroup each: N+(x) in an
 // LDS hash of up to kBigH / 2 members (beyond that a binary search in the
 // id-sorted row), T by global atomics, and for k = 4 the two adjacency bit
 // planes of N+(x), in LDS up to kPlaneD members and else in the workgroup's
 // slice of global memory (2 D rows of `words` words, D >= any d+).  d+ is at
-// most sqrt(2 m), so few x are here on sparse graphs (553 of 96,632 on the n =
-// 10^5 graph, none above 98).
+// most sqrt(2 m), so only large dense graphs have any (98 at most on the n =
+// 10^5, m = 10^6 graph).
 constexpr int kBigHB = 13;
 constexpr int kBigH = 1 << kBigHB;
 constexpr int kPlaneD = 256;
@@ -512,7 +599,7 @@ __global__ __launch_bounds__(512) void k_tri_big(DevGraph G, const uint16_t* __r
     __syncthreads();
   };
   u64* const gp = K4 ? planes + (int64_t)blockIdx.x * 2 * D * words : nullptr;
-  for_listed<NT>(
+  for_listed<NT, false>(
       G, vlist, count, 1, 0,
       [&](int32_t x) {
         const int32_t d = G.np_off[x + 1] - G.np_off[x];
@@ -582,6 +669,8 @@ __global__ __launch_bounds__(256) void k_wedge(DevGraph G, const uint16_t* __res
   static_assert((NT == 16 ? kCap16 : NT == 64 ? kCap64 : kCap256) <= H * 3 / 4, "hash load");
   __shared__ uint32_t s_key[NU][H];
   __shared__ u64 s_cnt[NU][H];
+  __shared__ uint16_t s_act[NU][H];  // slots with two wedges or more
+  __shared__ int32_t s_nact[NU];
   __shared__ u64 bins[81];
   if (st[kStatus] != 0) return;
   const int32_t count = nlist[NT == 16 ? kWedge16 : NT == 64 ? kWedge64 : kWedge256];
@@ -594,7 +683,9 @@ __global__ __launch_bounds__(256) void k_wedge(DevGraph G, const uint16_t* __res
     cnt[i] = 0;
   }
   for (int i = threadIdx.x; i < 81; i += 256) bins[i] = 0;
+  if (t == 0) s_nact[un] = 0;
   __syncthreads();
+  uint16_t* act = s_act[un];
   auto sync = [] {
     if constexpr (NT <= 64) wave_sync();
     else __syncthreads();
@@ -621,22 +712,36 @@ __global__ __launch_bounds__(256) void k_wedge(DevGraph G, const uint16_t* __res
     }
     sync();
     const uint32_t du = (uint32_t)(ub - ua);
+    // listed first: the ranks of all of them are then one load away
     for (int i = t; i < H; i += NT) {
       const u64 c = cnt[i];
       if (!c) continue;
+      if (one_wedge(c, kOnes7)) {
+        cnt[i] = 0;
+        key[i] = kNone;
+      } else {
+        act[atomicAdd(&s_nact[un], 1)] = (uint16_t)i;
+      }
+    }
+    sync();
+    const int32_t na = s_nact[un];
+    for (int k = t; k < na; k += NT) {
+      const int i = act[k];
+      const u64 c = cnt[i];
       cnt[i] = 0;
       const uint32_t w = key[i];
       key[i] = kNone;
-      if (one_wedge(c, kOnes7)) continue;
-      if (!ranked_below(G, (uint32_t)(G.gs_off[w + 1] - G.gs_off[w]), (int32_t)w, du, u)) continue;
+      if (!ranked_below(G, (uint32_t)G.deg[w], (int32_t)w, du, u)) continue;
       uint32_t f[9];
 #pragma unroll
-      for (int k = 0; k < 9; ++k) f[k] = (uint32_t)(c >> (7 * k)) & 127u;
+      for (int j = 0; j < 9; ++j) f[j] = (uint32_t)(c >> (7 * j)) & 127u;
       c4_pairs(f, bins);
     }
     sync();
+    if (t == 0) s_nact[un] = 0;
+    sync();
   };
-  for_listed<256>(G, vlist, count, NU, un, one, [&](int32_t g) {
+  for_listed<256, false>(G, vlist, count, NU, un, one, [&](int32_t g) {
     c4_flush(bins, lut4, totals<199, kRep4>(G, a4, g), threadIdx.x, 256);
     __syncthreads();
     if (threadIdx.x < 81) bins[threadIdx.x] = 0;
@@ -655,17 +760,24 @@ __global__ __launch_bounds__(256) void k_wedge(DevGraph G, const uint16_t* __res
 // pairs as 45 products per w summed in LDS took 1,300 us on the n = 10^5 graph,
 // where every wave's 45 additions meet on the same 45 words.
 //
-// split holds the first entry of every block in every row, so that a unit
-// reads its part of each row N(v) only (null: binary search).  The parts are
+// The blocks of a single graph: ids 0, kBlock, 2 kBlock, .. and, for the
+// vertices of more than kHugeD lower neighbours, kCuts equal shares of the G*
+// entries besides (a power-law graph's first ids are its hubs: of 1.7e7
+// entries that a first block took, 4.4e5 were one unit's, and the workgroups
+// with such units had three times the mean work).  split holds the first entry
+// of every block in every row, so that a unit reads its part of each row N(v)
+// only (null: binary search).  The parts are
 // listed in LDS first, empty ones left out, kParts rows at a time, so that the
-// loads that find them are one short chain for many rows; eight lanes then
-// read a part, whole waves those of more than kLongPart entries.
+// loads that find them are one short chain for many rows; 4, 16 or 64 lanes
+// then read a part, by its length.
 constexpr int kBlock = 12288;
 constexpr int kByteRow = kBlock + 64;  // bytes of a field's row: four fields on distinct banks
+constexpr int kCuts = 24;
+constexpr int64_t kCutsM = 32768;  // arcs from which the shares are cut
 constexpr int kHubs = 1024;
-constexpr int kLongPart = 64;
+constexpr int kShortPart = 16, kLongPart = 64, kLongs = 128;
 constexpr int kTopThreads = 1024;
-constexpr int kParts = 896;
+constexpr int kParts = 1024;
 constexpr int kGramRun = 1024;  // products of 64 w between flushes: 64 * 127^2 * 1024 < 2^31
 
 typedef int v4i __attribute__((ext_vector_type(4)));
@@ -686,7 +798,9 @@ struct Gram {
   // Into bins[9 i + j], i <= j: sums of n_i n_j; bins[81 + i]: sums of n_i.
   __device__ __forceinline__ void flush(u64* bins) {
     if (run == 0) return;
-    const int lane = threadIdx.x & 63, j = lane & 15;
+    int lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));  // (else the 24 addresses below live in registers through the caller's loop)
+    const int j = lane & 15;
 #pragma unroll
     for (int a = 0; a < ND; ++a)
 #pragma unroll
@@ -708,26 +822,30 @@ struct Gram {
   }
 };
 
-template <int ND>
+template <int ND, bool SPLIT>
 __global__ __launch_bounds__(kTopThreads) void k_wedge_top(DevGraph G, const uint16_t* __restrict__ lut4,
                                                            uint64_t* __restrict__ a4, const int32_t* st,
                                                            const int32_t* __restrict__ nlist,
                                                            const int32_t* __restrict__ top,
-                                                           const int32_t* __restrict__ split, int32_t nblk) {
+                                                           const int32_t* __restrict__ huge,
+                                                           const int32_t* __restrict__ split, int32_t nblk,
+                                                           int32_t nfine, const int32_t* __restrict__ bnd) {
+  // bnd: ids of the nfine + 1 boundaries, then the places among them of the
+  // nblk + 1 multiples of kBlock (null: these alone, within each graph)
   constexpr int NT = kTopThreads, NW = NT / 64, NQ = kBlock / 64;
   __shared__ __align__(16) uint32_t bytes[9 * kByteRow / 4];
   __shared__ __align__(16) uint32_t wide[9 * kHubs];
-  __shared__ int32_t pt_a[kParts], pt_n[kParts], pt_p[kParts];
+  __shared__ int32_t pt_a[kParts + kLongs], pt_n[kParts + kLongs];
   __shared__ u64 mlow[NQ], mhub[NQ];  // of the block's ids: of lower rank than u, of degree over 127
   __shared__ uint16_t hpre[NQ];       // hubs before each word of mhub
   __shared__ u64 bins[90];
-  __shared__ int32_t nshort, nlong, nhub;
+  __shared__ int32_t nshort, nmid, nlong, nhub;
   if (st[kStatus] != 0) return;
-  const int64_t units = (int64_t)nlist[kWedgeTop] * nblk;
+  const int64_t uhuge = (int64_t)nlist[kWedgeHuge] * nfine, units = uhuge + (int64_t)nlist[kWedgeTop] * nblk;
   if ((int64_t)blockIdx.x >= units) return;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   for (int i = threadIdx.x; i < 90; i += NT) bins[i] = 0;
-  if (threadIdx.x == 0) nshort = nlong = nhub = 0;
+  if (threadIdx.x == 0) nshort = nmid = nlong = nhub = 0;
   Gram<1> low;   // byte counts
   Gram<ND> hub;  // hub counts
   low.clear();
@@ -749,28 +867,102 @@ __global__ __launch_bounds__(kTopThreads) void k_wedge_top(DevGraph G, const uin
   };
   const v4i ones = v4i{0x01010101, 0x01010101, 0x01010101, 0x01010101}, none = v4i{0, 0, 0, 0};
   const int fld = lane & 15, kb = lane >> 4;
+  // A unit: its vertex, the vertex's N- row, its ids [w0, w0 + nw).
+  struct Unit {
+    int32_t u = 0, du = 0, ma = 0, dm = 0, f0 = 0, f1 = 0, g = 0, base = 0, w0 = 0, nw = 0;
+  };
+  auto scalar = [](int32_t v) { return __builtin_amdgcn_readfirstlane(v); };  // the same on every lane
+  auto vertex_of = [&](int64_t unit, Unit& X) {
+    const bool h = unit < uhuge;
+    const uint32_t i = (uint32_t)(h ? unit : unit - uhuge), per = (uint32_t)(h ? nfine : nblk);  // < 2^32: see units
+    const uint32_t at = i / per, blk = i - at * per;
+    X.u = scalar((h ? huge : top)[at]);
+    X.f0 = scalar((int32_t)(h || !bnd ? blk : bnd[nfine + 1 + blk]));
+    X.f1 = scalar((int32_t)(h || !bnd ? blk + 1 : bnd[nfine + 2 + blk]));
+  };
+  auto id_of = [&](int32_t f) { return bnd ? (int64_t)scalar(bnd[f]) : (int64_t)f * kBlock; };  // within the graph
+  auto rows_of = [&](Unit& X) {
+    const int32_t ua = scalar(G.gs_off[X.u]), ub = scalar(G.gs_off[X.u + 1]);
+    const int32_t pa = scalar(G.np_off[X.u]), pb = scalar(G.np_off[X.u + 1]);
+    X.du = ub - ua;
+    X.ma = ua - pa;
+    X.dm = ub - pb - X.ma;
+    X.g = G.gid ? scalar(G.gid[X.u]) : 0;
+    X.base = G.voff ? scalar((int32_t)G.voff[X.g]) : 0;
+    const int64_t ng = G.voff ? scalar((int32_t)G.voff[X.g + 1]) - X.base : (int64_t)G.n;
+    const int64_t i0 = min(ng, id_of(X.f0)), i1 = min(ng, id_of(X.f1));
+    X.w0 = X.base + (int32_t)i0;
+    X.nw = (int32_t)(i1 - i0);  // at most kBlock
+  };
+  // part of row v among the unit's ids
+  auto part_of = [&](const Unit& X, int32_t v, int32_t& a, int32_t& b) {
+    if constexpr (SPLIT) {
+      const int32_t* sp = split + (int64_t)v * (nfine + 1);
+      a = sp[X.f0];
+      b = sp[X.f1];
+    } else {
+      auto first = [&](int64_t id) {
+        int32_t lo = G.gs_off[v], hi = G.gs_off[v + 1];
+        while (lo < hi) {
+          const int32_t mid = (lo + hi) >> 1;
+          if ((int64_t)(G.gs_idx[mid] & kIdMask) < id) lo = mid + 1; else hi = mid;
+        }
+        return lo;
+      };
+      a = first(X.base + id_of(X.f0));
+      b = first(X.base + id_of(X.f1));
+    }
+  };
+  constexpr int PER = NQ / NW;  // words of the masks per wave
+  static_assert(NQ % NW == 0, "whole words per wave");
+  auto degrees = [&](const Unit& X, int32_t (&d)[PER]) {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int32_t w = (wv + i * NW) * 64 + lane;
+      d[i] = w < X.nw ? G.deg[X.w0 + w] : 0;
+    }
+  };
+  // What the next unit starts with (vertex, row, first parts, degrees of its
+  // ids) is loaded a step at a time between the phases of the current one, so
+  // that those chains of loads run beside it; and the counters are cleared as
+  // they are read, so that a unit finds them zero.
+  Unit U, V;
+  uint32_t ev = 0;
+  int32_t pa = 0, pb = 0, dg[PER];
+  vertex_of(blockIdx.x, U);
+  rows_of(U);
+  if (threadIdx.x < kParts && (int32_t)threadIdx.x < U.dm) {
+    ev = G.nm_idx[U.ma + threadIdx.x];
+    part_of(U, (int32_t)(ev & kIdMask), pa, pb);
+  }
+  degrees(U, dg);
+  for (int i = threadIdx.x; i < 9 * kByteRow / 16; i += NT) reinterpret_cast<uint4*>(bytes)[i] = make_uint4(0, 0, 0, 0);
+  for (int i = threadIdx.x; i < 9 * kHubs / 4; i += NT) reinterpret_cast<uint4*>(wide)[i] = make_uint4(0, 0, 0, 0);
   __syncthreads();
   for (int64_t unit = blockIdx.x; unit < units; unit += gridDim.x) {
-    const int32_t u = top[unit / nblk], blk = (int32_t)(unit % nblk);
-    const int32_t g = G.gid ? G.gid[u] : 0;
-    const int32_t base = G.voff ? (int32_t)G.voff[g] : 0;
-    const int32_t ng = G.voff ? (int32_t)(G.voff[g + 1] - G.voff[g]) : G.n;
-    if ((int64_t)blk * kBlock >= ng) continue;  // uniform over the workgroup
-    const int32_t ua = G.gs_off[u], ub = G.gs_off[u + 1], du = ub - ua;
-    const int32_t ma = ua - G.np_off[u], dm = ub - G.np_off[u + 1] - ma;
-    const int32_t w0 = base + blk * kBlock, nw = min(kBlock, ng - blk * kBlock), nq = (nw + 63) / 64;
+    vertex_of(unit + gridDim.x < units ? unit + gridDim.x : unit, V);
+    const int32_t u = U.u, du = U.du, dm = U.dm, w0 = U.w0, nw = U.nw, nq = (nw + 63) / 64;
     const bool divert = dm > 127;
-    if (g != cur) {
+    if (U.g != cur) {
       if (cur >= 0) give(cur);
-      cur = g;
+      cur = U.g;
     }
-    for (int k = 0; k < 9; ++k) {
-      uint4* t16 = reinterpret_cast<uint4*>(bytes) + k * (kByteRow / 16);
-      for (int32_t i = threadIdx.x; i < nq * 4; i += NT) t16[i] = make_uint4(0, 0, 0, 0);
-    }
-    for (int32_t q = wv; q < nq; q += NW) {
-      const int32_t w = q * 64 + lane, id = w0 + w;
-      const int32_t d = w < nw ? G.deg[id] : 0;
+    // parts by length: short ones from the front of the list, middle ones from
+    // its back, the long ones in a list of their own while it has room
+    auto list_part = [&](uint32_t e, int32_t a, int32_t b) {
+      const int32_t m = b - a;
+      if (m <= 0) return;
+      int32_t s = kLongs;
+      if (m > kLongPart) s = atomicAdd(&nlong, 1);
+      if (s < kLongs) s += kParts;
+      else s = m > kShortPart ? kParts - 1 - atomicAdd(&nmid, 1) : atomicAdd(&nshort, 1);
+      pt_a[s] = a;
+      pt_n[s] = m << 2 | (int32_t)((e >> kTypeShift) - 1u);  // m < 2^28: a row has at most kBlock of a block's ids
+    };
+    if (threadIdx.x < kParts && (int32_t)threadIdx.x < dm) list_part(ev, pa, pb);
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int32_t q = wv + i * NW, w = q * 64 + lane, id = w0 + w, d = dg[i];
       const u64 lo = __ballot(w < nw && (d < du || (d == du && id < u))), hb = __ballot(d > 127);
       if (lane == 0) {
         mlow[q] = lo;
@@ -778,6 +970,7 @@ __global__ __launch_bounds__(kTopThreads) void k_wedge_top(DevGraph G, const uin
       }
     }
     __syncthreads();
+    rows_of(V);
     int32_t nh = 0;
     if (divert) {
       if (wv == 0) {
@@ -798,13 +991,11 @@ __global__ __launch_bounds__(kTopThreads) void k_wedge_top(DevGraph G, const uin
       __syncthreads();
       nh = nhub;
     }
+    const bool have = threadIdx.x < kParts && (int32_t)threadIdx.x < V.dm;
+    if (have) ev = G.nm_idx[V.ma + threadIdx.x];
+    degrees(V, dg);
     for (int32_t h0 = 0; h0 == 0 || h0 < nh; h0 += kHubs) {
       const int32_t nhc = min(kHubs, nh - h0);  // hubs of this pass
-      if (nhc > 0) {
-        for (int32_t i = threadIdx.x; i < 9 * kHubs / 4; i += NT)
-          reinterpret_cast<uint4*>(wide)[i] = make_uint4(0, 0, 0, 0);
-        __syncthreads();
-      }
       auto hub_at = [&](int32_t w) {  // index of hub w in this pass (any value of kHubs or more: not in it)
         const u64 m = mhub[w >> 6];
         return (uint32_t)((int32_t)hpre[w >> 6] + __popcll(m & ((1ull << (w & 63)) - 1ull)) - h0);
@@ -822,74 +1013,77 @@ __global__ __launch_bounds__(kTopThreads) void k_wedge_top(DevGraph G, const uin
         }
         atomicAdd(&bytes[(k * kByteRow + (uint32_t)w) >> 2], 1u << (8 * (w & 3)));
       };
+      // part s by L lanes, of which this is l, four entries of each at a time;
+      // rows start with the same few hubs, so each part is read from another
+      // place of it
+      auto take = [&](int32_t s, int32_t l, int32_t L) {
+        const int32_t a = pt_a[s], mp = pt_n[s], m = mp >> 2, rot = (s * 5) % m;
+#pragma unroll 1
+        for (int32_t r = l; r < m; r += 4 * L) {
+          uint32_t f[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int32_t q = min(r + L * i, m - 1) + rot;
+            f[i] = G.gs_idx[a + (q >= m ? q - m : q)];
+          }
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (r + L * i < m) add((uint32_t)mp & 3u, f[i]);
+        }
+      };
       for (int32_t i0 = 0; i0 < dm; i0 += kParts) {
-        const int32_t i = i0 + (int32_t)threadIdx.x;
-        if (threadIdx.x < kParts && i < dm) {
-          const uint32_t ev = G.nm_idx[ma + i];
-          const int32_t v = (int32_t)(ev & kIdMask);
-          int32_t a, b;
-          if (split) {
-            const int32_t* sp = split + (int64_t)v * (nblk + 1) + blk;
-            a = sp[0];
-            b = sp[1];
-          } else {
-            auto first = [&](int64_t id) {
-              int32_t lo = G.gs_off[v], hi = G.gs_off[v + 1];
-              while (lo < hi) {
-                const int32_t mid = (lo + hi) >> 1;
-                if ((int64_t)(G.gs_idx[mid] & kIdMask) < id) lo = mid + 1; else hi = mid;
-              }
-              return lo;
-            };
-            a = first(w0);
-            b = first((int64_t)w0 + nw);
+        if (i0 > 0 || h0 > 0) {  // (the first rows were listed ahead)
+          const int32_t i = i0 + (int32_t)threadIdx.x;
+          if (threadIdx.x < kParts && i < dm) {
+            const uint32_t e = G.nm_idx[U.ma + i];
+            int32_t a, b;
+            part_of(U, (int32_t)(e & kIdMask), a, b);
+            list_part(e, a, b);
           }
-          if (b > a) {  // short parts from the front, long ones from the back
-            const int32_t s = b - a > kLongPart ? kParts - 1 - atomicAdd(&nlong, 1) : atomicAdd(&nshort, 1);
-            pt_a[s] = a;
-            pt_n[s] = b - a;
-            pt_p[s] = (int32_t)(ev >> kTypeShift) - 1;
+          __syncthreads();
+        }
+        const int32_t ns = nshort, nm = nmid, nl = min(nlong, kLongs);
+#pragma unroll 1
+        for (int32_t k = wv; k < nl; k += NW) take(kParts + k, lane, 64);
+#pragma unroll 1
+        for (int32_t k = threadIdx.x >> 4; k < nm; k += NT / 16) take(kParts - 1 - k, threadIdx.x & 15, 16);
+#pragma unroll 1
+        for (int32_t k = threadIdx.x >> 2; k < ns; k += NT / 4) take(k, threadIdx.x & 3, 4);
+        __syncthreads();
+        if (threadIdx.x == 0) nshort = nmid = nlong = 0;
+        if (i0 + kParts < dm || h0 + kHubs < nh) __syncthreads();
+      }
+      if (h0 == 0 && have) part_of(V, (int32_t)(ev & kIdMask), pa, pb);
+      // w of higher rank, and u itself (in every row N(v)), do not count:
+      // masked in the byte rows below, cleared among the hubs
+      if (nhc > 0) {
+#pragma unroll 1
+        for (int32_t q = threadIdx.x; q < nq; q += NT)
+          for (u64 m = mhub[q] & ~mlow[q]; m; m &= m - 1ull) {
+            const uint32_t h = hub_at(q * 64 + __builtin_ctzll(m));
+            if (h < (uint32_t)kHubs)
+              for (int k = 0; k < 9; ++k) wide[k * kHubs + h] = 0u;
           }
-        }
-        __syncthreads();
-        const int32_t ns = nshort, nl = nlong;
-        for (int32_t k = threadIdx.x >> 3; k < ns; k += NT / 8) {
-          const int32_t a = pt_a[k], m = pt_n[k];
-          const uint32_t p = (uint32_t)pt_p[k];
-          for (int32_t r = threadIdx.x & 7; r < m; r += 32)
-            each4(G.gs_idx + a, r, 8, m, [&](int32_t, uint32_t f) { add(p, f); });
-        }
-        for (int32_t k = wv; k < nl; k += NW) {
-          const int32_t s = kParts - 1 - k, a = pt_a[s], m = pt_n[s];
-          const uint32_t p = (uint32_t)pt_p[s];
-          for (int32_t r = lane; r < m; r += 256)
-            each4(G.gs_idx + a, r, 64, m, [&](int32_t, uint32_t f) { add(p, f); });
-        }
-        __syncthreads();
-        if (threadIdx.x == 0) nshort = nlong = 0;
         __syncthreads();
       }
-      // w of higher rank, and u itself (in every row N(v)), do not count
-      for (int32_t q = wv; q < nq; q += NW) {
-        const int32_t w = q * 64 + lane;
-        if (w >= nw || (mlow[q] >> lane) & 1ull) continue;
-        if (divert && (mhub[q] >> lane) & 1ull) {
-          const uint32_t h = hub_at(w);
-          if (h < (uint32_t)kHubs)
-            for (int k = 0; k < 9; ++k) wide[k * kHubs + h] = 0u;
-        } else if (h0 == 0) {
-          for (int k = 0; k < 9; ++k) reinterpret_cast<uint8_t*>(bytes)[k * kByteRow + w] = 0;
-        }
-      }
-      __syncthreads();
       if (h0 == 0) {
+#pragma unroll 2
         for (int32_t q = wv; q < nq; q += NW) {
-          v4i x = fld == 9 ? ones : none;
-          if (fld < 9) x = *reinterpret_cast<const v4i*>(bytes + (fld * kByteRow + q * 64 + kb * 16) / 4);
-          low.acc[0] = __builtin_amdgcn_mfma_i32_16x16x64_i8(x, x, low.acc[0], 0, 0, 0);
-          if (++low.run == kGramRun) low.flush(bins);
+          v4i x = fld == 9 ? ones : none, y = none;
+          if (fld < 9) {
+            v4i* p = reinterpret_cast<v4i*>(bytes + (fld * kByteRow + q * 64 + kb * 16) / 4);
+            x = *p;
+            *p = none;
+            const uint32_t m = (uint32_t)(mlow[q] >> (kb * 16)) & 0xFFFFu;
+#pragma unroll
+            for (int k = 0; k < 4; ++k)  // four mask bits to four mask bytes
+              y[k] = x[k] & (int)((((m >> (4 * k)) & 15u) * 0x00204081u & 0x01010101u) * 255u);
+          }
+          low.acc[0] = __builtin_amdgcn_mfma_i32_16x16x64_i8(y, x, low.acc[0], 0, 0, 0);
         }
+        if ((low.run += PER) >= kGramRun) low.flush(bins);
       }
+#pragma unroll 1
       for (int32_t q = wv; q < (nhc + 63) / 64; q += NW) {
         v4i x[ND];
 #pragma unroll
@@ -897,7 +1091,9 @@ __global__ __launch_bounds__(kTopThreads) void k_wedge_top(DevGraph G, const uin
         if (fld < 9) {
 #pragma unroll
           for (int k = 0; k < 4; ++k) {
-            const uint4 c = *reinterpret_cast<const uint4*>(wide + fld * kHubs + q * 64 + kb * 16 + 4 * k);
+            uint4* p = reinterpret_cast<uint4*>(wide + fld * kHubs + q * 64 + kb * 16 + 4 * k);
+            const uint4 c = *p;
+            *p = make_uint4(0, 0, 0, 0);
 #pragma unroll
             for (int a = 0; a < ND; ++a)
               x[a][k] = (int)(((c.x >> (7 * a)) & 127u) | ((c.y >> (7 * a)) & 127u) << 8 |
@@ -910,31 +1106,61 @@ __global__ __launch_bounds__(kTopThreads) void k_wedge_top(DevGraph G, const uin
           for (int b = 0; b <= a; ++b)
             hub.acc[a * (a + 1) / 2 + b] =
                 __builtin_amdgcn_mfma_i32_16x16x64_i8(x[a], x[b], hub.acc[a * (a + 1) / 2 + b], 0, 0, 0);
-        if (++hub.run == kGramRun) hub.flush(bins);
+        if (++hub.run >= kGramRun) hub.flush(bins);
       }
       __syncthreads();
     }
+    U = V;
   }
   __syncthreads();
   if (cur >= 0) give(cur);
 }
 
-// split[v * (nblk + 1) + i] = first entry of row v with id >= the start of
-// block i of its graph (i = nblk: the row's end).
-__global__ void k_split(DevGraph G, int32_t nblk, int32_t* __restrict__ split, const int32_t* st) {
+// Boundaries of the blocks of a single graph: the multiples of kBlock (nblk + 1
+// of them) and the kCuts - 1 inner ends of equal shares of the G* entries,
+// merged in order; then the places of the multiples.  One workgroup.
+__global__ void k_bounds(DevGraph G, int32_t nblk, int32_t* __restrict__ bnd, const int32_t* st) {
+  __shared__ int32_t cut[kCuts];
   if (st[kStatus] != 0) return;
-  const int64_t cols = nblk + 1, total = (int64_t)G.n * cols;
+  const int32_t total = G.gs_off[G.n];
+  for (int32_t i = threadIdx.x + 1; i < kCuts; i += blockDim.x) {  // cut i: first id with its share of entries before it
+    const int64_t key = (int64_t)total * i / kCuts;
+    int32_t lo = 0, hi = G.n;
+    while (lo < hi) {
+      const int32_t mid = (lo + hi) >> 1;
+      if (G.gs_off[mid] < key) lo = mid + 1; else hi = mid;
+    }
+    cut[i] = lo;
+  }
+  __syncthreads();
+  const int32_t nfine = nblk + kCuts - 1;
+  auto mult = [&](int32_t j) { return min(G.n, j * kBlock); };
+  for (int32_t i = threadIdx.x + 1; i < kCuts; i += blockDim.x) {
+    int32_t at = i - 1;  // cuts before it, then the multiples not above it
+    for (int32_t j = 0; j <= nblk && mult(j) <= cut[i]; ++j) ++at;
+    bnd[at] = cut[i];
+  }
+  for (int32_t j = threadIdx.x; j <= nblk; j += blockDim.x) {
+    int32_t at = j;
+    for (int32_t i = 1; i < kCuts && cut[i] < mult(j); ++i) ++at;
+    bnd[at] = mult(j);
+    bnd[nfine + 1 + j] = at;
+  }
+}
+
+// split[v * (nfine + 1) + i] = first entry of row v with id >= boundary i of
+// its graph.
+__global__ void k_split(DevGraph G, int32_t nfine, const int32_t* __restrict__ bnd, int32_t* __restrict__ split,
+                        const int32_t* st) {
+  if (st[kStatus] != 0) return;
+  const int64_t cols = nfine + 1, total = (int64_t)G.n * cols;
   for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < total; k += (int64_t)gridDim.x * blockDim.x) {
     const int32_t v = (int32_t)(k / cols), i = (int32_t)(k % cols);
-    const int64_t id = (G.voff ? G.voff[G.gid[v]] : 0) + (int64_t)i * kBlock;
+    const int64_t id = (G.voff ? G.voff[G.gid[v]] : 0) + (bnd ? (int64_t)bnd[i] : (int64_t)i * kBlock);
     int32_t lo = G.gs_off[v], hi = G.gs_off[v + 1];
-    if (i == nblk) {
-      lo = hi;
-    } else {
-      while (lo < hi) {
-        const int32_t mid = (lo + hi) >> 1;
-        if ((int64_t)(G.gs_idx[mid] & kIdMask) < id) lo = mid + 1; else hi = mid;
-      }
+    while (lo < hi) {
+      const int32_t mid = (lo + hi) >> 1;
+      if ((int64_t)(G.gs_idx[mid] & kIdMask) < id) lo = mid + 1; else hi = mid;
     }
     split[k] = lo;
   }
@@ -1169,18 +1395,19 @@ constexpr size_t kPlaneBytes = size_t(64) << 20;  // adjacency slices of k_tri_b
 
 struct CountPlan {
   bool wide;                 // degrees may reach 2^21
-  int32_t nblk;              // blocks of ids of k_wedge_top
+  int32_t nblk, nfine;       // blocks of ids of k_wedge_top, and with the shares of entries
   bool split;
   int64_t D, words;          // bound on d+ and the words of an adjacency row
   int slices;                // adjacency slices of k_tri_big in global memory (0: none can be needed)
 };
 
-CountPlan count_plan(int64_t n, int64_t m, int64_t maxn) {
+CountPlan count_plan(int64_t n, int64_t m, int64_t maxn, bool batch) {
   CountPlan c{};
   const int64_t mg = maxn > 0 ? maxn : n;
   c.wide = std::min(mg - 1, m) >= (int64_t(1) << 21);
   c.nblk = (int32_t)std::max<int64_t>(1, (mg + kBlock - 1) / kBlock);
-  c.split = n * (c.nblk + 1) <= kSplitCap;
+  c.nfine = c.nblk + (!batch && m >= kCutsM ? kCuts - 1 : 0);
+  c.split = n * (c.nfine + 1) <= kSplitCap;
   // N+(x) has at most sqrt(2 m*) entries: its members all have degree d(x) or more
   int64_t r = 1;
   while (r * r <= 2 * m) ++r;
@@ -1193,12 +1420,13 @@ CountPlan count_plan(int64_t n, int64_t m, int64_t maxn) {
 
 }  // namespace
 
-size_t count_bytes(int64_t n, int64_t m, int64_t maxn, bool k4) {
+size_t count_bytes(int64_t n, int64_t m, int64_t maxn, bool batch, bool k4) {
   auto al = [](size_t b) { return (b + 255) & ~size_t(255); };
   if (!k4) return 0;
-  const CountPlan c = count_plan(n, m, maxn);
-  size_t b = al(sizeof(uint32_t) * 9 * (size_t)(m + 1)) + 4 * al(sizeof(int32_t) * (size_t)(n + 1));
-  if (c.split) b += al(sizeof(int32_t) * (size_t)n * (c.nblk + 1));
+  const CountPlan c = count_plan(n, m, maxn, batch);
+  size_t b = al(sizeof(uint32_t) * 9 * (size_t)(m + 1)) + 5 * al(sizeof(int32_t) * (size_t)(n + 1));
+  if (c.split) b += al(sizeof(int32_t) * (size_t)n * (c.nfine + 1));
+  b += al(sizeof(int32_t) * (size_t)(c.nfine + c.nblk + 2));
   b += al((size_t)c.slices * (size_t)c.D * (size_t)c.words * 16 + 16);
   return b;
 }
@@ -1209,25 +1437,30 @@ void enqueue_counts(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_t* a4, 
   const int64_t n = g.n, m = (g.gs_cap - 1) / 2;
   if (n == 0) return;
   const int cus = p.num_cus;
-  const CountPlan c = count_plan(n, m, g.max_graph_n);
-  // lists in words that the build is done with (at most 2 m / 17 and 2 m / 65
-  // vertices have a degree of 17 or 65)
+  const CountPlan c = count_plan(n, m, g.max_graph_n, g.gid != nullptr);
+  // lists in words that the build is done with (at most 2 m / 17 vertices have
+  // a degree of 17 or more, 2 m / 65 one of 65)
   Lists L{};
   L.v[kTri16] = g.tmp_n;
   L.v[kTri64] = g.tmp_n2;
-  L.v[kTriBig] = g.tmp_n3;
+  L.v[kTri128] = g.tmp_n3;
+  L.v[kTriBig] = g.tmp_n3 + m;
   const unsigned cgrid = std::max(grid_of(n, 64, cus * 4), grid_of(n, kClassify, 1 << 20));
   // workgroups for a list of at most `most` vertices, `per` at a time
   auto list_grid = [&](int64_t most, int per, int wgs) { return dim3(grid_of(most, per, (int64_t)cus * wgs)); };
   // a vertex of tier d has at least d higher neighbours of at least its degree
-  const int64_t n16 = std::min(n, m), n64 = std::min(n, 2 * m / 17), nbig = c.D > 64 ? std::min(n, 2 * m / 65) : 0;
+  const int64_t n16 = std::min(n, m), n64 = std::min(n, 2 * m / 17);
+  const int64_t n128 = c.D > 64 ? std::min(n, 2 * m / 65) : 0, nbig = c.D > 128 ? std::min(n, 2 * m / 129) : 0;
   if (!a4) {
     hipLaunchKernelGGL((k_classify<false>), dim3(cgrid), dim3(256), 0, s, g, L, queue, p.status);
-    hipLaunchKernelGGL((k_tri<16, false>), list_grid(n16, 16, 8), dim3(256), 0, s, g, T.lut[3], T.lut[4], a3, nullptr,
+    hipLaunchKernelGGL((k_tri<16, 16, false>), list_grid(n16, 16, 8), dim3(256), 0, s, g, T.lut[3], T.lut[4], a3, nullptr,
                        nullptr, p.status, queue, L.v[kTri16]);
     if (c.D > 16)
-      hipLaunchKernelGGL((k_tri<64, false>), list_grid(n64, 4, 8), dim3(256), 0, s, g, T.lut[3], T.lut[4], a3, nullptr,
+      hipLaunchKernelGGL((k_tri<64, 64, false>), list_grid(n64, 4, 8), dim3(256), 0, s, g, T.lut[3], T.lut[4], a3, nullptr,
                          nullptr, p.status, queue, L.v[kTri64]);
+    if (n128 > 0)
+      hipLaunchKernelGGL((k_tri<64, 128, false>), list_grid(n128, 4, 8), dim3(256), 0, s, g, T.lut[3], T.lut[4], a3,
+                         nullptr, nullptr, p.status, queue, L.v[kTri128]);
     if (nbig > 0)
       hipLaunchKernelGGL((k_tri_big<false>), list_grid(nbig, 1, 3), dim3(512), 0, s, g, T.lut[3], T.lut[4], a3,
                          nullptr, nullptr, p.status, queue, L.v[kTriBig], nullptr, 0, 0);
@@ -1236,16 +1469,21 @@ void enqueue_counts(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_t* a4, 
     return;
   }
   uint32_t* Te = p.arena.take<uint32_t>(9 * (size_t)(m + 1));
-  for (int l : {kWedge16, kWedge64, kWedge256, kWedgeTop}) L.v[l] = p.arena.take<int32_t>((size_t)n + 1);
-  int32_t* split = c.split ? p.arena.take<int32_t>((size_t)n * (c.nblk + 1)) : nullptr;
+  for (int l : {kWedge16, kWedge64, kWedge256, kWedgeTop, kWedgeHuge}) L.v[l] = p.arena.take<int32_t>((size_t)n + 1);
+  int32_t* split = c.split ? p.arena.take<int32_t>((size_t)n * (c.nfine + 1)) : nullptr;
+  int32_t* bnd = p.arena.take<int32_t>((size_t)(c.nfine + c.nblk + 2));
+  if (c.nfine == c.nblk) bnd = nullptr;  // the multiples of kBlock alone
   u64* planes = p.arena.take<u64>((size_t)c.slices * (size_t)c.D * (size_t)c.words * 2 + 1);
   enqueue_zero(Te, sizeof(uint32_t) * 9 * (size_t)(m + 1), s);
   hipLaunchKernelGGL((k_classify<true>), dim3(cgrid), dim3(256), 0, s, g, L, queue, p.status);
-  hipLaunchKernelGGL((k_tri<16, true>), list_grid(n16, 16, 6), dim3(256), 0, s, g, T.lut[3], T.lut[4], a3, a4, Te,
+  hipLaunchKernelGGL((k_tri<16, 16, true>), list_grid(n16, 16, 6), dim3(256), 0, s, g, T.lut[3], T.lut[4], a3, a4, Te,
                      p.status, queue, L.v[kTri16]);
   if (c.D > 16)
-    hipLaunchKernelGGL((k_tri<64, true>), list_grid(n64, 4, 6), dim3(256), 0, s, g, T.lut[3], T.lut[4], a3, a4, Te,
+    hipLaunchKernelGGL((k_tri<64, 64, true>), list_grid(n64, 4, 6), dim3(256), 0, s, g, T.lut[3], T.lut[4], a3, a4, Te,
                        p.status, queue, L.v[kTri64]);
+  if (n128 > 0)
+    hipLaunchKernelGGL((k_tri<64, 128, true>), list_grid(n128, 4, 3), dim3(256), 0, s, g, T.lut[3], T.lut[4], a3, a4,
+                       Te, p.status, queue, L.v[kTri128]);
   if (nbig > 0)  // a workgroup whose x need a global slice has its own
     hipLaunchKernelGGL((k_tri_big<true>), dim3(std::min<unsigned>(c.slices ? c.slices : 512, grid_of(nbig, 1, cus * 2))),
                        dim3(512), 0, s, g, T.lut[3], T.lut[4], a3, a4, Te, p.status, queue, L.v[kTriBig], planes, c.D,
@@ -1259,16 +1497,17 @@ void enqueue_counts(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_t* a4, 
     hipLaunchKernelGGL((k_wedge<256, 12>), list_grid(n16, 1, 3), dim3(256), 0, s, g, T.lut[4], a4, p.status, queue,
                        L.v[kWedge256]);
   if (m > 127) {  // over 127 lower neighbours, or over kCap256 visits
+    if (bnd) hipLaunchKernelGGL(k_bounds, dim3(1), dim3(64), 0, s, g, c.nblk, bnd, p.status);
     if (split)
-      hipLaunchKernelGGL(k_split, dim3(grid_of(n * (c.nblk + 1), 256, 65536)), dim3(256), 0, s, g, c.nblk, split,
+      hipLaunchKernelGGL(k_split, dim3(grid_of(n * (c.nfine + 1), 256, 65536)), dim3(256), 0, s, g, c.nfine, bnd, split,
                          p.status);
-    const dim3 tg = list_grid(n * c.nblk, 1, 1);
-    if (c.wide)
-      hipLaunchKernelGGL((k_wedge_top<5>), tg, dim3(kTopThreads), 0, s, g, T.lut[4], a4, p.status, queue,
-                         L.v[kWedgeTop], split, c.nblk);
-    else
-      hipLaunchKernelGGL((k_wedge_top<3>), tg, dim3(kTopThreads), 0, s, g, T.lut[4], a4, p.status, queue,
-                         L.v[kWedgeTop], split, c.nblk);
+    const dim3 tg = list_grid(n * c.nfine, 1, 1);
+    auto launch_top = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, tg, dim3(kTopThreads), 0, s, g, T.lut[4], a4, p.status, queue, L.v[kWedgeTop],
+                         L.v[kWedgeHuge], split, c.nblk, c.nfine, bnd);
+    };
+    if (c.wide) launch_top(split ? k_wedge_top<5, true> : k_wedge_top<5, false>);
+    else launch_top(split ? k_wedge_top<3, true> : k_wedge_top<3, false>);
   }
   const dim3 lgrid(grid_of(n + m, 256, cus * 4));
   if (a3)

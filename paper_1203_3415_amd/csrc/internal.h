@@ -227,7 +227,7 @@ void enqueue_census(Pipeline& p, const DevGraph& g, int k, uint64_t* acc, uint64
 // into a3 and / or a4 (acc_words each; null: not wanted; both and the 64 queue
 // words zeroed by the caller), then the induced counts into out
 // through tmp (same size), written only if none is negative.
-size_t count_bytes(int64_t n, int64_t m, int64_t maxn, bool k4);
+size_t count_bytes(int64_t n, int64_t m, int64_t maxn, bool batch, bool k4);
 void enqueue_counts(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_t* a4, int32_t* queue, hipStream_t s);
 void enqueue_solve(int k, const uint64_t* acc, uint64_t* tmp, uint64_t* out, int64_t ngraphs, int32_t* status,
                    hipStream_t s);
