@@ -185,9 +185,10 @@ __device__ __forceinline__ void for_listed(const DevGraph& G, const int32_t* lis
     return;
   }
   __shared__ int32_t sh_run;
-  const int32_t s1 = (int32_t)((int64_t)count * (blockIdx.x + 1) / gridDim.x);
+  const int32_t nb = min((int32_t)gridDim.x, count);  // (the callers leave workgroups from `count` on out)
+  const int32_t s1 = (int32_t)((int64_t)count * (blockIdx.x + 1) / nb);
   int32_t cur = -1;
-  for (int32_t s0 = (int32_t)((int64_t)count * blockIdx.x / gridDim.x); s0 < s1;) {
+  for (int32_t s0 = (int32_t)((int64_t)count * blockIdx.x / nb); s0 < s1;) {
     const int32_t g = G.gid[list[s0]];
     __syncthreads();
     if (threadIdx.x == 0) sh_run = NT;
@@ -874,11 +875,13 @@ __global__ __launch_bounds__(kTopThreads) void k_wedge_top(DevGraph G, const uin
   auto scalar = [](int32_t v) { return __builtin_amdgcn_readfirstlane(v); };  // the same on every lane
   auto vertex_of = [&](int64_t unit, Unit& X) {
     const bool h = unit < uhuge;
-    const uint32_t i = (uint32_t)(h ? unit : unit - uhuge), per = (uint32_t)(h ? nfine : nblk);  // < 2^32: see units
-    const uint32_t at = i / per, blk = i - at * per;
+    const int64_t i = h ? unit : unit - uhuge;
+    const int32_t per = h ? nfine : nblk;
+    const int64_t at = i < (int64_t(1) << 31) ? (int64_t)((uint32_t)i / (uint32_t)per) : i / per;
+    const int32_t blk = (int32_t)(i - at * per);
     X.u = scalar((h ? huge : top)[at]);
-    X.f0 = scalar((int32_t)(h || !bnd ? blk : bnd[nfine + 1 + blk]));
-    X.f1 = scalar((int32_t)(h || !bnd ? blk + 1 : bnd[nfine + 2 + blk]));
+    X.f0 = scalar(h || !bnd ? blk : bnd[nfine + 1 + blk]);
+    X.f1 = scalar(h || !bnd ? blk + 1 : bnd[nfine + 2 + blk]);
   };
   auto id_of = [&](int32_t f) { return bnd ? (int64_t)scalar(bnd[f]) : (int64_t)f * kBlock; };  // within the graph
   auto rows_of = [&](Unit& X) {
