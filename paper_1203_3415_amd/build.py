@@ -13,7 +13,7 @@ import tempfile
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmotif.so")
-SOURCES = ["classes.cpp", "graph.hip", "counts.hip", "census.hip", "census6.hip", "nullmodel.hip", "api.cpp", "server.cpp",
+SOURCES = ["classes.cpp", "graph.hip", "counts.hip", "copies5.hip", "census.hip", "census6.hip", "nullmodel.hip", "api.cpp", "server.cpp",
            "ingest.cpp"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

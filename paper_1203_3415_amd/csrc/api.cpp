@@ -119,6 +119,26 @@ int32_t init_device_locked(int dev) {
       *dst[i] = (const int32_t*)b;
     }
   }
+  {
+    const Copies5 five = copies5_tables();
+    auto upload = [&](const void* src, size_t bytes, const void** dst) {
+      void* b = nullptr;
+      if (hipMalloc(&b, bytes) != hipSuccess) return MOTIF_ENOMEM;
+      d.owned.push_back(b);
+      if (hipMemcpy(b, src, bytes, hipMemcpyHostToDevice) != hipSuccess) return MOTIF_EDEVICE;
+      *dst = b;
+      return 0;
+    };
+    int32_t rc = upload(five.mult.data(), five.mult.size(), (const void**)&d.tables.five.mult);
+    auto words = [&](const std::vector<int32_t>& v, const int32_t** dst) {
+      if (!rc) rc = upload(v.data(), v.size() * sizeof(int32_t), (const void**)dst);
+    };
+    words(five.up_off, &d.tables.five.up_off);
+    words(five.up, &d.tables.five.up);
+    words(five.fold_off, &d.tables.five.fold_off);
+    words(five.fold, &d.tables.five.fold);
+    if (rc) return rc;
+  }
   // the allocation-free entry point's workspace: this device's copy of the
   // array, and a pinned word block its status is read back into
   void* sp = nullptr;
@@ -367,12 +387,68 @@ int32_t drain_after_error(Pipeline& p, hipStream_t s) {
 int32_t run_census_multi_enqueue(Pipeline& p, const BuildInput& in, int32_t nk, const int32_t* ks,
                                  uint64_t* const* hists, hipStream_t s);
 
+// Room for the k = 5 census by subgraph copies of one graph (0: not for graphs
+// of this size).
+size_t copies5_need(const BuildInput& in) {
+  return !in.gid && copies5_fits(in.n, in.m) ? build_bytes(in.n, in.m, 1, false) + copies5_bytes(in.n, in.m, 256) : 0;
+}
+
+// The sizes ks (5 among them) of one graph by subgraph copies, with a host wait
+// in the middle.  kNotTaken: not by this way (other scheme asked for, no room
+// in the workspace, or more triangles than the links have room for); no output
+// is written then and the caller starts over.  und: 5 alone, hists[0] receives
+// the undirected census.
+constexpr int32_t kNotTaken = 1;
+int32_t run_copies5(Pipeline& p, const BuildInput& in, int32_t nk, const int32_t* ks, uint64_t* const* hists, bool und,
+                    hipStream_t s) {
+  for (int32_t i = 0; i < nk; ++i)
+    if (ks[i] >= 4 && p.tune.k[ks[i]].heavy != 1) return kNotTaken;
+  const size_t need = copies5_need(in);
+  if (!need || need > p.arena.cap || p.num_cus > 256) return kNotTaken;
+  try {
+    p.arena.reset();
+    enqueue_zero(p.status, sizeof(int32_t) * kStatusWords, s);
+    for (int32_t i = 0; i < nk; ++i) profile_mark(ks[i], 0, true, s);
+    DevGraph g = enqueue_build(p, in, s);
+    if (und) enqueue_all_bidirected(g, s, p.status);
+    for (int32_t i = 0; i < nk; ++i) profile_mark(ks[i], 0, false, s);
+    uint64_t* tmp = p.arena.take<uint64_t>((size_t)motif_num_classes(5));
+    uint64_t* a3 = p.arena.take<uint64_t>((size_t)13 * kRep3);
+    uint64_t* a4 = p.arena.take<uint64_t>((size_t)199 * kRep4);
+    for (int32_t i = 0; i < nk; ++i) profile_mark(ks[i], 1, true, s);
+    Copies5Run run;
+    enqueue_copies5_start(p, g, a3, a4, &run, s);
+    const int32_t rc = read_status(p, s);
+    if (rc) return rc;
+    if (!copies5_go(p, in.m)) return kNotTaken;
+    for (int32_t i = 0; i < nk; ++i) {
+      if (ks[i] == 5) continue;
+      enqueue_solve(ks[i], ks[i] == 3 ? a3 : a4, nullptr, hists[i], 1, p.status, s);
+      profile_mark(ks[i], 1, false, s);
+    }
+    for (int32_t i = 0; i < nk; ++i) {
+      if (ks[i] != 5) continue;
+      enqueue_copies5_finish(p, g, run, und ? tmp : hists[i], s);
+      profile_mark(5, 1, false, s);
+    }
+    if (und)
+      enqueue_project_undirected(tmp, dev_tables().und_of[5], motif_num_classes(5),
+                                 (int32_t)class_table(5)->und_canon.size(), hists[0], p.status, s);
+  } catch (const WorkspaceError&) {
+    return drain_after_error(p, s);
+  }
+  return read_status(p, s);
+}
+
 // One census on a sized pipeline: build + status wait + census + status wait.
 // The census is enqueued right behind the build, with no host wait in
 // between: every census kernel returns at once when the build has set the
 // status word, and the exact division writes nothing then.
 int32_t run_census_on(Pipeline& p, const BuildInput& in, int32_t k, uint64_t* hist, hipStream_t s) {
-  const int C = motif_num_classes(k);
+  if (k == 5) {
+    const int32_t rc = run_copies5(p, in, 1, &k, &hist, false, s);
+    if (rc != kNotTaken) return rc;
+  }
   try {
     p.arena.reset();
     enqueue_zero(p.status, sizeof(int32_t) * kStatusWords, s);
@@ -393,6 +469,11 @@ int32_t run_census_on(Pipeline& p, const BuildInput& in, int32_t k, uint64_t* hi
 // largest census leaves idle at its end.  Each census has its own workspace.
 int32_t run_census_multi_on(Pipeline& p, const BuildInput& in, int32_t nk, const int32_t* ks, uint64_t* const* hists,
                             hipStream_t s) {
+  for (int32_t i = 0; i < nk; ++i)
+    if (ks[i] == 5) {
+      const int32_t rc = run_copies5(p, in, nk, ks, hists, false, s);
+      if (rc != kNotTaken) return rc;
+    }
   try {
     return run_census_multi_enqueue(p, in, nk, ks, hists, s);
   } catch (const WorkspaceError&) {
@@ -480,7 +561,8 @@ int32_t run_census(const BuildInput& in, int32_t k, uint64_t* hist, hipStream_t 
   if (rc) return rc;
   const TuningSet tune = tuning_for_call(dev, 1, &k, false, in.m);
   Pipeline* p = nullptr;
-  rc = get_pipeline(dev, s, pipeline_bytes(in.n, in.m, in.ngraphs, false, k, device_cus(dev), in.n, tune.k[k]), &p);
+  rc = get_pipeline(dev, s, std::max(pipeline_bytes(in.n, in.m, in.ngraphs, false, k, device_cus(dev), in.n, tune.k[k]),
+                                     k == 5 ? copies5_need(in) : 0), &p);
   if (rc) return rc;
   p->tune = tune;
   ensure_wpool(p, s, w_slice_bytes(k, in.n, tune.k[k], device_cus(dev)));
@@ -919,15 +1001,20 @@ int32_t motif_census_undirected(const int32_t* out_off, const int32_t* out_idx, 
   }
   const TuningSet tune = tuning_for_call(dev, 1, &k, false, m);
   Pipeline* p = nullptr;
-  rc = get_pipeline(dev, s, pipeline_bytes(n, m, 1, false, k, device_cus(dev), n, tune.k[k]), &p);
-  if (rc) return rc;
-  p->tune = tune;
-  ensure_wpool(p, s, w_slice_bytes(k, n, tune.k[k], device_cus(dev)));
   BuildInput in{};
   in.out_off = out_off;
   in.out_idx = out_idx;
   in.n = n;
   in.m = m;
+  rc = get_pipeline(dev, s, std::max(pipeline_bytes(n, m, 1, false, k, device_cus(dev), n, tune.k[k]),
+                                     k == 5 ? copies5_need(in) : 0), &p);
+  if (rc) return rc;
+  p->tune = tune;
+  ensure_wpool(p, s, w_slice_bytes(k, n, tune.k[k], device_cus(dev)));
+  if (k == 5) {
+    rc = run_copies5(*p, in, 1, &k, &hist, true, s);
+    if (rc != kNotTaken) return rc;
+  }
   try {
     p->arena.reset();
     enqueue_zero(p->status, sizeof(int32_t) * kStatusWords, s);
@@ -979,6 +1066,8 @@ int32_t motif_census_multi(const motif_graph_t* g, int32_t nk, const int32_t* ks
   size_t bytes = build;
   for (int32_t i = 0; i < nk; ++i)
     bytes += pipeline_bytes(in.n, in.m, 1, false, ks[i], device_cus(dev), in.n, tune.k[ks[i]]) - build;
+  for (int32_t i = 0; i < nk; ++i)
+    if (ks[i] == 5) bytes = std::max(bytes, copies5_need(in));
   Pipeline* p = nullptr;
   rc = get_pipeline(dev, s, bytes, &p);
   if (rc) return rc;

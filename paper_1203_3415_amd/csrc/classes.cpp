@@ -17,6 +17,7 @@
 #include "classes.h"
 
 #include <algorithm>
+#include <functional>
 #include <map>
 #include <mutex>
 
@@ -199,6 +200,122 @@ SubgraphInverse subgraph_inverse(int k) {
     m.off.push_back((int32_t)m.cls.size());
   }
   return m;
+}
+
+
+
+// A five-vertex sum of copies5.hip that also takes in maps of its skeleton to
+// four or three vertices: the vertex pairs that may fall together, and what one
+// copy's maps count for (num / den).
+namespace {
+struct Folded {
+  int edges;
+  uint8_t edge[7][2];
+  int pairs;
+  uint8_t pair[4][2];
+  bool one;  // at most one of the pairs at a time
+  int num, den;
+};
+const Folded kFolded[] = {
+    {4, {{0, 1}, {1, 2}, {0, 3}, {3, 4}}, 3, {{2, 3}, {1, 4}, {2, 4}}, false, 1, 2},                           // path
+    {4, {{0, 1}, {1, 2}, {0, 3}, {0, 4}}, 2, {{2, 3}, {2, 4}}, false, 1, 2},                                   // fork
+    {5, {{0, 2}, {1, 2}, {0, 3}, {1, 3}, {0, 4}}, 1, {{1, 4}}, false, 1, 2},                                   // C4 and pendant
+    {5, {{0, 1}, {0, 2}, {1, 2}, {0, 3}, {3, 4}}, 2, {{1, 4}, {2, 4}}, false, 1, 2},                           // triangle and path
+    {5, {{0, 1}, {0, 2}, {1, 2}, {1, 3}, {2, 4}}, 1, {{3, 4}}, false, 1, 2},                                   // bull
+    {6, {{0, 1}, {0, 2}, {1, 2}, {1, 3}, {3, 4}, {0, 4}}, 2, {{2, 3}, {2, 4}}, false, 1, 1},                   // house
+    {6, {{0, 1}, {0, 2}, {1, 2}, {0, 3}, {1, 3}, {2, 4}}, 1, {{3, 4}}, false, 1, 1},                           // kite
+    {6, {{0, 1}, {0, 2}, {1, 2}, {0, 3}, {0, 4}, {3, 4}}, 4, {{1, 3}, {1, 4}, {2, 3}, {2, 4}}, true, 1, 8},    // butterfly
+    {7, {{0, 1}, {0, 2}, {1, 2}, {0, 3}, {1, 3}, {0, 4}, {2, 4}}, 1, {{3, 4}}, false, 1, 2},                   // gem
+};
+
+// Times a copy is met by the sums, by its skeleton.
+int copies5_mult(uint32_t code) {
+  uint32_t nb[8];
+  skeleton(5, code, nb);
+  int d[5], e = 0;
+  for (int i = 0; i < 5; ++i) e += d[i] = __builtin_popcount(nb[i]);
+  std::sort(d, d + 5, std::greater<int>());
+  auto is = [&](int a, int b, int c, int x, int y) { return d[0] == a && d[1] == b && d[2] == c && d[3] == x && d[4] == y; };
+  if (is(3, 3, 2, 2, 2) || is(3, 3, 3, 2, 1)) return e == 12 ? 2 : 1;  // house, K2,3, kite
+  if (is(4, 4, 2, 2, 2) || is(3, 3, 3, 3, 2) || is(4, 4, 3, 3, 2)) return 2;
+  if (e == 18) return 3;
+  if (e == 20) return 5;
+  return 1;
+}
+}  // namespace
+
+Copies5 copies5_tables() {
+  const ClassTable* t = class_table(5);
+  const int C = (int)t->canon.size();
+  Copies5 out;
+  for (int c = 0; c < C; ++c) out.mult.push_back((uint8_t)copies5_mult(t->canon[c]));
+  // one edge left out
+  std::vector<std::map<int, int>> up(C);
+  for (int c = 0; c < C; ++c)
+    for (int i = 0; i < 5; ++i)
+      for (int j = i + 1; j < 5; ++j) {
+        const uint32_t bits = 1u << code_bit(5, i, j) | 1u << code_bit(5, j, i), x = t->canon[c];
+        if (!(x & bits)) continue;
+        const uint16_t sub = t->lut[x & ~bits];
+        if (sub != 0xFFFF) ++up[sub][c];
+      }
+  auto csr = [](const std::vector<std::map<int, int>>& rows, std::vector<int32_t>* off, std::vector<int32_t>* ent) {
+    off->push_back(0);
+    for (const auto& r : rows) {
+      for (const auto& kv : r) ent->push_back(kv.first | kv.second << 16);
+      off->push_back((int32_t)ent->size());
+    }
+  };
+  csr(up, &out.up_off, &out.up);
+  // maps of the folded sums onto the classes of three and four vertices
+  std::vector<std::map<int, int>> fold(C);
+  for (int k = 3; k <= 4; ++k) {
+    const ClassTable* q = class_table(k);
+    for (int c = 0; c < (int)q->canon.size(); ++c) {
+      uint32_t nb[8];
+      skeleton(k, q->canon[c], nb);
+      auto type = [&](int i, int j) {
+        return (uint32_t)(q->canon[c] >> code_bit(k, i, j) & 1u) | (uint32_t)(q->canon[c] >> code_bit(k, j, i) & 1u) << 1;
+      };
+      uint32_t all = 0;  // the edges of the class
+      for (int i = 0; i < k; ++i)
+        for (int j = i + 1; j < k; ++j)
+          if (nb[i] >> j & 1u) all |= 1u << (4 * i + j);
+      for (const Folded& P : kFolded) {
+        std::map<int, int> here;
+        int f[5];
+        const int total = k == 3 ? 243 : 1024;
+        for (int x = 0; x < total; ++x) {
+          for (int i = 0, y = x; i < 5; ++i, y /= k) f[i] = y % k;
+          uint32_t met = 0, code = 0;
+          bool ok = true;
+          for (int e = 0; e < P.edges && ok; ++e) {
+            const int i = P.edge[e][0], j = P.edge[e][1], a = f[i], b = f[j];
+            if (a == b || !(nb[a] >> b & 1u)) { ok = false; break; }
+            met |= 1u << (4 * std::min(a, b) + std::max(a, b));
+            const uint32_t ty = type(a, b);
+            if (ty & 1u) code |= 1u << code_bit(5, i, j);
+            if (ty & 2u) code |= 1u << code_bit(5, j, i);
+          }
+          if (!ok || met != all) continue;
+          int folds = 0;
+          for (int i = 0; i < 5 && ok; ++i)
+            for (int j = i + 1; j < 5; ++j) {
+              if (f[i] != f[j]) continue;
+              bool may = false;
+              for (int p = 0; p < P.pairs; ++p) may |= P.pair[p][0] == i && P.pair[p][1] == j;
+              ok = ok && may;
+              ++folds;
+            }
+          if (!ok || folds == 0 || (P.one && folds > 1)) continue;
+          here[t->lut[code]] += P.num;
+        }
+        for (const auto& kv : here) fold[kv.first][k == 3 ? 199 + c : c] += kv.second / P.den;
+      }
+    }
+  }
+  csr(fold, &out.fold_off, &out.fold);
+  return out;
 }
 
 }  // namespace motif

@@ -37,4 +37,13 @@ inline int code_bit(int k, int i, int j) { return i * (k - 1) + (j < i ? j : j -
 // Bit of the edge {i, j}, i < j, in a k-vertex undirected code (k(k-1)/2 bits).
 inline int und_bit(int k, int i, int j) { return i * (2 * k - i - 1) / 2 + (j - i - 1); }
 
+// Host tables of the k = 5 census by subgraph copies (copies5.hip).
+struct Copies5 {
+  std::vector<uint8_t> mult;             // times each class's copies are met
+  std::vector<int32_t> up_off, up;       // row c: classes with one edge more, class | (edges of it that leave c) << 16
+  std::vector<int32_t> fold_off, fold;   // row c: classes of four (0 ..) and three (199 ..) vertices whose copies the
+                                         // sums of c take in, class | times << 16
+};
+Copies5 copies5_tables();
+
 }  // namespace motif

@@ -29,31 +29,12 @@
 #include <type_traits>
 
 #include "codes.h"
+#include "counts.h"
 #include "internal.h"
 
 namespace motif {
 
 namespace {
-
-constexpr uint32_t kNone = 0xFFFFFFFFu;
-
-// Lists of vertices by the work they bring, counted in the zeroed queue words
-// of a census (64 int32).  Units are dealt out by position, not pulled from a
-// counter: a pull is an atomic on one address, about 25 ns each however many
-// waves wait for it, which was most of these kernels' time on 10^4 vertices.
-enum ListId : int { kTri16 = 0, kTri64 = 1, kTri128 = 2, kTriBig = 3, kWedge16 = 4, kWedge64 = 5, kWedge256 = 6,
-                    kWedgeTop = 7, kWedgeHuge = 8, kLists = 9 };
-struct Lists {
-  int32_t* v[kLists];
-};
-constexpr int kHugeD = 1000;  // lower neighbours from which a vertex's wedges are cut by row entries too
-constexpr int kCap16 = 96, kCap64 = 384, kCap256 = 3072;  // visits of a vertex in the three wedge hashes
-
-__device__ __forceinline__ uint32_t hash_mul(uint32_t x, int bits) { return (x * 2654435761u) >> (32 - bits); }
-
-__device__ __forceinline__ void gadd(uint64_t* a, u64 v) {
-  if (v) atomicAdd(reinterpret_cast<u64*>(a), v);
-}
 
 // The totals of graph g that this workgroup adds to.  A single graph has R
 // copies of its totals, summed by k_solve_one: additions to one address (and
@@ -63,8 +44,6 @@ template <int C, int R>
 __device__ __forceinline__ uint64_t* totals(const DevGraph& G, uint64_t* a, int32_t g) {
   return a + (int64_t)(G.gid ? g : (int32_t)blockIdx.x & (R - 1)) * C;
 }
-
-__device__ __forceinline__ uint32_t typ(const uint4& d, uint32_t t) { return t == 1u ? d.x : t == 2u ? d.y : d.z; }
 
 // ============================================================ triangles ==
 //
@@ -151,18 +130,6 @@ __device__ __forceinline__ void tri_add(const TriBins<K4>& b, uint32_t tau, cons
     atomicAdd(&p[3], (u64)dy.x); atomicAdd(&p[4], (u64)dy.y); atomicAdd(&p[5], (u64)dy.z);
     atomicAdd(&p[6], (u64)dz.x); atomicAdd(&p[7], (u64)dz.y); atomicAdd(&p[8], (u64)dz.z);
   }
-}
-
-// body(i, p[i]) for i = r, r + step, r + 2 step, r + 3 step below m, the four
-// loads issued together.
-template <class F>
-__device__ __forceinline__ void each4(const uint32_t* p, int32_t r, int32_t step, int32_t m, F&& body) {
-  uint32_t f[4];
-#pragma unroll
-  for (int k = 0; k < 4; ++k) f[k] = p[min(r + k * step, m - 1)];
-#pragma unroll
-  for (int k = 0; k < 4; ++k)
-    if (r + k * step < m) body(r + k * step, f[k]);
 }
 
 // Calls one(v) for the listed vertices, `groups` of them at a time per
@@ -624,18 +591,6 @@ __global__ __launch_bounds__(512) void k_tri_big(DevGraph G, const uint16_t* __r
 //                    w, for u with at most 96, 384 and 3,072 visits
 //   k_wedge_top      the rest: a direct table over one block of vertex ids at a
 //                    time, the work unit being (u, block)
-__device__ __forceinline__ bool ranked_below(const DevGraph& G, uint32_t dw, int32_t w, uint32_t du, int32_t u) {
-  return dw < du || (dw == du && w < u);
-}
-
-// A word of packed counters that holds one single wedge: one bit set, at the
-// foot of a field (ones: the feet).
-template <class W>
-__device__ __forceinline__ bool one_wedge(W c, W ones) {
-  return (c & (c - 1)) == 0 && (c & ones) != 0;
-}
-constexpr u64 kOnes7 = 1ull | 1ull << 7 | 1ull << 14 | 1ull << 21 | 1ull << 28 | 1ull << 35 | 1ull << 42 | 1ull << 49 |
-                       1ull << 56;
 
 // Pairs of wedges to one w, by the types of both, into bins[9 i + j], i <= j.
 __device__ __forceinline__ void c4_pairs(const uint32_t (&c)[9], u64* bins) {
@@ -1434,7 +1389,8 @@ size_t count_bytes(int64_t n, int64_t m, int64_t maxn, bool batch, bool k4) {
   return b;
 }
 
-void enqueue_counts(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_t* a4, int32_t* queue, hipStream_t s) {
+void enqueue_counts(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_t* a4, int32_t* queue, hipStream_t s,
+                    CountsOut* left) {
   // (the accumulators and the queue words are zeroed by the caller)
   const DevTables& T = dev_tables();
   const int64_t n = g.n, m = (g.gs_cap - 1) / 2;
@@ -1477,6 +1433,10 @@ void enqueue_counts(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_t* a4, 
   int32_t* bnd = p.arena.take<int32_t>((size_t)(c.nfine + c.nblk + 2));
   if (c.nfine == c.nblk) bnd = nullptr;  // the multiples of kBlock alone
   u64* planes = p.arena.take<u64>((size_t)c.slices * (size_t)c.D * (size_t)c.words * 2 + 1);
+  if (left) {
+    left->T = Te;
+    for (int l = 0; l < kLists; ++l) left->wedge[l] = L.v[l];
+  }
   enqueue_zero(Te, sizeof(uint32_t) * 9 * (size_t)(m + 1), s);
   hipLaunchKernelGGL((k_classify<true>), dim3(cgrid), dim3(256), 0, s, g, L, queue, p.status);
   hipLaunchKernelGGL((k_tri<16, 16, true>), list_grid(n16, 16, 6), dim3(256), 0, s, g, T.lut[3], T.lut[4], a3, a4, Te,

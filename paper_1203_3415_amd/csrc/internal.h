@@ -62,9 +62,16 @@ struct SubInverse {
   const int32_t* coef = nullptr;
 };
 
+// Copies5 (classes.h) on the device.
+struct Tables5 {
+  const uint8_t* mult = nullptr;
+  const int32_t *up_off = nullptr, *up = nullptr, *fold_off = nullptr, *fold = nullptr;
+};
+
 // Device class tables uploaded by motif_init.
 struct DevTables {
   SubInverse inv[6];
+  Tables5 five;
   const uint16_t* lut[6] = {};   // index k
   const uint8_t* mult[6] = {};
   const int16_t* und_of[6] = {};  // undirected class of each directed class, -1 if an arc is one-way
@@ -228,9 +235,29 @@ void enqueue_census(Pipeline& p, const DevGraph& g, int k, uint64_t* acc, uint64
 // words zeroed by the caller), then the induced counts into out
 // through tmp (same size), written only if none is negative.
 size_t count_bytes(int64_t n, int64_t m, int64_t maxn, bool batch, bool k4);
-void enqueue_counts(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_t* a4, int32_t* queue, hipStream_t s);
+struct CountsOut {  // what a k = 4 pass leaves behind
+  const uint32_t* T = nullptr;         // typed triangle counts per N+ entry, nine each
+  const int32_t* wedge[9] = {};        // lists of vertices (ListId in counts.h)
+};
+void enqueue_counts(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_t* a4, int32_t* queue, hipStream_t s,
+                    CountsOut* left = nullptr);
 void enqueue_solve(int k, const uint64_t* acc, uint64_t* tmp, uint64_t* out, int64_t ngraphs, int32_t* status,
                    hipStream_t s);
+// The k = 5 census of one graph by subgraph copies (copies5.hip): start
+// enqueues the k = 3, 4 totals (a3, a4: acc_words of a single graph, zeroed
+// here) and counts what the rest takes room for; once the status words are
+// read back, copies5_go says whether it fits, and finish enqueues the rest.
+struct Copies5Run {
+  uint64_t *a3 = nullptr, *a4 = nullptr, *acc = nullptr;
+  int32_t *queue = nullptr, *cnt = nullptr, *off = nullptr, *epos = nullptr;
+  uint32_t *emap = nullptr, *hi = nullptr, *tri = nullptr;
+  CountsOut counts;
+};
+bool copies5_fits(int64_t n, int64_t m);
+size_t copies5_bytes(int64_t n, int64_t m, int num_cus);
+void enqueue_copies5_start(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_t* a4, Copies5Run* R, hipStream_t s);
+bool copies5_go(const Pipeline& p, int64_t m);
+void enqueue_copies5_finish(Pipeline& p, const DevGraph& g, const Copies5Run& R, uint64_t* out, hipStream_t s);
 // Whether k's census under tuning t counts subgraph copies.
 inline bool by_copies(int k, const Tuning& t) { return k == 3 || (k == 4 && t.heavy == 1); }
 // Copies of a single graph's totals (a workgroup adds to one of them).
