@@ -75,6 +75,17 @@ struct Totals5 {
   __device__ __forceinline__ void add(uint32_t code, u64 w) const {
     if (w) atomicAdd(reinterpret_cast<u64*>(acc) + (int64_t)((int)blockIdx.x & (kRep5 - 1)) * kC5 + lut[code], w);
   }
+  // N of them, the table's entries loaded together
+  template <int N>
+  __device__ __forceinline__ void add(const uint32_t (&code)[N], const u64 (&w)[N]) const {
+    uint32_t c[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) c[i] = lut[code[i]];
+    u64* a = reinterpret_cast<u64*>(acc) + (int64_t)((int)blockIdx.x & (kRep5 - 1)) * kC5;
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+      if (w[i]) atomicAdd(a + c[i], w[i]);
+  }
 };
 
 __device__ __forceinline__ uint32_t ec(int i, int j, uint32_t t) { return edge_code<5>(i, j, t); }
@@ -222,24 +233,31 @@ __global__ __launch_bounds__(256) void k_links5(DevGraph G, Totals5 K, Links L, 
             const uint32_t* hzy = hi + 6 * (int64_t)(L.emap[py] >> 1);
             const uint32_t* hxy = hi + 6 * (int64_t)e;
             const uint4 Uy = up[y], Dz = G.dt[z], Dx = G.dt[x];
+            uint32_t code[16];
+            u64 w[16];
             // u above all three, joined to corner v: u v w w' v
-            auto walk_a = [&](uint32_t n, int s, uint32_t vw, uint32_t ww, uint32_t wv) {
+            auto walk_a = [&](int at, uint32_t n, int s, uint32_t vw, uint32_t ww, uint32_t wv) {
               const uint32_t t = s + 1;
-              K.add(ec(0, 1, flip(t)) | ec(1, 2, vw) | ec(2, 3, ww) | ec(3, 4, wv) | ec(4, 0, t), 0 - (u64)n);
+              code[at] = ec(0, 1, flip(t)) | ec(1, 2, vw) | ec(2, 3, ww) | ec(3, 4, wv) | ec(4, 0, t);
+              w[at] = 0 - (u64)n;
             };
             // u = y: u c w c o, w below u
-            auto walk_b = [&](u64 n, int s, uint32_t uc, uint32_t co, uint32_t ou) {
+            auto walk_b = [&](int at, u64 n, int s, uint32_t uc, uint32_t co, uint32_t ou) {
               const uint32_t t = s + 1;
-              K.add(ec(0, 1, uc) | ec(1, 2, t) | ec(2, 3, flip(t)) | ec(3, 4, co) | ec(4, 0, ou), 0 - n);
+              code[at] = ec(0, 1, uc) | ec(1, 2, t) | ec(2, 3, flip(t)) | ec(3, 4, co) | ec(4, 0, ou);
+              w[at] = 0 - n;
             };
+#pragma unroll
             for (int s = 0; s < 3; ++s) {
-              walk_a(hzy[3 + s], s, zx, xy, flip(zy));
-              walk_a(hxy[3 + s], s, flip(zx), zy, flip(xy));
-              walk_a(deg_of(Uy, s), s, flip(zy), zx, xy);
-              walk_b(other(Dz, s, zy, zx) - hzy[s], s, flip(zy), zx, xy);
-              walk_b(other(Dx, s, xy, flip(zx)) - hxy[s], s, flip(xy), flip(zx), zy);
+              walk_a(5 * s, hzy[3 + s], s, zx, xy, flip(zy));
+              walk_a(5 * s + 1, hxy[3 + s], s, flip(zx), zy, flip(xy));
+              walk_a(5 * s + 2, deg_of(Uy, s), s, flip(zy), zx, xy);
+              walk_b(5 * s + 3, other(Dz, s, zy, zx) - hzy[s], s, flip(zy), zx, xy);
+              walk_b(5 * s + 4, other(Dx, s, xy, flip(zx)) - hxy[s], s, flip(xy), flip(zx), zy);
             }
-            K.add(ec(0, 1, flip(zy)) | ec(1, 2, zx) | ec(2, 3, flip(zx)) | ec(3, 4, zx) | ec(4, 0, xy), 0 - 1ull);
+            code[15] = ec(0, 1, flip(zy)) | ec(1, 2, zx) | ec(2, 3, flip(zx)) | ec(3, 4, zx) | ec(4, 0, xy);
+            w[15] = 0 - 1ull;
+            K.add(code, w);
           }
         }
         run += __popcll(hit);
@@ -419,18 +437,27 @@ __device__ __forceinline__ int32_t link_at(const uint32_t* p, int32_t m, uint32_
   return lo < m && (p[lo] & kIdMask) == d ? lo : -1;
 }
 
-constexpr int kWheelT = 16;  // links of a unit up to which its wheels are taken pair by pair
+constexpr int kStaged = 512;  // links of a unit up to which a wave keeps them in LDS
+constexpr int kWheelT = 16;   // links of a unit up to which its wheels are taken pair by pair
 
 __global__ __launch_bounds__(256) void k_apex5(DevGraph G, Totals5 K, Links L, const u64* __restrict__ S,
                                                const int32_t* st) {
+  __shared__ uint32_t s_R[4][kStaged];
   if (st[kStatus] != 0) return;
   const int lane = threadIdx.x & 63;
+  uint32_t* sR = s_R[threadIdx.x >> 6];
   for_entries(G, L.cnt, 1, 1 << 30, [&](int32_t E) {
     const int32_t u = G.gs_row[E], ua = G.gs_off[u], t = L.cnt[E];
     const uint32_t bl = (uint32_t)(E - ua), pb = G.gs_idx[E] >> kTypeShift;
     const int32_t b = (int32_t)(G.gs_idx[E] & kIdMask);
     const uint32_t* R = L.idx + L.off[E];
     const uint4 Du = G.dt[u], Db = G.dt[b];
+    const bool staged = t <= kStaged;  // b's links in LDS: searched for every third of every c
+    if (staged)
+      for (int32_t k = lane; k < t; k += 64) sR[k] = R[k];
+    wave_sync();
+    auto at_b = [&](int32_t k) { return staged ? sR[k] : R[k]; };
+    auto place_b = [&](uint32_t d) { return staged ? link_at(sR, t, d) : link_at(R, t, d); };
     uint32_t tb[9];
     L.types(E, tb);
     const uint32_t cb = ec(0, 1, pb);
@@ -461,7 +488,7 @@ __global__ __launch_bounds__(256) void k_apex5(DevGraph G, Totals5 K, Links L, c
           }
       }
     for (int32_t k = lane; k < t; k += 64) {
-      const uint32_t f = R[k], cl = f & kIdMask, bc = f >> kTypeShift;
+      const uint32_t f = at_b(k), cl = f & kIdMask, bc = f >> kTypeShift;
       const uint32_t fc = G.gs_idx[ua + cl], pc = fc >> kTypeShift;
       const int32_t c = (int32_t)(fc & kIdMask), Ec = ua + (int32_t)cl;
       const uint4 Dc = G.dt[c];
@@ -482,18 +509,30 @@ __global__ __launch_bounds__(256) void k_apex5(DevGraph G, Totals5 K, Links L, c
             K.add(code | ec(0, 3, x / 3 + 1) | ec(1, 3, x % 3 + 1) | ec(2, 4, s + 1), n * xc[s]);
         }
       if (cl < bl) continue;  // each triangle u, b, c once from here
-      for (int s = 0; s < 3; ++s) {
-        const u64 x = other(Du, s, pb, pc);
-        for (int r = s; r < 3; ++r)  // two pendants at u
-          K.add(code | ec(0, 3, s + 1) | ec(0, 4, r + 1), r == s ? x * (x - 1) / 2 : x * other(Du, r, pb, pc));
-        for (int r = 0; r < 3; ++r) {
-          K.add(code | ec(1, 3, s + 1) | ec(2, 4, r + 1), xb[s] * xc[r]);  // bull
-          // a path of two edges from u
-          u64 w = S[(int64_t)u * 9 + 3 * s + r];
-          if (pb == (uint32_t)s + 1) w -= other(Db, r, flip(pb), 0);
-          if (pc == (uint32_t)s + 1) w -= other(Dc, r, flip(pc), 0);
-          K.add(code | ec(0, 3, s + 1) | ec(3, 4, r + 1), w);
+      {
+        uint32_t cs[24];
+        u64 ws[24];
+#pragma unroll
+        for (int s = 0; s < 3; ++s) {
+          const u64 x = other(Du, s, pb, pc);
+#pragma unroll
+          for (int q = 0; q < 3; ++q) {
+            const int at = 8 * s + 2 * q;
+            cs[at] = code | ec(1, 3, s + 1) | ec(2, 4, q + 1);  // bull
+            ws[at] = xb[s] * xc[q];
+            // a path of two edges from u
+            cs[at + 1] = code | ec(0, 3, s + 1) | ec(3, 4, q + 1);
+            ws[at + 1] = S[(int64_t)u * 9 + 3 * s + q] - (pb == (uint32_t)s + 1 ? other(Db, q, flip(pb), 0) : 0ull) -
+                         (pc == (uint32_t)s + 1 ? other(Dc, q, flip(pc), 0) : 0ull);
+          }
+          // two pendants at u: types s, s and s, s + 1 (the third and the first)
+          const int q = (s + 1) % 3;
+          cs[8 * s + 6] = code | ec(0, 3, s + 1) | ec(0, 4, s + 1);
+          ws[8 * s + 6] = x * (x - 1) / 2;
+          cs[8 * s + 7] = code | ec(0, 3, s + 1) | ec(0, 4, q + 1);
+          ws[8 * s + 7] = x * other(Du, q, pb, pc);
         }
+        K.add(cs, ws);
       }
       if (t < 2 && L.cnt[Ec] < 2) continue;
       uint32_t tc[9];
@@ -510,44 +549,53 @@ __global__ __launch_bounds__(256) void k_apex5(DevGraph G, Totals5 K, Links L, c
             K.add(code | ec(0, 3, x / 3 + 1) | ec(1, 3, x % 3 + 1) | ec(0, 4, y / 3 + 1) | ec(2, 4, y % 3 + 1), n * m);
         }
       }
-      // the vertices adjacent to u, b and c
-      const uint32_t* Rc = L.idx + L.off[Ec];
-      const int32_t mc = L.cnt[Ec];
-      for (int32_t i = 0; i < mc; ++i) {
-        const uint32_t dl = Rc[i] & kIdMask, cd = Rc[i] >> kTypeShift;
-        const int32_t at = dl == bl ? -1 : link_at(R, t, dl);
-        if (at < 0) continue;
-        const uint32_t bd = R[at] >> kTypeShift, pd = G.gs_idx[ua + dl] >> kTypeShift;
-        const uint32_t four = code | ec(0, 3, pd) | ec(1, 3, bd) | ec(2, 3, cd);
-        // two of them, not joined or joined
-        for (int32_t j = i + 1; j < mc; ++j) {
-          const uint32_t el = Rc[j] & kIdMask, ce = Rc[j] >> kTypeShift;
-          const int32_t ae = el == bl ? -1 : link_at(R, t, el);
-          if (ae < 0) continue;
-          const uint32_t pe = G.gs_idx[ua + el] >> kTypeShift;
-          const uint32_t c5 = four | ec(0, 4, pe) | ec(1, 4, R[ae] >> kTypeShift) | ec(2, 4, ce);
-          K.add(c5, 1ull);
-          if (dl <= cl) continue;  // K5: b < c < d < e
-          const int32_t Ed = ua + (int32_t)dl;
-          const int32_t de = link_at(L.idx + L.off[Ed], L.cnt[Ed], el);
-          if (de >= 0) K.add(c5 | ec(3, 4, L.idx[L.off[Ed] + de] >> kTypeShift), 1ull);
-        }
-        if (dl <= cl) continue;  // K4 u, b < c < d
-        for (int s = 0; s < 3; ++s) K.add(four | ec(0, 4, s + 1), other(Du, s, pb, pc, pd));
-        uint32_t td[9];
-        L.types(ua + (int32_t)dl, td);
-        const int ad = 3 * (int)(pd - 1) + (int)(bd - 1);
-        const int acd = 3 * (int)(pd - 1) + (int)(cd - 1);
-        const int adb = 3 * (int)(pb - 1) + (int)(flip(bd) - 1), adc = 3 * (int)(pc - 1) + (int)(flip(cd) - 1);
+    }
+    // the vertices adjacent to u, b and c, eight lanes per c
+    if (t >= 2)
+      for (int32_t k = lane >> 3; k < t; k += 8) {
+        const uint32_t f = at_b(k), cl = f & kIdMask, bc = f >> kTypeShift;
+        if (cl < bl) continue;
+        const int32_t Ec = ua + (int32_t)cl, mc = L.cnt[Ec];
+        if (mc < 2) continue;
+        const uint32_t pc = G.gs_idx[Ec] >> kTypeShift;
+        const uint32_t code = cb | ec(0, 2, pc) | ec(1, 2, bc);
+        const uint32_t* Rc = L.idx + L.off[Ec];
+        for (int32_t i = lane & 7; i < mc; i += 8) {
+          const uint32_t dl = Rc[i] & kIdMask, cd = Rc[i] >> kTypeShift;
+          const int32_t at = dl == bl ? -1 : place_b(dl);
+          if (at < 0) continue;
+          const uint32_t bd = at_b(at) >> kTypeShift, pd = G.gs_idx[ua + dl] >> kTypeShift;
+          const uint32_t four = code | ec(0, 3, pd) | ec(1, 3, bd) | ec(2, 3, cd);
+          // two of them, not joined or joined
+          for (int32_t j = i + 1; j < mc; ++j) {
+            const uint32_t el = Rc[j] & kIdMask, ce = Rc[j] >> kTypeShift;
+            const int32_t ae = el == bl ? -1 : place_b(el);
+            if (ae < 0) continue;
+            const uint32_t pe = G.gs_idx[ua + el] >> kTypeShift;
+            const uint32_t c5 = four | ec(0, 4, pe) | ec(1, 4, at_b(ae) >> kTypeShift) | ec(2, 4, ce);
+            K.add(c5, 1ull);
+            if (dl <= cl) continue;  // K5: b < c < d < e
+            const int32_t Ed = ua + (int32_t)dl;
+            const int32_t de = link_at(L.idx + L.off[Ed], L.cnt[Ed], el);
+            if (de >= 0) K.add(c5 | ec(3, 4, L.idx[L.off[Ed] + de] >> kTypeShift), 1ull);
+          }
+          if (dl <= cl) continue;  // K4 u, b < c < d
+          for (int s = 0; s < 3; ++s) K.add(four | ec(0, 4, s + 1), other(Du, s, pb, pc, pd));
+          uint32_t tc[9], td[9];
+          L.types(Ec, tc);
+          L.types(ua + (int32_t)dl, td);
+          const int ac = 3 * (int)(pc - 1) + (int)(bc - 1), ab = 3 * (int)(pb - 1) + (int)(flip(bc) - 1);
+          const int ad = 3 * (int)(pd - 1) + (int)(bd - 1), acd = 3 * (int)(pd - 1) + (int)(cd - 1);
+          const int adb = 3 * (int)(pb - 1) + (int)(flip(bd) - 1), adc = 3 * (int)(pc - 1) + (int)(flip(cd) - 1);
 #pragma unroll
-        for (int x = 0; x < 9; ++x) {  // a vertex on u and one of the three
-          const uint32_t e4 = four | ec(0, 4, x / 3 + 1);
-          K.add(e4 | ec(1, 4, x % 3 + 1), (u64)(tb[x] - (x == (int)ac) - (x == ad)));
-          K.add(e4 | ec(2, 4, x % 3 + 1), (u64)(tc[x] - (x == (int)ab) - (x == acd)));
-          K.add(e4 | ec(3, 4, x % 3 + 1), (u64)(td[x] - (x == adb) - (x == adc)));
+          for (int x = 0; x < 9; ++x) {  // a vertex on u and one of the three
+            const uint32_t e4 = four | ec(0, 4, x / 3 + 1);
+            K.add(e4 | ec(1, 4, x % 3 + 1), (u64)(tb[x] - (x == ac) - (x == ad)));
+            K.add(e4 | ec(2, 4, x % 3 + 1), (u64)(tc[x] - (x == ab) - (x == acd)));
+            K.add(e4 | ec(3, 4, x % 3 + 1), (u64)(td[x] - (x == adb) - (x == adc)));
+          }
         }
       }
-    }
     // wheels with hub u whose rim's first vertex is b: two thirds c < c' of
     // (u, b) and a vertex d adjacent to both
     if (t >= 2 && t <= kWheelT)
@@ -568,6 +616,7 @@ __global__ __launch_bounds__(256) void k_apex5(DevGraph G, Totals5 K, Links L, c
                     ec(3, 4, R2[y] >> kTypeShift), 1ull);
         }
       }
+    wave_sync();
   });
 }
 
@@ -658,21 +707,31 @@ __global__ __launch_bounds__(256) void k_wheel5(DevGraph G, Totals5 K, Links L, 
 // (counts.hip) over the whole rows: hashes of 7-bit counters while d(u) <= 127
 // and the visits fit, else 16-bit counters over one block of ids at a time.
 
+// Place of the triple i <= j <= k of nine.
+__host__ __device__ constexpr int triple(int i, int j, int k) {
+  int at = 0;
+  for (int a = 0; a < i; ++a) at += (9 - a) * (10 - a) / 2;
+  for (int b = i; b < j; ++b) at += 9 - b;
+  return at + k - j;
+}
+static_assert(triple(8, 8, 8) == 164, "165 triples");
+
 // Sums shared by the units of a workgroup.
 struct PairBins {
-  u64* three;  // [729] triples i <= j <= k
+  u64* three;  // [165] triples i <= j <= k
   u64* house;  // [729] (p, third's two types, q, j)
   u64* edge;   // [2187] (pa, pb, ab, qa, qb, j)
   __device__ __forceinline__ void clear(int t, int nt) const {
-    for (int i = t; i < 729; i += nt) three[i] = house[i] = 0;
+    for (int i = t; i < 165; i += nt) three[i] = 0;
+    for (int i = t; i < 729; i += nt) house[i] = 0;
     for (int i = t; i < 2187; i += nt) edge[i] = 0;
   }
   __device__ __forceinline__ void flush(const Totals5& K, int t, int nt) const {
     for (int k = t; k < 729; k += nt) {
       const int a = k / 81, b = (k / 9) % 9, c = k % 9;
-      if (three[k])
+      if (a <= b && b <= c && three[triple(a, b, c)])
         K.add(ec(0, 2, a / 3 + 1) | ec(2, 1, a % 3 + 1) | ec(0, 3, b / 3 + 1) | ec(3, 1, b % 3 + 1) |
-                  ec(0, 4, c / 3 + 1) | ec(4, 1, c % 3 + 1), three[k]);
+                  ec(0, 4, c / 3 + 1) | ec(4, 1, c % 3 + 1), three[triple(a, b, c)]);
       if (house[k]) {  // u 0, v 1, roof 2, w 3, other middle 4
         const int p = k / 243, x = (k / 81) % 3, y = (k / 27) % 3, q = (k / 9) % 3, j = k % 9;
         K.add(ec(0, 1, p + 1) | ec(0, 2, x + 1) | ec(1, 2, y + 1) | ec(1, 3, q + 1) | ec(0, 4, j / 3 + 1) |
@@ -705,23 +764,20 @@ __device__ __forceinline__ void pairs_and_triples(const uint32_t (&n)[9], u64* p
     }
   }
   if (sum < 3) return;
-#pragma unroll 1
-  for (int k = 0; k < 165; ++k) {  // i <= j <= l
-    int i = 0, r = k;
-    for (; r >= (9 - i) * (10 - i) / 2; ++i) r -= (9 - i) * (10 - i) / 2;
-    int j = i;
-    for (; r >= 9 - j; ++j) r -= 9 - j;
-    const int l = j + r;
-    u64 a = 0, b = 0, c = 0;
 #pragma unroll
-    for (int x = 0; x < 9; ++x) {
-      a = i == x ? n[x] : a;
-      b = j == x ? n[x] : b;
-      c = l == x ? n[x] : c;
+  for (int i = 0; i < 9; ++i) {
+    if (!n[i]) continue;
+    const u64 a = n[i];
+#pragma unroll
+    for (int j = i; j < 9; ++j) {
+      const u64 b = n[j], ab = i == j ? a * (a - 1) / 2 : a * b;
+      if (!ab) continue;
+#pragma unroll
+      for (int k = j; k < 9; ++k) {
+        const u64 c = n[k], w = i == k ? ab * (a - 2) / 3 : j == k ? a * (b * (b - 1) / 2) : ab * c;
+        if (w) atomicAdd(&B.three[triple(i, j, k)], w);
+      }
     }
-    if (!a || !b || !c) continue;
-    const u64 w = i == l ? a * (a - 1) / 2 * (a - 2) / 3 : i == j ? a * (a - 1) / 2 * c : j == l ? a * (b * (b - 1) / 2) : a * b * c;
-    if (w) atomicAdd(&B.three[81 * i + 9 * j + l], w);
   }
 }
 
@@ -738,11 +794,12 @@ __device__ __forceinline__ void house_add(uint32_t (&n)[9], const uint32_t (&tv)
 }
 
 // The edges (a, b) among N(u) with b after a in u's row, for G* entry E = (u,
-// a): every w adjacent to both, by lanes l, l + L .. of E's links.  n_of(w, n):
-// the wedges u .. w, false when w is not in the table.
+// a): every w adjacent to both; links l, l + step .. of E, of each the thirds
+// sub, sub + subs ...  n_of(w, n): the wedges u .. w, false when w is not in the
+// table.
 template <class F>
 __device__ __forceinline__ void edge_add(const DevGraph& G, const Links& L, int32_t u, int32_t ua, int32_t E, int32_t l,
-                                         int32_t step, const PairBins& B, F&& n_of) {
+                                         int32_t step, int32_t sub, int32_t subs, const PairBins& B, F&& n_of) {
   const uint32_t al = (uint32_t)(E - ua), pa = (G.gs_idx[E] >> kTypeShift) - 1u;
   const int32_t aa = G.gs_off[(int32_t)(G.gs_idx[E] & kIdMask)], o = L.off[E], t = L.cnt[E];
   for (int32_t k = l; k < t; k += step) {
@@ -750,7 +807,8 @@ __device__ __forceinline__ void edge_add(const DevGraph& G, const Links& L, int3
     if (bl < al) continue;
     const uint32_t pb = (G.gs_idx[ua + (int32_t)bl] >> kTypeShift) - 1u;
     const int32_t M = L.mate[o + k], mo = L.off[M], mt = L.cnt[M];  // entry (a, b)
-    for (int32_t x = 0; x < mt; ++x) {
+    if (mt < 2) continue;                                          // u alone
+    for (int32_t x = sub; x < mt; x += subs) {
       const uint32_t g = L.idx[mo + x], fw = G.gs_idx[aa + (int32_t)(g & kIdMask)];
       const uint32_t qa = (fw >> kTypeShift) - 1u, qb = (g >> kTypeShift) - 1u, w = fw & kIdMask;
       if ((int32_t)w == u) continue;
@@ -765,6 +823,7 @@ __device__ __forceinline__ void edge_add(const DevGraph& G, const Links& L, int3
     }
   }
 }
+constexpr int kManyLinks = 8;  // links of an entry from which a wave takes it, eight lanes per link
 
 // Lists the vertices with two neighbours or more by their visits.  Eight lanes
 // per vertex.
@@ -806,9 +865,12 @@ __global__ __launch_bounds__(NT < 256 ? 256 : NT) void k_pairs5(DevGraph G, Tota
                                                                 const int32_t* __restrict__ queue,
                                                                 const int32_t* __restrict__ list, const int32_t* st) {
   constexpr int BT = NT < 256 ? 256 : NT, NU = BT / NT, H = 1 << HB, LPR = 8;
+  constexpr int CAP = kCapPair[NT == 64 ? 0 : NT == 256 ? 1 : 2], LONG = 64;
   __shared__ uint32_t s_key[NU][H];
   __shared__ u64 s_cnt[NU][H], s_pair[NU][81];
-  __shared__ u64 s_three[729], s_house[729], s_edge[2187];
+  __shared__ uint16_t s_act[NU][CAP / 2];  // slots with two wedges or more
+  __shared__ int32_t s_nact[NU], s_row[NU][128], s_len[NU][128], s_tri[NU][128];  // N(u): rows, their lengths, links
+  __shared__ u64 s_three[165], s_house[729], s_edge[2187];
   if (st[kStatus] != 0) return;
   const int32_t count = queue[kPairQueue + (NT == 64 ? kPair64 : NT == 256 ? kPair256 : kPair1024)];
   if ((int32_t)blockIdx.x * NU >= count) return;
@@ -822,19 +884,35 @@ __global__ __launch_bounds__(NT < 256 ? 256 : NT) void k_pairs5(DevGraph G, Tota
     cnt[i] = 0;
   }
   for (int i = t; i < 81; i += NT) pair[i] = 0;
+  if (t == 0) s_nact[un] = 0;
   __syncthreads();
   auto sync = [] {
     if constexpr (NT <= 64) wave_sync();
     else __syncthreads();
   };
+  uint16_t* act = s_act[un];
+  int32_t *row = s_row[un], *len = s_len[un], *ntri = s_tri[un];
   // pendants at u: thread t holds the pairs (pi, pj), by the pendant's type
   u64 pend[2][3] = {{0, 0, 0}, {0, 0, 0}};
   for (int32_t k = (int32_t)blockIdx.x * NU + un; k < count; k += (int32_t)gridDim.x * NU) {
     const int32_t u = list[k], ua = G.gs_off[u], d = G.gs_off[u + 1] - ua;
-    for (int32_t i = t / LPR; i < d; i += NT / LPR) {
-      const uint32_t ev = G.gs_idx[ua + i];
-      const int32_t v = (int32_t)(ev & kIdMask), ra = G.gs_off[v], rb = G.gs_off[v + 1];
-      const int p7 = 21 * (int)((ev >> kTypeShift) - 1u);
+    for (int32_t i = t; i < d; i += NT) {
+      const int32_t v = (int32_t)(G.gs_idx[ua + i] & kIdMask), ra = G.gs_off[v];
+      row[i] = ra;
+      len[i] = G.gs_off[v + 1] - ra;
+      ntri[i] = L.cnt[ua + i];
+    }
+    sync();
+    // body(i, lane, lanes) for the rows of N(u): a wave for a long one
+    auto rows = [&](bool linked, auto&& body) {
+      for (int32_t i = t >> 6; i < d; i += NT / 64)
+        if (len[i] > LONG && (!linked || ntri[i])) body(i, t & 63, 64);
+      for (int32_t i = t / LPR; i < d; i += NT / LPR)
+        if (len[i] <= LONG && (!linked || ntri[i])) body(i, t % LPR, LPR);
+    };
+    rows(false, [&](int32_t i, int32_t l, int32_t step) {
+      const int p7 = 21 * (int)((G.gs_idx[ua + i] >> kTypeShift) - 1u);
+      const int32_t m = len[i];
       auto entry = [&](int32_t, uint32_t f) {
         const uint32_t w = f & kIdMask;
         if ((int32_t)w == u) return;
@@ -846,8 +924,8 @@ __global__ __launch_bounds__(NT < 256 ? 256 : NT) void k_pairs5(DevGraph G, Tota
         }
         atomicAdd(&cnt[h], 1ull << (p7 + 7 * (int)((f >> kTypeShift) - 1u)));
       };
-      for (int32_t r = t % LPR; r < rb - ra; r += 4 * LPR) each4(G.gs_idx + ra, r, LPR, rb - ra, entry);
-    }
+      for (int32_t r = l; r < m; r += 4 * step) each4(G.gs_idx + row[i], r, step, m, entry);
+    });
     sync();
     auto fields = [](u64 c, uint32_t (&n)[9]) {
 #pragma unroll
@@ -855,9 +933,13 @@ __global__ __launch_bounds__(NT < 256 ? 256 : NT) void k_pairs5(DevGraph G, Tota
     };
     for (int i = t; i < H; i += NT) {
       const u64 c = cnt[i];
-      if (!c || one_wedge(c, kOnes7)) continue;
+      if (c && !one_wedge(c, kOnes7)) act[atomicAdd(&s_nact[un], 1)] = (uint16_t)i;
+    }
+    sync();
+    const int32_t na = s_nact[un];
+    for (int x = t; x < na; x += NT) {
       uint32_t n[9];
-      fields(c, n);
+      fields(cnt[act[x]], n);
       pairs_and_triples(n, pair, B);
     }
     sync();
@@ -881,25 +963,30 @@ __global__ __launch_bounds__(NT < 256 ? 256 : NT) void k_pairs5(DevGraph G, Tota
       fields(c, n);
       return true;
     };
-    for (int32_t i = t / LPR; i < d; i += NT / LPR) {
-      const int32_t E = ua + i;
-      if (!L.cnt[E]) continue;
-      const uint32_t ev = G.gs_idx[E], p = (ev >> kTypeShift) - 1u;
-      const int32_t v = (int32_t)(ev & kIdMask), ra = G.gs_off[v], rb = G.gs_off[v + 1];
-      uint32_t tv[9];
-      L.types(E, tv);
-      for (int32_t r = ra + t % LPR; r < rb; r += LPR) {
-        const uint32_t f = G.gs_idx[r], w = f & kIdMask;
-        uint32_t n[9];
-        if ((int32_t)w != u && n_of(w, n)) house_add(n, tv, p, (f >> kTypeShift) - 1u, s_house);
-      }
-      edge_add(G, L, u, ua, E, t % LPR, LPR, B, n_of);
+    if (na > 0) {
+      rows(true, [&](int32_t i, int32_t l, int32_t step) {
+        const int32_t E = ua + i, m = len[i];
+        const uint32_t p = (G.gs_idx[E] >> kTypeShift) - 1u;
+        uint32_t tv[9];
+        L.types(E, tv);
+        auto entry = [&](int32_t, uint32_t f) {
+          const uint32_t w = f & kIdMask;
+          uint32_t n[9];
+          if ((int32_t)w != u && n_of(w, n)) house_add(n, tv, p, (f >> kTypeShift) - 1u, s_house);
+        };
+        for (int32_t r = l; r < m; r += 4 * step) each4(G.gs_idx + row[i], r, step, m, entry);
+      });
+      for (int32_t i = t >> 6; i < d; i += NT / 64)
+        if (ntri[i] > kManyLinks) edge_add(G, L, u, ua, ua + i, (t & 63) >> 3, 8, t & 7, 8, B, n_of);
+      for (int32_t i = t / LPR; i < d; i += NT / LPR)
+        if (ntri[i] > 0 && ntri[i] <= kManyLinks) edge_add(G, L, u, ua, ua + i, t % LPR, LPR, 0, 1, B, n_of);
     }
     sync();
     for (int i = t; i < H; i += NT) {
       key[i] = kNone;
       cnt[i] = 0;
     }
+    if (t == 0) s_nact[un] = 0;
     sync();
   }
 #pragma unroll
@@ -920,7 +1007,7 @@ __global__ __launch_bounds__(1024) void k_pairs5_block(DevGraph G, Totals5 K, Li
                                                        const int32_t* __restrict__ list, const int32_t* st) {
   constexpr int NT = 1024, NW = NT / 64;
   __shared__ uint32_t cnt[9 * kPairIds / 2];
-  __shared__ u64 pair[81], s_three[729], s_house[729], s_edge[2187];
+  __shared__ u64 pair[81], s_three[165], s_house[729], s_edge[2187];
   __shared__ int32_t pt_a[NT], pt_b[NT];
   if (st[kStatus] != 0) return;
   const int32_t nblk = (G.n + kPairIds - 1) / kPairIds;
@@ -1000,8 +1087,16 @@ __global__ __launch_bounds__(1024) void k_pairs5_block(DevGraph G, Totals5 K, Li
         if ((int32_t)w != u && n_of(w, n)) house_add(n, tv, p, (e >> kTypeShift) - 1u, s_house);
       }
     });
-    for (int32_t i = t >> 3; i < d; i += NT / 8)
-      if (L.cnt[ua + i]) edge_add(G, L, u, ua, ua + i, t & 7, 8, B, n_of);
+    for (int32_t i0 = 0; i0 < d; i0 += NT) {
+      pt_a[t] = i0 + t < d ? L.cnt[ua + i0 + t] : 0;
+      __syncthreads();
+      const int32_t m = min(NT, d - i0);
+      for (int32_t k = wv; k < m; k += NW)
+        if (pt_a[k] > kManyLinks) edge_add(G, L, u, ua, ua + i0 + k, lane >> 3, 8, lane & 7, 8, B, n_of);
+      for (int32_t k = t >> 3; k < m; k += NT / 8)
+        if (pt_a[k] > 0 && pt_a[k] <= kManyLinks) edge_add(G, L, u, ua, ua + i0 + k, t & 7, 8, 0, 1, B, n_of);
+      __syncthreads();
+    }
     __syncthreads();
     for (int i = t; i < 9 * kPairIds / 2; i += NT) cnt[i] = 0;
     __syncthreads();
@@ -1033,7 +1128,8 @@ __device__ __forceinline__ void c5_flush(const Totals5& K, const u64* bins, int 
 template <int NT, int HB>
 __global__ __launch_bounds__(256) void k_c5(DevGraph G, Totals5 K, const int32_t* __restrict__ queue,
                                             const int32_t* __restrict__ list, const int32_t* st) {
-  constexpr int NU = 256 / NT, H = 1 << HB, LPR = NT == 16 ? 4 : 8;
+  constexpr int NU = 256 / NT, H = 1 << HB, LPR = NT == 16 ? 4 : 8, LONG = 64;
+  __shared__ int32_t s_row[NU][NT], s_len[NU][NT];
   __shared__ uint32_t s_key[NU][H];
   __shared__ u64 s_cnt[NU][H], bins[243];
   __shared__ uint16_t s_act[NU][H];
@@ -1045,6 +1141,7 @@ __global__ __launch_bounds__(256) void k_c5(DevGraph G, Totals5 K, const int32_t
   uint32_t* key = s_key[un];
   u64* cnt = s_cnt[un];
   uint16_t* act = s_act[un];
+  int32_t *row = s_row[un], *len = s_len[un];
   for (int i = t; i < H; i += NT) {
     key[i] = kNone;
     cnt[i] = 0;
@@ -1085,31 +1182,47 @@ __global__ __launch_bounds__(256) void k_c5(DevGraph G, Totals5 K, const int32_t
       else cnt[i] = 0;
     }
     sync();
+    // NT of the listed w at a time: their rows N- first, then four lanes per
+    // row, the whole unit for a long one
     const int32_t na = s_nact[un];
-    for (int32_t x = t / LPR; x < na; x += NT / LPR) {
-      const int i = act[x];
-      const int32_t w = (int32_t)key[i], wa = G.gs_off[w] - G.np_off[w], wm = G.gs_off[w + 1] - G.np_off[w + 1] - wa;
-      const u64 c = cnt[i];
-      auto entry = [&](int32_t, uint32_t f) {
-        const uint32_t z = f & kIdMask;
-        uint32_t h = hash_mul(z, HB), kk;
-        while ((kk = key[h]) != z && kk != kNone) h = (h + 1) & (H - 1);
-        if (kk != z) return;
-        const u64 e = cnt[h];
-        if (!e) return;
-        const int ty = (int)(f >> kTypeShift) - 1;
+    for (int32_t x0 = 0; x0 < na; x0 += NT) {
+      if (x0 + t < na) {
+        const int32_t w = (int32_t)key[act[x0 + t]], wa = G.gs_off[w] - G.np_off[w];
+        row[t] = wa;
+        len[t] = G.gs_off[w + 1] - G.np_off[w + 1] - wa;
+      }
+      sync();
+      const int32_t nx = min(NT, na - x0);
+      auto take = [&](int32_t x, int32_t l, int32_t step) {
+        const u64 c = cnt[act[x0 + x]];
+        const int32_t wa = row[x], wm = len[x];
+        auto entry = [&](int32_t, uint32_t f) {
+          const uint32_t z = f & kIdMask;
+          uint32_t h = hash_mul(z, HB), kk;
+          while ((kk = key[h]) != z && kk != kNone) h = (h + 1) & (H - 1);
+          if (kk != z) return;
+          const u64 e = cnt[h];
+          if (!e) return;
+          const int ty = (int)(f >> kTypeShift) - 1;
 #pragma unroll
-        for (int p = 0; p < 9; ++p) {
-          const u64 a = (c >> (7 * p)) & 127u;
-          if (!a) continue;
+          for (int p = 0; p < 9; ++p) {
+            const u64 a = (c >> (7 * p)) & 127u;
+            if (!a) continue;
 #pragma unroll
-          for (int q = 0; q < 9; ++q) {
-            const u64 b = (e >> (7 * q)) & 127u;
-            if (b) atomicAdd(&bins[27 * p + 9 * ty + q], a * b);
+            for (int q = 0; q < 9; ++q) {
+              const u64 b = (e >> (7 * q)) & 127u;
+              if (b) atomicAdd(&bins[27 * p + 9 * ty + q], a * b);
+            }
           }
-        }
+        };
+        for (int32_t r = l; r < wm; r += 4 * step) each4(G.nm_idx + wa, r, step, wm, entry);
       };
-      for (int32_t r = t % LPR; r < wm; r += 4 * LPR) each4(G.nm_idx + wa, r, LPR, wm, entry);
+      if constexpr (NT > 16)
+        for (int32_t x = 0; x < nx; ++x)
+          if (len[x] > LONG) take(x, t, NT);
+      for (int32_t x = t / 4; x < nx; x += NT / 4)
+        if (NT == 16 || len[x] <= LONG) take(x, t % 4, 4);
+      sync();
     }
     sync();
     for (int i = t; i < H; i += NT) {
@@ -1128,7 +1241,7 @@ __global__ __launch_bounds__(kC5Top) void k_c5_top(DevGraph G, Totals5 K, const 
                                                    uint32_t* __restrict__ slices, const int32_t* st) {
   constexpr int NT = kC5Top;
   __shared__ u64 bins[243];
-  __shared__ int32_t nact;
+  __shared__ int32_t nact, wid[NT], row[NT], len[NT];
   if (st[kStatus] != 0) return;
   const int32_t nh = queue[kWedgeHuge], count = nh + queue[kWedgeTop];
   if ((int32_t)blockIdx.x >= count) return;
@@ -1149,45 +1262,77 @@ __global__ __launch_bounds__(kC5Top) void k_c5_top(DevGraph G, Totals5 K, const 
       const uint32_t ev = G.nm_idx[ma + i], v = ev & kIdMask;
       const int32_t ra = G.gs_off[v], rb = G.gs_off[v + 1];
       const uint32_t p = (ev >> kTypeShift) - 1u;
-      for (int32_t r = ra + (t & 15); r < rb; r += 16) {
-        const uint32_t f = G.gs_idx[r], w = f & kIdMask;
-        if ((int32_t)w == u || !ranked_below(G, (uint32_t)G.deg[w], (int32_t)w, du, u)) continue;
-        const uint32_t j = 3 * p + (f >> kTypeShift) - 1u;
-        uint32_t* c = cnt + (int64_t)w * 5;
-        // the sum sits above the ninth count
-        const uint32_t old = atomicAdd(&c[4], j == 8 ? 0x10001u : 0x10000u);
-        if (j < 8) atomicAdd(&c[j >> 1], 1u << (16 * (j & 1u)));
-        if (old >> 16 == 0) act[atomicAdd(&nact, 1)] = w;
+      for (int32_t r = ra + (t & 15); r < rb; r += 64) {
+        uint32_t f[4], old[4];
+        bool in[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) f[k] = G.gs_idx[min(r + 16 * k, rb - 1)];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const int32_t w = (int32_t)(f[k] & kIdMask);
+          in[k] = r + 16 * k < rb && w != u && ranked_below(G, (uint32_t)G.deg[w], w, du, u);
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const uint32_t j = 3 * p + (f[k] >> kTypeShift) - 1u;
+          uint32_t* c = cnt + (int64_t)(f[k] & kIdMask) * 5;
+          // the sum sits above the ninth count
+          old[k] = in[k] ? atomicAdd(&c[4], j == 8 ? 0x10001u : 0x10000u) : ~0u;
+          if (in[k] && j < 8) atomicAdd(&c[j >> 1], 1u << (16 * (j & 1u)));
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          if (old[k] >> 16 == 0) act[atomicAdd(&nact, 1)] = f[k] & kIdMask;
       }
     }
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     const int32_t na = nact;
-    for (int32_t x = t >> 4; x < na; x += NT / 16) {
-      const uint32_t w = __hip_atomic_load(&act[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const int32_t wa = G.gs_off[w] - G.np_off[w], wm = G.gs_off[w + 1] - G.np_off[w + 1] - wa;
-      uint32_t c[5];
+    for (int32_t x0 = 0; x0 < na; x0 += NT) {
+      if (x0 + t < na) {
+        const int32_t w = (int32_t)__hip_atomic_load(&act[x0 + t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int32_t wa = G.gs_off[w] - G.np_off[w];
+        wid[t] = w;
+        row[t] = wa;
+        len[t] = G.gs_off[w + 1] - G.np_off[w + 1] - wa;
+      }
+      __syncthreads();
+      const int32_t nx = min(NT, na - x0);
+      auto take = [&](int32_t x, int32_t l, int32_t step) {
+        const int32_t wa = row[x], wm = len[x];
+        uint32_t c[5];
 #pragma unroll
-      for (int i = 0; i < 5; ++i) c[i] = word(w, i);
-      for (int32_t r = t & 15; r < wm; r += 16) {
-        const uint32_t f = G.nm_idx[wa + r], z = f & kIdMask;
-        uint32_t e[5];
-        e[4] = word(z, 4);
-        if (!e[4]) continue;
+        for (int i = 0; i < 5; ++i) c[i] = word((uint32_t)wid[x], i);
+        for (int32_t r0 = l; r0 < wm; r0 += 4 * step) {
+          uint32_t f[4], e[4][5];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) e[i] = word(z, i);
-        const int ty = (int)(f >> kTypeShift) - 1;
+          for (int k = 0; k < 4; ++k) f[k] = G.nm_idx[wa + min(r0 + k * step, wm - 1)];
 #pragma unroll
-        for (int p = 0; p < 9; ++p) {
-          const u64 a = (c[p >> 1] >> (16 * (p & 1))) & 0xFFFFu;
-          if (!a) continue;
+          for (int k = 0; k < 4; ++k) e[k][4] = r0 + k * step < wm ? word(f[k] & kIdMask, 4) : 0u;
 #pragma unroll
-          for (int q = 0; q < 9; ++q) {
-            const u64 b = (e[q >> 1] >> (16 * (q & 1))) & 0xFFFFu;
-            if (b) atomicAdd(&bins[27 * p + 9 * ty + q], a * b);
+          for (int k = 0; k < 4; ++k) {
+            if (!e[k][4]) continue;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) e[k][i] = word(f[k] & kIdMask, i);
+            const int ty = (int)(f[k] >> kTypeShift) - 1;
+#pragma unroll
+            for (int p = 0; p < 9; ++p) {
+              const u64 a = (c[p >> 1] >> (16 * (p & 1))) & 0xFFFFu;
+              if (!a) continue;
+#pragma unroll
+              for (int q = 0; q < 9; ++q) {
+                const u64 b = (e[k][q >> 1] >> (16 * (q & 1))) & 0xFFFFu;
+                if (b) atomicAdd(&bins[27 * p + 9 * ty + q], a * b);
+              }
+            }
           }
         }
-      }
+      };
+      for (int32_t x = t >> 6; x < nx; x += NT / 64)
+        if (len[x] > 64) take(x, t & 63, 64);
+      for (int32_t x = t >> 2; x < nx; x += NT / 4)
+        if (len[x] > 0 && len[x] <= 64) take(x, t & 3, 4);
+      __syncthreads();
     }
     __syncthreads();
     for (int32_t x = t; x < na; x += NT) {
@@ -1239,10 +1384,13 @@ __global__ __launch_bounds__(256) void k_sum5(const uint64_t* __restrict__ acc, 
 __global__ __launch_bounds__(256) void k_step5(Tables5 T, int j, const uint64_t* __restrict__ P,
                                                uint64_t* __restrict__ Q, uint64_t* __restrict__ I, int32_t* st) {
   if (st[kStatus] != 0) return;
-  const int32_t c = blockIdx.x * 256 + threadIdx.x;
-  if (c >= kC5) return;
+  const int32_t c = blockIdx.x * 32 + (threadIdx.x >> 3), l8 = threadIdx.x & 7;
   u64 s = 0;
-  for (int32_t k = T.up_off[c], e = T.up_off[c + 1]; k < e; ++k) s += (u64)(T.up[k] >> 16) * P[T.up[k] & 0xFFFF];
+  if (c < kC5)
+    for (int32_t k = T.up_off[c] + l8, e = T.up_off[c + 1]; k < e; k += 8) s += (u64)(T.up[k] >> 16) * P[T.up[k] & 0xFFFF];
+#pragma unroll
+  for (int o = 4; o; o >>= 1) s += __shfl_xor(s, o);
+  if (c >= kC5 || l8) return;
   s /= (u64)j;
   Q[c] = s;
   const u64 v = j & 1 ? I[c] - s : I[c] + s;
@@ -1352,7 +1500,7 @@ void enqueue_copies5_finish(Pipeline& p, const DevGraph& g, const Copies5Run& R,
   const dim3 cg((kC5 + 255) / 256);
   hipLaunchKernelGGL(k_sum5, cg, dim3(256), 0, s, R.acc, R.a4, R.a3, T.five, P[0], I, p.status);
   for (int j = 1; j <= 6; ++j)
-    hipLaunchKernelGGL(k_step5, cg, dim3(256), 0, s, T.five, j, P[(j + 1) & 1], P[j & 1], I, p.status);
+    hipLaunchKernelGGL(k_step5, dim3((kC5 + 31) / 32), dim3(256), 0, s, T.five, j, P[(j + 1) & 1], P[j & 1], I, p.status);
   hipLaunchKernelGGL(k_write5, cg, dim3(256), 0, s, I, out, p.status);
 }
 
