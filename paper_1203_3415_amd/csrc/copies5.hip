@@ -48,9 +48,11 @@ constexpr int kC5 = 9364;
 constexpr int kRep5 = 32;                // copies of the totals (see totals() in counts.hip)
 constexpr int kC5Top = 1024;             // threads of k_c5_top
 constexpr size_t kSliceBytes = size_t(96) << 20;  // wedge tables of k_c5_top
-enum PairList : int { kPair64 = 0, kPair256 = 1, kPair1024 = 2, kPairBlock = 3, kPairLists = 4 };
+// Lists of vertices by their wedge table in k_pairs5.
+enum PairList : int { kPair9 = 0, kPair10 = 1, kPair11 = 2, kPair12 = 3, kPair13 = 4, kPairBlock = 5, kPairLists = 6 };
 constexpr int kPairQueue = 16;           // queue words of the pair lists
-constexpr int kCapPair[3] = {384, 3072, 6144};  // visits of a vertex in the three wedge hashes of k_pairs5
+// visits of a vertex in a hash of 2^HB words
+constexpr int pair_cap(int HB) { return (1 << HB) * 3 / 4; }
 
 struct Links {
   const uint32_t* emap;  // per G* entry (u, b): N+ position of the edge << 1 | u is its higher end
@@ -438,6 +440,7 @@ __device__ __forceinline__ int32_t link_at(const uint32_t* p, int32_t m, uint32_
 }
 
 constexpr int kStaged = 512;  // links of a unit up to which a wave keeps them in LDS
+constexpr int kApexParts = 4;  // waves that share a unit's thirds, 64 (and, for the K4s, 8) at a time
 constexpr int kWheelT = 16;   // links of a unit up to which its wheels are taken pair by pair
 
 __global__ __launch_bounds__(256) void k_apex5(DevGraph G, Totals5 K, Links L, const u64* __restrict__ S,
@@ -446,12 +449,14 @@ __global__ __launch_bounds__(256) void k_apex5(DevGraph G, Totals5 K, Links L, c
   if (st[kStatus] != 0) return;
   const int lane = threadIdx.x & 63;
   uint32_t* sR = s_R[threadIdx.x >> 6];
-  for_entries(G, L.cnt, 1, 1 << 30, [&](int32_t E) {
+  const int part = blockIdx.y;
+  for_entries(G, L.cnt, 64 * part + 1, 1 << 30, [&](int32_t E) {
     const int32_t u = G.gs_row[E], ua = G.gs_off[u], t = L.cnt[E];
     const uint32_t bl = (uint32_t)(E - ua), pb = G.gs_idx[E] >> kTypeShift;
     const int32_t b = (int32_t)(G.gs_idx[E] & kIdMask);
     const uint32_t* R = L.idx + L.off[E];
     const uint4 Du = G.dt[u], Db = G.dt[b];
+    const int parts = min((int)gridDim.y, (t + 63) / 64);  // the waves on this unit
     const bool staged = t <= kStaged;  // b's links in LDS: searched for every third of every c
     if (staged)
       for (int32_t k = lane; k < t; k += 64) sR[k] = R[k];
@@ -462,7 +467,7 @@ __global__ __launch_bounds__(256) void k_apex5(DevGraph G, Totals5 K, Links L, c
     L.types(E, tb);
     const uint32_t cb = ec(0, 1, pb);
     // pairs and triples of thirds: a pendant at u; a book
-    if (t >= 2)
+    if (t >= 2 && part == 0)
       for (int k = lane; k < 45; k += 64) {
         int i = 0, j = k;
         for (; j >= 9 - i; ++i) j -= 9 - i;
@@ -487,7 +492,7 @@ __global__ __launch_bounds__(256) void k_apex5(DevGraph G, Totals5 K, Links L, c
             K.add(c | ec(0, 4, x / 3 + 1) | ec(1, 4, x % 3 + 1), w3);
           }
       }
-    for (int32_t k = lane; k < t; k += 64) {
+    for (int32_t k = 64 * part + lane; k < t; k += 64 * (int32_t)gridDim.y) {
       const uint32_t f = at_b(k), cl = f & kIdMask, bc = f >> kTypeShift;
       const uint32_t fc = G.gs_idx[ua + cl], pc = fc >> kTypeShift;
       const int32_t c = (int32_t)(fc & kIdMask), Ec = ua + (int32_t)cl;
@@ -552,7 +557,7 @@ __global__ __launch_bounds__(256) void k_apex5(DevGraph G, Totals5 K, Links L, c
     }
     // the vertices adjacent to u, b and c, eight lanes per c
     if (t >= 2)
-      for (int32_t k = lane >> 3; k < t; k += 8) {
+      for (int32_t k = 8 * part + (lane >> 3); k < t; k += 8 * parts) {
         const uint32_t f = at_b(k), cl = f & kIdMask, bc = f >> kTypeShift;
         if (cl < bl) continue;
         const int32_t Ec = ua + (int32_t)cl, mc = L.cnt[Ec];
@@ -598,7 +603,7 @@ __global__ __launch_bounds__(256) void k_apex5(DevGraph G, Totals5 K, Links L, c
       }
     // wheels with hub u whose rim's first vertex is b: two thirds c < c' of
     // (u, b) and a vertex d adjacent to both
-    if (t >= 2 && t <= kWheelT)
+    if (t >= 2 && t <= kWheelT && part == 0)
       for (int32_t k = lane; k < t * t; k += 64) {
         const int32_t i = k / t, j = k % t;
         const uint32_t cl = R[i] & kIdMask, c2 = R[j] & kIdMask;
@@ -827,8 +832,11 @@ constexpr int kManyLinks = 8;  // links of an entry from which a wave takes it, 
 
 // Lists the vertices with two neighbours or more by their visits.  Eight lanes
 // per vertex.
-__global__ __launch_bounds__(256) void k_classify5(DevGraph G, int32_t* l0, int32_t* l1, int32_t* l2, int32_t* l3,
-                                                   int32_t* __restrict__ queue, const int32_t* st) {
+struct PairListsOf {
+  int32_t* v[kPairLists];
+};
+__global__ __launch_bounds__(256) void k_classify5(DevGraph G, PairListsOf L, int32_t* __restrict__ queue,
+                                                   const int32_t* st) {
   __shared__ int32_t cnt[kPairLists], base[kPairLists];
   __shared__ uint16_t where[256];  // list and place of each of this workgroup's vertices
   if (st[kStatus] != 0) return;
@@ -840,12 +848,13 @@ __global__ __launch_bounds__(256) void k_classify5(DevGraph G, int32_t* l0, int3
     const int32_t a = G.gs_off[v], b = G.gs_off[v + 1], d = b - a;
     int32_t vis = 0;
     if (d <= 127)
-      for (int32_t i = a + l8; i < b; i += 8) vis += min(G.deg[G.gs_idx[i] & kIdMask], kCapPair[2] + 1);
+      for (int32_t i = a + l8; i < b; i += 8) vis += min(G.deg[G.gs_idx[i] & kIdMask], pair_cap(13) + 1);
 #pragma unroll
     for (int o = 4; o; o >>= 1) vis += __shfl_xor(vis, o);
     if (l8 == 0) {
-      const int l = d < 2 ? 15 : d > 127 ? kPairBlock : vis <= kCapPair[0] ? kPair64 : vis <= kCapPair[1] ? kPair256
-                                                        : vis <= kCapPair[2] ? kPair1024 : kPairBlock;
+      int l = d < 2 ? 15 : d > 127 ? kPairBlock : kPair9;
+      if (l == kPair9)
+        while (l < kPairBlock && vis > pair_cap(9 + l)) ++l;
       where[v - v0] = (uint16_t)(l | (l < kPairLists ? atomicAdd(&cnt[l], 1) : 0) << 4);
     }
   }
@@ -856,23 +865,24 @@ __global__ __launch_bounds__(256) void k_classify5(DevGraph G, int32_t* l0, int3
   const int32_t v = v0 + (int32_t)threadIdx.x;
   if (v >= v1) return;
   const int l = where[threadIdx.x] & 15, at = where[threadIdx.x] >> 4;
-  if (l < kPairLists) (l == 0 ? l0 : l == 1 ? l1 : l == 2 ? l2 : l3)[base[l] + at] = v;
+  if (l < kPairLists) L.v[l][base[l] + at] = v;
 }
 
-// NT threads per u; a hash of 2^HB vertices.
-template <int NT, int HB>
-__global__ __launch_bounds__(NT < 256 ? 256 : NT) void k_pairs5(DevGraph G, Totals5 K, Links L,
+// NT threads per u, BT per workgroup; a hash of 2^HB vertices.
+template <int NT, int HB, int BT>
+__global__ __launch_bounds__(BT) void k_pairs5(DevGraph G, Totals5 K, Links L,
                                                                 const int32_t* __restrict__ queue,
                                                                 const int32_t* __restrict__ list, const int32_t* st) {
-  constexpr int BT = NT < 256 ? 256 : NT, NU = BT / NT, H = 1 << HB, LPR = 8;
-  constexpr int CAP = kCapPair[NT == 64 ? 0 : NT == 256 ? 1 : 2], LONG = 64;
+  constexpr int NU = BT / NT, H = 1 << HB, LPR = 8;
+  static_assert(NU == 1 || NT == 64, "a barrier is the unit's own");
+  constexpr int CAP = pair_cap(HB), LONG = 64;
   __shared__ uint32_t s_key[NU][H];
   __shared__ u64 s_cnt[NU][H], s_pair[NU][81];
   __shared__ uint16_t s_act[NU][CAP / 2];  // slots with two wedges or more
   __shared__ int32_t s_nact[NU], s_row[NU][128], s_len[NU][128], s_tri[NU][128];  // N(u): rows, their lengths, links
   __shared__ u64 s_three[165], s_house[729], s_edge[2187];
   if (st[kStatus] != 0) return;
-  const int32_t count = queue[kPairQueue + (NT == 64 ? kPair64 : NT == 256 ? kPair256 : kPair1024)];
+  const int32_t count = queue[kPairQueue + HB - 9];
   if ((int32_t)blockIdx.x * NU >= count) return;
   const int un = threadIdx.x / NT, t = threadIdx.x % NT;
   uint32_t* key = s_key[un];
@@ -1125,17 +1135,17 @@ __device__ __forceinline__ void c5_flush(const Totals5& K, const u64* bins, int 
   }
 }
 
-template <int NT, int HB>
-__global__ __launch_bounds__(256) void k_c5(DevGraph G, Totals5 K, const int32_t* __restrict__ queue,
+template <int NT, int HB, int LIST>
+__global__ __launch_bounds__(NT < 256 ? 256 : NT) void k_c5(DevGraph G, Totals5 K, const int32_t* __restrict__ queue,
                                             const int32_t* __restrict__ list, const int32_t* st) {
-  constexpr int NU = 256 / NT, H = 1 << HB, LPR = NT == 16 ? 4 : 8, LONG = 64;
+  constexpr int BT = NT < 256 ? 256 : NT, NU = BT / NT, H = 1 << HB, LPR = NT == 16 ? 4 : 8, LONG = 64;
   __shared__ int32_t s_row[NU][NT], s_len[NU][NT];
   __shared__ uint32_t s_key[NU][H];
   __shared__ u64 s_cnt[NU][H], bins[243];
   __shared__ uint16_t s_act[NU][H];
   __shared__ int32_t s_nact[NU];
   if (st[kStatus] != 0) return;
-  const int32_t count = queue[NT == 16 ? kWedge16 : NT == 64 ? kWedge64 : kWedge256];
+  const int32_t count = queue[LIST];
   if ((int32_t)blockIdx.x * NU >= count) return;
   const int un = threadIdx.x / NT, t = threadIdx.x % NT;
   uint32_t* key = s_key[un];
@@ -1146,7 +1156,7 @@ __global__ __launch_bounds__(256) void k_c5(DevGraph G, Totals5 K, const int32_t
     key[i] = kNone;
     cnt[i] = 0;
   }
-  for (int i = threadIdx.x; i < 243; i += 256) bins[i] = 0;
+  for (int i = threadIdx.x; i < 243; i += BT) bins[i] = 0;
   if (t == 0) s_nact[un] = 0;
   __syncthreads();
   auto sync = [] {
@@ -1218,8 +1228,8 @@ __global__ __launch_bounds__(256) void k_c5(DevGraph G, Totals5 K, const int32_t
         for (int32_t r = l; r < wm; r += 4 * step) each4(G.nm_idx + wa, r, step, wm, entry);
       };
       if constexpr (NT > 16)
-        for (int32_t x = 0; x < nx; ++x)
-          if (len[x] > LONG) take(x, t, NT);
+        for (int32_t x = t >> 6; x < nx; x += NT / 64)
+          if (len[x] > LONG) take(x, t & 63, 64);
       for (int32_t x = t / 4; x < nx; x += NT / 4)
         if (NT == 16 || len[x] <= LONG) take(x, t % 4, 4);
       sync();
@@ -1233,7 +1243,7 @@ __global__ __launch_bounds__(256) void k_c5(DevGraph G, Totals5 K, const int32_t
     sync();
   }
   __syncthreads();
-  c5_flush(K, bins, threadIdx.x, 256);
+  c5_flush(K, bins, threadIdx.x, BT);
 }
 
 __global__ __launch_bounds__(kC5Top) void k_c5_top(DevGraph G, Totals5 K, const int32_t* __restrict__ queue,
@@ -1422,7 +1432,7 @@ size_t copies5_bytes(int64_t n, int64_t m, int num_cus) {
          al(sizeof(uint64_t) * 199 * kRep4) + al(sizeof(uint64_t) * kC5 * kRep5) + 4 * al(sizeof(uint64_t) * kC5) +
          3 * al(4 * gs) + al(8 * (size_t)(m + 1)) + al(24 * (size_t)(m + 1)) + scan1_bytes((int64_t)gs) +
          2 * al(4 * (size_t)link_room(m)) + al(72 * (size_t)n) + al(16 * (size_t)n) + al(108 * (size_t)n) +
-         4 * al(4 * (size_t)n) + al(24 * (size_t)n * (size_t)c5_slices(n, num_cus)) + 8192;
+         kPairLists * al(4 * (size_t)n) + al(24 * (size_t)n * (size_t)c5_slices(n, num_cus)) + 8192;
 }
 
 void enqueue_copies5_start(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_t* a4, Copies5Run* R, hipStream_t s) {
@@ -1468,8 +1478,9 @@ void enqueue_copies5_finish(Pipeline& p, const DevGraph& g, const Copies5Run& R,
   int32_t* mate = A.take<int32_t>((size_t)link_room(m));
   u64* S = A.take<u64>(9 * (size_t)n);
   uint4* up = A.take<uint4>((size_t)n);
-  int32_t* list[kPairLists];
-  for (auto& l : list) l = A.take<int32_t>((size_t)n);
+  PairListsOf lists;
+  for (auto& l : lists.v) l = A.take<int32_t>((size_t)n);
+  int32_t** list = lists.v;
   const int slices = c5_slices(n, cus);
   uint32_t* slice = A.take<uint32_t>((size_t)slices * 6 * (size_t)n);
   uint64_t* P[2] = {A.take<uint64_t>(kC5), A.take<uint64_t>(kC5)};
@@ -1481,22 +1492,25 @@ void enqueue_copies5_finish(Pipeline& p, const DevGraph& g, const Copies5Run& R,
     return dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>((int64_t)cus * wgs, (items + per - 1) / per)));
   };
   hipLaunchKernelGGL(k_vertex5, grid(n, 4, 4), dim3(256), 0, s, g, K, S, up, p.status);
-  hipLaunchKernelGGL(k_classify5, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, g, list[0], list[1], list[2],
-                     list[3], R.queue, p.status);
+  hipLaunchKernelGGL(k_classify5, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, g, lists, R.queue, p.status);
   hipLaunchKernelGGL(k_links5, grid(m, 4, 8), dim3(256), 0, s, g, K, L, R.epos, R.hi, up, idx, mate, R.tri, p.status);
   hipLaunchKernelGGL(k_butterfly5, grid(n, 4, 4), dim3(256), 0, s, g, K, R.tri, p.status);
-  hipLaunchKernelGGL(k_apex5, grid(2 * m, 4, 6), dim3(256), 0, s, g, K, L, S, p.status);
+  dim3 ag = grid(2 * m, 4, 6);
+  ag.y = kApexParts;
+  hipLaunchKernelGGL(k_apex5, ag, dim3(256), 0, s, g, K, L, S, p.status);
   hipLaunchKernelGGL(k_wheel5, grid(2 * m, 256, 2), dim3(256), 0, s, g, K, L, p.status);
   hipLaunchKernelGGL(k_pairs5_block, grid(n * ((n + kPairIds - 1) / kPairIds), 1, 1), dim3(1024), 0, s, g, K, L, R.queue,
                      list[kPairBlock], p.status);
-  hipLaunchKernelGGL((k_pairs5<1024, 13>), grid(n, 1, 1), dim3(1024), 0, s, g, K, L, R.queue, list[kPair1024], p.status);
-  hipLaunchKernelGGL((k_pairs5<256, 12>), grid(n, 1, 2), dim3(256), 0, s, g, K, L, R.queue, list[kPair256], p.status);
-  hipLaunchKernelGGL((k_pairs5<64, 9>), grid(n, 4, 2), dim3(256), 0, s, g, K, L, R.queue, list[kPair64], p.status);
+  hipLaunchKernelGGL((k_pairs5<1024, 13, 1024>), grid(n, 1, 1), dim3(1024), 0, s, g, K, L, R.queue, list[kPair13], p.status);
+  hipLaunchKernelGGL((k_pairs5<512, 12, 512>), grid(n, 1, 2), dim3(512), 0, s, g, K, L, R.queue, list[kPair12], p.status);
+  hipLaunchKernelGGL((k_pairs5<256, 11, 256>), grid(n, 1, 3), dim3(256), 0, s, g, K, L, R.queue, list[kPair11], p.status);
+  hipLaunchKernelGGL((k_pairs5<128, 10, 128>), grid(n, 1, 4), dim3(128), 0, s, g, K, L, R.queue, list[kPair10], p.status);
+  hipLaunchKernelGGL((k_pairs5<64, 9, 256>), grid(n, 4, 2), dim3(256), 0, s, g, K, L, R.queue, list[kPair9], p.status);
   hipLaunchKernelGGL(k_c5_top, dim3((unsigned)slices), dim3(kC5Top), 0, s, g, K, R.queue, R.counts.wedge[kWedgeTop],
                      R.counts.wedge[kWedgeHuge], slice, p.status);
-  hipLaunchKernelGGL((k_c5<256, 12>), grid(n, 1, 3), dim3(256), 0, s, g, K, R.queue, R.counts.wedge[kWedge256], p.status);
-  hipLaunchKernelGGL((k_c5<64, 9>), grid(n, 4, 4), dim3(256), 0, s, g, K, R.queue, R.counts.wedge[kWedge64], p.status);
-  hipLaunchKernelGGL((k_c5<16, 7>), grid(n, 16, 4), dim3(256), 0, s, g, K, R.queue, R.counts.wedge[kWedge16], p.status);
+  hipLaunchKernelGGL((k_c5<512, 12, kWedge256>), grid(n, 1, 2), dim3(512), 0, s, g, K, R.queue, R.counts.wedge[kWedge256], p.status);
+  hipLaunchKernelGGL((k_c5<256, 9, kWedge64>), grid(n, 1, 8), dim3(256), 0, s, g, K, R.queue, R.counts.wedge[kWedge64], p.status);
+  hipLaunchKernelGGL((k_c5<64, 7, kWedge16>), grid(n, 4, 8), dim3(256), 0, s, g, K, R.queue, R.counts.wedge[kWedge16], p.status);
   const dim3 cg((kC5 + 255) / 256);
   hipLaunchKernelGGL(k_sum5, cg, dim3(256), 0, s, R.acc, R.a4, R.a3, T.five, P[0], I, p.status);
   for (int j = 1; j <= 6; ++j)
