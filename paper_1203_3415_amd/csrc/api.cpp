@@ -390,7 +390,7 @@ int32_t run_census_multi_enqueue(Pipeline& p, const BuildInput& in, int32_t nk, 
 // Room for the k = 5 census by subgraph copies of one graph (0: not for graphs
 // of this size).
 size_t copies5_need(const BuildInput& in) {
-  return !in.gid && copies5_fits(in.n, in.m) ? build_bytes(in.n, in.m, 1, false) + copies5_bytes(in.n, in.m, 256) : 0;
+  return !in.gid && copies5_fits(in.n, in.m) ? build_bytes(in.n, in.m, 1, false) + copies5_bytes(in.n, in.m) : 0;
 }
 
 // The sizes ks (5 among them) of one graph by subgraph copies, with a host wait
@@ -404,7 +404,7 @@ int32_t run_copies5(Pipeline& p, const BuildInput& in, int32_t nk, const int32_t
   for (int32_t i = 0; i < nk; ++i)
     if (ks[i] >= 4 && p.tune.k[ks[i]].heavy != 1) return kNotTaken;
   const size_t need = copies5_need(in);
-  if (!need || need > p.arena.cap || p.num_cus > 256) return kNotTaken;
+  if (!need || need > p.arena.cap) return kNotTaken;
   try {
     p.arena.reset();
     enqueue_zero(p.status, sizeof(int32_t) * kStatusWords, s);

@@ -46,11 +46,10 @@ namespace {
 
 constexpr int kC5 = 9364;
 constexpr int kRep5 = 32;                // copies of the totals (see totals() in counts.hip)
-constexpr int kC5Top = 1024;             // threads of k_c5_top
-constexpr size_t kSliceBytes = size_t(96) << 20;  // wedge tables of k_c5_top
+constexpr size_t kSliceBytes = size_t(96) << 20;  // wedge tables of k_c5_fill
 // Lists of vertices by their wedge table in k_pairs5.
 enum PairList : int { kPair9 = 0, kPair10 = 1, kPair11 = 2, kPair12 = 3, kPair13 = 4, kPairBlock = 5, kPairLists = 6 };
-constexpr int kPairQueue = 16;           // queue words of the pair lists
+constexpr int kPairQueue = 16, kPairCursor = 24;  // queue words of the pair lists, and of the pulls
 // visits of a vertex in a hash of 2^HB words
 constexpr int pair_cap(int HB) { return (1 << HB) * 3 / 4; }
 
@@ -60,6 +59,7 @@ struct Links {
   const int32_t* off;    // its first link
   const uint32_t* idx;   // link: place of the third z in u's row | type of z seen from b
   const int32_t* mate;   // G* entry (b, z)
+  const int32_t* src;    // G* entry (u, b)
   const uint32_t* T;     // per N+ entry: typed triangle counts (counts.hip)
 
   // T of G* entry E as t[3 (type of the third seen from u - 1) + (from b) - 1]
@@ -119,14 +119,20 @@ __device__ __forceinline__ bool two_lower(const DevGraph& G, int32_t w) {
 // lower end that lie above its higher end, by type (hi[6 e ..]), and those of
 // them that k_c5 starts from, having two lower neighbours or more (hi[6 e + 3
 // ..]).  st + 8: sum
-// of the triangles over the G* entries (64 bits); st + 10: the most at one.
+// of the triangles over the G* entries (64 bits); st + 10: the most at one; st +
+// 11: vertices of k_c5_fill.
 __global__ __launch_bounds__(256) void k_edges5(DevGraph G, const uint32_t* __restrict__ T, uint32_t* __restrict__ emap,
                                                 int32_t* __restrict__ cnt, int32_t* __restrict__ epos,
-                                                uint32_t* __restrict__ hi, int32_t* st) {
+                                                uint32_t* __restrict__ hi, const int32_t* __restrict__ queue,
+                                                int32_t* st) {
   __shared__ u64 sum;
   __shared__ int32_t most;
   if (st[kStatus] != 0) return;
-  if (threadIdx.x == 0) { sum = 0; most = 0; }
+  if (threadIdx.x == 0) {
+    sum = 0;
+    most = 0;
+    if (blockIdx.x == 0) st[11] = queue[kWedgeTop] + queue[kWedgeHuge];
+  }
   __syncthreads();
   const int32_t ne = G.np_off[G.n];
   u64 s = 0;
@@ -192,7 +198,7 @@ struct LinkCount {
 __global__ __launch_bounds__(256) void k_links5(DevGraph G, Totals5 K, Links L, const int32_t* __restrict__ epos,
                                                 const uint32_t* __restrict__ hi, const uint4* __restrict__ up,
                                                 uint32_t* __restrict__ idx, int32_t* __restrict__ mate,
-                                                uint32_t* __restrict__ tri, const int32_t* st) {
+                                                int32_t* __restrict__ src, uint32_t* __restrict__ tri, const int32_t* st) {
   if (st[kStatus] != 0) return;
   const int lane = threadIdx.x & 63;
   const int32_t ne = G.np_off[G.n], nw = gridDim.x * 4, w0 = blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -225,8 +231,10 @@ __global__ __launch_bounds__(256) void k_links5(DevGraph G, Totals5 K, Links L, 
           const uint32_t tx = G.gs_idx[px] >> kTypeShift, ty = G.gs_idx[py] >> kTypeShift;
           idx[o1 + k] = (uint32_t)(px - xa) | ty << kTypeShift;
           mate[o1 + k] = py;
+          src[o1 + k] = epos[2 * e];
           idx[o2 + k] = (uint32_t)(py - ya) | tx << kTypeShift;
           mate[o2 + k] = px;
+          src[o2 + k] = epos[2 * e + 1];
           const uint32_t p = flip(tx), q = flip(ty);
           const uint32_t c1 = (p - 1) * 9 + (q - 1) * 3 + (xy - 1), c2 = (q - 1) * 9 + (p - 1) * 3 + (flip(xy) - 1);
           atomicAdd(&tri[(int64_t)z * 27 + min(c1, c2)], 1u);
@@ -510,8 +518,14 @@ __global__ __launch_bounds__(256) void k_apex5(DevGraph G, Totals5 K, Links L, c
         for (int x = 0; x < 9; ++x) {
           const u64 n = tb[x] - (x == (int)ac);
           if (!n) continue;
-          for (int s = 0; s < 3; ++s)
-            K.add(code | ec(0, 3, x / 3 + 1) | ec(1, 3, x % 3 + 1) | ec(2, 4, s + 1), n * xc[s]);
+          uint32_t cs[3];
+          u64 ws[3];
+#pragma unroll
+          for (int s = 0; s < 3; ++s) {
+            cs[s] = code | ec(0, 3, x / 3 + 1) | ec(1, 3, x % 3 + 1) | ec(2, 4, s + 1);
+            ws[s] = n * xc[s];
+          }
+          K.add(cs, ws);
         }
       if (cl < bl) continue;  // each triangle u, b, c once from here
       {
@@ -547,12 +561,14 @@ __global__ __launch_bounds__(256) void k_apex5(DevGraph G, Totals5 K, Links L, c
       for (int x = 0; x < 9; ++x) {  // gem: a third of (u, b), one of (u, c)
         const u64 n = tb[x] - (x == (int)ac);
         if (!n) continue;
+        uint32_t cs[9];
+        u64 ws[9];
 #pragma unroll
         for (int y = 0; y < 9; ++y) {
-          const u64 m = tc[y] - (y == (int)ab);
-          if (m)
-            K.add(code | ec(0, 3, x / 3 + 1) | ec(1, 3, x % 3 + 1) | ec(0, 4, y / 3 + 1) | ec(2, 4, y % 3 + 1), n * m);
+          cs[y] = code | ec(0, 3, x / 3 + 1) | ec(1, 3, x % 3 + 1) | ec(0, 4, y / 3 + 1) | ec(2, 4, y % 3 + 1);
+          ws[y] = n * (u64)(tc[y] - (y == (int)ab));
         }
+        K.add(cs, ws);
       }
     }
     // the vertices adjacent to u, b and c, eight lanes per c
@@ -593,11 +609,16 @@ __global__ __launch_bounds__(256) void k_apex5(DevGraph G, Totals5 K, Links L, c
           const int ad = 3 * (int)(pd - 1) + (int)(bd - 1), acd = 3 * (int)(pd - 1) + (int)(cd - 1);
           const int adb = 3 * (int)(pb - 1) + (int)(flip(bd) - 1), adc = 3 * (int)(pc - 1) + (int)(flip(cd) - 1);
 #pragma unroll
-          for (int x = 0; x < 9; ++x) {  // a vertex on u and one of the three
-            const uint32_t e4 = four | ec(0, 4, x / 3 + 1);
-            K.add(e4 | ec(1, 4, x % 3 + 1), (u64)(tb[x] - (x == ac) - (x == ad)));
-            K.add(e4 | ec(2, 4, x % 3 + 1), (u64)(tc[x] - (x == ab) - (x == acd)));
-            K.add(e4 | ec(3, 4, x % 3 + 1), (u64)(td[x] - (x == adb) - (x == adc)));
+          for (int v = 1; v <= 3; ++v) {  // a vertex on u and one of the three
+            uint32_t cs[9];
+            u64 ws[9];
+#pragma unroll
+            for (int x = 0; x < 9; ++x) {
+              cs[x] = four | ec(0, 4, x / 3 + 1) | ec(v, 4, x % 3 + 1);
+              ws[x] = v == 1 ? tb[x] - (x == ac) - (x == ad) : v == 2 ? tc[x] - (x == ab) - (x == acd)
+                                                                     : td[x] - (x == adb) - (x == adc);
+            }
+            K.add(cs, ws);
           }
         }
       }
@@ -712,31 +733,22 @@ __global__ __launch_bounds__(256) void k_wheel5(DevGraph G, Totals5 K, Links L, 
 // (counts.hip) over the whole rows: hashes of 7-bit counters while d(u) <= 127
 // and the visits fit, else 16-bit counters over one block of ids at a time.
 
-// Place of the triple i <= j <= k of nine.
-__host__ __device__ constexpr int triple(int i, int j, int k) {
-  int at = 0;
-  for (int a = 0; a < i; ++a) at += (9 - a) * (10 - a) / 2;
-  for (int b = i; b < j; ++b) at += 9 - b;
-  return at + k - j;
-}
-static_assert(triple(8, 8, 8) == 164, "165 triples");
-
 // Sums shared by the units of a workgroup.
 struct PairBins {
-  u64* three;  // [165] triples i <= j <= k
+  u64* three;  // [405] triples i <= j <= k, nine per pair
   u64* house;  // [729] (p, third's two types, q, j)
   u64* edge;   // [2187] (pa, pb, ab, qa, qb, j)
   __device__ __forceinline__ void clear(int t, int nt) const {
-    for (int i = t; i < 165; i += nt) three[i] = 0;
+    for (int i = t; i < 405; i += nt) three[i] = 0;
     for (int i = t; i < 729; i += nt) house[i] = 0;
     for (int i = t; i < 2187; i += nt) edge[i] = 0;
   }
   __device__ __forceinline__ void flush(const Totals5& K, int t, int nt) const {
     for (int k = t; k < 729; k += nt) {
-      const int a = k / 81, b = (k / 9) % 9, c = k % 9;
-      if (a <= b && b <= c && three[triple(a, b, c)])
+      const int a = k / 81, b = (k / 9) % 9, c = k % 9, at = (a * 9 - a * (a - 1) / 2 + b - a) * 9 + c;
+      if (a <= b && b <= c && three[at])
         K.add(ec(0, 2, a / 3 + 1) | ec(2, 1, a % 3 + 1) | ec(0, 3, b / 3 + 1) | ec(3, 1, b % 3 + 1) |
-                  ec(0, 4, c / 3 + 1) | ec(4, 1, c % 3 + 1), three[triple(a, b, c)]);
+                  ec(0, 4, c / 3 + 1) | ec(4, 1, c % 3 + 1), three[at]);
       if (house[k]) {  // u 0, v 1, roof 2, w 3, other middle 4
         const int p = k / 243, x = (k / 81) % 3, y = (k / 27) % 3, q = (k / 9) % 3, j = k % 9;
         K.add(ec(0, 1, p + 1) | ec(0, 2, x + 1) | ec(1, 2, y + 1) | ec(1, 3, q + 1) | ec(0, 4, j / 3 + 1) |
@@ -752,74 +764,67 @@ struct PairBins {
   }
 };
 
-// Pairs and triples of the wedges to one w.
-__device__ __forceinline__ void pairs_and_triples(const uint32_t (&n)[9], u64* pair, const PairBins& B) {
-  uint32_t sum = 0;
+// Pairs and triples of the wedges to one w, n(i) the counts of its types.  Most
+// w have two or three types, so the loops run over those.
+template <class N>
+__device__ __forceinline__ void pairs_and_triples(N&& n, u64* pair, const PairBins& B) {
+  uint32_t have = 0;
 #pragma unroll
-  for (int i = 0; i < 9; ++i) sum += n[i];
-  if (sum < 2) return;
-#pragma unroll
-  for (int i = 0; i < 9; ++i) {
-    if (!n[i]) continue;
-#pragma unroll
-    for (int j = i; j < 9; ++j) {
-      const u64 a = n[i], b = n[j], w = i == j ? a * (a - 1) / 2 : a * b;
-      if (!w) continue;
-      atomicAdd(&pair[9 * i + j], w);
-    }
-  }
-  if (sum < 3) return;
-#pragma unroll
-  for (int i = 0; i < 9; ++i) {
-    if (!n[i]) continue;
-    const u64 a = n[i];
-#pragma unroll
-    for (int j = i; j < 9; ++j) {
-      const u64 b = n[j], ab = i == j ? a * (a - 1) / 2 : a * b;
+  for (int i = 0; i < 9; ++i) have |= n(i) ? 1u << i : 0u;
+  for (uint32_t r = have; r; r &= r - 1u) {
+    const int i = __builtin_ctz(r);
+    const u64 a = n(i);
+    for (uint32_t q = r; q; q &= q - 1u) {
+      const int j = __builtin_ctz(q);
+      const u64 b = n(j), ab = i == j ? a * (a - 1) / 2 : a * b;
       if (!ab) continue;
-#pragma unroll
-      for (int k = j; k < 9; ++k) {
-        const u64 c = n[k], w = i == k ? ab * (a - 2) / 3 : j == k ? a * (b * (b - 1) / 2) : ab * c;
-        if (w) atomicAdd(&B.three[triple(i, j, k)], w);
+      atomicAdd(&pair[9 * i + j], ab);
+      const int at = i * 9 - i * (i - 1) / 2 + j - i;  // of 45 pairs
+      for (uint32_t o = q; o; o &= o - 1u) {
+        const int k = __builtin_ctz(o);
+        const u64 c = n(k), w = i == k ? ab * (a - 2) / 3 : j == k ? a * (b * (b - 1) / 2) : ab * c;
+        if (w) atomicAdd(&B.three[at * 9 + k], w);
       }
     }
   }
 }
 
 // Triangles on the edge E = (u, v) with the wedges to w next to v's own.
-__device__ __forceinline__ void house_add(uint32_t (&n)[9], const uint32_t (&tv)[9], uint32_t p, uint32_t q, u64* house) {
+__device__ __forceinline__ void house_add(const uint32_t (&n)[9], const uint32_t (&tv)[9], uint32_t p, uint32_t q,
+                                          u64* house) {
 #pragma unroll
-  for (int j = 0; j < 9; ++j) {
-    const u64 m = n[j] - (j == (int)(3 * p + q));
-    if (!m) continue;
+  for (int x = 0; x < 9; ++x) {
+    if (!tv[x]) continue;
+    u64* h = house + 243 * p + 27 * x + 9 * q;
 #pragma unroll
-    for (int x = 0; x < 9; ++x)
-      if (tv[x]) atomicAdd(&house[243 * p + 27 * x + 9 * q + j], m * tv[x]);
+    for (int j = 0; j < 9; ++j) {
+      const u64 m = n[j] - (j == (int)(3 * p + q));
+      if (m) atomicAdd(&h[j], m * tv[x]);
+    }
   }
 }
 
-// The edges (a, b) among N(u) with b after a in u's row, for G* entry E = (u,
-// a): every w adjacent to both; links l, l + step .. of E, of each the thirds
-// sub, sub + subs ...  n_of(w, n): the wedges u .. w, false when w is not in the
-// table.
+// The edges (a, b) among N(u) with b after a in u's row: the links of u's
+// entries are one run of the link arrays, eight lanes take one and its thirds w.
+// n_of(w, n): the wedges u .. w, false when w is not in the table.
 template <class F>
-__device__ __forceinline__ void edge_add(const DevGraph& G, const Links& L, int32_t u, int32_t ua, int32_t E, int32_t l,
-                                         int32_t step, int32_t sub, int32_t subs, const PairBins& B, F&& n_of) {
-  const uint32_t al = (uint32_t)(E - ua), pa = (G.gs_idx[E] >> kTypeShift) - 1u;
-  const int32_t aa = G.gs_off[(int32_t)(G.gs_idx[E] & kIdMask)], o = L.off[E], t = L.cnt[E];
-  for (int32_t k = l; k < t; k += step) {
-    const uint32_t f = L.idx[o + k], bl = f & kIdMask, ab = (f >> kTypeShift) - 1u;
-    if (bl < al) continue;
-    const uint32_t pb = (G.gs_idx[ua + (int32_t)bl] >> kTypeShift) - 1u;
-    const int32_t M = L.mate[o + k], mo = L.off[M], mt = L.cnt[M];  // entry (a, b)
-    if (mt < 2) continue;                                          // u alone
-    for (int32_t x = sub; x < mt; x += subs) {
+__device__ __forceinline__ void edge_add(const DevGraph& G, const Links& L, int32_t u, int32_t ua, int32_t ub, int32_t t,
+                                         int32_t nt, const PairBins& B, F&& n_of) {
+  const int32_t k1 = L.off[ub];
+  for (int32_t k = L.off[ua] + (t >> 3); k < k1; k += nt >> 3) {
+    const int32_t E = L.src[k], M = L.mate[k];  // entries (u, a) and (a, b)
+    const uint32_t f = L.idx[k], ea = G.gs_idx[E], bl = f & kIdMask, ab = (f >> kTypeShift) - 1u;
+    const int32_t mt = L.cnt[M], mo = L.off[M];
+    if ((int32_t)bl < E - ua || mt < 2) continue;  // (one third: u)
+    const uint32_t pa = (ea >> kTypeShift) - 1u, pb = (G.gs_idx[ua + (int32_t)bl] >> kTypeShift) - 1u;
+    const int32_t aa = G.gs_off[(int32_t)(ea & kIdMask)];
+    u64* const e0 = B.edge + ((pa * 3 + pb) * 3 + ab) * 81;
+    for (int32_t x = t & 7; x < mt; x += 8) {
       const uint32_t g = L.idx[mo + x], fw = G.gs_idx[aa + (int32_t)(g & kIdMask)];
       const uint32_t qa = (fw >> kTypeShift) - 1u, qb = (g >> kTypeShift) - 1u, w = fw & kIdMask;
-      if ((int32_t)w == u) continue;
       uint32_t n[9];
-      if (!n_of(w, n)) continue;
-      u64* e = B.edge + ((((pa * 3 + pb) * 3 + ab) * 3 + qa) * 3 + qb) * 9;
+      if ((int32_t)w == u || !n_of(w, n)) continue;
+      u64* e = e0 + (qa * 3 + qb) * 9;
 #pragma unroll
       for (int j = 0; j < 9; ++j) {
         const uint32_t m = n[j] - (j == (int)(3 * pa + qa)) - (j == (int)(3 * pb + qb));
@@ -828,7 +833,6 @@ __device__ __forceinline__ void edge_add(const DevGraph& G, const Links& L, int3
     }
   }
 }
-constexpr int kManyLinks = 8;  // links of an entry from which a wave takes it, eight lanes per link
 
 // Lists the vertices with two neighbours or more by their visits.  Eight lanes
 // per vertex.
@@ -868,19 +872,34 @@ __global__ __launch_bounds__(256) void k_classify5(DevGraph G, PairListsOf L, in
   if (l < kPairLists) L.v[l][base[l] + at] = v;
 }
 
-// NT threads per u, BT per workgroup; a hash of 2^HB vertices.
+// The next unit of a workgroup: dealt out by position, or pulled from a counter
+// where units are long and uneven (a pull is 25 ns, such a unit 20 us and more).
+template <bool PULL>
+__device__ __forceinline__ int64_t next_unit(int64_t k, int64_t step, int32_t* cursor, int32_t* slot) {
+  if constexpr (!PULL) return k + step;
+  __syncthreads();
+  if (threadIdx.x == 0) *slot = (int32_t)gridDim.x + atomicAdd(cursor, 1);
+  __syncthreads();
+  return *slot;
+}
+
+// NT threads per u, BT per workgroup; a hash of 2^HB vertices.  The rows of N(u)
+// are cut into pieces of 64 entries, sixteen lanes each: whole rows kept a wave
+// on one hub's row while the others were done (20 us for a unit's 2,000 visits).
 template <int NT, int HB, int BT>
-__global__ __launch_bounds__(BT) void k_pairs5(DevGraph G, Totals5 K, Links L,
-                                                                const int32_t* __restrict__ queue,
-                                                                const int32_t* __restrict__ list, const int32_t* st) {
-  constexpr int NU = BT / NT, H = 1 << HB, LPR = 8;
+__global__ __launch_bounds__(BT) void k_pairs5(DevGraph G, Totals5 K, Links L, int32_t* __restrict__ queue,
+                                               const int32_t* __restrict__ list, const int32_t* st) {
+  constexpr int NU = BT / NT, H = 1 << HB;
   static_assert(NU == 1 || NT == 64, "a barrier is the unit's own");
-  constexpr int CAP = pair_cap(HB), LONG = 64;
+  constexpr int CAP = pair_cap(HB), MAXP = CAP / 64 + 128;
+  constexpr bool PULL = NT >= 512;
   __shared__ uint32_t s_key[NU][H];
   __shared__ u64 s_cnt[NU][H], s_pair[NU][81];
   __shared__ uint16_t s_act[NU][CAP / 2];  // slots with two wedges or more
-  __shared__ int32_t s_nact[NU], s_row[NU][128], s_len[NU][128], s_tri[NU][128];  // N(u): rows, their lengths, links
-  __shared__ u64 s_three[165], s_house[729], s_edge[2187];
+  __shared__ uint32_t s_piece[NU][MAXP];   // neighbour << 16 | piece: of rows with triangles from the front, else the back
+  __shared__ int32_t s_n[NU][4], s_row[NU][128], s_len[NU][128];
+  __shared__ u64 s_three[405], s_house[729], s_edge[2187];
+  __shared__ int32_t s_next;
   if (st[kStatus] != 0) return;
   const int32_t count = queue[kPairQueue + HB - 9];
   if ((int32_t)blockIdx.x * NU >= count) return;
@@ -894,36 +913,41 @@ __global__ __launch_bounds__(BT) void k_pairs5(DevGraph G, Totals5 K, Links L,
     cnt[i] = 0;
   }
   for (int i = t; i < 81; i += NT) pair[i] = 0;
-  if (t == 0) s_nact[un] = 0;
+  int32_t* nn = s_n[un];  // listed slots, pieces at the front, at the back
+  if (t < 3) nn[t] = 0;
   __syncthreads();
   auto sync = [] {
     if constexpr (NT <= 64) wave_sync();
     else __syncthreads();
   };
   uint16_t* act = s_act[un];
-  int32_t *row = s_row[un], *len = s_len[un], *ntri = s_tri[un];
+  uint32_t* piece = s_piece[un];
+  int32_t *row = s_row[un], *len = s_len[un];
   // pendants at u: thread t holds the pairs (pi, pj), by the pendant's type
   u64 pend[2][3] = {{0, 0, 0}, {0, 0, 0}};
-  for (int32_t k = (int32_t)blockIdx.x * NU + un; k < count; k += (int32_t)gridDim.x * NU) {
-    const int32_t u = list[k], ua = G.gs_off[u], d = G.gs_off[u + 1] - ua;
+  for (int64_t k = (int64_t)blockIdx.x * NU + un; k < count;
+       k = next_unit<PULL>(k, (int64_t)gridDim.x * NU, &queue[kPairCursor + HB - 9], &s_next)) {
+    const int32_t u = list[k], ua = G.gs_off[u], ub = G.gs_off[u + 1], d = ub - ua;
     for (int32_t i = t; i < d; i += NT) {
-      const int32_t v = (int32_t)(G.gs_idx[ua + i] & kIdMask), ra = G.gs_off[v];
+      const int32_t v = (int32_t)(G.gs_idx[ua + i] & kIdMask), ra = G.gs_off[v], m = G.gs_off[v + 1] - ra;
       row[i] = ra;
-      len[i] = G.gs_off[v + 1] - ra;
-      ntri[i] = L.cnt[ua + i];
+      len[i] = m;
+      const int32_t q = (m + 63) >> 6;
+      if (L.cnt[ua + i]) {
+        const int32_t at = atomicAdd(&nn[1], q);
+        for (int32_t j = 0; j < q; ++j) piece[at + j] = (uint32_t)i << 16 | (uint32_t)j;
+      } else {
+        const int32_t at = atomicAdd(&nn[2], q);
+        for (int32_t j = 0; j < q; ++j) piece[MAXP - 1 - at - j] = (uint32_t)i << 16 | (uint32_t)j;
+      }
     }
     sync();
-    // body(i, lane, lanes) for the rows of N(u): a wave for a long one
-    auto rows = [&](bool linked, auto&& body) {
-      for (int32_t i = t >> 6; i < d; i += NT / 64)
-        if (len[i] > LONG && (!linked || ntri[i])) body(i, t & 63, 64);
-      for (int32_t i = t / LPR; i < d; i += NT / LPR)
-        if (len[i] <= LONG && (!linked || ntri[i])) body(i, t % LPR, LPR);
-    };
-    rows(false, [&](int32_t i, int32_t l, int32_t step) {
+    const int32_t nf = nn[1], np = nf + nn[2];
+    for (int32_t x = t >> 4; x < np; x += NT / 16) {
+      const uint32_t pc = piece[x < nf ? x : MAXP - 1 - (x - nf)];
+      const int32_t i = (int32_t)(pc >> 16), off = (int32_t)(pc & 0xFFFFu) * 64;
       const int p7 = 21 * (int)((G.gs_idx[ua + i] >> kTypeShift) - 1u);
-      const int32_t m = len[i];
-      auto entry = [&](int32_t, uint32_t f) {
+      each4(G.gs_idx + row[i] + off, t & 15, 16, min(64, len[i] - off), [&](int32_t, uint32_t f) {
         const uint32_t w = f & kIdMask;
         if ((int32_t)w == u) return;
         uint32_t h = hash_mul(w, HB);
@@ -933,24 +957,18 @@ __global__ __launch_bounds__(BT) void k_pairs5(DevGraph G, Totals5 K, Links L,
           h = (h + 1) & (H - 1);
         }
         atomicAdd(&cnt[h], 1ull << (p7 + 7 * (int)((f >> kTypeShift) - 1u)));
-      };
-      for (int32_t r = l; r < m; r += 4 * step) each4(G.gs_idx + row[i], r, step, m, entry);
-    });
-    sync();
-    auto fields = [](u64 c, uint32_t (&n)[9]) {
-#pragma unroll
-      for (int j = 0; j < 9; ++j) n[j] = (uint32_t)(c >> (7 * j)) & 127u;
-    };
-    for (int i = t; i < H; i += NT) {
-      const u64 c = cnt[i];
-      if (c && !one_wedge(c, kOnes7)) act[atomicAdd(&s_nact[un], 1)] = (uint16_t)i;
+      });
     }
     sync();
-    const int32_t na = s_nact[un];
+    for (int i = t; i < H; i += NT) {
+      const u64 c = cnt[i];
+      if (c && !one_wedge(c, kOnes7)) act[atomicAdd(&nn[0], 1)] = (uint16_t)i;
+    }
+    sync();
+    const int32_t na = nn[0];
     for (int x = t; x < na; x += NT) {
-      uint32_t n[9];
-      fields(cnt[act[x]], n);
-      pairs_and_triples(n, pair, B);
+      const u64 c = cnt[act[x]];
+      pairs_and_triples([c](int i) { return (uint32_t)(c >> (7 * i)) & 127u; }, pair, B);
     }
     sync();
     const uint4 D = G.dt[u];
@@ -964,39 +982,36 @@ __global__ __launch_bounds__(BT) void k_pairs5(DevGraph G, Totals5 K, Links L,
         for (int s = 0; s < 3; ++s) pend[r][s] += w * other(D, s, (uint32_t)(i / 27) + 1, (uint32_t)(i % 9) / 3 + 1);
       }
     }
-    auto n_of = [&](uint32_t w, uint32_t (&n)[9]) {  // w is two steps from u: it is in the hash
-      uint32_t h = hash_mul(w, HB);
-      uint32_t kk;
-      while ((kk = key[h]) != w && kk != kNone) h = (h + 1) & (H - 1);
-      const u64 c = cnt[h];
-      if (kk != w || one_wedge(c, kOnes7)) return false;
-      fields(c, n);
-      return true;
-    };
     if (na > 0) {
-      rows(true, [&](int32_t i, int32_t l, int32_t step) {
-        const int32_t E = ua + i, m = len[i];
-        const uint32_t p = (G.gs_idx[E] >> kTypeShift) - 1u;
+      auto n_of = [&](uint32_t w, uint32_t (&n)[9]) {
+        uint32_t h = hash_mul(w, HB), kk;
+        while ((kk = key[h]) != w && kk != kNone) h = (h + 1) & (H - 1);
+        const u64 c = cnt[h];
+        if (kk != w || one_wedge(c, kOnes7)) return false;
+#pragma unroll
+        for (int j = 0; j < 9; ++j) n[j] = (uint32_t)(c >> (7 * j)) & 127u;
+        return true;
+      };
+      for (int32_t x = t >> 4; x < nf; x += NT / 16) {
+        const uint32_t pc = piece[x];
+        const int32_t i = (int32_t)(pc >> 16), off = (int32_t)(pc & 0xFFFFu) * 64;
+        const uint32_t p = (G.gs_idx[ua + i] >> kTypeShift) - 1u;
         uint32_t tv[9];
-        L.types(E, tv);
-        auto entry = [&](int32_t, uint32_t f) {
+        L.types(ua + i, tv);
+        each4(G.gs_idx + row[i] + off, t & 15, 16, min(64, len[i] - off), [&](int32_t, uint32_t f) {
           const uint32_t w = f & kIdMask;
           uint32_t n[9];
           if ((int32_t)w != u && n_of(w, n)) house_add(n, tv, p, (f >> kTypeShift) - 1u, s_house);
-        };
-        for (int32_t r = l; r < m; r += 4 * step) each4(G.gs_idx + row[i], r, step, m, entry);
-      });
-      for (int32_t i = t >> 6; i < d; i += NT / 64)
-        if (ntri[i] > kManyLinks) edge_add(G, L, u, ua, ua + i, (t & 63) >> 3, 8, t & 7, 8, B, n_of);
-      for (int32_t i = t / LPR; i < d; i += NT / LPR)
-        if (ntri[i] > 0 && ntri[i] <= kManyLinks) edge_add(G, L, u, ua, ua + i, t % LPR, LPR, 0, 1, B, n_of);
+        });
+      }
+      edge_add(G, L, u, ua, ub, t, NT, B, n_of);
     }
     sync();
     for (int i = t; i < H; i += NT) {
       key[i] = kNone;
       cnt[i] = 0;
     }
-    if (t == 0) s_nact[un] = 0;
+    if (t < 3) nn[t] = 0;
     sync();
   }
 #pragma unroll
@@ -1013,55 +1028,63 @@ __global__ __launch_bounds__(BT) void k_pairs5(DevGraph G, Totals5 K, Links L,
 
 // (u, block of ids) units, 16-bit counters (n <= 65,536).
 constexpr int kPairIds = 6144;
-__global__ __launch_bounds__(1024) void k_pairs5_block(DevGraph G, Totals5 K, Links L, const int32_t* __restrict__ queue,
+__global__ __launch_bounds__(1024) void k_pairs5_block(DevGraph G, Totals5 K, Links L, int32_t* __restrict__ queue,
                                                        const int32_t* __restrict__ list, const int32_t* st) {
-  constexpr int NT = 1024, NW = NT / 64;
+  constexpr int NT = 1024, MAXP = 1536;
   __shared__ uint32_t cnt[9 * kPairIds / 2];
-  __shared__ u64 pair[81], s_three[165], s_house[729], s_edge[2187];
-  __shared__ int32_t pt_a[NT], pt_b[NT];
+  __shared__ u64 pair[81], s_three[405], s_house[729], s_edge[2187];
+  __shared__ int32_t pt_i[MAXP], pt_a[MAXP], npiece, s_next;  // pieces of rows: neighbour | entries << 20, first entry
   if (st[kStatus] != 0) return;
   const int32_t nblk = (G.n + kPairIds - 1) / kPairIds;
   const int64_t units = (int64_t)queue[kPairQueue + kPairBlock] * nblk;
   if ((int64_t)blockIdx.x >= units) return;
-  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  const int t = threadIdx.x;
   const PairBins B{s_three, s_house, s_edge};
   B.clear(t, NT);
   for (int i = t; i < 9 * kPairIds / 2; i += NT) cnt[i] = 0;
   if (t < 81) pair[t] = 0;
+  if (t == 0) npiece = 0;
   u64 pend[3] = {0, 0, 0};
   __syncthreads();
-  for (int64_t unit = blockIdx.x; unit < units; unit += gridDim.x) {
+  for (int64_t unit = blockIdx.x; unit < units; unit = next_unit<true>(unit, 0, &queue[kPairCursor + kPairBlock], &s_next)) {
     const int32_t u = list[unit / nblk], w0 = (int32_t)(unit % nblk) * kPairIds, w1 = min(G.n, w0 + kPairIds);
-    const int32_t ua = G.gs_off[u], d = G.gs_off[u + 1] - ua;
-    // the parts of the rows of N(u) in the block, NT rows at a time; a wave
-    // takes the long ones, eight lanes the others
-    auto each_part = [&](bool linked, auto&& f) {  // f(row i of N(u), its part's first and end, lane, lanes)
+    const int32_t ua = G.gs_off[u], ub = G.gs_off[u + 1], d = ub - ua;
+    // f(i, first entry, entries, lane of 16) for the pieces of 64 entries of the
+    // parts of the rows of N(u) in the block, NT rows at a time
+    auto each_piece = [&](bool linked, auto&& f) {
       for (int32_t i0 = 0; i0 < d; i0 += NT) {
         const int32_t i = i0 + t;
-        int32_t a = 0, b = 0;
+        int32_t a = 0, m = 0;
         if (i < d && (!linked || L.cnt[ua + i])) {
           const int32_t v = (int32_t)(G.gs_idx[ua + i] & kIdMask), ra = G.gs_off[v], rb = G.gs_off[v + 1];
           a = find_in(G.gs_idx, ra, rb, (uint32_t)w0);
-          b = find_in(G.gs_idx, a, rb, (uint32_t)w1);
+          m = find_in(G.gs_idx, a, rb, (uint32_t)w1) - a;
         }
-        pt_a[t] = a;
-        pt_b[t] = b;
-        __syncthreads();
-        const int32_t m = min(NT, d - i0);
-        for (int32_t k = wv; k < m; k += NW)
-          if (pt_b[k] - pt_a[k] > 64) f(i0 + k, pt_a[k], pt_b[k], lane, 64);
-        for (int32_t k = t >> 3; k < m; k += NT / 8)
-          if (pt_b[k] - pt_a[k] <= 64) f(i0 + k, pt_a[k], pt_b[k], t & 7, 8);
-        __syncthreads();
+        for (;;) {  // until every row's pieces were listed
+          while (m > 0) {
+            const int32_t at = atomicAdd(&npiece, 1);
+            if (at >= MAXP) break;
+            pt_i[at] = i - i0 | min(m, 64) << 20;
+            pt_a[at] = a;
+            a += 64;
+            m -= 64;
+          }
+          const bool more = __syncthreads_or(m > 0);
+          const int32_t np = min(npiece, MAXP);
+          for (int32_t x = t >> 4; x < np; x += NT / 16) f(i0 + (pt_i[x] & 0xFFFFF), pt_a[x], pt_i[x] >> 20, t & 15);
+          __syncthreads();
+          if (t == 0) npiece = 0;
+          __syncthreads();
+          if (!more) break;
+        }
       }
     };
-    each_part(false, [&](int32_t i, int32_t a, int32_t b, int32_t l, int32_t step) {
+    each_piece(false, [&](int32_t i, int32_t a, int32_t m, int32_t l) {
       const uint32_t p = (G.gs_idx[ua + i] >> kTypeShift) - 1u;
-      for (int32_t r = a + l; r < b; r += step) {
-        const uint32_t e = G.gs_idx[r], w = (e & kIdMask) - (uint32_t)w0;
-        const uint32_t at = (3 * p + (e >> kTypeShift) - 1u) * kPairIds + w;
+      each4(G.gs_idx + a, l, 16, m, [&](int32_t, uint32_t e) {
+        const uint32_t at = (3 * p + (e >> kTypeShift) - 1u) * kPairIds + (e & kIdMask) - (uint32_t)w0;
         atomicAdd(&cnt[at >> 1], 1u << (16 * (at & 1u)));
-      }
+      });
     });
     auto n_of = [&](uint32_t w, uint32_t (&n)[9]) {
       if (w < (uint32_t)w0 || w >= (uint32_t)w1) return false;
@@ -1074,10 +1097,12 @@ __global__ __launch_bounds__(1024) void k_pairs5_block(DevGraph G, Totals5 K, Li
       }
       return sum > 1;
     };
-    for (int32_t w = w0 + t; w < w1; w += NT) {
-      uint32_t n[9];
-      if (w != u && n_of((uint32_t)w, n)) pairs_and_triples(n, pair, B);
-    }
+    for (int32_t w = w0 + t; w < w1; w += NT)
+      if (w != u)
+        pairs_and_triples([&](int i) {
+          const uint32_t at = i * kPairIds + (uint32_t)(w - w0);
+          return (cnt[at >> 1] >> (16 * (at & 1u))) & 0xFFFFu;
+        }, pair, B);
     __syncthreads();
     if (t < 81 && pair[t]) {
       const u64 w = pair[t];
@@ -1085,28 +1110,17 @@ __global__ __launch_bounds__(1024) void k_pairs5_block(DevGraph G, Totals5 K, Li
       pair[t] = 0;
       for (int s = 0; s < 3; ++s) pend[s] += w * other(D, s, (uint32_t)(t / 27) + 1, (uint32_t)(t % 9) / 3 + 1);
     }
-    each_part(true, [&](int32_t i, int32_t a, int32_t b, int32_t l, int32_t step) {
-      const int32_t E = ua + i;
-      if (!L.cnt[E]) return;
-      const uint32_t p = (G.gs_idx[E] >> kTypeShift) - 1u;
+    each_piece(true, [&](int32_t i, int32_t a, int32_t m, int32_t l) {
+      const uint32_t p = (G.gs_idx[ua + i] >> kTypeShift) - 1u;
       uint32_t tv[9];
-      L.types(E, tv);
-      for (int32_t r = a + l; r < b; r += step) {
-        const uint32_t e = G.gs_idx[r], w = e & kIdMask;
+      L.types(ua + i, tv);
+      each4(G.gs_idx + a, l, 16, m, [&](int32_t, uint32_t e) {
+        const uint32_t w = e & kIdMask;
         uint32_t n[9];
         if ((int32_t)w != u && n_of(w, n)) house_add(n, tv, p, (e >> kTypeShift) - 1u, s_house);
-      }
+      });
     });
-    for (int32_t i0 = 0; i0 < d; i0 += NT) {
-      pt_a[t] = i0 + t < d ? L.cnt[ua + i0 + t] : 0;
-      __syncthreads();
-      const int32_t m = min(NT, d - i0);
-      for (int32_t k = wv; k < m; k += NW)
-        if (pt_a[k] > kManyLinks) edge_add(G, L, u, ua, ua + i0 + k, lane >> 3, 8, lane & 7, 8, B, n_of);
-      for (int32_t k = t >> 3; k < m; k += NT / 8)
-        if (pt_a[k] > 0 && pt_a[k] <= kManyLinks) edge_add(G, L, u, ua, ua + i0 + k, t & 7, 8, 0, 1, B, n_of);
-      __syncthreads();
-    }
+    edge_add(G, L, u, ua, ub, t, NT, B, n_of);
     __syncthreads();
     for (int i = t; i < 9 * kPairIds / 2; i += NT) cnt[i] = 0;
     __syncthreads();
@@ -1124,14 +1138,25 @@ __global__ __launch_bounds__(1024) void k_pairs5_block(DevGraph G, Totals5 K, Li
 // From the vertex u of highest rank: n(w) the typed wedges u - v - w with v and
 // w of lower rank, and for every edge w - w' among them with w' below w the
 // products n(w) n(w').  The tables and lists of u are k_wedge's (counts.hip);
-// the u of k_wedge_top have a table in global memory, five words per vertex
-// (nine 16-bit counts and their sum), one slice per workgroup.
+// the u of k_wedge_top have tables in global memory.
 
-__device__ __forceinline__ void c5_flush(const Totals5& K, const u64* bins, int t, int nt) {
+// A bit at the foot of every 7-bit field that is not zero.
+__device__ __forceinline__ u64 flags7(u64 c) {
+  // the low six bits carry into the seventh unless all are zero
+  constexpr u64 low = 63ull * kOnes7;
+  return ((c | ((c & low) + low)) >> 6) & kOnes7;
+}
+
+// A workgroup keeps several copies of its sums, one per some lanes: the
+// products of a wave meet on the same few of the 243.
+constexpr int kCopies = 4, kTopCopies = 16;
+__device__ __forceinline__ void c5_flush(const Totals5& K, const u64* all, int copies, int t, int nt) {
   for (int k = t; k < 243; k += nt) {
     const int i = k / 27, e = (k / 9) % 3, j = k % 9;
+    u64 sum = 0;
+    for (int r = 0; r < copies; ++r) sum += all[r * 243 + k];
     K.add(ec(0, 1, i / 3 + 1) | ec(1, 2, i % 3 + 1) | ec(2, 3, e + 1) | ec(4, 3, j % 3 + 1) | ec(0, 4, j / 3 + 1),
-          bins[k]);
+          sum);
   }
 }
 
@@ -1141,7 +1166,7 @@ __global__ __launch_bounds__(NT < 256 ? 256 : NT) void k_c5(DevGraph G, Totals5 
   constexpr int BT = NT < 256 ? 256 : NT, NU = BT / NT, H = 1 << HB, LPR = NT == 16 ? 4 : 8, LONG = 64;
   __shared__ int32_t s_row[NU][NT], s_len[NU][NT];
   __shared__ uint32_t s_key[NU][H];
-  __shared__ u64 s_cnt[NU][H], bins[243];
+  __shared__ u64 s_cnt[NU][H], bins[kCopies * 243];
   __shared__ uint16_t s_act[NU][H];
   __shared__ int32_t s_nact[NU];
   if (st[kStatus] != 0) return;
@@ -1152,11 +1177,12 @@ __global__ __launch_bounds__(NT < 256 ? 256 : NT) void k_c5(DevGraph G, Totals5 
   u64* cnt = s_cnt[un];
   uint16_t* act = s_act[un];
   int32_t *row = s_row[un], *len = s_len[un];
+  u64* mine = bins + (threadIdx.x & (kCopies - 1)) * 243;
   for (int i = t; i < H; i += NT) {
     key[i] = kNone;
     cnt[i] = 0;
   }
-  for (int i = threadIdx.x; i < 243; i += BT) bins[i] = 0;
+  for (int i = threadIdx.x; i < kCopies * 243; i += BT) bins[i] = 0;
   if (t == 0) s_nact[un] = 0;
   __syncthreads();
   auto sync = [] {
@@ -1204,7 +1230,7 @@ __global__ __launch_bounds__(NT < 256 ? 256 : NT) void k_c5(DevGraph G, Totals5 
       sync();
       const int32_t nx = min(NT, na - x0);
       auto take = [&](int32_t x, int32_t l, int32_t step) {
-        const u64 c = cnt[act[x0 + x]];
+        const u64 c = cnt[act[x0 + x]], fc = flags7(c);
         const int32_t wa = row[x], wm = len[x];
         auto entry = [&](int32_t, uint32_t f) {
           const uint32_t z = f & kIdMask;
@@ -1213,15 +1239,14 @@ __global__ __launch_bounds__(NT < 256 ? 256 : NT) void k_c5(DevGraph G, Totals5 
           if (kk != z) return;
           const u64 e = cnt[h];
           if (!e) return;
-          const int ty = (int)(f >> kTypeShift) - 1;
-#pragma unroll
-          for (int p = 0; p < 9; ++p) {
-            const u64 a = (c >> (7 * p)) & 127u;
-            if (!a) continue;
-#pragma unroll
-            for (int q = 0; q < 9; ++q) {
-              const u64 b = (e >> (7 * q)) & 127u;
-              if (b) atomicAdd(&bins[27 * p + 9 * ty + q], a * b);
+          // loops over the types that occur, the fields' top bits as flags
+          u64* to = mine + 9 * ((int)(f >> kTypeShift) - 1);
+          for (u64 x = fc; x; x &= x - 1ull) {
+            const int p = __builtin_ctzll(x);
+            const u64 a = (c >> p) & 127u;
+            for (u64 y = flags7(e); y; y &= y - 1ull) {
+              const int q = __builtin_ctzll(y);
+              atomicAdd(&to[27 * (p / 7) + q / 7], a * ((e >> q) & 127u));
             }
           }
         };
@@ -1243,119 +1268,137 @@ __global__ __launch_bounds__(NT < 256 ? 256 : NT) void k_c5(DevGraph G, Totals5 
     sync();
   }
   __syncthreads();
-  c5_flush(K, bins, threadIdx.x, BT);
+  c5_flush(K, bins, kCopies, threadIdx.x, BT);
 }
 
-__global__ __launch_bounds__(kC5Top) void k_c5_top(DevGraph G, Totals5 K, const int32_t* __restrict__ queue,
-                                                   const int32_t* __restrict__ top, const int32_t* __restrict__ huge,
-                                                   uint32_t* __restrict__ slices, const int32_t* st) {
-  constexpr int NT = kC5Top;
-  __shared__ u64 bins[243];
-  __shared__ int32_t nact, wid[NT], row[NT], len[NT];
+__device__ __forceinline__ int32_t top_vertex(const int32_t* queue, const int32_t* top, const int32_t* huge, int32_t k) {
+  const int32_t nh = queue[kWedgeHuge];
+  return k < nh ? huge[k] : top[k - nh];
+}
+
+// The table of the first + blockIdx.y-th listed u in slice blockIdx.y: per vertex
+// w nine 16-bit counts and above the ninth their sum; then the w met, and their
+// number.  Several workgroups per u, as the rows phase below: the first of the
+// 77 such u of the 20,000-vertex graph alone took 1,500 us as one workgroup.
+constexpr int kFillParts = 8, kRowParts = 32;
+__global__ __launch_bounds__(512) void k_c5_fill(DevGraph G, const int32_t* __restrict__ queue,
+                                                 const int32_t* __restrict__ top, const int32_t* __restrict__ huge,
+                                                 int32_t first, uint32_t* __restrict__ slices, const int32_t* st) {
   if (st[kStatus] != 0) return;
-  const int32_t nh = queue[kWedgeHuge], count = nh + queue[kWedgeTop];
-  if ((int32_t)blockIdx.x >= count) return;
-  const int t = threadIdx.x;
-  uint32_t* cnt = slices + (int64_t)blockIdx.x * 6 * G.n;  // five words a vertex, zero between vertices u
-  uint32_t* act = cnt + (int64_t)5 * G.n;
-  auto word = [&](uint32_t w, int i) {
-    return __hip_atomic_load(cnt + (int64_t)w * 5 + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  };
-  for (int i = t; i < 243; i += NT) bins[i] = 0;
-  if (t == 0) nact = 0;
-  __syncthreads();
-  for (int32_t k = blockIdx.x; k < count; k += gridDim.x) {
-    const int32_t u = k < nh ? huge[k] : top[k - nh], ua = G.gs_off[u], ub = G.gs_off[u + 1];
-    const int32_t ma = ua - G.np_off[u], dm = ub - G.np_off[u + 1] - ma;
-    const uint32_t du = (uint32_t)(ub - ua);
-    for (int32_t i = t >> 4; i < dm; i += NT / 16) {
+  const int t = threadIdx.x, lane = t & 63;
+  uint32_t* cnt = slices + (int64_t)blockIdx.y * (6 * (int64_t)G.n + 1);
+  uint32_t *act = cnt + (int64_t)5 * G.n, *nact = act + G.n;
+  const int32_t u = top_vertex(queue, top, huge, first + (int32_t)blockIdx.y), ua = G.gs_off[u], ub = G.gs_off[u + 1];
+  const int32_t ma = ua - G.np_off[u], dm = ub - G.np_off[u + 1] - ma;
+  const uint32_t du = (uint32_t)(ub - ua);
+  const int32_t group = (int32_t)blockIdx.x * 32 + (t >> 4), groups = (int32_t)gridDim.x * 32;
+  for (int32_t i0 = 0; i0 < dm; i0 += groups) {
+    const int32_t i = i0 + group;
+    int32_t ra = 0, m = 0;
+    uint32_t p = 0;
+    if (i < dm) {
       const uint32_t ev = G.nm_idx[ma + i], v = ev & kIdMask;
-      const int32_t ra = G.gs_off[v], rb = G.gs_off[v + 1];
-      const uint32_t p = (ev >> kTypeShift) - 1u;
-      for (int32_t r = ra + (t & 15); r < rb; r += 64) {
-        uint32_t f[4], old[4];
-        bool in[4];
+      ra = G.gs_off[v];
+      m = G.gs_off[v + 1] - ra;
+      p = (ev >> kTypeShift) - 1u;
+    }
+    for (int32_t r = t & 15; __ballot(r < m); r += 64) {
+      uint32_t f[4], old[4];
+      bool in[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) f[k] = G.gs_idx[min(r + 16 * k, rb - 1)];
+      for (int k = 0; k < 4; ++k) f[k] = r + 16 * k < m ? G.gs_idx[ra + r + 16 * k] : 0u;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const int32_t w = (int32_t)(f[k] & kIdMask);
-          in[k] = r + 16 * k < rb && w != u && ranked_below(G, (uint32_t)G.deg[w], w, du, u);
-        }
+      for (int k = 0; k < 4; ++k) {
+        const int32_t w = (int32_t)(f[k] & kIdMask);
+        in[k] = r + 16 * k < m && w != u && ranked_below(G, (uint32_t)G.deg[w], w, du, u);
+      }
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const uint32_t j = 3 * p + (f[k] >> kTypeShift) - 1u;
-          uint32_t* c = cnt + (int64_t)(f[k] & kIdMask) * 5;
-          // the sum sits above the ninth count
-          old[k] = in[k] ? atomicAdd(&c[4], j == 8 ? 0x10001u : 0x10000u) : ~0u;
-          if (in[k] && j < 8) atomicAdd(&c[j >> 1], 1u << (16 * (j & 1u)));
-        }
+      for (int k = 0; k < 4; ++k) {
+        const uint32_t j = 3 * p + (f[k] >> kTypeShift) - 1u;
+        uint32_t* c = cnt + (int64_t)(f[k] & kIdMask) * 5;
+        old[k] = in[k] ? atomicAdd(&c[4], j == 8 ? 0x10001u : 0x10000u) : ~0u;
+        if (in[k] && j < 8) atomicAdd(&c[j >> 1], 1u << (16 * (j & 1u)));
+      }
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
-          if (old[k] >> 16 == 0) act[atomicAdd(&nact, 1)] = f[k] & kIdMask;
+      for (int k = 0; k < 4; ++k) {
+        const u64 met = __ballot(old[k] >> 16 == 0);
+        if (!met) continue;
+        uint32_t at = 0;
+        if (lane == 0) at = atomicAdd(nact, (uint32_t)__popcll(met));
+        at = __shfl(at, 0);
+        if (old[k] >> 16 == 0) act[at + __popcll(met & ((1ull << lane) - 1ull))] = f[k] & kIdMask;
       }
     }
-    __builtin_amdgcn_s_waitcnt(0);
+  }
+}
+
+__global__ __launch_bounds__(256) void k_c5_rows(DevGraph G, Totals5 K, const uint32_t* __restrict__ slices,
+                                                 const int32_t* st) {
+  constexpr int NT = 256;
+  __shared__ u64 bins[kTopCopies * 243];
+  __shared__ int32_t wid[NT], row[NT], len[NT];
+  if (st[kStatus] != 0) return;
+  const int t = threadIdx.x;
+  const uint32_t* cnt = slices + (int64_t)blockIdx.y * (6 * (int64_t)G.n + 1);
+  const uint32_t* act = cnt + (int64_t)5 * G.n;
+  const int32_t na = (int32_t)act[G.n];
+  if ((int32_t)blockIdx.x * NT >= na) return;
+  for (int i = t; i < kTopCopies * 243; i += NT) bins[i] = 0;
+  u64* mine = bins + (t & (kTopCopies - 1)) * 243;
+  for (int32_t x0 = (int32_t)blockIdx.x * NT; x0 < na; x0 += (int32_t)gridDim.x * NT) {
     __syncthreads();
-    const int32_t na = nact;
-    for (int32_t x0 = 0; x0 < na; x0 += NT) {
-      if (x0 + t < na) {
-        const int32_t w = (int32_t)__hip_atomic_load(&act[x0 + t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const int32_t wa = G.gs_off[w] - G.np_off[w];
-        wid[t] = w;
-        row[t] = wa;
-        len[t] = G.gs_off[w + 1] - G.np_off[w + 1] - wa;
+    if (x0 + t < na) {
+      const int32_t w = (int32_t)act[x0 + t], wa = G.gs_off[w] - G.np_off[w];
+      wid[t] = w;
+      row[t] = wa;
+      len[t] = G.gs_off[w + 1] - G.np_off[w + 1] - wa;
+    }
+    __syncthreads();
+    const int32_t nx = min(NT, na - x0);
+    auto take = [&](int32_t x, int32_t l, int32_t step) {
+      const int32_t wa = row[x], wm = len[x];
+      uint32_t c[9];
+#pragma unroll
+      for (int i = 0; i < 5; ++i) {
+        const uint32_t h = cnt[(int64_t)wid[x] * 5 + i];
+        c[2 * i] = h & 0xFFFFu;
+        if (i < 4) c[2 * i + 1] = h >> 16;
       }
-      __syncthreads();
-      const int32_t nx = min(NT, na - x0);
-      auto take = [&](int32_t x, int32_t l, int32_t step) {
-        const int32_t wa = row[x], wm = len[x];
-        uint32_t c[5];
+      for (int32_t r0 = l; r0 < wm; r0 += 4 * step) {
+        uint32_t f[4], last[4];
 #pragma unroll
-        for (int i = 0; i < 5; ++i) c[i] = word((uint32_t)wid[x], i);
-        for (int32_t r0 = l; r0 < wm; r0 += 4 * step) {
-          uint32_t f[4], e[4][5];
+        for (int k = 0; k < 4; ++k) f[k] = G.nm_idx[wa + min(r0 + k * step, wm - 1)];
 #pragma unroll
-          for (int k = 0; k < 4; ++k) f[k] = G.nm_idx[wa + min(r0 + k * step, wm - 1)];
+        for (int k = 0; k < 4; ++k) last[k] = r0 + k * step < wm ? cnt[(int64_t)(f[k] & kIdMask) * 5 + 4] : 0u;
 #pragma unroll
-          for (int k = 0; k < 4; ++k) e[k][4] = r0 + k * step < wm ? word(f[k] & kIdMask, 4) : 0u;
+        for (int k = 0; k < 4; ++k) {
+          if (!last[k]) continue;
+          uint32_t e[9];
 #pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            if (!e[k][4]) continue;
+          for (int i = 0; i < 4; ++i) {
+            const uint32_t h = cnt[(int64_t)(f[k] & kIdMask) * 5 + i];
+            e[2 * i] = h & 0xFFFFu;
+            e[2 * i + 1] = h >> 16;
+          }
+          e[8] = last[k] & 0xFFFFu;
+          u64* to = mine + 9 * ((int)(f[k] >> kTypeShift) - 1);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) e[k][i] = word(f[k] & kIdMask, i);
-            const int ty = (int)(f[k] >> kTypeShift) - 1;
+          for (int p = 0; p < 9; ++p) {
+            if (!c[p]) continue;
 #pragma unroll
-            for (int p = 0; p < 9; ++p) {
-              const u64 a = (c[p >> 1] >> (16 * (p & 1))) & 0xFFFFu;
-              if (!a) continue;
-#pragma unroll
-              for (int q = 0; q < 9; ++q) {
-                const u64 b = (e[k][q >> 1] >> (16 * (q & 1))) & 0xFFFFu;
-                if (b) atomicAdd(&bins[27 * p + 9 * ty + q], a * b);
-              }
-            }
+            for (int q = 0; q < 9; ++q)
+              if (e[q]) atomicAdd(&to[27 * p + q], (u64)c[p] * e[q]);
           }
         }
-      };
-      for (int32_t x = t >> 6; x < nx; x += NT / 64)
-        if (len[x] > 64) take(x, t & 63, 64);
-      for (int32_t x = t >> 2; x < nx; x += NT / 4)
-        if (len[x] > 0 && len[x] <= 64) take(x, t & 3, 4);
-      __syncthreads();
-    }
-    __syncthreads();
-    for (int32_t x = t; x < na; x += NT) {
-      const uint32_t w = __hip_atomic_load(&act[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-      for (int i = 0; i < 5; ++i)
-        __hip_atomic_store(cnt + (int64_t)w * 5 + i, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    if (t == 0) nact = 0;
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
+      }
+    };
+    for (int32_t x = t >> 6; x < nx; x += NT / 64)
+      if (len[x] > 64) take(x, t & 63, 64);
+    for (int32_t x = t >> 2; x < nx; x += NT / 4)
+      if (len[x] > 0 && len[x] <= 64) take(x, t & 3, 4);
   }
-  c5_flush(K, bins, t, NT);
+  __syncthreads();
+  c5_flush(K, bins, kTopCopies, t, NT);
 }
 
 // ============================================================== the counts ==
@@ -1416,8 +1459,9 @@ __global__ void k_write5(const uint64_t* __restrict__ in, uint64_t* __restrict__
 
 size_t al(size_t b) { return (b + 255) & ~size_t(255); }
 
-int c5_slices(int64_t n, int num_cus) {
-  return (int)std::max<size_t>(1, std::min<size_t>((size_t)num_cus, kSliceBytes / (24 * (size_t)n)));
+size_t slice_words(int64_t n) { return 6 * (size_t)n + 1; }
+int c5_slices(int64_t n) {
+  return (int)std::max<size_t>(1, std::min<size_t>((size_t)n, std::min<size_t>(1024, kSliceBytes / (4 * slice_words(n)))));
 }
 
 int64_t link_room(int64_t m) { return 16 * m + 1024; }
@@ -1426,13 +1470,13 @@ int64_t link_room(int64_t m) { return 16 * m + 1024; }
 
 bool copies5_fits(int64_t n, int64_t m) { return n > 0 && n <= 65536 && m <= (int64_t(1) << 20); }
 
-size_t copies5_bytes(int64_t n, int64_t m, int num_cus) {
+size_t copies5_bytes(int64_t n, int64_t m) {
   const size_t gs = (size_t)(2 * m + 1);
   return count_bytes(n, m, n, false, true) + 2 * al(64 * 4) + al(sizeof(uint64_t) * 13 * kRep3) +
          al(sizeof(uint64_t) * 199 * kRep4) + al(sizeof(uint64_t) * kC5 * kRep5) + 4 * al(sizeof(uint64_t) * kC5) +
          3 * al(4 * gs) + al(8 * (size_t)(m + 1)) + al(24 * (size_t)(m + 1)) + scan1_bytes((int64_t)gs) +
-         2 * al(4 * (size_t)link_room(m)) + al(72 * (size_t)n) + al(16 * (size_t)n) + al(108 * (size_t)n) +
-         kPairLists * al(4 * (size_t)n) + al(24 * (size_t)n * (size_t)c5_slices(n, num_cus)) + 8192;
+         3 * al(4 * (size_t)link_room(m)) + al(72 * (size_t)n) + al(16 * (size_t)n) + al(108 * (size_t)n) +
+         kPairLists * al(4 * (size_t)n) + al(4 * slice_words(n) * (size_t)c5_slices(n)) + 8192;
 }
 
 void enqueue_copies5_start(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_t* a4, Copies5Run* R, hipStream_t s) {
@@ -1458,7 +1502,7 @@ void enqueue_copies5_start(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_
   enqueue_zero_batch(z, s);
   enqueue_counts(p, g, a3, a4, R->queue, s, &R->counts);
   hipLaunchKernelGGL(k_edges5, dim3((unsigned)std::min<int64_t>(4096, (m + 255) / 256 + 1)), dim3(256), 0, s, g,
-                     R->counts.T, R->emap, R->cnt, R->epos, R->hi, p.status);
+                     R->counts.T, R->emap, R->cnt, R->epos, R->hi, R->queue, p.status);
   enqueue_scan1(sc, R->off, LinkCount{R->cnt, g.gs_off, g.n}, p.status, s);
 }
 
@@ -1476,24 +1520,24 @@ void enqueue_copies5_finish(Pipeline& p, const DevGraph& g, const Copies5Run& R,
   const int cus = p.num_cus;
   uint32_t* idx = A.take<uint32_t>((size_t)link_room(m));
   int32_t* mate = A.take<int32_t>((size_t)link_room(m));
+  int32_t* src = A.take<int32_t>((size_t)link_room(m));
   u64* S = A.take<u64>(9 * (size_t)n);
   uint4* up = A.take<uint4>((size_t)n);
   PairListsOf lists;
   for (auto& l : lists.v) l = A.take<int32_t>((size_t)n);
   int32_t** list = lists.v;
-  const int slices = c5_slices(n, cus);
-  uint32_t* slice = A.take<uint32_t>((size_t)slices * 6 * (size_t)n);
+  const int slices = c5_slices(n), tops = p.host_status[11];
+  uint32_t* slice = A.take<uint32_t>((size_t)slices * slice_words(n));
   uint64_t* P[2] = {A.take<uint64_t>(kC5), A.take<uint64_t>(kC5)};
   uint64_t* I = A.take<uint64_t>(kC5);
   const Totals5 K{T.lut[5], R.acc};
-  const Links L{R.emap, R.cnt, R.off, idx, mate, R.counts.T};
-  enqueue_zero(slice, sizeof(uint32_t) * (size_t)slices * 6 * (size_t)n, s);
+  const Links L{R.emap, R.cnt, R.off, idx, mate, src, R.counts.T};
   auto grid = [&](int64_t items, int per, int wgs) {
     return dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>((int64_t)cus * wgs, (items + per - 1) / per)));
   };
   hipLaunchKernelGGL(k_vertex5, grid(n, 4, 4), dim3(256), 0, s, g, K, S, up, p.status);
   hipLaunchKernelGGL(k_classify5, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, g, lists, R.queue, p.status);
-  hipLaunchKernelGGL(k_links5, grid(m, 4, 8), dim3(256), 0, s, g, K, L, R.epos, R.hi, up, idx, mate, R.tri, p.status);
+  hipLaunchKernelGGL(k_links5, grid(m, 4, 8), dim3(256), 0, s, g, K, L, R.epos, R.hi, up, idx, mate, src, R.tri, p.status);
   hipLaunchKernelGGL(k_butterfly5, grid(n, 4, 4), dim3(256), 0, s, g, K, R.tri, p.status);
   dim3 ag = grid(2 * m, 4, 6);
   ag.y = kApexParts;
@@ -1506,8 +1550,13 @@ void enqueue_copies5_finish(Pipeline& p, const DevGraph& g, const Copies5Run& R,
   hipLaunchKernelGGL((k_pairs5<256, 11, 256>), grid(n, 1, 3), dim3(256), 0, s, g, K, L, R.queue, list[kPair11], p.status);
   hipLaunchKernelGGL((k_pairs5<128, 10, 128>), grid(n, 1, 4), dim3(128), 0, s, g, K, L, R.queue, list[kPair10], p.status);
   hipLaunchKernelGGL((k_pairs5<64, 9, 256>), grid(n, 4, 2), dim3(256), 0, s, g, K, L, R.queue, list[kPair9], p.status);
-  hipLaunchKernelGGL(k_c5_top, dim3((unsigned)slices), dim3(kC5Top), 0, s, g, K, R.queue, R.counts.wedge[kWedgeTop],
-                     R.counts.wedge[kWedgeHuge], slice, p.status);
+  for (int first = 0; first < tops; first += slices) {
+    const unsigned now = (unsigned)std::min(slices, tops - first);
+    enqueue_zero(slice, sizeof(uint32_t) * now * slice_words(n), s);
+    hipLaunchKernelGGL(k_c5_fill, dim3(kFillParts, now), dim3(512), 0, s, g, R.queue, R.counts.wedge[kWedgeTop],
+                       R.counts.wedge[kWedgeHuge], first, slice, p.status);
+    hipLaunchKernelGGL(k_c5_rows, dim3(kRowParts, now), dim3(256), 0, s, g, K, slice, p.status);
+  }
   hipLaunchKernelGGL((k_c5<512, 12, kWedge256>), grid(n, 1, 2), dim3(512), 0, s, g, K, R.queue, R.counts.wedge[kWedge256], p.status);
   hipLaunchKernelGGL((k_c5<256, 9, kWedge64>), grid(n, 1, 8), dim3(256), 0, s, g, K, R.queue, R.counts.wedge[kWedge64], p.status);
   hipLaunchKernelGGL((k_c5<64, 7, kWedge16>), grid(n, 4, 8), dim3(256), 0, s, g, K, R.queue, R.counts.wedge[kWedge16], p.status);

@@ -254,7 +254,7 @@ struct Copies5Run {
   CountsOut counts;
 };
 bool copies5_fits(int64_t n, int64_t m);
-size_t copies5_bytes(int64_t n, int64_t m, int num_cus);
+size_t copies5_bytes(int64_t n, int64_t m);
 void enqueue_copies5_start(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_t* a4, Copies5Run* R, hipStream_t s);
 bool copies5_go(const Pipeline& p, int64_t m);
 void enqueue_copies5_finish(Pipeline& p, const DevGraph& g, const Copies5Run& R, uint64_t* out, hipStream_t s);
