@@ -46,6 +46,7 @@ namespace {
 
 constexpr int kC5 = 9364;
 constexpr int kRep5 = 32;                // copies of the totals (see totals() in counts.hip)
+constexpr int kLocalCopies = 256;        // copies written by k_apex5, at most
 constexpr size_t kSliceBytes = size_t(96) << 20;  // wedge tables of k_c5_fill
 // Lists of vertices by their wedge table in k_pairs5.
 enum PairList : int { kPair9 = 0, kPair10 = 1, kPair11 = 2, kPair12 = 3, kPair13 = 4, kPairBlock = 5, kPairLists = 6 };
@@ -87,6 +88,34 @@ struct Totals5 {
 #pragma unroll
     for (int i = 0; i < N; ++i)
       if (w[i]) atomicAdd(a + c[i], w[i]);
+  }
+};
+
+// The totals of one workgroup in LDS, for the kernels that add millions of small
+// numbers all over the classes (additions in global memory: 4 per ns on the whole
+// chip), and their own copy of the totals in memory, written at the end.
+struct Local5 {
+  const uint16_t* lut;
+  u64* sum;  // [kC5] in LDS
+  __device__ __forceinline__ void clear() const {
+    for (int i = threadIdx.x; i < kC5; i += blockDim.x) sum[i] = 0;
+    __syncthreads();
+  }
+  __device__ __forceinline__ void add(uint32_t code, u64 w) const {
+    if (w) atomicAdd(&sum[lut[code]], w);
+  }
+  template <int N>
+  __device__ __forceinline__ void add(const uint32_t (&code)[N], const u64 (&w)[N]) const {
+    uint32_t c[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) c[i] = lut[code[i]];
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+      if (w[i]) atomicAdd(&sum[c[i]], w[i]);
+  }
+  __device__ __forceinline__ void write(uint64_t* copies, int copy) const {
+    __syncthreads();
+    for (int i = threadIdx.x; i < kC5; i += blockDim.x) copies[(int64_t)copy * kC5 + i] = sum[i];
   }
 };
 
@@ -420,19 +449,27 @@ __global__ __launch_bounds__(256) void k_butterfly5(DevGraph G, Totals5 K, const
 
 // ================================================ graphs around a triangle ==
 //
+constexpr int kApexThreads = 1024;
+constexpr int kStaged = 256;  // links of a unit up to which a wave keeps them in LDS
+constexpr int kApexParts = 16;  // most waves that share a unit, four thirds each (64 in what a lane does alone)
+constexpr int kCommon = 64;     // vertices adjacent to u, b and c that a wave keeps in LDS
+constexpr int kWheelT = 8;    // links of a unit up to which its wheels are taken pair by pair
+
 // A unit is a G* entry (u, b) with triangles, its links the vertices c adjacent
 // to both.  One wave per unit, a lane per c; the units are dealt out with a
 // stride so that a hub's many heavy entries land on different waves.  What a
 // lane finds goes to the totals at once: of 1.1e5 links on the 20,000-vertex
 // graph most have a handful of non-zero sums.
 template <class F>
-__device__ __forceinline__ void for_entries(const DevGraph& G, const int32_t* cnt, int32_t least, int32_t most, F&& f) {
+__device__ __forceinline__ void for_entries(const DevGraph& G, const int32_t* cnt, int32_t least, int32_t turn, F&& f) {
   const int lane = threadIdx.x & 63;
   const int32_t total = G.gs_off[G.n], per = blockDim.x >> 6, nw = gridDim.x * per;
-  for (int64_t base = blockIdx.x * per + (threadIdx.x >> 6); base < total; base += (int64_t)nw * 64) {
+  // (turn: another wave's entries, in parts of nw / kApexParts)
+  const int32_t wave = (blockIdx.x * per + (threadIdx.x >> 6) + turn * (nw / kApexParts)) % nw;
+  for (int64_t base = wave; base < total; base += (int64_t)nw * 64) {
     const int64_t el = base + (int64_t)lane * nw;
     const int32_t c = el < total ? cnt[el] : 0;
-    for (u64 todo = __ballot(c >= least && c <= most); todo; todo &= todo - 1ull)
+    for (u64 todo = __ballot(c >= least); todo; todo &= todo - 1ull)
       f((int32_t)(base + (int64_t)__builtin_ctzll(todo) * nw));
   }
 }
@@ -447,24 +484,26 @@ __device__ __forceinline__ int32_t link_at(const uint32_t* p, int32_t m, uint32_
   return lo < m && (p[lo] & kIdMask) == d ? lo : -1;
 }
 
-constexpr int kStaged = 512;  // links of a unit up to which a wave keeps them in LDS
-constexpr int kApexParts = 4;  // waves that share a unit's thirds, 64 (and, for the K4s, 8) at a time
-constexpr int kWheelT = 16;   // links of a unit up to which its wheels are taken pair by pair
 
-__global__ __launch_bounds__(256) void k_apex5(DevGraph G, Totals5 K, Links L, const u64* __restrict__ S,
-                                               const int32_t* st) {
-  __shared__ uint32_t s_R[4][kStaged];
+__global__ __launch_bounds__(kApexThreads) void k_apex5(DevGraph G, const uint16_t* __restrict__ lut,
+                                                        uint64_t* __restrict__ copies, Links L,
+                                                        const u64* __restrict__ S, const int32_t* st) {
+  __shared__ uint32_t s_R[kApexThreads / 64][kStaged], s_com[kApexThreads / 64][2 * kCommon];
+  __shared__ u64 sum[kC5];
   if (st[kStatus] != 0) return;
+  const Local5 K{lut, sum};
+  K.clear();
   const int lane = threadIdx.x & 63;
-  uint32_t* sR = s_R[threadIdx.x >> 6];
-  const int part = blockIdx.y;
-  for_entries(G, L.cnt, 64 * part + 1, 1 << 30, [&](int32_t E) {
+  uint32_t *sR = s_R[threadIdx.x >> 6], *com = s_com[threadIdx.x >> 6];
+  constexpr int nparts = kApexParts;
+  for (int part = 0; part < nparts; ++part)
+  for_entries(G, L.cnt, 4 * part + 1, part, [&](int32_t E) {
     const int32_t u = G.gs_row[E], ua = G.gs_off[u], t = L.cnt[E];
     const uint32_t bl = (uint32_t)(E - ua), pb = G.gs_idx[E] >> kTypeShift;
     const int32_t b = (int32_t)(G.gs_idx[E] & kIdMask);
     const uint32_t* R = L.idx + L.off[E];
     const uint4 Du = G.dt[u], Db = G.dt[b];
-    const int parts = min((int)gridDim.y, (t + 63) / 64);  // the waves on this unit
+    const int parts = min(nparts, (t + 3) / 4);  // the waves on this unit
     const bool staged = t <= kStaged;  // b's links in LDS: searched for every third of every c
     if (staged)
       for (int32_t k = lane; k < t; k += 64) sR[k] = R[k];
@@ -500,7 +539,7 @@ __global__ __launch_bounds__(256) void k_apex5(DevGraph G, Totals5 K, Links L, c
             K.add(c | ec(0, 4, x / 3 + 1) | ec(1, 4, x % 3 + 1), w3);
           }
       }
-    for (int32_t k = 64 * part + lane; k < t; k += 64 * (int32_t)gridDim.y) {
+    for (int32_t k = 64 * part + lane; k < t; k += 64 * nparts) {
       const uint32_t f = at_b(k), cl = f & kIdMask, bc = f >> kTypeShift;
       const uint32_t fc = G.gs_idx[ua + cl], pc = fc >> kTypeShift;
       const int32_t c = (int32_t)(fc & kIdMask), Ec = ua + (int32_t)cl;
@@ -571,36 +610,54 @@ __global__ __launch_bounds__(256) void k_apex5(DevGraph G, Totals5 K, Links L, c
         K.add(cs, ws);
       }
     }
-    // the vertices adjacent to u, b and c, eight lanes per c
+    // the vertices adjacent to u, b and c, c by c: listed first, then taken
+    // alone (K4) and in pairs
     if (t >= 2)
-      for (int32_t k = 8 * part + (lane >> 3); k < t; k += 8 * parts) {
+      for (int32_t k = part; k < t; k += parts) {
         const uint32_t f = at_b(k), cl = f & kIdMask, bc = f >> kTypeShift;
-        if (cl < bl) continue;
         const int32_t Ec = ua + (int32_t)cl, mc = L.cnt[Ec];
-        if (mc < 2) continue;
+        if (cl < bl || mc < 2) continue;
+        const uint32_t* Rc = L.idx + L.off[Ec];
+        int32_t nc = 0;
+        for (int32_t i0 = 0; i0 < mc; i0 += 64) {
+          const int32_t i = i0 + lane;
+          const uint32_t dl = i < mc ? Rc[i] & kIdMask : bl;
+          const int32_t at = dl == bl ? -1 : place_b(dl);
+          const u64 hit = __ballot(at >= 0);
+          const int32_t x = nc + __popcll(hit & ((1ull << lane) - 1ull));
+          if (at >= 0 && x < kCommon) {
+            com[x] = Rc[i];
+            com[kCommon + x] = at_b(at);
+          }
+          nc += __popcll(hit);
+        }
+        wave_sync();
+        if (nc == 0) continue;
         const uint32_t pc = G.gs_idx[Ec] >> kTypeShift;
         const uint32_t code = cb | ec(0, 2, pc) | ec(1, 2, bc);
-        const uint32_t* Rc = L.idx + L.off[Ec];
-        for (int32_t i = lane & 7; i < mc; i += 8) {
-          const uint32_t dl = Rc[i] & kIdMask, cd = Rc[i] >> kTypeShift;
-          const int32_t at = dl == bl ? -1 : place_b(dl);
-          if (at < 0) continue;
-          const uint32_t bd = at_b(at) >> kTypeShift, pd = G.gs_idx[ua + dl] >> kTypeShift;
-          const uint32_t four = code | ec(0, 3, pd) | ec(1, 3, bd) | ec(2, 3, cd);
-          // two of them, not joined or joined
-          for (int32_t j = i + 1; j < mc; ++j) {
-            const uint32_t el = Rc[j] & kIdMask, ce = Rc[j] >> kTypeShift;
-            const int32_t ae = el == bl ? -1 : place_b(el);
-            if (ae < 0) continue;
-            const uint32_t pe = G.gs_idx[ua + el] >> kTypeShift;
-            const uint32_t c5 = four | ec(0, 4, pe) | ec(1, 4, at_b(ae) >> kTypeShift) | ec(2, 4, ce);
-            K.add(c5, 1ull);
-            if (dl <= cl) continue;  // K5: b < c < d < e
-            const int32_t Ed = ua + (int32_t)dl;
-            const int32_t de = link_at(L.idx + L.off[Ed], L.cnt[Ed], el);
-            if (de >= 0) K.add(c5 | ec(3, 4, L.idx[L.off[Ed] + de] >> kTypeShift), 1ull);
+        // d at place x of the list (beyond its room: found again)
+        auto common = [&](int32_t x, uint32_t& fc, uint32_t& fb) {
+          if (x < kCommon) {
+            fc = com[x];
+            fb = com[kCommon + x];
+            return;
           }
+          for (int32_t i = 0, y = 0; i < mc; ++i) {
+            const uint32_t dl = Rc[i] & kIdMask;
+            const int32_t at = dl == bl ? -1 : place_b(dl);
+            if (at < 0 || y++ < x) continue;
+            fc = Rc[i];
+            fb = at_b(at);
+            return;
+          }
+        };
+        for (int32_t x = lane; x < nc; x += 64) {
+          uint32_t fc = 0, fb = 0;
+          common(x, fc, fb);
+          const uint32_t dl = fc & kIdMask, cd = fc >> kTypeShift, bd = fb >> kTypeShift;
           if (dl <= cl) continue;  // K4 u, b < c < d
+          const uint32_t pd = G.gs_idx[ua + dl] >> kTypeShift;
+          const uint32_t four = code | ec(0, 3, pd) | ec(1, 3, bd) | ec(2, 3, cd);
           for (int s = 0; s < 3; ++s) K.add(four | ec(0, 4, s + 1), other(Du, s, pb, pc, pd));
           uint32_t tc[9], td[9];
           L.types(Ec, tc);
@@ -613,37 +670,61 @@ __global__ __launch_bounds__(256) void k_apex5(DevGraph G, Totals5 K, Links L, c
             uint32_t cs[9];
             u64 ws[9];
 #pragma unroll
-            for (int x = 0; x < 9; ++x) {
-              cs[x] = four | ec(0, 4, x / 3 + 1) | ec(v, 4, x % 3 + 1);
-              ws[x] = v == 1 ? tb[x] - (x == ac) - (x == ad) : v == 2 ? tc[x] - (x == ab) - (x == acd)
-                                                                     : td[x] - (x == adb) - (x == adc);
+            for (int i = 0; i < 9; ++i) {
+              cs[i] = four | ec(0, 4, i / 3 + 1) | ec(v, 4, i % 3 + 1);
+              ws[i] = v == 1 ? tb[i] - (i == ac) - (i == ad) : v == 2 ? tc[i] - (i == ab) - (i == acd)
+                                                                     : td[i] - (i == adb) - (i == adc);
             }
             K.add(cs, ws);
           }
         }
+        // two of them, not joined or joined
+        for (int64_t q = lane; q < (int64_t)nc * nc; q += 64) {
+          const int32_t x = (int32_t)(q / nc), y = (int32_t)(q % nc);
+          if (x >= y) continue;
+          uint32_t dc = 0, db = 0, ec_ = 0, eb = 0;
+          common(x, dc, db);
+          common(y, ec_, eb);
+          const uint32_t dl = dc & kIdMask, el = ec_ & kIdMask;
+          const uint32_t c5 = code | ec(0, 3, G.gs_idx[ua + dl] >> kTypeShift) | ec(1, 3, db >> kTypeShift) |
+                              ec(2, 3, dc >> kTypeShift) | ec(0, 4, G.gs_idx[ua + el] >> kTypeShift) |
+                              ec(1, 4, eb >> kTypeShift) | ec(2, 4, ec_ >> kTypeShift);
+          K.add(c5, 1ull);
+          if (dl <= cl) continue;  // K5: b < c < d < e
+          const int32_t Ed = ua + (int32_t)dl;
+          const int32_t de = link_at(L.idx + L.off[Ed], L.cnt[Ed], el);
+          if (de >= 0) K.add(c5 | ec(3, 4, L.idx[L.off[Ed] + de] >> kTypeShift), 1ull);
+        }
+        wave_sync();
       }
     // wheels with hub u whose rim's first vertex is b: two thirds c < c' of
     // (u, b) and a vertex d adjacent to both
     if (t >= 2 && t <= kWheelT && part == 0)
-      for (int32_t k = lane; k < t * t; k += 64) {
+      for (int32_t k = lane >> 3; k < t * t; k += 8) {  // eight lanes per pair: the shorter row against the longer
         const int32_t i = k / t, j = k % t;
-        const uint32_t cl = R[i] & kIdMask, c2 = R[j] & kIdMask;
-        if (cl < bl || i >= j) continue;
-        const int32_t E1 = ua + (int32_t)cl, E2 = ua + (int32_t)c2, m1 = L.cnt[E1], m2 = L.cnt[E2];
+        const uint32_t f1 = at_b(i), f2 = at_b(j);
+        if ((f1 & kIdMask) < bl || i >= j) continue;
+        const int32_t E1 = ua + (int32_t)(f1 & kIdMask), E2 = ua + (int32_t)(f2 & kIdMask);
+        const int32_t m1 = L.cnt[E1], m2 = L.cnt[E2];
+        if (m1 < 2 || m2 < 2) continue;
         const uint32_t *R1 = L.idx + L.off[E1], *R2 = L.idx + L.off[E2];
         const uint32_t code = cb | ec(0, 2, G.gs_idx[E1] >> kTypeShift) | ec(0, 3, G.gs_idx[E2] >> kTypeShift) |
-                              ec(1, 2, R[i] >> kTypeShift) | ec(1, 3, R[j] >> kTypeShift);
-        for (int32_t x = 0; x < m1; ++x) {
-          const uint32_t dl = R1[x] & kIdMask;
+                              ec(1, 2, f1 >> kTypeShift) | ec(1, 3, f2 >> kTypeShift);
+        const bool first = m1 <= m2;
+        const uint32_t *Ra = first ? R1 : R2, *Rb = first ? R2 : R1;
+        const int32_t ma = first ? m1 : m2, mb = first ? m2 : m1, sa = first ? 2 : 3;
+        for (int32_t x = lane & 7; x < ma; x += 8) {
+          const uint32_t dl = Ra[x] & kIdMask;
           if (dl <= bl) continue;
-          const int32_t y = link_at(R2, m2, dl);
+          const int32_t y = link_at(Rb, mb, dl);
           if (y < 0) continue;
-          K.add(code | ec(0, 4, G.gs_idx[ua + dl] >> kTypeShift) | ec(2, 4, R1[x] >> kTypeShift) |
-                    ec(3, 4, R2[y] >> kTypeShift), 1ull);
+          K.add(code | ec(0, 4, G.gs_idx[ua + dl] >> kTypeShift) | ec(sa, 4, Ra[x] >> kTypeShift) |
+                    ec(5 - sa, 4, Rb[y] >> kTypeShift), 1ull);
         }
       }
     wave_sync();
   });
+  K.write(copies, blockIdx.x);
 }
 
 // Wheels of the units with more links, one workgroup each: the paths b - c - d
@@ -744,22 +825,36 @@ struct PairBins {
     for (int i = t; i < 2187; i += nt) edge[i] = 0;
   }
   __device__ __forceinline__ void flush(const Totals5& K, int t, int nt) const {
-    for (int k = t; k < 729; k += nt) {
-      const int a = k / 81, b = (k / 9) % 9, c = k % 9, at = (a * 9 - a * (a - 1) / 2 + b - a) * 9 + c;
-      if (a <= b && b <= c && three[at])
-        K.add(ec(0, 2, a / 3 + 1) | ec(2, 1, a % 3 + 1) | ec(0, 3, b / 3 + 1) | ec(3, 1, b % 3 + 1) |
-                  ec(0, 4, c / 3 + 1) | ec(4, 1, c % 3 + 1), three[at]);
-      if (house[k]) {  // u 0, v 1, roof 2, w 3, other middle 4
-        const int p = k / 243, x = (k / 81) % 3, y = (k / 27) % 3, q = (k / 9) % 3, j = k % 9;
-        K.add(ec(0, 1, p + 1) | ec(0, 2, x + 1) | ec(1, 2, y + 1) | ec(1, 3, q + 1) | ec(0, 4, j / 3 + 1) |
-                  ec(4, 3, j % 3 + 1), house[k]);
+    constexpr int N = 6;  // at a time
+    for (int k0 = t; k0 < 3645; k0 += N * nt) {
+      uint32_t code[N];
+      u64 w[N];
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        int k = k0 + i * nt;
+        code[i] = 0;
+        w[i] = 0;
+        if (k < 729) {
+          const int a = k / 81, b = (k / 9) % 9, c = k % 9;
+          if (a > b || b > c) continue;
+          w[i] = three[(a * 9 - a * (a - 1) / 2 + b - a) * 9 + c];
+          code[i] = ec(0, 2, a / 3 + 1) | ec(2, 1, a % 3 + 1) | ec(0, 3, b / 3 + 1) | ec(3, 1, b % 3 + 1) |
+                    ec(0, 4, c / 3 + 1) | ec(4, 1, c % 3 + 1);
+        } else if (k < 1458) {  // u 0, v 1, roof 2, w 3, other middle 4
+          k -= 729;
+          w[i] = house[k];
+          const int p = k / 243, x = (k / 81) % 3, y = (k / 27) % 3, q = (k / 9) % 3, j = k % 9;
+          code[i] = ec(0, 1, p + 1) | ec(0, 2, x + 1) | ec(1, 2, y + 1) | ec(1, 3, q + 1) | ec(0, 4, j / 3 + 1) |
+                    ec(4, 3, j % 3 + 1);
+        } else if (k < 3645) {
+          k -= 1458;
+          w[i] = edge[k];
+          const int j = k % 9, qb = (k / 9) % 3, qa = (k / 27) % 3, ab = (k / 81) % 3, pb = (k / 243) % 3, pa = k / 729;
+          code[i] = ec(0, 1, pa + 1) | ec(0, 2, pb + 1) | ec(1, 2, ab + 1) | ec(1, 3, qa + 1) | ec(2, 3, qb + 1) |
+                    ec(0, 4, j / 3 + 1) | ec(4, 3, j % 3 + 1);
+        }
       }
-    }
-    for (int k = t; k < 2187; k += nt) {
-      if (!edge[k]) continue;
-      const int j = k % 9, qb = (k / 9) % 3, qa = (k / 27) % 3, ab = (k / 81) % 3, pb = (k / 243) % 3, pa = k / 729;
-      K.add(ec(0, 1, pa + 1) | ec(0, 2, pb + 1) | ec(1, 2, ab + 1) | ec(1, 3, qa + 1) | ec(2, 3, qb + 1) |
-                ec(0, 4, j / 3 + 1) | ec(4, 3, j % 3 + 1), edge[k]);
+      K.add(code, w);
     }
   }
 };
@@ -1405,27 +1500,35 @@ __global__ __launch_bounds__(256) void k_c5_rows(DevGraph G, Totals5 K, const ui
 
 // Copies of each class: its totals less the folded walks, over the times a copy
 // is met.  acc4, acc3: the copies' totals of k = 4 and 3 (kRep4, kRep3 of them).
-__global__ __launch_bounds__(256) void k_sum5(const uint64_t* __restrict__ acc, const uint64_t* __restrict__ acc4,
-                                              const uint64_t* __restrict__ acc3, Tables5 T, uint64_t* __restrict__ P,
-                                              uint64_t* __restrict__ I, int32_t* st) {
+__global__ __launch_bounds__(256) void k_sum5(const uint64_t* __restrict__ acc, int copies,
+                                              const uint64_t* __restrict__ acc4, const uint64_t* __restrict__ acc3,
+                                              Tables5 T, uint64_t* __restrict__ P, uint64_t* __restrict__ I, int32_t* st) {
+  __shared__ u64 sums[8][32];
   if (st[kStatus] != 0) return;
-  const int32_t c = blockIdx.x * 256 + threadIdx.x;
-  if (c >= kC5) return;
+  const int32_t c = blockIdx.x * 32 + (threadIdx.x & 31);  // eight threads per class
+  const int part = threadIdx.x >> 5;
   u64 s = 0;
-#pragma unroll 8
-  for (int r = 0; r < kRep5; ++r) s += acc[(int64_t)r * kC5 + c];
-  for (int32_t k = T.fold_off[c]; k < T.fold_off[c + 1]; ++k) {
-    const int32_t q = T.fold[k] & 0xFFFF;
-    const u64 times = (u64)(T.fold[k] >> 16);
-    u64 n = 0;
-    if (q < 199) {
-#pragma unroll 8
-      for (int r = 0; r < kRep4; ++r) n += acc4[r * 199 + q];
-    } else {
-      for (int r = 0; r < kRep3; ++r) n += acc3[r * 13 + q - 199];
+  if (c < kC5) {
+#pragma unroll 12
+    for (int r = part; r < copies; r += 8) s += acc[(int64_t)r * kC5 + c];
+    const int32_t f0 = T.fold_off[c], f1 = T.fold_off[c + 1];
+    for (int32_t k = f0; k < f1; ++k) {
+      const int32_t q = T.fold[k] & 0xFFFF;
+      u64 n = 0;
+      if (q < 199) {
+#pragma unroll
+        for (int r = 0; r < kRep4 / 8; ++r) n += acc4[(part + 8 * r) * 199 + q];
+      } else {
+#pragma unroll
+        for (int r = 0; r < kRep3 / 8; ++r) n += acc3[(part + 8 * r) * 13 + q - 199];
+      }
+      s -= (u64)(T.fold[k] >> 16) * n;
     }
-    s -= times * n;
   }
+  sums[part][threadIdx.x & 31] = s;
+  __syncthreads();
+  if (part || c >= kC5) return;
+  for (int r = 1; r < 8; ++r) s += sums[r][threadIdx.x];
   const u64 m = T.mult[c];
   if (s % m) atomicMin(&st[kStatus], MOTIF_EINTERNAL);
   P[c] = I[c] = s / m;
@@ -1473,7 +1576,7 @@ bool copies5_fits(int64_t n, int64_t m) { return n > 0 && n <= 65536 && m <= (in
 size_t copies5_bytes(int64_t n, int64_t m) {
   const size_t gs = (size_t)(2 * m + 1);
   return count_bytes(n, m, n, false, true) + 2 * al(64 * 4) + al(sizeof(uint64_t) * 13 * kRep3) +
-         al(sizeof(uint64_t) * 199 * kRep4) + al(sizeof(uint64_t) * kC5 * kRep5) + 4 * al(sizeof(uint64_t) * kC5) +
+         al(sizeof(uint64_t) * 199 * kRep4) + al(sizeof(uint64_t) * kC5 * (kRep5 + kLocalCopies)) + 4 * al(sizeof(uint64_t) * kC5) +
          3 * al(4 * gs) + al(8 * (size_t)(m + 1)) + al(24 * (size_t)(m + 1)) + scan1_bytes((int64_t)gs) +
          3 * al(4 * (size_t)link_room(m)) + al(72 * (size_t)n) + al(16 * (size_t)n) + al(108 * (size_t)n) +
          kPairLists * al(4 * (size_t)n) + al(4 * slice_words(n) * (size_t)c5_slices(n)) + 8192;
@@ -1486,7 +1589,7 @@ void enqueue_copies5_start(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_
   R->a3 = a3;
   R->a4 = a4;
   R->queue = A.take<int32_t>(64);
-  R->acc = A.take<uint64_t>((size_t)kC5 * kRep5);
+  R->acc = A.take<uint64_t>((size_t)kC5 * (kRep5 + kLocalCopies));
   R->emap = A.take<uint32_t>((size_t)g.gs_cap);
   R->cnt = A.take<int32_t>((size_t)g.gs_cap);
   R->off = A.take<int32_t>((size_t)g.gs_cap);
@@ -1539,9 +1642,8 @@ void enqueue_copies5_finish(Pipeline& p, const DevGraph& g, const Copies5Run& R,
   hipLaunchKernelGGL(k_classify5, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, g, lists, R.queue, p.status);
   hipLaunchKernelGGL(k_links5, grid(m, 4, 8), dim3(256), 0, s, g, K, L, R.epos, R.hi, up, idx, mate, src, R.tri, p.status);
   hipLaunchKernelGGL(k_butterfly5, grid(n, 4, 4), dim3(256), 0, s, g, K, R.tri, p.status);
-  dim3 ag = grid(2 * m, 4, 6);
-  ag.y = kApexParts;
-  hipLaunchKernelGGL(k_apex5, ag, dim3(256), 0, s, g, K, L, S, p.status);
+  const dim3 ag((unsigned)std::max<int64_t>(1, std::min<int64_t>(kLocalCopies, (2 * m + 63) / 64)));
+  hipLaunchKernelGGL(k_apex5, ag, dim3(kApexThreads), 0, s, g, T.lut[5], R.acc + (size_t)kRep5 * kC5, L, S, p.status);
   hipLaunchKernelGGL(k_wheel5, grid(2 * m, 256, 2), dim3(256), 0, s, g, K, L, p.status);
   hipLaunchKernelGGL(k_pairs5_block, grid(n * ((n + kPairIds - 1) / kPairIds), 1, 1), dim3(1024), 0, s, g, K, L, R.queue,
                      list[kPairBlock], p.status);
@@ -1561,7 +1663,7 @@ void enqueue_copies5_finish(Pipeline& p, const DevGraph& g, const Copies5Run& R,
   hipLaunchKernelGGL((k_c5<256, 9, kWedge64>), grid(n, 1, 8), dim3(256), 0, s, g, K, R.queue, R.counts.wedge[kWedge64], p.status);
   hipLaunchKernelGGL((k_c5<64, 7, kWedge16>), grid(n, 4, 8), dim3(256), 0, s, g, K, R.queue, R.counts.wedge[kWedge16], p.status);
   const dim3 cg((kC5 + 255) / 256);
-  hipLaunchKernelGGL(k_sum5, cg, dim3(256), 0, s, R.acc, R.a4, R.a3, T.five, P[0], I, p.status);
+  hipLaunchKernelGGL(k_sum5, dim3((kC5 + 31) / 32), dim3(256), 0, s, R.acc, kRep5 + (int)ag.x, R.a4, R.a3, T.five, P[0], I, p.status);
   for (int j = 1; j <= 6; ++j)
     hipLaunchKernelGGL(k_step5, dim3((kC5 + 31) / 32), dim3(256), 0, s, T.five, j, P[(j + 1) & 1], P[j & 1], I, p.status);
   hipLaunchKernelGGL(k_write5, cg, dim3(256), 0, s, I, out, p.status);
