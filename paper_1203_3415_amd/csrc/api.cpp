@@ -186,6 +186,7 @@ int32_t get_pipeline(int dev, hipStream_t s, size_t bytes, Pipeline** out) {
     if (p->arena.base) {  // a failure here shows up as a failed allocation below
       (void)hipStreamSynchronize(s);
       if (p->side) (void)hipStreamSynchronize(p->side);
+      sync_chains(*p);
       (void)hipFree(p->arena.base);
       p->arena.base = nullptr;
       p->arena.cap = 0;
@@ -381,6 +382,7 @@ void profile_mark(int k, int what, bool begin, hipStream_t s) {
 int32_t drain_after_error(Pipeline& p, hipStream_t s) {
   (void)hipStreamSynchronize(s);  // best effort: the error below is what the caller acts on
   if (p.side) (void)hipStreamSynchronize(p.side);
+  sync_chains(p);
   return MOTIF_EINTERNAL;
 }
 
@@ -642,6 +644,7 @@ int32_t motif_shutdown(void) {
     free_tables6(&kv.second.t6);
     for (auto& pp : kv.second.pipes) {
       if (pp.second->side) (void)hipStreamDestroy(pp.second->side);
+      free_chains(*pp.second);
       if (pp.second->ev_fork) (void)hipEventDestroy(pp.second->ev_fork);
       if (pp.second->ev_join) (void)hipEventDestroy(pp.second->ev_join);
       if (pp.second->ev_pre) (void)hipEventDestroy(pp.second->ev_pre);
@@ -967,6 +970,7 @@ int32_t motif_census_noalloc(const int32_t* out_off, const int32_t* out_idx, con
   p.host_status = host_status;
   p.num_cus = cus;
   p.tune = tune;
+  p.may_fork = false;
   if (n == 0) {
     enqueue_zero(hist, sizeof(uint64_t) * motif_num_classes(k), s);
     return hipStreamSynchronize(s) == hipSuccess ? 0 : MOTIF_EDEVICE;

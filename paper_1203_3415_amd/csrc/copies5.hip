@@ -452,7 +452,7 @@ __global__ __launch_bounds__(256) void k_butterfly5(DevGraph G, Totals5 K, const
 constexpr int kApexThreads = 1024;
 constexpr int kStaged = 256;  // links of a unit up to which a wave keeps them in LDS
 constexpr int kApexParts = 16;  // most waves that share a unit, four thirds each (64 in what a lane does alone)
-constexpr int kCommon = 64;     // vertices adjacent to u, b and c that a wave keeps in LDS
+constexpr int kCommon = 64;     // of the vertices adjacent to u, b and c, those a wave has in one list
 constexpr int kWheelT = 8;    // links of a unit up to which its wheels are taken pair by pair
 
 // A unit is a G* entry (u, b) with triangles, its links the vertices c adjacent
@@ -488,13 +488,13 @@ __device__ __forceinline__ int32_t link_at(const uint32_t* p, int32_t m, uint32_
 __global__ __launch_bounds__(kApexThreads) void k_apex5(DevGraph G, const uint16_t* __restrict__ lut,
                                                         uint64_t* __restrict__ copies, Links L,
                                                         const u64* __restrict__ S, const int32_t* st) {
-  __shared__ uint32_t s_R[kApexThreads / 64][kStaged], s_com[kApexThreads / 64][2 * kCommon];
+  __shared__ uint32_t s_R[kApexThreads / 64][kStaged], s_com[kApexThreads / 64][4 * kCommon + 27];
   __shared__ u64 sum[kC5];
   if (st[kStatus] != 0) return;
   const Local5 K{lut, sum};
   K.clear();
   const int lane = threadIdx.x & 63;
-  uint32_t *sR = s_R[threadIdx.x >> 6], *com = s_com[threadIdx.x >> 6];
+  uint32_t *sR = s_R[threadIdx.x >> 6], *com = s_com[threadIdx.x >> 6], *hist = com + 4 * kCommon;
   constexpr int nparts = kApexParts;
   for (int part = 0; part < nparts; ++part)
   for_entries(G, L.cnt, 4 * part + 1, part, [&](int32_t E) {
@@ -610,90 +610,104 @@ __global__ __launch_bounds__(kApexThreads) void k_apex5(DevGraph G, const uint16
         K.add(cs, ws);
       }
     }
-    // the vertices adjacent to u, b and c, c by c: listed first, then taken
-    // alone (K4) and in pairs
+    // the vertices d adjacent to u, b and c, c by c: counted by type, for two of
+    // them whatever their own pair, and those after c listed, for the K4s and,
+    // two by two, the K5s
     if (t >= 2)
       for (int32_t k = part; k < t; k += parts) {
         const uint32_t f = at_b(k), cl = f & kIdMask, bc = f >> kTypeShift;
         const int32_t Ec = ua + (int32_t)cl, mc = L.cnt[Ec];
         if (cl < bl || mc < 2) continue;
         const uint32_t* Rc = L.idx + L.off[Ec];
-        int32_t nc = 0;
-        for (int32_t i0 = 0; i0 < mc; i0 += 64) {
-          const int32_t i = i0 + lane;
-          const uint32_t dl = i < mc ? Rc[i] & kIdMask : bl;
-          const int32_t at = dl == bl ? -1 : place_b(dl);
-          const u64 hit = __ballot(at >= 0);
-          const int32_t x = nc + __popcll(hit & ((1ull << lane) - 1ull));
-          if (at >= 0 && x < kCommon) {
-            com[x] = Rc[i];
-            com[kCommon + x] = at_b(at);
-          }
-          nc += __popcll(hit);
-        }
-        wave_sync();
-        if (nc == 0) continue;
         const uint32_t pc = G.gs_idx[Ec] >> kTypeShift;
         const uint32_t code = cb | ec(0, 2, pc) | ec(1, 2, bc);
-        // d at place x of the list (beyond its room: found again)
-        auto common = [&](int32_t x, uint32_t& fc, uint32_t& fb) {
-          if (x < kCommon) {
-            fc = com[x];
-            fb = com[kCommon + x];
-            return;
-          }
-          for (int32_t i = 0, y = 0; i < mc; ++i) {
-            const uint32_t dl = Rc[i] & kIdMask;
-            const int32_t at = dl == bl ? -1 : place_b(dl);
-            if (at < 0 || y++ < x) continue;
-            fc = Rc[i];
-            fb = at_b(at);
-            return;
-          }
-        };
-        for (int32_t x = lane; x < nc; x += 64) {
-          uint32_t fc = 0, fb = 0;
-          common(x, fc, fb);
-          const uint32_t dl = fc & kIdMask, cd = fc >> kTypeShift, bd = fb >> kTypeShift;
-          if (dl <= cl) continue;  // K4 u, b < c < d
-          const uint32_t pd = G.gs_idx[ua + dl] >> kTypeShift;
-          const uint32_t four = code | ec(0, 3, pd) | ec(1, 3, bd) | ec(2, 3, cd);
-          for (int s = 0; s < 3; ++s) K.add(four | ec(0, 4, s + 1), other(Du, s, pb, pc, pd));
-          uint32_t tc[9], td[9];
-          L.types(Ec, tc);
-          L.types(ua + (int32_t)dl, td);
-          const int ac = 3 * (int)(pc - 1) + (int)(bc - 1), ab = 3 * (int)(pb - 1) + (int)(flip(bc) - 1);
-          const int ad = 3 * (int)(pd - 1) + (int)(bd - 1), acd = 3 * (int)(pd - 1) + (int)(cd - 1);
-          const int adb = 3 * (int)(pb - 1) + (int)(flip(bd) - 1), adc = 3 * (int)(pc - 1) + (int)(flip(cd) - 1);
-#pragma unroll
-          for (int v = 1; v <= 3; ++v) {  // a vertex on u and one of the three
-            uint32_t cs[9];
-            u64 ws[9];
-#pragma unroll
-            for (int i = 0; i < 9; ++i) {
-              cs[i] = four | ec(0, 4, i / 3 + 1) | ec(v, 4, i % 3 + 1);
-              ws[i] = v == 1 ? tb[i] - (i == ac) - (i == ad) : v == 2 ? tc[i] - (i == ab) - (i == acd)
-                                                                     : td[i] - (i == adb) - (i == adc);
+        if (lane < 27) hist[lane] = 0;
+        wave_sync();
+        // lists from the skip-th on of the d after c into out[0 .. 2 kCommon);
+        // the first time, all are counted by type; returns how many there are
+        int32_t nall = 0;
+        auto list_after = [&](int32_t skip, uint32_t* out, bool count) {
+          int32_t nd = 0;
+          for (int32_t i0 = 0; i0 < mc; i0 += 64) {
+            const int32_t i = i0 + lane;
+            const uint32_t fc = i < mc ? Rc[i] : bl, dl = fc & kIdMask;
+            const int32_t at = dl == bl || (!count && dl <= cl) ? -1 : place_b(dl);
+            if (count) {
+              if (at >= 0)
+                atomicAdd(&hist[9 * ((G.gs_idx[ua + dl] >> kTypeShift) - 1) + 3 * ((at_b(at) >> kTypeShift) - 1) +
+                                (fc >> kTypeShift) - 1], 1u);
+              nall += __popcll(__ballot(at >= 0));
             }
-            K.add(cs, ws);
+            const bool in = at >= 0 && dl > cl;
+            const u64 hit = __ballot(in);
+            const int32_t x = nd + __popcll(hit & ((1ull << lane) - 1ull)) - skip;
+            if (in && x >= 0 && x < kCommon) {
+              out[x] = fc;
+              out[kCommon + x] = at_b(at);
+            }
+            nd += __popcll(hit);
+          }
+          wave_sync();
+          return nd;
+        };
+        const int32_t nd = list_after(0, com, true);
+        if (nall >= 2) {
+          const uint32_t n = lane < 27 ? hist[lane] : 0u;
+          for (u64 have = __ballot(n > 0u); have; have &= have - 1ull) {
+            const int i = __builtin_ctzll(have);
+            const u64 ni = __shfl(n, i);
+            if (lane < i || !n) continue;  // (lane: the second one's type)
+            K.add(code | ec(0, 3, i / 9 + 1) | ec(1, 3, (i / 3) % 3 + 1) | ec(2, 3, i % 3 + 1) | ec(0, 4, lane / 9 + 1) |
+                      ec(1, 4, (lane / 3) % 3 + 1) | ec(2, 4, lane % 3 + 1),
+                  lane == i ? ni * (ni - 1) / 2 : ni * (u64)n);
           }
         }
-        // two of them, not joined or joined
-        for (int64_t q = lane; q < (int64_t)nc * nc; q += 64) {
-          const int32_t x = (int32_t)(q / nc), y = (int32_t)(q % nc);
-          if (x >= y) continue;
-          uint32_t dc = 0, db = 0, ec_ = 0, eb = 0;
-          common(x, dc, db);
-          common(y, ec_, eb);
-          const uint32_t dl = dc & kIdMask, el = ec_ & kIdMask;
-          const uint32_t c5 = code | ec(0, 3, G.gs_idx[ua + dl] >> kTypeShift) | ec(1, 3, db >> kTypeShift) |
-                              ec(2, 3, dc >> kTypeShift) | ec(0, 4, G.gs_idx[ua + el] >> kTypeShift) |
-                              ec(1, 4, eb >> kTypeShift) | ec(2, 4, ec_ >> kTypeShift);
-          K.add(c5, 1ull);
-          if (dl <= cl) continue;  // K5: b < c < d < e
+        // the K5 of d at x0 + x of one list and e at y of another
+        auto five = [&](const uint32_t* A, const uint32_t* B, int32_t x, int32_t y) {
+          const uint32_t dl = A[x] & kIdMask, el = B[y] & kIdMask;
           const int32_t Ed = ua + (int32_t)dl;
           const int32_t de = link_at(L.idx + L.off[Ed], L.cnt[Ed], el);
-          if (de >= 0) K.add(c5 | ec(3, 4, L.idx[L.off[Ed] + de] >> kTypeShift), 1ull);
+          if (de >= 0)
+            K.add(code | ec(0, 3, G.gs_idx[Ed] >> kTypeShift) | ec(1, 3, A[kCommon + x] >> kTypeShift) |
+                      ec(2, 3, A[x] >> kTypeShift) | ec(0, 4, G.gs_idx[ua + el] >> kTypeShift) |
+                      ec(1, 4, B[kCommon + y] >> kTypeShift) | ec(2, 4, B[y] >> kTypeShift) |
+                      ec(3, 4, L.idx[L.off[Ed] + de] >> kTypeShift), 1ull);
+        };
+        for (int32_t x0 = 0; x0 < nd; x0 += kCommon) {  // (one list, but for the largest)
+          if (x0 > 0) list_after(x0, com, false);
+          const int32_t nx = min(kCommon, nd - x0);
+          for (int32_t x = lane; x < nx; x += 64) {  // K4 u, b < c < d
+            const uint32_t dl = com[x] & kIdMask, cd = com[x] >> kTypeShift, bd = com[kCommon + x] >> kTypeShift;
+            const uint32_t pd = G.gs_idx[ua + dl] >> kTypeShift;
+            const uint32_t four = code | ec(0, 3, pd) | ec(1, 3, bd) | ec(2, 3, cd);
+            for (int s = 0; s < 3; ++s) K.add(four | ec(0, 4, s + 1), other(Du, s, pb, pc, pd));
+            uint32_t tc[9], td[9];
+            L.types(Ec, tc);
+            L.types(ua + (int32_t)dl, td);
+            const int ac = 3 * (int)(pc - 1) + (int)(bc - 1), ab = 3 * (int)(pb - 1) + (int)(flip(bc) - 1);
+            const int ad = 3 * (int)(pd - 1) + (int)(bd - 1), acd = 3 * (int)(pd - 1) + (int)(cd - 1);
+            const int adb = 3 * (int)(pb - 1) + (int)(flip(bd) - 1), adc = 3 * (int)(pc - 1) + (int)(flip(cd) - 1);
+#pragma unroll
+            for (int v = 1; v <= 3; ++v) {  // a vertex on u and one of the three
+              uint32_t cs[9];
+              u64 ws[9];
+#pragma unroll
+              for (int i = 0; i < 9; ++i) {
+                cs[i] = four | ec(0, 4, i / 3 + 1) | ec(v, 4, i % 3 + 1);
+                ws[i] = v == 1 ? tb[i] - (i == ac) - (i == ad) : v == 2 ? tc[i] - (i == ab) - (i == acd)
+                                                                       : td[i] - (i == adb) - (i == adc);
+              }
+              K.add(cs, ws);
+            }
+          }
+          for (int32_t q = lane; q < nx * nx; q += 64)
+            if (q / nx < q % nx) five(com, com, q / nx, q % nx);
+          for (int32_t y0 = x0 + kCommon; y0 < nd; y0 += kCommon) {
+            list_after(y0, com + 2 * kCommon, false);
+            const int32_t ny = min(kCommon, nd - y0);
+            for (int32_t q = lane; q < nx * ny; q += 64) five(com, com + 2 * kCommon, q / ny, q % ny);
+            wave_sync();
+          }
         }
         wave_sync();
       }
@@ -727,15 +741,21 @@ __global__ __launch_bounds__(kApexThreads) void k_apex5(DevGraph G, const uint16
   K.write(copies, blockIdx.x);
 }
 
-// Wheels of the units with more links, one workgroup each: the paths b - c - d
-// among N(u) as nodes chained by d, each paired with the earlier ones of its d.
-// Nodes that do not fit are taken in several passes over shares of the d.
+// Wheels of the units with more links, one workgroup each.  The paths b - c - d
+// among N(u) are counted per d by their 27 types while the row of u is short
+// enough for that table, and the pairs taken in closed form (n = 115, m = 1,380:
+// 476 us as single pairs).  Else they are nodes chained by d, each paired with
+// the earlier ones of its d; nodes that do not fit are taken in several passes
+// over shares of the d.
 constexpr int kNodes = 8192, kHeads = 2048;
+constexpr int kWheelRow = 1024;      // neighbours of u up to which d has a table entry
 constexpr int32_t kMaxThirds = 4096;  // links of a unit (fourteen bits of a node; one d fits in a pass)
 
 __global__ __launch_bounds__(256) void k_wheel5(DevGraph G, Totals5 K, Links L, const int32_t* st) {
-  __shared__ uint32_t node[kNodes], head[kHeads];
-  __shared__ uint16_t next[kNodes];
+  __shared__ uint32_t words[kNodes + kHeads + kNodes / 2];
+  static_assert(sizeof(words) >= kWheelRow * 27 * 2, "table of 16-bit counts");
+  uint32_t *node = words, *head = words + kNodes;
+  uint16_t* next = reinterpret_cast<uint16_t*>(words + kNodes + kHeads);
   __shared__ int32_t list[256], nlist, nnode;
   if (st[kStatus] != 0) return;
   const int32_t total = G.gs_off[G.n];
@@ -752,6 +772,41 @@ __global__ __launch_bounds__(256) void k_wheel5(DevGraph G, Totals5 K, Links L, 
       const uint32_t bl = (uint32_t)(E - ua);
       const uint32_t* R = L.idx + L.off[E];
       const uint32_t cb = ec(0, 1, G.gs_idx[E] >> kTypeShift);
+      const int32_t du = G.gs_off[u + 1] - ua;
+      if (du <= kWheelRow) {
+        for (int i = threadIdx.x; i < (du * 27 + 1) / 2; i += 256) words[i] = 0;
+        __syncthreads();
+        for (int32_t i = threadIdx.x >> 3; i < t; i += 32) {
+          const uint32_t cl = R[i] & kIdMask;
+          if (cl < bl) continue;
+          const int32_t Ec = ua + (int32_t)cl, m = L.cnt[Ec];
+          const uint32_t* Rc = L.idx + L.off[Ec];
+          const uint32_t ty = 9 * ((G.gs_idx[Ec] >> kTypeShift) - 1u) + 3 * ((R[i] >> kTypeShift) - 1u);
+          for (int32_t x = threadIdx.x & 7; x < m; x += 8) {
+            const uint32_t f = Rc[x], dl = f & kIdMask;
+            if (dl <= bl) continue;
+            const uint32_t at = dl * 27 + ty + (f >> kTypeShift) - 1u;
+            atomicAdd(&words[at >> 1], 1u << (16 * (at & 1u)));
+          }
+        }
+        __syncthreads();
+        auto n_at = [&](int32_t i) { return (words[i >> 1] >> (16 * (i & 1))) & 0xFFFFu; };
+        for (int32_t x = threadIdx.x; x < du * 27; x += 256) {  // this type with itself and the later ones
+          const u64 n = n_at(x);
+          if (!n) continue;
+          const int32_t dl = x / 27, i = x % 27;
+          const uint32_t code = cb | ec(0, 4, G.gs_idx[ua + dl] >> kTypeShift) | ec(0, 2, i / 9 + 1) |
+                                ec(1, 2, (i / 3) % 3 + 1) | ec(2, 4, i % 3 + 1);
+          for (int j = i; j < 27; ++j) {
+            const u64 m = j == i ? n - 1 : n_at(dl * 27 + j);
+            if (m)
+              K.add(code | ec(0, 3, j / 9 + 1) | ec(1, 3, (j / 3) % 3 + 1) | ec(3, 4, j % 3 + 1),
+                    j == i ? n * m / 2 : n * m);
+          }
+        }
+        __syncthreads();
+        continue;
+      }
       // share of a pass: the d that are res modulo mod (a power of two); halved
       // while it does not fit, down to one d, whose nodes are at most t
       for (uint32_t mod = 1, res = 0; mod;) {
@@ -1567,7 +1622,7 @@ int c5_slices(int64_t n) {
   return (int)std::max<size_t>(1, std::min<size_t>((size_t)n, std::min<size_t>(1024, kSliceBytes / (4 * slice_words(n)))));
 }
 
-int64_t link_room(int64_t m) { return 16 * m + 1024; }
+int64_t link_room(int64_t m) { return 16 * m + (int64_t(1) << 20); }
 
 }  // namespace
 
@@ -1581,6 +1636,35 @@ size_t copies5_bytes(int64_t n, int64_t m) {
          3 * al(4 * (size_t)link_room(m)) + al(72 * (size_t)n) + al(16 * (size_t)n) + al(108 * (size_t)n) +
          kPairLists * al(4 * (size_t)n) + al(4 * slice_words(n) * (size_t)c5_slices(n)) + 8192;
 }
+
+// Side streams of a pipeline (default priority), made on first use; when one
+// cannot be had its work stays on the caller's stream.
+struct Chains {
+  Pipeline& p;
+  hipStream_t s;
+  bool used[Pipeline::kChains] = {};
+  Chains(Pipeline& pl, hipStream_t st) : p(pl), s(st) {
+    if (!p.may_fork) return;
+    if (!p.ev_chain && hipEventCreateWithFlags(&p.ev_chain, hipEventDisableTiming) != hipSuccess) p.ev_chain = nullptr;
+    for (int i = 0; i < Pipeline::kChains; ++i) {
+      if (!p.chain[i] && hipStreamCreateWithFlags(&p.chain[i], hipStreamNonBlocking) != hipSuccess) p.chain[i] = nullptr;
+      if (!p.ev_end[i] && hipEventCreateWithFlags(&p.ev_end[i], hipEventDisableTiming) != hipSuccess) p.ev_end[i] = nullptr;
+    }
+  }
+  hipStream_t on(int i) const { return used[i] ? p.chain[i] : s; }
+  void fork(int i) {  // chain i goes on from here
+    if (p.may_fork && p.chain[i] && p.ev_end[i] && p.ev_chain && hipEventRecord(p.ev_chain, s) == hipSuccess &&
+        hipStreamWaitEvent(p.chain[i], p.ev_chain, 0) == hipSuccess)
+      used[i] = true;
+  }
+  void join() {
+    for (int i = 0; i < Pipeline::kChains; ++i)
+      if (used[i] && (hipEventRecord(p.ev_end[i], p.chain[i]) != hipSuccess ||
+                      hipStreamWaitEvent(s, p.ev_end[i], 0) != hipSuccess))
+        (void)hipStreamSynchronize(p.chain[i]);
+  }
+};
+constexpr int64_t kFewUnits = 512;
 
 void enqueue_copies5_start(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_t* a4, Copies5Run* R, hipStream_t s) {
   const int64_t n = g.n, m = (g.gs_cap - 1) / 2;
@@ -1626,7 +1710,7 @@ void enqueue_copies5_finish(Pipeline& p, const DevGraph& g, const Copies5Run& R,
   int32_t* src = A.take<int32_t>((size_t)link_room(m));
   u64* S = A.take<u64>(9 * (size_t)n);
   uint4* up = A.take<uint4>((size_t)n);
-  PairListsOf lists;
+  PairListsOf lists{};
   for (auto& l : lists.v) l = A.take<int32_t>((size_t)n);
   int32_t** list = lists.v;
   const int slices = c5_slices(n), tops = p.host_status[11];
@@ -1638,35 +1722,72 @@ void enqueue_copies5_finish(Pipeline& p, const DevGraph& g, const Copies5Run& R,
   auto grid = [&](int64_t items, int per, int wgs) {
     return dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>((int64_t)cus * wgs, (items + per - 1) / per)));
   };
+  // Up to four chains of kernels at a time: on small graphs each lasts as long as
+  // its longest unit, on larger ones they fill each other's ends.
+  Chains ch(p, s);
+  ch.fork(0);
+  for (int first = 0; first < tops; first += slices) {
+    const unsigned now = (unsigned)std::min(slices, tops - first);
+    enqueue_zero(slice, sizeof(uint32_t) * now * slice_words(n), ch.on(0));
+    hipLaunchKernelGGL(k_c5_fill, dim3(kFillParts, now), dim3(512), 0, ch.on(0), g, R.queue, R.counts.wedge[kWedgeTop],
+                       R.counts.wedge[kWedgeHuge], first, slice, p.status);
+    hipLaunchKernelGGL(k_c5_rows, dim3(kRowParts, now), dim3(256), 0, ch.on(0), g, K, slice, p.status);
+  }
+  hipLaunchKernelGGL((k_c5<512, 12, kWedge256>), grid(n, 1, 2), dim3(512), 0, ch.on(0), g, K, R.queue,
+                     R.counts.wedge[kWedge256], p.status);
+  hipLaunchKernelGGL((k_c5<256, 9, kWedge64>), grid(n, 1, 8), dim3(256), 0, ch.on(0), g, K, R.queue,
+                     R.counts.wedge[kWedge64], p.status);
+  hipLaunchKernelGGL((k_c5<64, 7, kWedge16>), grid(n, 4, 8), dim3(256), 0, ch.on(0), g, K, R.queue,
+                     R.counts.wedge[kWedge16], p.status);
   hipLaunchKernelGGL(k_vertex5, grid(n, 4, 4), dim3(256), 0, s, g, K, S, up, p.status);
   hipLaunchKernelGGL(k_classify5, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, g, lists, R.queue, p.status);
   hipLaunchKernelGGL(k_links5, grid(m, 4, 8), dim3(256), 0, s, g, K, L, R.epos, R.hi, up, idx, mate, src, R.tri, p.status);
-  hipLaunchKernelGGL(k_butterfly5, grid(n, 4, 4), dim3(256), 0, s, g, K, R.tri, p.status);
+  ch.fork(1);
+  ch.fork(2);
+  auto pairs = [&](auto kernel, int hb, int units, int threads, int wgs, hipStream_t on) {
+    hipLaunchKernelGGL(kernel, grid(n, units, wgs), dim3(threads), 0, on, g, K, L, R.queue, list[hb - 9], p.status);
+  };
+  // Below kFewUnits vertices no list fills the chip and a unit gets more threads
+  // than otherwise pays (n = 115, m = 1,380: 64 to 512 threads 440 us in all).
+  const bool few = n <= kFewUnits;
+  hipLaunchKernelGGL(k_pairs5_block, grid(n * ((n + kPairIds - 1) / kPairIds), 1, 1), dim3(1024), 0, s, g, K, L, R.queue,
+                     list[kPairBlock], p.status);
+  pairs(k_pairs5<1024, 13, 1024>, 13, 1, 1024, 1, ch.on(1));
+  if (few) pairs(k_pairs5<1024, 12, 1024>, 12, 1, 1024, 1, ch.on(1));
+  else pairs(k_pairs5<512, 12, 512>, 12, 1, 512, 2, ch.on(1));
+  if (few) pairs(k_pairs5<1024, 11, 1024>, 11, 1, 1024, 2, ch.on(2));
+  else pairs(k_pairs5<256, 11, 256>, 11, 1, 256, 3, ch.on(2));
+  if (few) pairs(k_pairs5<512, 10, 512>, 10, 1, 512, 4, ch.on(2));
+  else pairs(k_pairs5<128, 10, 128>, 10, 1, 128, 4, ch.on(2));
+  if (few) pairs(k_pairs5<256, 9, 256>, 9, 1, 256, 4, ch.on(1));
+  else pairs(k_pairs5<64, 9, 256>, 9, 4, 256, 2, ch.on(1));
   const dim3 ag((unsigned)std::max<int64_t>(1, std::min<int64_t>(kLocalCopies, (2 * m + 63) / 64)));
   hipLaunchKernelGGL(k_apex5, ag, dim3(kApexThreads), 0, s, g, T.lut[5], R.acc + (size_t)kRep5 * kC5, L, S, p.status);
   hipLaunchKernelGGL(k_wheel5, grid(2 * m, 256, 2), dim3(256), 0, s, g, K, L, p.status);
-  hipLaunchKernelGGL(k_pairs5_block, grid(n * ((n + kPairIds - 1) / kPairIds), 1, 1), dim3(1024), 0, s, g, K, L, R.queue,
-                     list[kPairBlock], p.status);
-  hipLaunchKernelGGL((k_pairs5<1024, 13, 1024>), grid(n, 1, 1), dim3(1024), 0, s, g, K, L, R.queue, list[kPair13], p.status);
-  hipLaunchKernelGGL((k_pairs5<512, 12, 512>), grid(n, 1, 2), dim3(512), 0, s, g, K, L, R.queue, list[kPair12], p.status);
-  hipLaunchKernelGGL((k_pairs5<256, 11, 256>), grid(n, 1, 3), dim3(256), 0, s, g, K, L, R.queue, list[kPair11], p.status);
-  hipLaunchKernelGGL((k_pairs5<128, 10, 128>), grid(n, 1, 4), dim3(128), 0, s, g, K, L, R.queue, list[kPair10], p.status);
-  hipLaunchKernelGGL((k_pairs5<64, 9, 256>), grid(n, 4, 2), dim3(256), 0, s, g, K, L, R.queue, list[kPair9], p.status);
-  for (int first = 0; first < tops; first += slices) {
-    const unsigned now = (unsigned)std::min(slices, tops - first);
-    enqueue_zero(slice, sizeof(uint32_t) * now * slice_words(n), s);
-    hipLaunchKernelGGL(k_c5_fill, dim3(kFillParts, now), dim3(512), 0, s, g, R.queue, R.counts.wedge[kWedgeTop],
-                       R.counts.wedge[kWedgeHuge], first, slice, p.status);
-    hipLaunchKernelGGL(k_c5_rows, dim3(kRowParts, now), dim3(256), 0, s, g, K, slice, p.status);
-  }
-  hipLaunchKernelGGL((k_c5<512, 12, kWedge256>), grid(n, 1, 2), dim3(512), 0, s, g, K, R.queue, R.counts.wedge[kWedge256], p.status);
-  hipLaunchKernelGGL((k_c5<256, 9, kWedge64>), grid(n, 1, 8), dim3(256), 0, s, g, K, R.queue, R.counts.wedge[kWedge64], p.status);
-  hipLaunchKernelGGL((k_c5<64, 7, kWedge16>), grid(n, 4, 8), dim3(256), 0, s, g, K, R.queue, R.counts.wedge[kWedge16], p.status);
+  hipLaunchKernelGGL(k_butterfly5, grid(n, 4, 4), dim3(256), 0, s, g, K, R.tri, p.status);
+  ch.join();
   const dim3 cg((kC5 + 255) / 256);
   hipLaunchKernelGGL(k_sum5, dim3((kC5 + 31) / 32), dim3(256), 0, s, R.acc, kRep5 + (int)ag.x, R.a4, R.a3, T.five, P[0], I, p.status);
   for (int j = 1; j <= 6; ++j)
     hipLaunchKernelGGL(k_step5, dim3((kC5 + 31) / 32), dim3(256), 0, s, T.five, j, P[(j + 1) & 1], P[j & 1], I, p.status);
   hipLaunchKernelGGL(k_write5, cg, dim3(256), 0, s, I, out, p.status);
+}
+
+void sync_chains(Pipeline& p) {
+  for (hipStream_t c : p.chain)
+    if (c) (void)hipStreamSynchronize(c);
+}
+
+void free_chains(Pipeline& p) {
+  sync_chains(p);
+  for (int i = 0; i < Pipeline::kChains; ++i) {
+    if (p.chain[i]) (void)hipStreamDestroy(p.chain[i]);
+    if (p.ev_end[i]) (void)hipEventDestroy(p.ev_end[i]);
+    p.chain[i] = nullptr;
+    p.ev_end[i] = nullptr;
+  }
+  if (p.ev_chain) (void)hipEventDestroy(p.ev_chain);
+  p.ev_chain = nullptr;
 }
 
 }  // namespace motif

@@ -143,6 +143,11 @@ struct Pipeline {
   hipStream_t side = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
   hipEvent_t ev_pre = nullptr;  // the largest census's big-core tables are clear (cleared on `side`)
+  // further streams for the independent kernels of a k = 5 census by copies
+  static constexpr int kChains = 3;
+  hipStream_t chain[kChains] = {};
+  hipEvent_t ev_chain = nullptr, ev_end[kChains] = {};
+  bool may_fork = true;  // false: nothing may be allocated, those stay unmade
   TuningSet tune;  // the tuning this call was sized with (set before any enqueue)
   // Per-workgroup W rows of the k = 4, 5 core-reuse kernels for the census
   // on this pipeline's own stream: zeroed once when allocated, and left zero
@@ -155,6 +160,10 @@ struct Pipeline {
   uint8_t* k6_buf = nullptr;
   size_t k6_bytes = 0;
 };
+
+// Waits for, and gives back, a pipeline's further streams (best effort).
+void sync_chains(Pipeline& p);
+void free_chains(Pipeline& p);
 
 // The class table of size k (len = 2^(k(k-1)) entries, indexed by row-major
 // adjacency codes) rewritten in the code order the census kernels use.

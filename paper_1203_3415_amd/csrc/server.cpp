@@ -182,6 +182,7 @@ void motif_server::worker_main(int /*wid*/) {
   }
   lk.unlock();
   // tear-down: errors here change nothing that a caller could act on
+  free_chains(p);
   if (s) {
     (void)hipStreamSynchronize(s);
     (void)hipStreamDestroy(s);
