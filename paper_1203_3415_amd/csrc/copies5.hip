@@ -797,11 +797,19 @@ __global__ __launch_bounds__(256) void k_wheel5(DevGraph G, Totals5 K, Links L, 
           const int32_t dl = x / 27, i = x % 27;
           const uint32_t code = cb | ec(0, 4, G.gs_idx[ua + dl] >> kTypeShift) | ec(0, 2, i / 9 + 1) |
                                 ec(1, 2, (i / 3) % 3 + 1) | ec(2, 4, i % 3 + 1);
-          for (int j = i; j < 27; ++j) {
-            const u64 m = j == i ? n - 1 : n_at(dl * 27 + j);
-            if (m)
-              K.add(code | ec(0, 3, j / 9 + 1) | ec(1, 3, (j / 3) % 3 + 1) | ec(3, 4, j % 3 + 1),
-                    j == i ? n * m / 2 : n * m);
+#pragma unroll 1
+          for (int j0 = i - i % 9; j0 < 27; j0 += 9) {
+            uint32_t cs[9];
+            u64 ws[9], any = 0;
+#pragma unroll
+            for (int q = 0; q < 9; ++q) {
+              const int j = j0 + q;
+              const u64 m = j < i ? 0ull : j == i ? n - 1 : n_at(dl * 27 + j);
+              cs[q] = code | ec(0, 3, j0 / 9 + 1) | ec(1, 3, q / 3 + 1) | ec(3, 4, q % 3 + 1);
+              ws[q] = j == i ? n * m / 2 : n * m;
+              any |= ws[q];
+            }
+            if (any) K.add(cs, ws);
           }
         }
         __syncthreads();
@@ -1761,9 +1769,9 @@ void enqueue_copies5_finish(Pipeline& p, const DevGraph& g, const Copies5Run& R,
   else pairs(k_pairs5<128, 10, 128>, 10, 1, 128, 4, ch.on(2));
   if (few) pairs(k_pairs5<256, 9, 256>, 9, 1, 256, 4, ch.on(1));
   else pairs(k_pairs5<64, 9, 256>, 9, 4, 256, 2, ch.on(1));
-  const dim3 ag((unsigned)std::max<int64_t>(1, std::min<int64_t>(kLocalCopies, (2 * m + 63) / 64)));
+  const dim3 ag((unsigned)std::max<int64_t>(1, std::min<int64_t>(kLocalCopies, (2 * m + 15) / 16)));
   hipLaunchKernelGGL(k_apex5, ag, dim3(kApexThreads), 0, s, g, T.lut[5], R.acc + (size_t)kRep5 * kC5, L, S, p.status);
-  hipLaunchKernelGGL(k_wheel5, grid(2 * m, 256, 2), dim3(256), 0, s, g, K, L, p.status);
+  hipLaunchKernelGGL(k_wheel5, grid(2 * m, 1, 2), dim3(256), 0, s, g, K, L, p.status);
   hipLaunchKernelGGL(k_butterfly5, grid(n, 4, 4), dim3(256), 0, s, g, K, R.tri, p.status);
   ch.join();
   const dim3 cg((kC5 + 255) / 256);
