@@ -85,23 +85,33 @@ __device__ __forceinline__ int32_t row_of(const int32_t* off, int32_t n, int32_t
   return lo;
 }
 
-// Targets are compared without bit 31 (the slot kind of the mutual-preserving
-// switch).
-constexpr int32_t kTarget = 0x7FFFFFFF;
-constexpr int32_t kMutualBit = (int32_t)0x80000000u;
+// A target as the kernel holds it: 16 bits in LDS (the graphs that fit there
+// have fewer than 2^15 vertices), where two targets share a bank's word and a
+// row takes half the reads, else 32.  Targets are compared without the top bit,
+// the slot kind of the mutual-preserving switch.
+template <bool LDS, bool MUT>
+struct Target {
+  using Word = int32_t;
+  static constexpr int32_t mask = 0x7FFFFFFF, mutual = (int32_t)0x80000000u;
+};
+template <bool MUT>
+struct Target<true, MUT> {
+  using Word = uint16_t;
+  static constexpr int32_t mask = MUT ? 0x7FFF : 0xFFFF, mutual = 0x8000;
+};
 
-// Does row [p, pe) of idx hold x?  Eight loads per step, issued together, so a
-// long (hub) row is not a chain of dependent loads.
-__device__ __forceinline__ bool row_has(const int32_t* idx, int32_t p, int32_t pe, int32_t x) {
+// Does row [p, pe) of idx hold x?
+template <class T>
+__device__ __forceinline__ bool row_has(const typename T::Word* idx, int32_t p, int32_t pe, int32_t x) {
   bool hit = false;
   for (; p + 8 <= pe && !hit; p += 8) {
     int32_t v[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u) v[u] = idx[p + u];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) hit |= (v[u] & kTarget) == x;
+    for (int u = 0; u < 8; ++u) hit |= (v[u] & T::mask) == x;
   }
-  for (; p < pe && !hit; ++p) hit = (idx[p] & kTarget) == x;
+  for (; p < pe && !hit; ++p) hit = ((int32_t)idx[p] & T::mask) == x;
   return hit;
 }
 
@@ -114,6 +124,7 @@ __device__ __forceinline__ bool row_has(const int32_t* idx, int32_t p, int32_t p
 // of a lane at once.  1,000 copies of n = 2,000, m = 8,000 with their census
 // and z-scores: 40.0 -> 33.0 ms; 256 graphs of n = 500 to 5,000, m = 4n, with
 // reciprocated pairs kept: 51.9 -> 34.0 ms.
+constexpr int32_t kTarget = 0x7FFFFFFF;
 constexpr int32_t kShortRow = 16;
 __device__ __forceinline__ bool pair_has(const int32_t* idx, bool act, int32_t p0, int32_t e0, int32_t x0, int32_t p1,
                                          int32_t e1, int32_t x1) {
@@ -148,9 +159,86 @@ __device__ __forceinline__ bool pair_has(const int32_t* idx, bool act, int32_t p
   return hit;
 }
 
+// The same on 16-bit targets in LDS, two to a word: rows of up to kShortWords
+// words by their lanes, both halves compared at once (the smaller of each pair
+// of differences is kept), the last word apart, whose upper half may be the next
+// row's; the longer rows by the wave, their bounds read from their lane's
+// registers.  With two workgroups on a CU a round is bound by its vector
+// instructions, and most of them are here.
+constexpr int32_t kShortWords = 8;
+typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t min_halves(uint32_t a, uint32_t b) {
+  return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(ushort2v, a), __builtin_bit_cast(ushort2v, b)));
+}
+__device__ __forceinline__ bool zero_half(uint32_t t) { return (t & 0xFFFFu) == 0u || (t >> 16) == 0u; }
+template <int32_t MASK>
+__device__ __forceinline__ bool pair_has16(const uint16_t* idx, bool act, int32_t p0, int32_t e0, int32_t x0, int32_t p1,
+                                           int32_t e1, int32_t x1) {
+  const uint32_t* words = reinterpret_cast<const uint32_t*>(idx);
+  const int32_t lane = (int32_t)(threadIdx.x & 63u);
+  constexpr uint32_t M = (uint32_t)MASK | (uint32_t)MASK << 16;
+  const uint32_t y0 = (uint32_t)x0 * 0x10001u, y1 = (uint32_t)x1 * 0x10001u;
+  const int32_t b0 = p0 >> 1, t0 = (e0 - 1) >> 1, b1 = p1 >> 1, t1 = (e1 - 1) >> 1;  // first and last words
+  const int32_t n0 = act ? t0 - b0 + 1 : 0, n1 = act ? t1 - b1 + 1 : 0;
+  const uint64_t l0 = __ballot(n0 > kShortWords), l1 = __ballot(n1 > kShortWords);
+  const int32_t s0 = n0 > kShortWords ? 0 : n0, s1 = n1 > kShortWords ? 0 : n1;
+  const int32_t q0 = s0 ? b0 : 0, q1 = s1 ? b1 : 0, z0 = s0 ? t0 : 0, z1 = s1 ? t1 : 0;
+  // the last words; halves outside the row are made to differ
+  const uint32_t d0 = ((words[z0] ^ y0) & M) | ((uint32_t)e0 & 1u) << 16 | (n0 == 1 ? (uint32_t)p0 & 1u : 0u);
+  const uint32_t d1 = ((words[z1] ^ y1) & M) | ((uint32_t)e1 & 1u) << 16 | (n1 == 1 ? (uint32_t)p1 & 1u : 0u);
+  bool hit = (s0 > 0 && zero_half(d0)) || (s1 > 0 && zero_half(d1));
+  uint32_t m0 = 0xFFFFFFFFu, m1 = 0xFFFFFFFFu;
+  const int32_t i0 = max(z0 - 1, q0), i1 = max(z1 - 1, q1);  // (past the end: the last of these again)
+#pragma unroll
+  for (int32_t s = 0; s < kShortWords; s += 4) {
+    if (!__ballot(s < s0 - 1 || s < s1 - 1)) break;
+    uint32_t v[4], w[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      v[u] = words[min(q0 + s + u, i0)];
+      w[u] = words[min(q1 + s + u, i1)];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      v[u] = (v[u] ^ y0) & M;
+      w[u] = (w[u] ^ y1) & M;
+      if (s + u == 0) {
+        v[u] |= (uint32_t)p0 & 1u;
+        w[u] |= (uint32_t)p1 & 1u;
+      } else {  // (a row of two words reads its first again here)
+        v[u] |= i0 == q0 ? (uint32_t)p0 & 1u : 0u;
+        w[u] |= i1 == q1 ? (uint32_t)p1 & 1u : 0u;
+      }
+      m0 = min_halves(m0, v[u]);
+      m1 = min_halves(m1, w[u]);
+    }
+  }
+  hit |= (s0 > 1 && zero_half(m0)) || (s1 > 1 && zero_half(m1));
+  auto whole = [&](uint64_t mask, int32_t p_, int32_t e_, uint32_t y_) {
+    for (; mask; mask &= mask - 1ull) {
+      const int src = __builtin_ctzll(mask);
+      const int32_t p = __builtin_amdgcn_readlane(p_, src), e = __builtin_amdgcn_readlane(e_, src);
+      const uint32_t y = (uint32_t)__builtin_amdgcn_readlane((int)y_, src);
+      const int32_t b = p >> 1, t = (e - 1) >> 1;
+      bool h = false;
+      for (int32_t q = b + lane; q <= t; q += 64) {
+        uint32_t d = (words[q] ^ y) & M;
+        if (q == b) d |= (uint32_t)p & 1u;
+        if (q == t) d |= ((uint32_t)e & 1u) << 16;
+        h |= zero_half(d);
+      }
+      if (__ballot(h) && lane == src) hit = true;
+    }
+  };
+  whole(l0, p0, e0, y0);
+  whole(l1, p1, e1, y1);
+  return hit;
+}
+
 // Position of target x in row [p, pe) (present by construction).
-__device__ __forceinline__ int32_t row_find(const int32_t* idx, int32_t p, int32_t pe, int32_t x) {
-  while (p < pe - 1 && (idx[p] & kTarget) != x) ++p;
+template <class T>
+__device__ __forceinline__ int32_t row_find(const typename T::Word* idx, int32_t p, int32_t pe, int32_t x) {
+  while (p < pe - 1 && ((int32_t)idx[p] & T::mask) != x) ++p;
   return p;
 }
 
@@ -176,6 +264,14 @@ template <bool LDS>
 __device__ __forceinline__ void sw_barrier() {
   if constexpr (!LDS) __builtin_amdgcn_s_waitcnt(0);  // global atomics and stores of this wave done
   __syncthreads();
+}
+
+// Between the phases of a round.  In LDS everything that the waves tell each
+// other is in LDS, and the next round's loads of the slot list go on across it.
+template <bool LDS>
+__device__ __forceinline__ void round_barrier() {
+  if constexpr (LDS) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  else sw_barrier<false>();
 }
 
 // Randomise the graphs list[0..count) of gs, one workgroup per graph.  LDS:
@@ -206,16 +302,18 @@ __global__ __launch_bounds__(kSwB, PER_CU * kSwB / 256) void k_switch(const Swit
     const SwitchGraph G = gs[list[q]];
     const int32_t n = G.n, m = G.m;
     if (m < 2 || n < 2) continue;  // nothing to switch (uniform over the workgroup)
+    using T = Target<LDS, MUT>;
+    using Word = typename T::Word;
     const int32_t* off;
-    int32_t* idx;
+    Word* idx;
     uint32_t* lock;
     uint32_t* claim = nullptr;  // MUT: target-row claims
     if constexpr (LDS) {
       int32_t* loff = lds;
-      int32_t* lidx = lds + (n + 1);
-      uint32_t* llock = reinterpret_cast<uint32_t*>(lidx + m);
+      uint16_t* lidx = reinterpret_cast<uint16_t*>(lds + (n + 1));
+      uint32_t* llock = reinterpret_cast<uint32_t*>(lds + (n + 1) + (m + 1) / 2);
       for (int32_t i = tid; i <= n; i += kSwB) loff[i] = G.off[i];
-      for (int32_t i = tid; i < m; i += kSwB) lidx[i] = G.idx[i];
+      for (int32_t i = tid; i < m; i += kSwB) lidx[i] = (uint16_t)G.idx[i];
       for (int32_t i = tid; i < (MUT ? 2 * n : n); i += kSwB) llock[i] = kFree;
       off = loff;
       idx = lidx;
@@ -231,8 +329,8 @@ __global__ __launch_bounds__(kSwB, PER_CU * kSwB / 256) void k_switch(const Swit
     sw_barrier<LDS>();
     const uint16_t* srow = nullptr;  // source row of each slot, when it fits (uniform per graph)
     if constexpr (LDS) {
-      const int64_t used = (int64_t)(n + 1) + m + (MUT ? 2 : 1) * (int64_t)n;
-      if (n <= 65536 && used + (m + 1) / 2 <= kSwLds / PER_CU) {
+      const int64_t used = (int64_t)(n + 1) + (m + 1) / 2 + (MUT ? 2 : 1) * (int64_t)n;
+      if (used + (m + 1) / 2 <= kSwLds / PER_CU) {
         uint16_t* s16 = reinterpret_cast<uint16_t*>(lds + used);
         for (int32_t i = tid; i < m; i += kSwB) s16[i] = (uint16_t)row_of(off, n, i);
         srow = s16;
@@ -248,9 +346,9 @@ __global__ __launch_bounds__(kSwB, PER_CU * kSwB / 256) void k_switch(const Swit
       const int32_t lane = (int32_t)(tid & 63u), wv = (int32_t)(tid >> 6);
       int32_t mine = 0;
       for (int32_t i = tid; i < m; i += kSwB) {
-        const int32_t a = slot_row(i), b = idx[i] & kTarget;
-        if (row_has(idx, off[b], off[b + 1], a)) {
-          idx[i] |= kMutualBit;
+        const int32_t a = slot_row(i), b = (int32_t)idx[i] & T::mask;
+        if (row_has<T>(idx, off[b], off[b + 1], a)) {
+          idx[i] = (Word)(idx[i] | T::mutual);
           ++mine;
         }
       }
@@ -264,7 +362,7 @@ __global__ __launch_bounds__(kSwB, PER_CU * kSwB / 256) void k_switch(const Swit
       int32_t next_m = 0, next_s = nmut;
       for (int32_t c0 = 0; c0 < m; c0 += kSwB) {
         const int32_t i = c0 + (int32_t)tid;
-        const bool live = i < m, f = live && (idx[i] & kMutualBit);
+        const bool live = i < m, f = live && (idx[i] & T::mutual);
         const uint64_t bm = __ballot(f), bl = __ballot(live);
         sw_barrier<LDS>();  // the previous chunk's counts have been read
         if (lane == 0) {
@@ -306,7 +404,7 @@ __global__ __launch_bounds__(kSwB, PER_CU * kSwB / 256) void k_switch(const Swit
     // below 2^31.
     uint32_t* lock2 = nullptr;
     if constexpr (LDS && !MUT) {
-      const int64_t used = (int64_t)(n + 1) + m + n + (m + 1) / 2;
+      const int64_t used = (int64_t)(n + 1) + 2 * (((int64_t)m + 1) / 2) + n;
       if (srow && used + n <= kSwLds / PER_CU && G.rounds < (int64_t(1) << 20)) {
         lock2 = reinterpret_cast<uint32_t*>(lds + used);
         for (int32_t i = tid; i < n; i += kSwB) {
@@ -316,12 +414,31 @@ __global__ __launch_bounds__(kSwB, PER_CU * kSwB / 256) void k_switch(const Swit
         sw_barrier<LDS>();
       }
     }
+    auto pair = [&](bool act, int32_t p0, int32_t e0, int32_t x0, int32_t p1, int32_t e1, int32_t x1) {
+      if constexpr (LDS) return pair_has16<T::mask>(idx, act, p0, e0, x0, p1, e1, x1);
+      else return pair_has(idx, act, p0, e0, x0, p1, e1, x1);
+    };
+    // The slots of the next round's proposal, called once a round.  MUT: the first uniform, the second
+    // uniform among the slots of its kind.
+    uint64_t counter = G.key + (uint64_t)(tid + 1) * kGamma;  // of round r: + r kSwB gamma
+    auto draw = [&](int32_t& i, int32_t& j) {
+      const uint64_t x = sm64_mix(counter);
+      counter += (uint64_t)kSwB * kGamma;
+      i = (int32_t)__umulhi((uint32_t)x, (uint32_t)m);
+      if constexpr (MUT) {
+        const bool km = i < nmut;
+        const int32_t lo = km ? 0 : nmut, nk = km ? nmut : m - nmut;
+        j = perm[lo + (int32_t)__umulhi((uint32_t)(x >> 32), (uint32_t)nk)];
+        i = perm[i];
+      } else {
+        j = (int32_t)__umulhi((uint32_t)(x >> 32), (uint32_t)m);
+      }
+    };
     if (lock2) {
+      int32_t i, j, ni = 0, nj = 0;
+      draw(i, j);
+      int32_t a = slot_row(i), c = slot_row(j);
       for (int64_t r = 0; r < G.rounds; ++r) {
-        const uint64_t x = sm64_mix(G.key + (uint64_t)(r * kSwB + tid + 1) * kGamma);
-        const int32_t i = (int32_t)(((x & 0xFFFFFFFFull) * (uint64_t)m) >> 32);
-        const int32_t j = (int32_t)(((x >> 32) * (uint64_t)m) >> 32);
-        const int32_t a = slot_row(i), c = slot_row(j);
         const bool cand = a != c;
         uint32_t* L = (r & 1) ? lock2 : lock;
         const uint32_t v = ((uint32_t)(r + 1) << 11) | (2047u - tid);
@@ -329,47 +446,48 @@ __global__ __launch_bounds__(kSwB, PER_CU * kSwB / 256) void k_switch(const Swit
           atomicMax(&L[a], v);
           atomicMax(&L[c], v);
         }
-        sw_barrier<LDS>();
+        draw(ni, nj);  // (the next round's rows are read beside this one's barrier)
+        const int32_t na = slot_row(ni), nc = slot_row(nj);
+        round_barrier<LDS>();
         bool run = cand && L[a] == v && L[c] == v;
-        if (!__ballot(run)) continue;  // uniform over the wave
-        const int32_t b = idx[i], d = idx[j];
-        run = run && a != d && c != b && b != d;
-        if (run & !pair_has(idx, run, off[a], off[a + 1], d, off[c], off[c + 1], b)) {
-          idx[i] = d;
-          idx[j] = b;
+        if (__ballot(run)) {  // uniform over the wave
+          const int32_t b = idx[i], d = idx[j];
+          run = run && a != d && c != b && b != d;
+          if (run & !pair(run, off[a], off[a + 1], d, off[c], off[c + 1], b)) {
+            idx[i] = (Word)d;
+            idx[j] = (Word)b;
+          }
         }
+        i = ni;
+        j = nj;
+        a = na;
+        c = nc;
       }
       sw_barrier<LDS>();  // the last round's switches before the write-back
     } else {
-      for (int64_t r = 0; r < G.rounds; ++r) {
-        const uint64_t x = sm64_mix(G.key + (uint64_t)(r * kSwB + tid + 1) * kGamma);
-        int32_t i = (int32_t)(((x & 0xFFFFFFFFull) * (uint64_t)m) >> 32);
-        int32_t j = (int32_t)(((x >> 32) * (uint64_t)m) >> 32);
-        if constexpr (MUT) {  // first slot uniform, second uniform among the slots of its kind
-          const bool km = i < nmut;
-          const int32_t lo = km ? 0 : nmut, nk = km ? nmut : m - nmut;
-          j = perm[lo + (int32_t)(((x >> 32) * (uint64_t)nk) >> 32)];
-          i = perm[i];
-        }
+      int32_t i, j, ni = 0, nj = 0;
+      draw(i, j);
+      for (int64_t r = 0; r < G.rounds; ++r, i = ni, j = nj) {
         const int32_t a = slot_row(i), c = slot_row(j);
         const bool cand = a != c;  // two arcs of one row: the switch changes nothing
         if (cand) {
           lock_min<LDS>(&lock[a], tid);
           lock_min<LDS>(&lock[c], tid);
         }
-        sw_barrier<LDS>();
+        draw(ni, nj);
+        round_barrier<LDS>();
         if constexpr (!MUT) {
           bool run = cand && lock_get<LDS>(&lock[a]) == tid && lock_get<LDS>(&lock[c]) == tid;
           if (__ballot(run)) {
             // rows a and c are this proposal's alone until the next barrier
             const int32_t b = idx[i], d = idx[j];
             run = run && a != d && c != b && b != d;
-            if (run & !pair_has(idx, run, off[a], off[a + 1], d, off[c], off[c + 1], b)) {
-              idx[i] = d;
-              idx[j] = b;
+            if (run & !pair(run, off[a], off[a + 1], d, off[c], off[c + 1], b)) {
+              idx[i] = (Word)d;
+              idx[j] = (Word)b;
             }
           }
-          sw_barrier<LDS>();
+          round_barrier<LDS>();
           if (cand) {
             lock_set<LDS>(&lock[a], kFree);
             lock_set<LDS>(&lock[c], kFree);
@@ -383,14 +501,14 @@ __global__ __launch_bounds__(kSwB, PER_CU * kSwB / 256) void k_switch(const Swit
             lock_set<LDS>(&lock[c], tid | kHeld);
             wi = idx[i];
             wj = idx[j];
-            held = (wi & kMutualBit) == (wj & kMutualBit);
+            held = (wi & T::mutual) == (wj & T::mutual);
           }
-          const int32_t b = wi & kTarget, d = wj & kTarget;
+          const int32_t b = wi & T::mask, d = wj & T::mask;
           if (held) {
             lock_min<LDS>(&claim[b], tid);
             lock_min<LDS>(&claim[d], tid);
           }
-          sw_barrier<LDS>();
+          round_barrier<LDS>();
           auto held_by_other = [&](int32_t row) {
             return row != a && row != c && (lock_get<LDS>(&lock[row]) & kHeldMask) == kHeld;
           };
@@ -398,23 +516,23 @@ __global__ __launch_bounds__(kSwB, PER_CU * kSwB / 256) void k_switch(const Swit
           bool run = held && lock_get<LDS>(&claim[b]) == tid && lock_get<LDS>(&claim[d]) == tid && !held_by_other(b) &&
                      !held_by_other(d) && a != d && c != b && b != d;
           if (__ballot(run)) {
-            run = run & !pair_has(idx, run, off[a], off[a + 1], d, off[c], off[c + 1], b);
+            run = run & !pair(run, off[a], off[a + 1], d, off[c], off[c + 1], b);
             // rows b and d may be empty: then they hold nothing
             const int32_t nb = off[b + 1] - off[b], nd = off[d + 1] - off[d];
             const int32_t pb = nb ? off[b] : off[a], eb = nb ? off[b + 1] : off[a + 1];
             const int32_t pd = nd ? off[d] : off[c], ed = nd ? off[d + 1] : off[c + 1];
-            run = run & !pair_has(idx, run, pb, eb, nb ? c : -1, pd, ed, nd ? a : -1);
+            run = run & !pair(run, pb, eb, nb ? c : -1, pd, ed, nd ? a : -1);
             if (run) {
-              const int32_t kind = wi & kMutualBit;
-              idx[i] = d | kind;
-              idx[j] = b | kind;
+              const int32_t kind = wi & T::mutual;
+              idx[i] = (Word)(d | kind);
+              idx[j] = (Word)(b | kind);
               if (kind) {  // the reverse arcs: b->a becomes b->c, d->c becomes d->a
-                idx[row_find(idx, off[b], off[b + 1], a)] = c | kind;
-                idx[row_find(idx, off[d], off[d + 1], c)] = a | kind;
+                idx[row_find<T>(idx, off[b], off[b + 1], a)] = (Word)(c | kind);
+                idx[row_find<T>(idx, off[d], off[d + 1], c)] = (Word)(a | kind);
               }
             }
           }
-          sw_barrier<LDS>();
+          round_barrier<LDS>();
           if (cand) {
             lock_set<LDS>(&lock[a], kFree);
             lock_set<LDS>(&lock[c], kFree);
@@ -424,13 +542,13 @@ __global__ __launch_bounds__(kSwB, PER_CU * kSwB / 256) void k_switch(const Swit
             lock_set<LDS>(&claim[d], kFree);
           }
         }
-        sw_barrier<LDS>();
+        round_barrier<LDS>();
       }
     }
     if constexpr (LDS) {
-      for (int32_t i = tid; i < m; i += kSwB) G.idx[i] = idx[i] & kTarget;
+      for (int32_t i = tid; i < m; i += kSwB) G.idx[i] = (int32_t)idx[i] & T::mask;
     } else if constexpr (MUT) {
-      for (int32_t i = tid; i < m; i += kSwB) idx[i] &= kTarget;
+      for (int32_t i = tid; i < m; i += kSwB) idx[i] &= T::mask;
     }
     sw_barrier<LDS>();
   }
@@ -518,20 +636,41 @@ __device__ __forceinline__ double to_double(U128 a) { return (double)a.hi * 1844
 //   z = (N h_real - S1) / N / sqrt(var_num / (N (N - 1))).
 // NaN where N < 2, var = 0, or a count of the class reaches 2^40 (its sums
 // would then need more than 128 bits for N up to 2^16 graphs).
-__global__ void k_zscores(const uint64_t* __restrict__ hists, int32_t C, int32_t count, double* __restrict__ z,
-                          const int32_t* st) {
+// Sixteen classes a workgroup, 64 threads per class that sum every 64th graph
+// (one thread per class: 333 us for 1,000 graphs and 199 classes).
+constexpr int kZClasses = 16, kZSlices = 64;
+__global__ __launch_bounds__(kZClasses * kZSlices) void k_zscores(const uint64_t* __restrict__ hists, int32_t C,
+                                                                  int32_t count, double* __restrict__ z,
+                                                                  const int32_t* st) {
+  __shared__ uint64_t part[4][kZSlices][kZClasses];
+  __shared__ int32_t large[kZClasses];
   if (st[kStatus] != 0) return;
-  const int32_t c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= C) return;
+  const int32_t lc = threadIdx.x % kZClasses, slice = threadIdx.x / kZClasses, c = blockIdx.x * kZClasses + lc;
+  if (threadIdx.x < kZClasses) large[threadIdx.x] = 0;
+  __syncthreads();
+  U128 s1, s2;
+  if (c < C) {
+    bool small = true;
+    for (int32_t g = 1 + slice; g <= count; g += kZSlices) {
+      const uint64_t h = hists[(int64_t)g * C + c];
+      small = small && h < (1ull << 40);
+      s1 = add(s1, U128{h, 0});
+      s2 = add(s2, mul64(h, h));
+    }
+    if (!small) large[lc] = 1;
+  }
+  part[0][slice][lc] = s1.lo;
+  part[1][slice][lc] = s1.hi;
+  part[2][slice][lc] = s2.lo;
+  part[3][slice][lc] = s2.hi;
+  __syncthreads();
+  if (c >= C || slice) return;
   const uint64_t real = hists[c];
   const uint64_t N = (uint64_t)count;
-  bool exact = N >= 2 && N <= 65536 && real < (1ull << 40);
-  U128 s1, s2;
-  for (int32_t g = 1; g <= count; ++g) {
-    const uint64_t h = hists[(int64_t)g * C + c];
-    exact = exact && h < (1ull << 40);
-    s1 = add(s1, U128{h, 0});
-    s2 = add(s2, mul64(h, h));
+  const bool exact = N >= 2 && N <= 65536 && real < (1ull << 40) && !large[lc];
+  for (int i = 1; i < kZSlices; ++i) {
+    s1 = add(s1, U128{part[0][i][lc], part[1][i][lc]});
+    s2 = add(s2, U128{part[2][i][lc], part[3][i][lc]});
   }
   double out = __builtin_nan("");
   if (exact) {
@@ -559,13 +698,18 @@ int32_t enqueue_switch(Pipeline& p, const SwitchGraph* host_graphs, int32_t coun
   // CU), graphs that need all of it (one per CU), graphs switched in global
   // memory; each list largest graph first, so that the graphs taken last by
   // the persistent workgroups are the short ones
-  auto words = [&](const SwitchGraph& G) { return (int64_t)(G.n + 1) + G.m + (mutual ? 2 : 1) * (int64_t)G.n; };
+  auto words = [&](const SwitchGraph& G) {
+    return (int64_t)(G.n + 1) + ((int64_t)G.m + 1) / 2 + (mutual ? 2 : 1) * (int64_t)G.n;
+  };
   std::vector<int32_t> half_list, full_list, glob_list;
   int64_t max_glob_n = 0;
   for (int32_t g = 0; g < count; ++g) {
     const SwitchGraph& G = host_graphs[g];
-    const int64_t w = words(G);
-    if (w <= kSwLds / kSwPerCu) {
+    const int64_t w = words(G), rows = ((int64_t)G.m + 1) / 2;
+    // With a CU for every graph all run at once, each as long as its own rounds
+    // take, and two on a CU only slow each other down; else half the LDS where
+    // the rows of the slots fit there too.
+    if (count > p.num_cus && w + rows <= kSwLds / kSwPerCu) {
       half_list.push_back(g);
     } else if (w <= kSwLds) {
       full_list.push_back(g);
@@ -593,7 +737,9 @@ int32_t enqueue_switch(Pipeline& p, const SwitchGraph* host_graphs, int32_t coun
   int64_t max_n = 0;
   for (int32_t g = 0; g < count; ++g) max_n = std::max<int64_t>(max_n, host_graphs[g].n);
   if (count > 0) {
-    const dim3 cg((unsigned)std::min<int64_t>(64, (max_n + 256) / 256), (unsigned)std::min(count, 4096));
+    // about 2,048 workgroups: starting them was most of the check (1,000 graphs of n = 2,000: 8,000, 95 us a pass)
+    const dim3 cg((unsigned)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(64, 2048 / count), (max_n + 256) / 256)),
+                  (unsigned)std::min(count, 4096));
     for (int32_t pass = 0; pass < 2; ++pass)
       hipLaunchKernelGGL(k_check_graphs, cg, dim3(256), 0, s, dg, count, pass, p.status);
   }
@@ -660,7 +806,8 @@ void enqueue_replicate(const int32_t* src, int64_t m, int32_t copies, int32_t* d
 }
 
 void enqueue_zscores(const uint64_t* hists, int32_t C, int32_t count, double* z, const int32_t* st, hipStream_t s) {
-  hipLaunchKernelGGL(k_zscores, dim3(blocks(C, 256)), dim3(256), 0, s, hists, C, count, z, st);
+  hipLaunchKernelGGL(k_zscores, dim3((unsigned)((C + kZClasses - 1) / kZClasses)), dim3(kZClasses * kZSlices), 0, s, hists,
+                     C, count, z, st);
 }
 
 }  // namespace motif
