@@ -391,8 +391,8 @@ int32_t run_census_multi_enqueue(Pipeline& p, const BuildInput& in, int32_t nk, 
 
 // Room for the k = 5 census by subgraph copies of one graph (0: not for graphs
 // of this size).
-size_t copies5_need(const BuildInput& in) {
-  return !in.gid && copies5_fits(in.n, in.m) ? build_bytes(in.n, in.m, 1, false) + copies5_bytes(in.n, in.m) : 0;
+size_t copies5_need(const BuildInput& in, bool lean = false) {
+  return !in.gid && copies5_fits(in.n, in.m) ? build_bytes(in.n, in.m, 1, false) + copies5_bytes(in.n, in.m, lean) : 0;
 }
 
 // The sizes ks (5 among them) of one graph by subgraph copies, with a host wait
@@ -405,7 +405,8 @@ int32_t run_copies5(Pipeline& p, const BuildInput& in, int32_t nk, const int32_t
                     hipStream_t s) {
   for (int32_t i = 0; i < nk; ++i)
     if (ks[i] >= 4 && p.tune.k[ks[i]].heavy != 1) return kNotTaken;
-  const size_t need = copies5_need(in);
+  const bool lean = copies5_need(in) > p.arena.cap;
+  const size_t need = copies5_need(in, lean);
   if (!need || need > p.arena.cap) return kNotTaken;
   try {
     p.arena.reset();
@@ -419,6 +420,7 @@ int32_t run_copies5(Pipeline& p, const BuildInput& in, int32_t nk, const int32_t
     uint64_t* a4 = p.arena.take<uint64_t>((size_t)199 * kRep4);
     for (int32_t i = 0; i < nk; ++i) profile_mark(ks[i], 1, true, s);
     Copies5Run run;
+    run.lean = lean;
     enqueue_copies5_start(p, g, a3, a4, &run, s);
     const int32_t rc = read_status(p, s);
     if (rc) return rc;

@@ -45,9 +45,7 @@ namespace motif {
 namespace {
 
 constexpr int kC5 = 9364;
-constexpr int kRep5 = 32;                // copies of the totals (see totals() in counts.hip)
 constexpr int kLocalCopies = 256;        // copies written by k_apex5, at most
-constexpr size_t kSliceBytes = size_t(96) << 20;  // wedge tables of k_c5_fill
 // Lists of vertices by their wedge table in k_pairs5.
 enum PairList : int { kPair9 = 0, kPair10 = 1, kPair11 = 2, kPair12 = 3, kPair13 = 4, kPairBlock = 5, kPairLists = 6 };
 constexpr int kPairQueue = 16, kPairCursor = 24;  // queue words of the pair lists, and of the pulls
@@ -72,11 +70,14 @@ struct Links {
   }
 };
 
+// Totals that the workgroups share, a few copies of them (a power of two; see
+// totals() in counts.hip).
 struct Totals5 {
   const uint16_t* lut;
   uint64_t* acc;
+  int copies;
   __device__ __forceinline__ void add(uint32_t code, u64 w) const {
-    if (w) atomicAdd(reinterpret_cast<u64*>(acc) + (int64_t)((int)blockIdx.x & (kRep5 - 1)) * kC5 + lut[code], w);
+    if (w) atomicAdd(reinterpret_cast<u64*>(acc) + (int64_t)((int)blockIdx.x & (copies - 1)) * kC5 + lut[code], w);
   }
   // N of them, the table's entries loaded together
   template <int N>
@@ -84,7 +85,7 @@ struct Totals5 {
     uint32_t c[N];
 #pragma unroll
     for (int i = 0; i < N; ++i) c[i] = lut[code[i]];
-    u64* a = reinterpret_cast<u64*>(acc) + (int64_t)((int)blockIdx.x & (kRep5 - 1)) * kC5;
+    u64* a = reinterpret_cast<u64*>(acc) + (int64_t)((int)blockIdx.x & (copies - 1)) * kC5;
 #pragma unroll
     for (int i = 0; i < N; ++i)
       if (w[i]) atomicAdd(a + c[i], w[i]);
@@ -1626,11 +1627,22 @@ __global__ void k_write5(const uint64_t* __restrict__ in, uint64_t* __restrict__
 size_t al(size_t b) { return (b + 255) & ~size_t(255); }
 
 size_t slice_words(int64_t n) { return 6 * (size_t)n + 1; }
+// Wedge tables of k_c5_fill at a time: 2 KB of them per vertex, 96 MB at most.
 int c5_slices(int64_t n) {
-  return (int)std::max<size_t>(1, std::min<size_t>((size_t)n, std::min<size_t>(1024, kSliceBytes / (4 * slice_words(n)))));
+  const size_t room = std::min<size_t>(size_t(96) << 20, size_t(2048) * (size_t)n);
+  return (int)std::max<size_t>(1, std::min<size_t>((size_t)n, room / (4 * slice_words(n))));
 }
+// Workgroups of k_apex5, each with its copy of the totals.
+// (lean: an eighth of them, for a workspace that was sized for the per-core scan.)
+int apex_groups(int64_t m, bool lean) {
+  const int64_t per = lean ? 128 : 16;
+  return (int)std::max<int64_t>(4, std::min<int64_t>(kLocalCopies, (2 * m + per - 1) / per));
+}
+int shared_copies(int64_t m) { return m < 4096 ? 4 : 16; }
 
-int64_t link_room(int64_t m) { return 16 * m + (int64_t(1) << 20); }
+// Room for links: 6 per triangle.  Small dense graphs have the most per arc (n =
+// 100, m = 2,000: 36; the power-law ones of 10^4 arcs and more 1 to 8).
+int64_t link_room(int64_t m) { return std::max(16 * m, std::min(48 * m, int64_t(1) << 20)) + 4096; }
 
 }  // namespace
 
@@ -1643,10 +1655,10 @@ bool copies5_fits(int64_t n, int64_t m) {
   return n > 0 && n <= 65536 && m <= (int64_t(1) << 20) && 3 * m <= n * (n - 1);
 }
 
-size_t copies5_bytes(int64_t n, int64_t m) {
+size_t copies5_bytes(int64_t n, int64_t m, bool lean) {
   const size_t gs = (size_t)(2 * m + 1);
   return count_bytes(n, m, n, false, true) + 2 * al(64 * 4) + al(sizeof(uint64_t) * 13 * kRep3) +
-         al(sizeof(uint64_t) * 199 * kRep4) + al(sizeof(uint64_t) * kC5 * (kRep5 + kLocalCopies)) + 4 * al(sizeof(uint64_t) * kC5) +
+         al(sizeof(uint64_t) * 199 * kRep4) + al(sizeof(uint64_t) * kC5 * (size_t)(shared_copies(m) + apex_groups(m, lean))) + 4 * al(sizeof(uint64_t) * kC5) +
          3 * al(4 * gs) + al(8 * (size_t)(m + 1)) + al(24 * (size_t)(m + 1)) + scan1_bytes((int64_t)gs) +
          3 * al(4 * (size_t)link_room(m)) + al(72 * (size_t)n) + al(16 * (size_t)n) + al(108 * (size_t)n) +
          kPairLists * al(4 * (size_t)n) + al(4 * slice_words(n) * (size_t)c5_slices(n)) + 8192;
@@ -1688,7 +1700,7 @@ void enqueue_copies5_start(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_
   R->a3 = a3;
   R->a4 = a4;
   R->queue = A.take<int32_t>(64);
-  R->acc = A.take<uint64_t>((size_t)kC5 * (kRep5 + kLocalCopies));
+  R->acc = A.take<uint64_t>((size_t)kC5 * (size_t)(shared_copies(m) + apex_groups(m, R->lean)));
   R->emap = A.take<uint32_t>((size_t)g.gs_cap);
   R->cnt = A.take<int32_t>((size_t)g.gs_cap);
   R->off = A.take<int32_t>((size_t)g.gs_cap);
@@ -1699,7 +1711,7 @@ void enqueue_copies5_start(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_
   z.add(R->queue, 64 * sizeof(int32_t));
   z.add(a3, sizeof(uint64_t) * 13 * kRep3);
   z.add(a4, sizeof(uint64_t) * 199 * kRep4);
-  z.add(R->acc, sizeof(uint64_t) * kC5 * kRep5);
+  z.add(R->acc, sizeof(uint64_t) * kC5 * (size_t)shared_copies(m));
   z.add(R->tri, sizeof(uint32_t) * 27 * (size_t)n);
   enqueue_zero_batch(z, s);
   enqueue_counts(p, g, a3, a4, R->queue, s, &R->counts);
@@ -1732,7 +1744,8 @@ void enqueue_copies5_finish(Pipeline& p, const DevGraph& g, const Copies5Run& R,
   uint32_t* slice = A.take<uint32_t>((size_t)slices * slice_words(n));
   uint64_t* P[2] = {A.take<uint64_t>(kC5), A.take<uint64_t>(kC5)};
   uint64_t* I = A.take<uint64_t>(kC5);
-  const Totals5 K{T.lut[5], R.acc};
+  const int shared = shared_copies(m);
+  const Totals5 K{T.lut[5], R.acc, shared};
   const Links L{R.emap, R.cnt, R.off, idx, mate, src, R.counts.T};
   auto grid = [&](int64_t items, int per, int wgs) {
     return dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>((int64_t)cus * wgs, (items + per - 1) / per)));
@@ -1776,13 +1789,13 @@ void enqueue_copies5_finish(Pipeline& p, const DevGraph& g, const Copies5Run& R,
   else pairs(k_pairs5<128, 10, 128>, 10, 1, 128, 4, ch.on(2));
   if (few) pairs(k_pairs5<256, 9, 256>, 9, 1, 256, 4, ch.on(1));
   else pairs(k_pairs5<64, 9, 256>, 9, 4, 256, 2, ch.on(1));
-  const dim3 ag((unsigned)std::max<int64_t>(1, std::min<int64_t>(kLocalCopies, (2 * m + 15) / 16)));
-  hipLaunchKernelGGL(k_apex5, ag, dim3(kApexThreads), 0, s, g, T.lut[5], R.acc + (size_t)kRep5 * kC5, L, S, p.status);
+  const dim3 ag((unsigned)apex_groups(m, R.lean));
+  hipLaunchKernelGGL(k_apex5, ag, dim3(kApexThreads), 0, s, g, T.lut[5], R.acc + (size_t)shared * kC5, L, S, p.status);
   hipLaunchKernelGGL(k_wheel5, grid(2 * m, 1, 2), dim3(256), 0, s, g, K, L, p.status);
   hipLaunchKernelGGL(k_butterfly5, grid(n, 4, 4), dim3(256), 0, s, g, K, R.tri, p.status);
   ch.join();
   const dim3 cg((kC5 + 255) / 256);
-  hipLaunchKernelGGL(k_sum5, dim3((kC5 + 31) / 32), dim3(256), 0, s, R.acc, kRep5 + (int)ag.x, R.a4, R.a3, T.five, P[0], I, p.status);
+  hipLaunchKernelGGL(k_sum5, dim3((kC5 + 31) / 32), dim3(256), 0, s, R.acc, shared + (int)ag.x, R.a4, R.a3, T.five, P[0], I, p.status);
   for (int j = 1; j <= 6; ++j)
     hipLaunchKernelGGL(k_step5, dim3((kC5 + 31) / 32), dim3(256), 0, s, T.five, j, P[(j + 1) & 1], P[j & 1], I, p.status);
   hipLaunchKernelGGL(k_write5, cg, dim3(256), 0, s, I, out, p.status);

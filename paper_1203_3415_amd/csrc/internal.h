@@ -257,13 +257,14 @@ void enqueue_solve(int k, const uint64_t* acc, uint64_t* tmp, uint64_t* out, int
 // here) and counts what the rest takes room for; once the status words are
 // read back, copies5_go says whether it fits, and finish enqueues the rest.
 struct Copies5Run {
+  bool lean = false;  // in: the workspace has copies5_bytes(.., true) only
   uint64_t *a3 = nullptr, *a4 = nullptr, *acc = nullptr;
   int32_t *queue = nullptr, *cnt = nullptr, *off = nullptr, *epos = nullptr;
   uint32_t *emap = nullptr, *hi = nullptr, *tri = nullptr;
   CountsOut counts;
 };
 bool copies5_fits(int64_t n, int64_t m);
-size_t copies5_bytes(int64_t n, int64_t m);
+size_t copies5_bytes(int64_t n, int64_t m, bool lean);
 void enqueue_copies5_start(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_t* a4, Copies5Run* R, hipStream_t s);
 bool copies5_go(const Pipeline& p, int64_t m);
 void enqueue_copies5_finish(Pipeline& p, const DevGraph& g, const Copies5Run& R, uint64_t* out, hipStream_t s);
