@@ -53,9 +53,8 @@ __device__ __forceinline__ int32_t row_of(const int32_t* off, int32_t n, int64_t
   return lo;
 }
 
-// Arcs are taken kArcsPerThread consecutive ones per thread: one binary
-// search for the row of the first, then a forward walk over the offsets.
-constexpr int kArcsPerThread = 8;
+constexpr int kArcB = 1024;         // threads of the counting and scatter kernels
+constexpr int kArcsPerThread = 2;
 constexpr int kPlaceArcs = 2;  // elements per thread of the sorted-input placement
 
 __device__ __forceinline__ bool rank_less(int32_t dv, int32_t v, int32_t dw, int32_t w) {
@@ -119,7 +118,7 @@ __global__ void k_check_offsets(const int32_t* off, int32_t n, int64_t m, int32_
 // consecutive arcs, counts them per target in an LDS hash (kAggSlots keys, at
 // most half full), and touches each target's global counter once.  Hubs with
 // thousands of in-arcs then see one atomic per block instead of one per arc.
-constexpr int kArcsPerBlock = kB * kArcsPerThread;
+constexpr int kArcsPerBlock = kArcB * kArcsPerThread;
 constexpr int kAggSlots = 2 * kArcsPerBlock;
 constexpr uint32_t kAggEmpty = 0xFFFFFFFFu;
 
@@ -132,35 +131,75 @@ __device__ __forceinline__ int32_t agg_insert(uint32_t* keys, uint32_t d) {
   }
 }
 
-__global__ __launch_bounds__(kB) void k_count_in(const int32_t* off, const int32_t* idx, int32_t n, int64_t m,
+// Rows of the block's arcs [b0, b1), into row[0 .. b1 - b0): the rows that start
+// in the block mark their first arc (of several at one arc, all but one empty,
+// the last), and a running maximum carries them on.  A search per thread and a
+// walk from there were one chain of loads for its eight arcs (m = 520: 9 and 19
+// us for the two kernels below; m = 100,003: 18 and 30).
+__device__ __forceinline__ void block_rows(const int32_t* off, int32_t n, int64_t b0, int64_t b1, int32_t* row,
+                                           int32_t* wmax) {
+  const int len = (int)(b1 - b0), t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  const int32_t u0 = row_of(off, n, b0), u1 = row_of(off, n, b1 - 1);  // (every thread alike)
+  for (int i = t; i < kArcsPerBlock; i += kArcB) row[i] = u0;
+  __syncthreads();
+  for (int32_t v = u0 + 1 + t; v <= u1; v += kArcB) {
+    const int64_t o = off[v] - b0;
+    if (o >= 0 && o < len) atomicMax(&row[o], v);  // bounded even if the offsets were not valid
+  }
+  __syncthreads();
+  int32_t r[kArcsPerThread], m = u0;
+#pragma unroll
+  for (int k = 0; k < kArcsPerThread; ++k) {
+    m = max(m, row[t * kArcsPerThread + k]);
+    r[k] = m;
+  }
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int32_t y = __shfl_up(m, o);
+    if (lane >= o) m = max(m, y);
+  }
+  if (lane == 63) wmax[wv] = m;
+  int32_t before = __shfl_up(m, 1);
+  if (lane == 0) before = u0;
+  __syncthreads();
+  for (int w = 0; w < wv; ++w) before = max(before, wmax[w]);
+#pragma unroll
+  for (int k = 0; k < kArcsPerThread; ++k) row[t * kArcsPerThread + k] = max(before, r[k]);
+  __syncthreads();
+}
+
+__global__ __launch_bounds__(kArcB) void k_count_in(const int32_t* off, const int32_t* idx, int32_t n, int64_t m,
                                                  int32_t* in_cnt, int32_t* st, const int32_t* skip) {
   __shared__ uint32_t akey[kAggSlots];
-  __shared__ int32_t acnt[kAggSlots];
+  __shared__ int32_t acnt[kAggSlots], row[kArcsPerBlock], wmax[kArcB / 64];
   if (st[kStatus] != 0) return;
   if (skip && *skip == 0) {
     // every row was in order: the in-CSR lookups of the placement stand
     if (blockIdx.x == 0 && threadIdx.x == 0 && st[kInMismatch]) set_status(st, MOTIF_ETRANSPOSE);
     return;
   }
-  for (int i = threadIdx.x; i < kAggSlots; i += kB) {
+  for (int i = threadIdx.x; i < kAggSlots; i += kArcB) {
     akey[i] = kAggEmpty;
     acnt[i] = 0;
   }
-  __syncthreads();
   for (int64_t b0 = (int64_t)blockIdx.x * kArcsPerBlock; b0 < m; b0 += (int64_t)gridDim.x * kArcsPerBlock) {
-    const int64_t i0 = b0 + (int64_t)threadIdx.x * kArcsPerThread, i1 = min(m, i0 + kArcsPerThread);
-    if (i0 < m) {
-      int32_t u = row_of(off, n, i0);
-      for (int64_t i = i0; i < i1; ++i) {
-        while (u < n - 1 && off[u + 1] <= i) ++u;  // bounded even if the offsets were not valid
-        const int32_t d = idx[i];
-        if (d < 0 || d >= n) { set_status(st, MOTIF_EINDEX); continue; }
-        if (d == u) { set_status(st, MOTIF_ESELFLOOP); continue; }
-        atomicAdd(&acnt[agg_insert(akey, (uint32_t)d)], 1);
-      }
+    const int64_t b1 = min(m, b0 + kArcsPerBlock);
+    int32_t d[kArcsPerThread];
+#pragma unroll
+    for (int t = 0; t < kArcsPerThread; ++t) {
+      const int64_t i = b0 + t * kArcB + threadIdx.x;
+      d[t] = i < b1 ? idx[i] : 0;
+    }
+    block_rows(off, n, b0, b1, row, wmax);
+#pragma unroll
+    for (int t = 0; t < kArcsPerThread; ++t) {
+      if (b0 + t * kArcB + threadIdx.x >= b1) continue;
+      if (d[t] < 0 || d[t] >= n) { set_status(st, MOTIF_EINDEX); continue; }
+      if (d[t] == row[t * kArcB + threadIdx.x]) { set_status(st, MOTIF_ESELFLOOP); continue; }
+      atomicAdd(&acnt[agg_insert(akey, (uint32_t)d[t])], 1);
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < kAggSlots; i += kB) {
+    for (int i = threadIdx.x; i < kAggSlots; i += kArcB) {
       if (akey[i] != kAggEmpty) {
         atomicAdd(&in_cnt[akey[i]], acnt[i]);
         akey[i] = kAggEmpty;
@@ -185,59 +224,49 @@ struct HalfCount {
 // local rank among the block's arcs to its target, one global atomic per
 // (block, target) reserves the range, and the arc's slot is base + rank (the
 // order inside a row is arbitrary; rows are sorted next).
-__global__ __launch_bounds__(kB) void k_scatter(const int32_t* off, const int32_t* idx, int32_t n, int64_t m,
+__global__ __launch_bounds__(kArcB) void k_scatter(const int32_t* off, const int32_t* idx, int32_t n, int64_t m,
                                                 const int32_t* hoff, int32_t* fill, uint32_t* keys, int32_t* hrow,
                                                 const int32_t* st, const int32_t* skip) {
   __shared__ uint32_t akey[kAggSlots];
-  __shared__ int32_t acnt[kAggSlots];
+  __shared__ int32_t acnt[kAggSlots], row[kArcsPerBlock], wmax[kArcB / 64];
   if (st[kStatus] != 0 || (skip && *skip == 0)) return;
-  for (int i = threadIdx.x; i < kAggSlots; i += kB) {
+  for (int i = threadIdx.x; i < kAggSlots; i += kArcB) {
     akey[i] = kAggEmpty;
     acnt[i] = 0;
   }
-  __syncthreads();
   for (int64_t b0 = (int64_t)blockIdx.x * kArcsPerBlock; b0 < m; b0 += (int64_t)gridDim.x * kArcsPerBlock) {
-    const int64_t i0 = b0 + (int64_t)threadIdx.x * kArcsPerThread, i1 = min(m, i0 + kArcsPerThread);
-    int32_t slot[kArcsPerThread], rank[kArcsPerThread];
-    int32_t u0 = 0;
-    if (i0 < m) {
-      int32_t u = u0 = row_of(off, n, i0);
+    const int64_t b1 = min(m, b0 + kArcsPerBlock);
+    int32_t d[kArcsPerThread], u[kArcsPerThread], slot[kArcsPerThread], rank[kArcsPerThread];
 #pragma unroll
-      for (int t = 0; t < kArcsPerThread; ++t) {
-        const int64_t i = i0 + t;
-        slot[t] = -1;
-        if (i < i1) {
-          while (u < n - 1 && off[u + 1] <= i) ++u;
-          const int32_t d = idx[i];
-          const int32_t a = hoff[u] + (int32_t)(i - off[u]);
-          keys[a] = ((uint32_t)d << 1);
-          hrow[a] = u;
-          slot[t] = agg_insert(akey, (uint32_t)d);
-          rank[t] = atomicAdd(&acnt[slot[t]], 1);
-        }
-      }
+    for (int t = 0; t < kArcsPerThread; ++t) {
+      const int64_t i = b0 + t * kArcB + threadIdx.x;
+      d[t] = i < b1 ? idx[i] : -1;
+    }
+    block_rows(off, n, b0, b1, row, wmax);
+#pragma unroll
+    for (int t = 0; t < kArcsPerThread; ++t) {
+      if (d[t] < 0) continue;
+      u[t] = row[t * kArcB + threadIdx.x];
+      const int32_t a = hoff[u[t]] + (int32_t)(b0 + t * kArcB + threadIdx.x - off[u[t]]);
+      keys[a] = ((uint32_t)d[t] << 1);
+      hrow[a] = u[t];
+      slot[t] = agg_insert(akey, (uint32_t)d[t]);
+      rank[t] = atomicAdd(&acnt[slot[t]], 1);
     }
     __syncthreads();
     // reserve each target's range once; acnt becomes the range base
-    for (int i = threadIdx.x; i < kAggSlots; i += kB)
+    for (int i = threadIdx.x; i < kAggSlots; i += kArcB)
       if (akey[i] != kAggEmpty) acnt[i] = atomicAdd(&fill[akey[i]], acnt[i]);
     __syncthreads();
-    if (i0 < m) {
-      int32_t u = u0;
 #pragma unroll
-      for (int t = 0; t < kArcsPerThread; ++t) {
-        const int64_t i = i0 + t;
-        if (i < i1) {
-          while (u < n - 1 && off[u + 1] <= i) ++u;
-          const int32_t d = (int32_t)akey[slot[t]];
-          const int32_t b = hoff[d] + (off[d + 1] - off[d]) + acnt[slot[t]] + rank[t];
-          keys[b] = ((uint32_t)u << 1) | 1u;
-          hrow[b] = d;
-        }
-      }
+    for (int t = 0; t < kArcsPerThread; ++t) {
+      if (d[t] < 0) continue;
+      const int32_t b = hoff[d[t]] + (off[d[t] + 1] - off[d[t]]) + acnt[slot[t]] + rank[t];
+      keys[b] = ((uint32_t)u[t] << 1) | 1u;
+      hrow[b] = d[t];
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < kAggSlots; i += kB) {
+    for (int i = threadIdx.x; i < kAggSlots; i += kArcB) {
       akey[i] = kAggEmpty;
       acnt[i] = 0;
     }
@@ -915,7 +944,7 @@ DevGraph enqueue_build(Pipeline& p, const BuildInput& in, hipStream_t s, hipEven
   // takes them.
   const bool from_in = !in.gid && in.in_off && m > 0;
   const int32_t* skip = from_in ? st + kUnsorted : nullptr;
-  const unsigned arc_grid = grid_for((m + kArcsPerThread - 1) / kArcsPerThread);  // caps at 65536 blocks
+  const unsigned arc_grid = grid_for((m + kArcsPerThread - 1) / kArcsPerThread, kArcB);  // caps at 65536 blocks
   if (!in.gid) hipLaunchKernelGGL(k_check_offsets, dim3(grid_for(n + 1)), dim3(kB), 0, s, in.out_off, n, m, st);
   if (from_in) {
     hipLaunchKernelGGL(k_check_offsets, dim3(grid_for(n + 1)), dim3(kB), 0, s, in.in_off, n, m, st);
@@ -923,10 +952,10 @@ DevGraph enqueue_build(Pipeline& p, const BuildInput& in, hipStream_t s, hipEven
                        in.out_off, in.out_idx, in.in_off, in.in_idx, n, m, hoff, keys, hrow, st);
   }
   if (m > 0)
-    hipLaunchKernelGGL(k_count_in, dim3(arc_grid), dim3(kB), 0, s, in.out_off, in.out_idx, n, m, in_cnt, st, skip);
+    hipLaunchKernelGGL(k_count_in, dim3(arc_grid), dim3(kArcB), 0, s, in.out_off, in.out_idx, n, m, in_cnt, st, skip);
   enqueue_scan1(sc_half, hoff, HalfCount{in.out_off, in_cnt, n}, st, s, skip);
   if (m > 0)
-    hipLaunchKernelGGL(k_scatter, dim3(arc_grid), dim3(kB), 0, s, in.out_off, in.out_idx, n, m, hoff, fill, keys,
+    hipLaunchKernelGGL(k_scatter, dim3(arc_grid), dim3(kArcB), 0, s, in.out_off, in.out_idx, n, m, hoff, fill, keys,
                        hrow, st, skip);
   // With the bitmap in LDS a row costs about the same whatever its length
   // (a few words per thread to clear, count and compact), which beats the
