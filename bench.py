@@ -192,6 +192,30 @@ def k3_kernel_bytes(st) -> float:
     return float(8.0 * deg.sum() + 4.0 * dplus.sum() + ((deg - dplus) * (8.0 + 4.0 * dplus)).sum())
 
 
+def _lower_visits(st) -> float:
+    """Entries of G* rows read for the wedges of every vertex's lower-ranked
+    neighbours: the sum of d(v) over edges v -> u, v of lower rank."""
+    _, side = _core_side(st)
+    return float(st["deg"].astype(np.float64)[side].sum())
+
+
+def copies4_bytes(st) -> float:
+    """Algorithmic bytes of one k = 4 census by subgraph copies: the triangles
+    as for k = 3, nine counters per edge written and read (72 B), the row
+    entries of the wedges (4 B each) and the typed degrees of each edge's ends
+    (32 B)."""
+    return k3_kernel_bytes(st) + 104.0 * st["mstar"] + 4.0 * _lower_visits(st)
+
+
+def copies5_bytes(st) -> float:
+    """Algorithmic bytes of one k = 5 census by subgraph copies: the k = 4
+    pass, the rows of all neighbours of every vertex (4 B per wedge end), the
+    links of each triangle (six of 12 B, written and read) and the wedges of
+    lower neighbours once more."""
+    deg = st["deg"].astype(np.float64)
+    return copies4_bytes(st) + 4.0 * float((deg ** 2).sum()) + 48.0 * float(st["tri"].sum()) + 4.0 * _lower_visits(st)
+
+
 # ------------------------------------------------------------ main bench ---
 
 def bench_census(args):
@@ -245,8 +269,8 @@ def bench_census(args):
     dominant = max(ks)
     kms = float(np.mean(kern_ms[dominant]))
     kname = kernel_name(dominant, pm.get_tuning(dominant)["heavy"] if dominant > 3 else 0)
-    kbytes = {"k3_kernel": k3_kernel_bytes, "k4_kernel": k4_kernel_bytes, "kr_kernel<4>": kr4_kernel_bytes,
-              "kr_kernel<5>": kr5_kernel_bytes}.get(kname, lambda _: None)(st)
+    kbytes = {"copies<3>": k3_kernel_bytes, "k4_kernel": k4_kernel_bytes, "copies<4>": copies4_bytes,
+              "copies<5>": copies5_bytes}.get(kname, lambda _: None)(st)
     roofline = None
     if kbytes is not None:
         achieved = kbytes / (kms * 1e-3) / 1e9
@@ -254,7 +278,7 @@ def bench_census(args):
                     "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": stored_traffic(kname, args.workload),
                     "kernel": kname, "kernel_ms": round(kms, 3), "algorithmic_bytes": kbytes}
         # The per-anchor byte model (what the paper's method, one anchor at a
-        # time, must read).  The core-reuse kernel reads far fewer
+        # time, must read).  The copies read far fewer
         # bytes than that, from a working set that sits in the caches, so the
         # model's rate can exceed the HBM peak: it is reported beside the
         # kernel's own floor, and the counters below say what binds.
@@ -298,13 +322,14 @@ def bench_census(args):
 
 
 def kernel_name(k: int, scheme: int) -> str:
-    if k == 3:
-        return "k3_kernel"
-    return f"kr_kernel<{k}>" if scheme == 1 else f"k{k}_kernel"
+    """The kernels between the census events: the subgraph copies (for k = 5
+    where the graph fits), or the per-anchor kernel."""
+    return f"copies<{k}>" if k == 3 or scheme == 1 else f"k{k}_kernel"
 
 
 TRAFFIC_DIR = os.path.join(ROOT, "profiles")
-CENSUS_SRC = os.path.join(ROOT, "paper_1203_3415_amd", "csrc", "census.hip")
+CENSUS_SRC = [os.path.join(ROOT, "paper_1203_3415_amd", "csrc", f)
+              for f in ("census.hip", "counts.h", "counts.hip", "copies5.hip")]
 
 
 def _src_digest() -> str:
@@ -312,8 +337,10 @@ def _src_digest() -> str:
     that the stored traffic stays valid across comment edits only."""
     import hashlib
     import re
-    with open(CENSUS_SRC) as f:
-        code = [re.sub(r"//.*$", "", line).rstrip() for line in f]
+    code = []
+    for path in CENSUS_SRC:
+        with open(path) as f:
+            code += [re.sub(r"//.*$", "", line).rstrip() for line in f]
     return hashlib.sha256("\n".join(x for x in code if x).encode()).hexdigest()
 
 
@@ -858,7 +885,7 @@ def main():
                     help="after the timed steps, copy this many MiB on the device (reference for HBM counters)")
     ap.add_argument("--traffic-from", nargs=2, metavar=("FETCH_CSV", "WRITE_CSV"),
                     help="no GPU: turn two rocprofv3 --pmc csv files into the stored traffic record")
-    ap.add_argument("--kernel", default="kr_kernel<4>", help="kernel of --traffic-from / --counters-from")
+    ap.add_argument("--kernel", default="copies<4>", help="kernel of --traffic-from / --counters-from")
     ap.add_argument("--counters-from", nargs="+", metavar="CSV",
                     help="no GPU: turn rocprofv3 --pmc csv files into the stored counter record")
     args = ap.parse_args()

@@ -58,17 +58,16 @@ int32_t g_init_err = 0;
 TuningSet g_tuning = {{
     {256, 4, 16, 1}, {256, 4, 16, 1}, {256, 4, 16, 1},
     {256, 4, 16, 1},    // k = 3: tile*16 vertices per tile (at most 1024)
-    // k = 4: core reuse (tile = cost tiles per workgroup); solo / light limits
-    // from a sweep on the n = 1e5, m = 1e6 workload
+    // k = 4: copies, which have no parameters; block, grid and tile are the
+    // per-anchor scheme's
     {1024, 1, 4, 1, 48, 224, 512},
     // k = 5: core reuse, light-partner limit from a sweep on the n = 2e4 workload
     {1024, 1, 128, 1, 64, 192, 384},
 }};
 // Batches of small graphs (one fused census of many graphs of at most
-// kBatchSmallN vertices): for k = 4 the autotuner's choice on 1,001 graphs of
-// n = 2,000 (null-model ensembles: many small cores, so smaller workgroups,
-// two per CU, finer tiles; fused census 25.0 -> 23.0 ms).  Used while k's
-// tuning has not been set explicitly.
+// kBatchSmallN vertices): the per-anchor scheme's parameters for k = 4 (many
+// small anchors, so smaller workgroups, two per CU, finer tiles).  Used while
+// k's tuning has not been set explicitly.
 const Tuning kBatchTuning4 = {512, 2, 16, 1, 32, 256, 512};
 constexpr int64_t kBatchSmallN = 16384;
 bool g_batch_default[6] = {false, false, false, false, true, false};
@@ -350,9 +349,7 @@ std::vector<TuneAxis> tune_axes(int k) {
     return {{&Tuning::heavy, {1, 0}, false},
             {&Tuning::block, {512, 1024}, false},
             {&Tuning::grid_per_cu, {1, 2}, false},
-            {&Tuning::tile, {2, 3, 4, 8, 16}, false},
-            {&Tuning::solo_deg, {16, 32, 48, 64}, true},
-            {&Tuning::light_deg, {96, 128, 160, 192, 224, 256}, true}};
+            {&Tuning::tile, {2, 3, 4, 8, 16}, false}};
   return {{&Tuning::block, {512, 1024}, false},
           {&Tuning::tile, {16, 32, 64, 128, 256}, false},
           {&Tuning::light5, {128, 256, 384, 512, 640, 767}, true}};

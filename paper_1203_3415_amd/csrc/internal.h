@@ -113,10 +113,10 @@ struct Tuning {
   int block = 256;
   int grid_per_cu = 4;
   int tile = 16;
-  int heavy = 1;  // census scheme for k = 4, 5: 1 = core reuse, 0 = per-anchor scan
-  // Work-placement limits of the core-reuse kernels (degrees in G*):
-  int solo_deg = 64;    // k = 4: cores of at most this degree run whole anchors on one wave (<= 64)
-  int light_deg = 192;  // k = 4: sides of at most this degree run on one wave (<= 256)
+  int heavy = 1;  // census scheme for k = 4, 5: 1 = subgraph copies or core reuse, 0 = per-anchor scan
+  int solo_deg = 64;    // k = 4: kept for callers and tuning files, no effect (1..64)
+  int light_deg = 192;  // the same (1..256)
+  // Work-placement limit of the core-reuse kernel (degree in G*):
   int light5 = 512;     // k = 5: lighter sides of at most this degree take the factored path (<= 767)
 };
 // The tuning of every k, copied once per call so that a concurrent
@@ -149,7 +149,7 @@ struct Pipeline {
   hipEvent_t ev_chain = nullptr, ev_end[kChains] = {};
   bool may_fork = true;  // false: nothing may be allocated, those stay unmade
   TuningSet tune;  // the tuning this call was sized with (set before any enqueue)
-  // Per-workgroup W rows of the k = 4, 5 core-reuse kernels for the census
+  // Per-workgroup W rows of the k = 5 core-reuse kernel for the census
   // on this pipeline's own stream: zeroed once when allocated, and left zero
   // by every census (each core's tear-down clears the rows it touched), so
   // no call has to clear them.  Null where the W rows come from the arena.
@@ -216,7 +216,7 @@ void enqueue_check_in(const BuildInput& in, const DevGraph& g, const InCheck& c,
 // p.wpool (only for work on the pipeline's own stream, one census at a time).
 struct ZeroBatch;
 
-// Big-core tables of a k = 4, 5 core-reuse census (nbig = 0: none).
+// Big-core tables of a k = 5 core-reuse census (nbig = 0: none).
 struct BigTables {
   int nbig = 0;
   int32_t* big_id = nullptr;    // [n + 1]
@@ -307,7 +307,7 @@ int32_t enqueue_anchors6(const DevGraph& g, int4* out, unsigned long long* ctr, 
 // `grid` zeroed slices of label_words words).
 void enqueue_census6(const DevGraph& g, const int4* anchors, int64_t nanchors, const Tables6& T, uint64_t* acc,
                      uint32_t* labels, int64_t label_words, int grid, int32_t* status, hipStream_t s);
-// Bytes of the per-workgroup W rows of a k = 4, 5 core-reuse census (0 otherwise).
+// Bytes of the per-workgroup W rows of a k = 5 core-reuse census (0 otherwise).
 size_t w_slice_bytes(int k, int64_t maxn, const Tuning& t, int num_cus);
 
 // Pack `count` device graphs into one union CSR inside the arena.
