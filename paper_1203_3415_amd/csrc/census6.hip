@@ -545,6 +545,165 @@ __global__ __launch_bounds__(kB6) void k6_census(DevGraph G, const int4* __restr
   flush();
 }
 
+// The same with one wave per anchor, for graphs of at most kWaveN6 vertices:
+// labels, counts and members in the wave's own LDS, no barrier between the
+// waves, and one table of class sums for the sixteen of them.  An anchor is a
+// chain of short dependent steps (rows, labels, N+ rows, the class of each code
+// from the 4 GiB table), about 6 us whoever takes it; as a workgroup's it kept
+// 1,024 anchors in flight on the chip and its labels in global memory (n = 300,
+// m = 700: 958 us), as a wave's 4,096.  Larger graphs keep the kernel above:
+// sixteen label slices beside the table are all that LDS holds.
+constexpr int kWaveN6 = 1024, kWaves6b = 16;
+constexpr int kWaveAggBits6 = 13, kWaveAgg6 = 1 << kWaveAggBits6;
+constexpr int kWaveMem6 = 512;  // members listed (more: every vertex is looked at)
+__global__ __launch_bounds__(64 * kWaves6b) void k6_census_wave(DevGraph G, const int4* __restrict__ anchors,
+                                                                int64_t nanchors, const uint32_t* __restrict__ lut,
+                                                                uint64_t* __restrict__ acc, int32_t* st) {
+  __shared__ uint64_t aval[kWaveAgg6];
+  __shared__ uint32_t akey[kWaveAgg6], s_lab[kWaves6b][kWaveN6 / 4];
+  __shared__ int32_t s_cnt[kWaves6b][256], s_n[kWaves6b][2];
+  __shared__ uint16_t s_mem[kWaves6b][kWaveMem6];
+  __shared__ uint8_t s_zl[kWaves6b][256];
+  if (st[kStatus] != 0) return;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  uint32_t* lab = s_lab[wv];
+  int32_t *cnt = s_cnt[wv], *nn = s_n[wv];  // nn: members, label sets
+  uint16_t* mem = s_mem[wv];
+  uint8_t* zl = s_zl[wv];
+  for (int i = threadIdx.x; i < kWaveAgg6; i += 64 * kWaves6b) {
+    akey[i] = kEmpty6;
+    aval[i] = 0;
+  }
+  for (int i = lane; i < kWaveN6 / 4; i += 64) lab[i] = 0;
+  for (int i = lane; i < 256; i += 64) cnt[i] = 0;
+  if (lane < 2) nn[lane] = 0;
+  __syncthreads();
+  auto label = [&](int32_t v) { return (lab[v >> 2] >> (8 * (v & 3))) & 0xFFu; };
+  auto add = [&](uint32_t c, uint64_t w) {
+    if (c == kNoClass) {  // a connected 6-set always has a class
+      atomicMin(&st[kStatus], MOTIF_EINTERNAL);
+      return;
+    }
+    uint32_t h = (c * 2654435761u) >> (32 - kWaveAggBits6);
+    for (int i = 0; i < kAggProbe6; ++i) {
+      const uint32_t old = atomicCAS(&akey[h], kEmpty6, c);
+      if (old == kEmpty6 || old == c) {
+        atomicAdd(&aval[h], w);
+        return;
+      }
+      h = (h + 1) & (kWaveAgg6 - 1);
+    }
+    atomicAdd(&acc[c], w);  // a crowded stretch of the table
+  };
+  for (int64_t q = (int64_t)blockIdx.x * kWaves6b + wv; q < nanchors; q += (int64_t)gridDim.x * kWaves6b) {
+    const int4 A = anchors[q];
+    const int32_t t[4] = {A.x, A.y, A.z, A.w};
+    auto in_t = [&](int32_t v) { return v == t[0] || v == t[1] || v == t[2] || v == t[3]; };
+    int32_t r0[4], d0[4];
+    uint32_t f0[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      r0[i] = G.gs_off[t[i]];
+      d0[i] = G.gs_off[t[i] + 1] - r0[i];
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) f0[i] = lane < d0[i] ? G.gs_idx[r0[i] + lane] : 0u;
+    // the anchor's own arcs (slots 0..3)
+    uint32_t base = 0;
+    if (lane < 6) {
+      const int i = lane < 3 ? 0 : lane < 5 ? 1 : 2;
+      const int j = lane < 3 ? lane + 1 : lane < 5 ? lane - 1 : 3;
+      const int32_t ti = i == 0 ? t[0] : i == 1 ? t[1] : t[2], tj = j == 1 ? t[1] : j == 2 ? t[2] : t[3];
+      const uint32_t ty = gs_type(G, ti, tj);
+      base = ((ty & 1u) ? 1u << bit6(i, j) : 0u) | ((ty & 2u) ? 1u << bit6(j, i) : 0u);
+    }
+#pragma unroll
+    for (int o = 1; o < 8; o <<= 1) base |= __shfl_xor(base, o);
+    base = (uint32_t)__shfl((int)base, 0);
+    // labels of the neighbours of T (first writer of a vertex lists it)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      for (int32_t e = lane; e < d0[i]; e += 64) {
+        const uint32_t f = e < 64 ? f0[i] : G.gs_idx[r0[i] + e];
+        const int32_t w = (int32_t)(f & kIdMask);
+        if (in_t(w)) continue;
+        const int sh = 8 * (w & 3);
+        const uint32_t old = atomicOr(&lab[w >> 2], ((f >> kTypeShift) << (2 * i)) << sh);
+        if (((old >> sh) & 0xFFu) == 0u) {
+          const int32_t s = atomicAdd(&nn[0], 1);
+          if (s < kWaveMem6) mem[s] = (uint16_t)w;
+        }
+      }
+    wave_sync6();
+    const int32_t M = nn[0];
+    auto members = [&](auto&& f) {
+      if (M <= kWaveMem6) {
+        for (int32_t i = lane; i < M; i += 64) f((int32_t)mem[i]);
+      } else {
+        for (int32_t v = lane; v < G.n; v += 64)
+          if (label(v)) f(v);
+      }
+    };
+    members([&](int32_t x) {
+      const uint32_t Lx = label(x);
+      if (atomicAdd(&cnt[Lx], 1) == 0) zl[atomicAdd(&nn[1], 1)] = (uint8_t)Lx;
+      // edges between two labelled vertices, each from the N+ row of its lower-rank end
+      const int32_t pa = G.np_off[x], pe = G.np_off[x + 1];
+      for (int32_t p0 = pa; p0 < pe; p0 += 4) {
+        uint32_t f[4], c0[4], c1[4];
+        bool in[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) f[u] = G.np_idx[min(p0 + u, pe - 1)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int32_t y = (int32_t)(f[u] & kIdMask);
+          const uint32_t Ly = p0 + u < pe && !in_t(y) ? label(y) : 0u;
+          in[u] = Ly != 0u;
+          c0[u] = base | slot6<4>(Lx) | slot6<5>(Ly);
+          const uint32_t r = f[u] >> kTypeShift;  // type of y relative to x
+          c1[u] = c0[u] | ((r & 1u) ? 1u << bit6(4, 5) : 0u) | ((r & 2u) ? 1u << bit6(5, 4) : 0u);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (in[u]) {
+            c1[u] = lut[c1[u]];
+            c0[u] = lut[c0[u]];
+          }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (in[u]) {
+            add(c1[u], 1ull);
+            add(c0[u], ~0ull);
+          }
+      }
+    });
+    wave_sync6();
+    // closed form over the pairs of non-empty label sets
+    const int32_t Z = nn[1];
+    for (int32_t u = lane; u < Z * Z; u += 64) {
+      const int32_t i = u / Z, j = u % Z;
+      if (i > j) continue;
+      const uint32_t La = zl[i], Lb = zl[j];
+      const uint64_t na = (uint64_t)cnt[La], nb = (uint64_t)cnt[Lb];
+      const uint64_t w = i == j ? na * (na - 1) / 2 : na * nb;
+      if (w) add(lut[base | slot6<4>(La) | slot6<5>(Lb)], w);
+    }
+    wave_sync6();
+    members([&](int32_t x) { cnt[label(x)] = 0; });
+    wave_sync6();
+    if (M <= kWaveMem6) {
+      for (int32_t i = lane; i < M; i += 64) lab[mem[i] >> 2] = 0;
+    } else {
+      for (int i = lane; i < kWaveN6 / 4; i += 64) lab[i] = 0;
+    }
+    if (lane < 2) nn[lane] = 0;
+    wave_sync6();
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < kWaveAgg6; i += 64 * kWaves6b)
+    if (akey[i] != kEmpty6) atomicAdd(&acc[akey[i]], aval[i]);
+}
+
 // The bit map of every relabelling of 6 vertices (lexicographic order,
 // identity first): pos[p * 30 + b] = where bit b goes.
 std::vector<uint8_t> perm_bit_maps6() {
@@ -657,6 +816,11 @@ int32_t enqueue_anchors6(const DevGraph& g, int4* out, unsigned long long* ctr, 
 
 void enqueue_census6(const DevGraph& g, const int4* anchors, int64_t nanchors, const Tables6& T, uint64_t* acc,
                      uint32_t* labels, int64_t label_words, int grid, int32_t* status, hipStream_t s) {
+  if (g.n <= kWaveN6) {  // one workgroup per CU (a quarter of the grid, which has four)
+    hipLaunchKernelGGL(k6_census_wave, dim3((unsigned)std::max(1, (grid + 3) / 4)), dim3(64 * kWaves6b), 0, s, g, anchors,
+                       nanchors, T.lut, acc, status);
+    return;
+  }
   hipLaunchKernelGGL(k6_census, dim3((unsigned)std::max(1, grid)), dim3(kB6), 0, s, g, anchors, nanchors, T.lut, acc,
                      labels, label_words, status);
 }

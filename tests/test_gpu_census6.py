@@ -112,3 +112,18 @@ def test_too_big_anchor_edge(pm):
     with pytest.raises(pm.MotifError) as e:
         pm.census6(off, idx, g.n)
     assert e.value.name == "ETOOBIG"
+
+
+@pytest.mark.parametrize("n,m", [(300, 700), (1024, 1400)])
+def test_padding_changes_nothing(pm, codes, n, m):
+    """Vertices without arcs beyond 1,024 move the census from the wave per anchor to the workgroup per anchor."""
+    g = gg.chung_lu(n, m, 2.6, 2.6, 0.2, seed=n)
+    print(f"[case] k=6 padded n={n} m={m}", flush=True)
+    assert _by_code(pm, codes, g) == _by_code(pm, codes, gg.from_arcs(1025, g.arcs()))
+
+
+def test_more_members_than_a_wave_lists(pm, codes):
+    """A hub of 514 leaves, two of them joined: anchors with more than 512 labelled vertices."""
+    arcs = [(0, i) for i in range(1, 515)] + [(1, 2)]
+    print("[case] k=6 hub", flush=True)
+    assert _by_code(pm, codes, gg.from_arcs(515, arcs)) == _by_code(pm, codes, gg.from_arcs(1025, arcs))
