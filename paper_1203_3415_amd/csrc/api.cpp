@@ -386,6 +386,13 @@ int32_t drain_after_error(Pipeline& p, hipStream_t s) {
 int32_t run_census_multi_enqueue(Pipeline& p, const BuildInput& in, int32_t nk, const int32_t* ks,
                                  uint64_t* const* hists, hipStream_t s);
 
+// Marks a call that waits on the host before it returns.
+struct ForkNow {
+  Pipeline& p;
+  explicit ForkNow(Pipeline& pl) : p(pl) { p.fork_now = p.may_fork; }
+  ~ForkNow() { p.fork_now = false; }
+};
+
 // Room for the k = 5 census by subgraph copies of one graph (0: not for graphs
 // of this size).
 size_t copies5_need(const BuildInput& in, bool lean = false) {
@@ -446,6 +453,7 @@ int32_t run_copies5(Pipeline& p, const BuildInput& in, int32_t nk, const int32_t
 // between: every census kernel returns at once when the build has set the
 // status word, and the exact division writes nothing then.
 int32_t run_census_on(Pipeline& p, const BuildInput& in, int32_t k, uint64_t* hist, hipStream_t s) {
+  const ForkNow forks(p);
   if (k == 5) {
     const int32_t rc = run_copies5(p, in, 1, &k, &hist, false, s);
     if (rc != kNotTaken) return rc;
@@ -470,6 +478,7 @@ int32_t run_census_on(Pipeline& p, const BuildInput& in, int32_t k, uint64_t* hi
 // largest census leaves idle at its end.  Each census has its own workspace.
 int32_t run_census_multi_on(Pipeline& p, const BuildInput& in, int32_t nk, const int32_t* ks, uint64_t* const* hists,
                             hipStream_t s) {
+  const ForkNow forks(p);
   for (int32_t i = 0; i < nk; ++i)
     if (ks[i] == 5) {
       const int32_t rc = run_copies5(p, in, nk, ks, hists, false, s);

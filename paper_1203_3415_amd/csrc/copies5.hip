@@ -1664,33 +1664,6 @@ size_t copies5_bytes(int64_t n, int64_t m, bool lean) {
          kPairLists * al(4 * (size_t)n) + al(4 * slice_words(n) * (size_t)c5_slices(n)) + 8192;
 }
 
-// Side streams of a pipeline (default priority), made on first use; when one
-// cannot be had its work stays on the caller's stream.
-struct Chains {
-  Pipeline& p;
-  hipStream_t s;
-  bool used[Pipeline::kChains] = {};
-  Chains(Pipeline& pl, hipStream_t st) : p(pl), s(st) {
-    if (!p.may_fork) return;
-    if (!p.ev_chain && hipEventCreateWithFlags(&p.ev_chain, hipEventDisableTiming) != hipSuccess) p.ev_chain = nullptr;
-    for (int i = 0; i < Pipeline::kChains; ++i) {
-      if (!p.chain[i] && hipStreamCreateWithFlags(&p.chain[i], hipStreamNonBlocking) != hipSuccess) p.chain[i] = nullptr;
-      if (!p.ev_end[i] && hipEventCreateWithFlags(&p.ev_end[i], hipEventDisableTiming) != hipSuccess) p.ev_end[i] = nullptr;
-    }
-  }
-  hipStream_t on(int i) const { return used[i] ? p.chain[i] : s; }
-  void fork(int i) {  // chain i goes on from here
-    if (p.may_fork && p.chain[i] && p.ev_end[i] && p.ev_chain && hipEventRecord(p.ev_chain, s) == hipSuccess &&
-        hipStreamWaitEvent(p.chain[i], p.ev_chain, 0) == hipSuccess)
-      used[i] = true;
-  }
-  void join() {
-    for (int i = 0; i < Pipeline::kChains; ++i)
-      if (used[i] && (hipEventRecord(p.ev_end[i], p.chain[i]) != hipSuccess ||
-                      hipStreamWaitEvent(s, p.ev_end[i], 0) != hipSuccess))
-        (void)hipStreamSynchronize(p.chain[i]);
-  }
-};
 constexpr int64_t kFewUnits = 512;
 
 void enqueue_copies5_start(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_t* a4, Copies5Run* R, hipStream_t s) {

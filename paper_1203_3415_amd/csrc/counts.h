@@ -55,4 +55,29 @@ __device__ __forceinline__ bool one_wedge(W c, W ones) {
 constexpr u64 kOnes7 = 1ull | 1ull << 7 | 1ull << 14 | 1ull << 21 | 1ull << 28 | 1ull << 35 | 1ull << 42 | 1ull << 49 |
                        1ull << 56;
 
+// Side streams of a pipeline (default priority), made on first use; when one
+// cannot be had its work stays on the caller's stream.
+struct Chains {
+  Pipeline& p;
+  hipStream_t s;
+  bool used[Pipeline::kChains] = {};
+  Chains(Pipeline& pl, hipStream_t st) : p(pl), s(st) {}
+  hipStream_t on(int i) const { return used[i] ? p.chain[i] : s; }
+  void fork(int i) {  // chain i goes on from here
+    if (!p.may_fork) return;
+    if (!p.ev_chain && hipEventCreateWithFlags(&p.ev_chain, hipEventDisableTiming) != hipSuccess) p.ev_chain = nullptr;
+    if (!p.chain[i] && hipStreamCreateWithFlags(&p.chain[i], hipStreamNonBlocking) != hipSuccess) p.chain[i] = nullptr;
+    if (!p.ev_end[i] && hipEventCreateWithFlags(&p.ev_end[i], hipEventDisableTiming) != hipSuccess) p.ev_end[i] = nullptr;
+    if (p.chain[i] && p.ev_end[i] && p.ev_chain && hipEventRecord(p.ev_chain, s) == hipSuccess &&
+        hipStreamWaitEvent(p.chain[i], p.ev_chain, 0) == hipSuccess)
+      used[i] = true;
+  }
+  void join() {
+    for (int i = 0; i < Pipeline::kChains; ++i)
+      if (used[i] && (hipEventRecord(p.ev_end[i], p.chain[i]) != hipSuccess ||
+                      hipStreamWaitEvent(s, p.ev_end[i], 0) != hipSuccess))
+        (void)hipStreamSynchronize(p.chain[i]);
+  }
+};
+
 }  // namespace motif

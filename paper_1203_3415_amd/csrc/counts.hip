@@ -1439,17 +1439,23 @@ void enqueue_counts(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_t* a4, 
   }
   enqueue_zero(Te, sizeof(uint32_t) * 9 * (size_t)(m + 1), s);
   hipLaunchKernelGGL((k_classify<true>), dim3(cgrid), dim3(256), 0, s, g, L, queue, p.status);
-  hipLaunchKernelGGL((k_tri<16, 16, true>), list_grid(n16, 16, 6), dim3(256), 0, s, g, T.lut[3], T.lut[4], a3, a4, Te,
+  // The triangles beside the wedges where both are long (n = 10^5, m = 10^6: 450
+  // and 1,030 us; the wedge table of a workgroup leaves half of a CU's waves and
+  // a quarter of its LDS) and the caller's streams allow it.
+  Chains ch(p, s);
+  if (p.fork_now && !g.gid && m >= kCutsM) ch.fork(0);
+  const hipStream_t ts = ch.on(0);
+  hipLaunchKernelGGL((k_tri<16, 16, true>), list_grid(n16, 16, 6), dim3(256), 0, ts, g, T.lut[3], T.lut[4], a3, a4, Te,
                      p.status, queue, L.v[kTri16]);
   if (c.D > 16)
-    hipLaunchKernelGGL((k_tri<64, 64, true>), list_grid(n64, 4, 6), dim3(256), 0, s, g, T.lut[3], T.lut[4], a3, a4, Te,
+    hipLaunchKernelGGL((k_tri<64, 64, true>), list_grid(n64, 4, 6), dim3(256), 0, ts, g, T.lut[3], T.lut[4], a3, a4, Te,
                        p.status, queue, L.v[kTri64]);
   if (n128 > 0)
-    hipLaunchKernelGGL((k_tri<64, 128, true>), list_grid(n128, 4, 3), dim3(256), 0, s, g, T.lut[3], T.lut[4], a3, a4,
+    hipLaunchKernelGGL((k_tri<64, 128, true>), list_grid(n128, 4, 3), dim3(256), 0, ts, g, T.lut[3], T.lut[4], a3, a4,
                        Te, p.status, queue, L.v[kTri128]);
   if (nbig > 0)  // a workgroup whose x need a global slice has its own
     hipLaunchKernelGGL((k_tri_big<true>), dim3(std::min<unsigned>(c.slices ? c.slices : 512, grid_of(nbig, 1, cus * 2))),
-                       dim3(512), 0, s, g, T.lut[3], T.lut[4], a3, a4, Te, p.status, queue, L.v[kTriBig], planes, c.D,
+                       dim3(512), 0, ts, g, T.lut[3], T.lut[4], a3, a4, Te, p.status, queue, L.v[kTriBig], planes, c.D,
                        c.words);
   hipLaunchKernelGGL((k_wedge<16, 7>), list_grid(n16, 16, 6), dim3(256), 0, s, g, T.lut[4], a4, p.status, queue,
                      L.v[kWedge16]);
@@ -1472,6 +1478,7 @@ void enqueue_counts(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_t* a4, 
     if (c.wide) launch_top(split ? k_wedge_top<5, true> : k_wedge_top<5, false>);
     else launch_top(split ? k_wedge_top<3, true> : k_wedge_top<3, false>);
   }
+  ch.join();
   const dim3 lgrid(grid_of(n + m, 256, cus * 4));
   if (a3)
     hipLaunchKernelGGL((k_local<true, true>), lgrid, dim3(256), 0, s, g, T.lut[3], T.lut[4], a3, a4, Te, p.status);

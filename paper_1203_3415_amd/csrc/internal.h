@@ -147,7 +147,8 @@ struct Pipeline {
   static constexpr int kChains = 3;
   hipStream_t chain[kChains] = {};
   hipEvent_t ev_chain = nullptr, ev_end[kChains] = {};
-  bool may_fork = true;  // false: nothing may be allocated, those stay unmade
+  bool may_fork = true;   // false: nothing may be allocated, those stay unmade
+  bool fork_now = false;  // this call waits on the host and is not captured: its kernels may use them
   TuningSet tune;  // the tuning this call was sized with (set before any enqueue)
   // Per-workgroup W rows of the k = 5 core-reuse kernel for the census
   // on this pipeline's own stream: zeroed once when allocated, and left zero
