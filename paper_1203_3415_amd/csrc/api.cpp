@@ -611,6 +611,7 @@ int32_t census_batch_with(const motif_graph_t* graphs, int32_t count, int32_t k,
   if (rc) return rc;
   p->tune = tune;
   ensure_wpool(p, s, w_slice_bytes(k, maxn, tune.k[k], device_cus(dev)));
+  const ForkNow forks(*p);
   try {
     p->arena.reset();
     enqueue_zero(p->status, sizeof(int32_t) * kStatusWords, s);
@@ -1023,6 +1024,7 @@ int32_t motif_census_undirected(const int32_t* out_off, const int32_t* out_idx, 
   if (rc) return rc;
   p->tune = tune;
   ensure_wpool(p, s, w_slice_bytes(k, n, tune.k[k], device_cus(dev)));
+  const ForkNow forks(*p);
   if (k == 5) {
     rc = run_copies5(*p, in, 1, &k, &hist, true, s);
     if (rc != kNotTaken) return rc;

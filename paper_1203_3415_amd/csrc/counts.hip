@@ -1443,7 +1443,7 @@ void enqueue_counts(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_t* a4, 
   // and 1,030 us; the wedge table of a workgroup leaves half of a CU's waves and
   // a quarter of its LDS) and the caller's streams allow it.
   Chains ch(p, s);
-  if (p.fork_now && !g.gid && m >= kCutsM) ch.fork(0);
+  if (p.fork_now && m >= kCutsM) ch.fork(0);
   const hipStream_t ts = ch.on(0);
   hipLaunchKernelGGL((k_tri<16, 16, true>), list_grid(n16, 16, 6), dim3(256), 0, ts, g, T.lut[3], T.lut[4], a3, a4, Te,
                      p.status, queue, L.v[kTri16]);
