@@ -235,6 +235,39 @@ __device__ __forceinline__ bool pair_has16(const uint16_t* idx, bool act, int32_
   return hit;
 }
 
+// Position of target x in row [p, pe) of 16-bit targets (present by
+// construction), for every lane with act, the rows one after another by the
+// whole wave: few lanes of a wave move reciprocated pairs, and one alone on a
+// hub's row held the round up (256 graphs of n = 500 to 5,000, m = 4n,
+// pairs kept, 100 attempts an arc: 17.8 -> 15.2 ms a call).
+template <int32_t MASK>
+__device__ __forceinline__ int32_t wave_find16(const uint16_t* idx, bool act, int32_t p_, int32_t e_, int32_t x_) {
+  const uint32_t* words = reinterpret_cast<const uint32_t*>(idx);
+  const int32_t lane = (int32_t)(threadIdx.x & 63u);
+  int32_t found = p_;
+  for (uint64_t mask = __ballot(act); mask; mask &= mask - 1ull) {
+    const int src = __builtin_ctzll(mask);
+    const int32_t p = __builtin_amdgcn_readlane(p_, src), e = __builtin_amdgcn_readlane(e_, src);
+    const int32_t x = __builtin_amdgcn_readlane(x_, src);
+    for (int32_t q0 = p >> 1; q0 <= (e - 1) >> 1; q0 += 64) {
+      const int32_t q = q0 + lane;
+      int32_t at = -1;
+      if (q <= (e - 1) >> 1) {
+        const uint32_t w = words[q];
+        if (2 * q >= p && (int32_t)(w & 0xFFFFu & MASK) == x) at = 2 * q;
+        else if (2 * q + 1 < e && (int32_t)((w >> 16) & MASK) == x) at = 2 * q + 1;
+      }
+      const uint64_t hit = __ballot(at >= 0);
+      if (hit) {
+        const int32_t pos = __builtin_amdgcn_readlane(at, __builtin_ctzll(hit));
+        if (lane == src) found = pos;
+        break;
+      }
+    }
+  }
+  return found;
+}
+
 // Position of target x in row [p, pe) (present by construction).
 template <class T>
 __device__ __forceinline__ int32_t row_find(const typename T::Word* idx, int32_t p, int32_t pe, int32_t x) {
@@ -522,13 +555,23 @@ __global__ __launch_bounds__(kSwB, PER_CU * kSwB / 256) void k_switch(const Swit
             const int32_t pb = nb ? off[b] : off[a], eb = nb ? off[b + 1] : off[a + 1];
             const int32_t pd = nd ? off[d] : off[c], ed = nd ? off[d + 1] : off[c + 1];
             run = run & !pair(run, pb, eb, nb ? c : -1, pd, ed, nd ? a : -1);
+            // the reverse arcs of a reciprocated pair: b->a becomes b->c, d->c becomes d->a
+            const int32_t kind = wi & T::mutual;
+            const bool both = run && kind;
+            int32_t fb = 0, fd = 0;
+            if constexpr (LDS) {
+              fb = wave_find16<T::mask>(idx, both, off[b], off[b + 1], a);
+              fd = wave_find16<T::mask>(idx, both, off[d], off[d + 1], c);
+            } else if (both) {
+              fb = row_find<T>(idx, off[b], off[b + 1], a);
+              fd = row_find<T>(idx, off[d], off[d + 1], c);
+            }
             if (run) {
-              const int32_t kind = wi & T::mutual;
               idx[i] = (Word)(d | kind);
               idx[j] = (Word)(b | kind);
-              if (kind) {  // the reverse arcs: b->a becomes b->c, d->c becomes d->a
-                idx[row_find<T>(idx, off[b], off[b + 1], a)] = (Word)(c | kind);
-                idx[row_find<T>(idx, off[d], off[d + 1], c)] = (Word)(a | kind);
+              if (kind) {
+                idx[fb] = (Word)(c | kind);
+                idx[fd] = (Word)(a | kind);
               }
             }
           }
