@@ -1457,6 +1457,12 @@ void enqueue_counts(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_t* a4, 
     hipLaunchKernelGGL((k_tri_big<true>), dim3(std::min<unsigned>(c.slices ? c.slices : 512, grid_of(nbig, 1, cus * 2))),
                        dim3(512), 0, ts, g, T.lut[3], T.lut[4], a3, a4, Te, p.status, queue, L.v[kTriBig], planes, c.D,
                        c.words);
+  // (the diamonds need the triangles only)
+  const dim3 lgrid(grid_of(n + m, 256, cus * 4));
+  if (a3)
+    hipLaunchKernelGGL((k_local<true, true>), lgrid, dim3(256), 0, ts, g, T.lut[3], T.lut[4], a3, a4, Te, p.status);
+  else
+    hipLaunchKernelGGL((k_local<false, true>), lgrid, dim3(256), 0, ts, g, T.lut[3], T.lut[4], a3, a4, Te, p.status);
   hipLaunchKernelGGL((k_wedge<16, 7>), list_grid(n16, 16, 6), dim3(256), 0, s, g, T.lut[4], a4, p.status, queue,
                      L.v[kWedge16]);
   if (2 * m > kCap16)
@@ -1479,11 +1485,6 @@ void enqueue_counts(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_t* a4, 
     else launch_top(split ? k_wedge_top<3, true> : k_wedge_top<3, false>);
   }
   ch.join();
-  const dim3 lgrid(grid_of(n + m, 256, cus * 4));
-  if (a3)
-    hipLaunchKernelGGL((k_local<true, true>), lgrid, dim3(256), 0, s, g, T.lut[3], T.lut[4], a3, a4, Te, p.status);
-  else
-    hipLaunchKernelGGL((k_local<false, true>), lgrid, dim3(256), 0, s, g, T.lut[3], T.lut[4], a3, a4, Te, p.status);
 }
 
 void enqueue_solve(int k, const uint64_t* acc, uint64_t* tmp, uint64_t* out, int64_t ngraphs, int32_t* status,
