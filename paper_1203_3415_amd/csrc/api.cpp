@@ -229,13 +229,13 @@ int32_t ensure_wpool(Pipeline* p, hipStream_t s, size_t bytes) {
 
 }  // namespace
 
-// Copy the device status word to the host and wait for the stream.
+// Copy the device status words to the host and wait for the stream.
 int32_t read_status(Pipeline& p, hipStream_t s) {
   if (hipMemcpyAsync(p.host_status, p.status, sizeof(int32_t) * kStatusWords, hipMemcpyDeviceToHost, s) !=
       hipSuccess)
     return MOTIF_EDEVICE;
   if (hipStreamSynchronize(s) != hipSuccess) return MOTIF_EDEVICE;
-  return p.host_status[kStatus];
+  return std::min(p.host_status[kStatus], p.host_status[kBeside]);
 }
 
 namespace {

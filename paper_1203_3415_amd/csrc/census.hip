@@ -1517,14 +1517,14 @@ __global__ __launch_bounds__(256) void k_core_tables(DevGraph G, const int32_t* 
 // Exact division of every class total by its anchor multiplicity; a non-zero
 // remainder is a self-check failure and blocks the write.
 __global__ void k_div_check(const uint64_t* acc, const uint8_t* mult, int32_t C, int64_t total, int32_t* st) {
-  if (st[kStatus] != 0) return;
+  if (failed(st)) return;
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x)
     if (acc[i] % mult[i % C]) atomicMin(&st[kStatus], MOTIF_EINTERNAL);
 }
 
 __global__ void k_div_write(const uint64_t* acc, const uint8_t* mult, int32_t C, int64_t total, uint64_t* out,
                             const int32_t* st) {
-  if (st[kStatus] != 0) return;
+  if (failed(st)) return;
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x)
     out[i] = acc[i] / mult[i % C];
 }

@@ -5,9 +5,15 @@
 
 #include <cstdint>
 
+#include "internal.h"
+
 namespace motif {
 
 using u64 = unsigned long long;
+
+// Whether an earlier step of the call failed, an in-CSR check beside the
+// censuses included: for the last steps, which run after it on the stream.
+__device__ __forceinline__ bool failed(const int32_t* st) { return st[kStatus] != 0 || st[kBeside] != 0; }
 
 // Bit of the arc i -> j (i != j) in the adjacency codes that index the
 // device class tables.  Row-major with the diagonal left out, except for

@@ -1292,7 +1292,7 @@ __global__ __launch_bounds__(kSolve1) void k_solve_one(const uint64_t* __restric
                                                        int32_t* st) {
   constexpr int kRows = 2;  // classes per eight lanes: C <= kSolve1 / 8 * kRows
   __shared__ u64 sum[256];
-  if (st[kStatus] != 0) return;
+  if (failed(st)) return;
   if (threadIdx.x < 256) sum[threadIdx.x] = 0;
   __syncthreads();
   const int32_t c0 = threadIdx.x & 255;
@@ -1323,7 +1323,7 @@ __global__ __launch_bounds__(kSolve1) void k_solve_one(const uint64_t* __restric
 }
 __global__ __launch_bounds__(256) void k_solve(const uint64_t* __restrict__ acc, const SubInverse M,
                                                uint64_t* __restrict__ out, int32_t C, int64_t total, int32_t* st) {
-  if (st[kStatus] != 0) return;
+  if (failed(st)) return;
   const int64_t stride = (int64_t)gridDim.x * 32;
   for (int64_t i = blockIdx.x * (int64_t)32 + (threadIdx.x >> 3); i < total; i += stride) {
     const int32_t c = (int32_t)(i % C);
@@ -1337,7 +1337,7 @@ __global__ __launch_bounds__(256) void k_solve(const uint64_t* __restrict__ acc,
 
 __global__ void k_solve_write(const uint64_t* __restrict__ in, uint64_t* __restrict__ out, int64_t total,
                               const int32_t* st) {
-  if (st[kStatus] != 0) return;
+  if (failed(st)) return;
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x)
     out[i] = in[i];
 }

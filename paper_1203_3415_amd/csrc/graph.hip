@@ -41,7 +41,7 @@ constexpr int kLdsBitmapGrid = 512;    // LDS bitmap sorts in flight (two 64 KB 
 constexpr int kBigSlots = 32;     // concurrent bitmap sorts with the bitmaps in global memory
 constexpr int kCheckGrid = 256;   // workgroups of an in-CSR check run beside a census
 
-__device__ __forceinline__ void set_status(int32_t* st, int32_t code) { atomicMin(&st[kStatus], code); }
+__device__ __forceinline__ void set_status(int32_t* st, int32_t code, int slot = kStatus) { atomicMin(&st[slot], code); }
 
 __device__ __forceinline__ int32_t row_of(const int32_t* off, int32_t n, int64_t i) {
   // last v in [0, n) with off[v] <= i (off valid, off[n] > i)
@@ -104,12 +104,12 @@ unsigned grid_for(int64_t items, int block = kB) {
 
 // ------------------------------------------------------------- validation --
 
-__global__ void k_check_offsets(const int32_t* off, int32_t n, int64_t m, int32_t* st) {
+__global__ void k_check_offsets(const int32_t* off, int32_t n, int64_t m, int32_t* st, int slot) {
   for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v <= n; v += (int64_t)gridDim.x * blockDim.x) {
     int32_t a = off[v];
-    if (v == 0 && a != 0) set_status(st, MOTIF_EINVAL_SHAPE);
-    if (v == n && (int64_t)a != m) set_status(st, MOTIF_EINVAL_SHAPE);
-    if (v < n && off[v + 1] < a) set_status(st, MOTIF_EINVAL_SHAPE);
+    if (v == 0 && a != 0) set_status(st, MOTIF_EINVAL_SHAPE, slot);
+    if (v == n && (int64_t)a != m) set_status(st, MOTIF_EINVAL_SHAPE, slot);
+    if (v < n && off[v + 1] < a) set_status(st, MOTIF_EINVAL_SHAPE, slot);
   }
 }
 
@@ -597,34 +597,34 @@ __global__ void k_write_plus(const uint32_t* gs_idx, const int32_t* flag_pos, co
 // the out-CSR, listed once, and each row must have the in-degree counted from
 // the out-CSR.  `has_in` (batch) marks the graphs that supplied an in-CSR.
 __global__ void k_check_in_rows(const int32_t* in_off, const int32_t* in_cnt, int32_t n, const int32_t* gid,
-                                const int32_t* has_in, int32_t* st) {
+                                const int32_t* has_in, int32_t* st, int slot) {
   if (st[kStatus] != 0) return;
   for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
     if (gid && !has_in[gid[v]]) continue;
-    if (in_off[v + 1] - in_off[v] != in_cnt[v]) set_status(st, MOTIF_ETRANSPOSE);
+    if (in_off[v + 1] - in_off[v] != in_cnt[v]) set_status(st, MOTIF_ETRANSPOSE, slot);
   }
 }
 
 __global__ void k_check_in_arcs(const int32_t* in_off, const int32_t* in_idx, int32_t n, int64_t m,
                                 const int32_t* gs_off, const uint32_t* gs_idx, const int32_t* gid,
-                                const int32_t* has_in, uint32_t* marks, int32_t* st) {
+                                const int32_t* has_in, uint32_t* marks, int32_t* st, int slot) {
   if (st[kStatus] != 0) return;
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < m; i += (int64_t)gridDim.x * blockDim.x) {
     int32_t v = row_of(in_off, n, i);
     if (gid && !has_in[gid[v]]) continue;
     int32_t s = in_idx[i];
-    if (s < 0 || s >= n) { set_status(st, MOTIF_EINDEX); continue; }
+    if (s < 0 || s >= n) { set_status(st, MOTIF_EINDEX, slot); continue; }
     int32_t lo = gs_off[v], hi = gs_off[v + 1];
     while (lo < hi) {
       int32_t mid = (lo + hi) >> 1;
       if ((int32_t)(gs_idx[mid] & kIdMask) < s) lo = mid + 1; else hi = mid;
     }
     if (lo >= gs_off[v + 1] || (int32_t)(gs_idx[lo] & kIdMask) != s || !((gs_idx[lo] >> kTypeShift) & 2u)) {
-      set_status(st, MOTIF_ETRANSPOSE);
+      set_status(st, MOTIF_ETRANSPOSE, slot);
       continue;
     }
     uint32_t bit = 1u << (lo & 31);
-    if (atomicOr(&marks[lo >> 5], bit) & bit) set_status(st, MOTIF_ETRANSPOSE);
+    if (atomicOr(&marks[lo >> 5], bit) & bit) set_status(st, MOTIF_ETRANSPOSE, slot);
   }
 }
 
@@ -636,23 +636,23 @@ __global__ void k_check_in_arcs(const int32_t* in_off, const int32_t* in_idx, in
 // were taken from.
 __global__ void k_check_in_arcs_out(const int32_t* in_off, const int32_t* in_idx, int32_t n, int64_t m,
                                     const int32_t* gs_off, const uint32_t* gs_idx, uint32_t* marks, int32_t* st,
-                                    const int32_t* skip) {
+                                    int slot, const int32_t* skip) {
   if (st[kStatus] != 0 || (skip && *skip == 0)) return;
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < m; i += (int64_t)gridDim.x * blockDim.x) {
     const int32_t v = row_of(in_off, n, i);
     const int32_t s = in_idx[i];
-    if (s < 0 || s >= n) { set_status(st, MOTIF_EINDEX); continue; }
+    if (s < 0 || s >= n) { set_status(st, MOTIF_EINDEX, slot); continue; }
     int32_t lo = gs_off[s], hi = gs_off[s + 1];
     while (lo < hi) {
       const int32_t mid = (lo + hi) >> 1;
       if ((int32_t)(gs_idx[mid] & kIdMask) < v) lo = mid + 1; else hi = mid;
     }
     if (lo >= gs_off[s + 1] || (int32_t)(gs_idx[lo] & kIdMask) != v || !((gs_idx[lo] >> kTypeShift) & 1u)) {
-      set_status(st, MOTIF_ETRANSPOSE);
+      set_status(st, MOTIF_ETRANSPOSE, slot);
       continue;
     }
     const uint32_t bit = 1u << (lo & 31);
-    if (atomicOr(&marks[lo >> 5], bit) & bit) set_status(st, MOTIF_ETRANSPOSE);
+    if (atomicOr(&marks[lo >> 5], bit) & bit) set_status(st, MOTIF_ETRANSPOSE, slot);
   }
 }
 
@@ -945,9 +945,9 @@ DevGraph enqueue_build(Pipeline& p, const BuildInput& in, hipStream_t s, hipEven
   const bool from_in = !in.gid && in.in_off && m > 0;
   const int32_t* skip = from_in ? st + kUnsorted : nullptr;
   const unsigned arc_grid = grid_for((m + kArcsPerThread - 1) / kArcsPerThread, kArcB);  // caps at 65536 blocks
-  if (!in.gid) hipLaunchKernelGGL(k_check_offsets, dim3(grid_for(n + 1)), dim3(kB), 0, s, in.out_off, n, m, st);
+  if (!in.gid) hipLaunchKernelGGL(k_check_offsets, dim3(grid_for(n + 1)), dim3(kB), 0, s, in.out_off, n, m, st, kStatus);
   if (from_in) {
-    hipLaunchKernelGGL(k_check_offsets, dim3(grid_for(n + 1)), dim3(kB), 0, s, in.in_off, n, m, st);
+    hipLaunchKernelGGL(k_check_offsets, dim3(grid_for(n + 1)), dim3(kB), 0, s, in.in_off, n, m, st, kStatus);
     hipLaunchKernelGGL(k_place_sorted, dim3(grid_for(2 * ((m + kPlaceArcs - 1) / kPlaceArcs))), dim3(kB), 0, s,
                        in.out_off, in.out_idx, in.in_off, in.in_idx, n, m, hoff, keys, hrow, st);
   }
@@ -998,22 +998,23 @@ void enqueue_check_in(const BuildInput& in, const DevGraph& g, const InCheck& c,
   // and a full grid would hold back the census's own launches
   unsigned grid = grid_for(m);
   if (background) grid = std::min(grid, (unsigned)kCheckGrid);
+  const int slot = background ? kBeside : kStatus;
   if (!in.gid) {
     if (!c.offsets_checked)
-      hipLaunchKernelGGL(k_check_offsets, dim3(grid_for(n + 1)), dim3(kB), 0, s, in.in_off, n, m, st);
+      hipLaunchKernelGGL(k_check_offsets, dim3(grid_for(n + 1)), dim3(kB), 0, s, in.in_off, n, m, st, slot);
     enqueue_zero(c.marks, sizeof(uint32_t) * ((2 * m + 31) / 32 + 1), s);
     // after a placement from sorted rows the in-CSR is already checked
     if (m > 0)
       hipLaunchKernelGGL(k_check_in_arcs_out, dim3(grid), dim3(kB), 0, s, in.in_off, in.in_idx, n, m, g.gs_off,
-                         g.gs_idx, c.marks, st, c.offsets_checked ? st + kUnsorted : nullptr);
+                         g.gs_idx, c.marks, st, slot, c.offsets_checked ? st + kUnsorted : nullptr);
     return;
   }
   hipLaunchKernelGGL(k_check_in_rows, dim3(grid_for(n)), dim3(kB), 0, s, in.in_off, c.in_cnt, n, in.gid, in.has_in,
-                     st);
+                     st, slot);
   enqueue_zero(c.marks, sizeof(uint32_t) * ((2 * m + 31) / 32 + 1), s);
   if (m > 0)
     hipLaunchKernelGGL(k_check_in_arcs, dim3(grid), dim3(kB), 0, s, in.in_off, in.in_idx, n, m, g.gs_off, g.gs_idx,
-                       in.gid, in.has_in, c.marks, st);
+                       in.gid, in.has_in, c.marks, st, slot);
 }
 
 }  // namespace motif

@@ -30,6 +30,8 @@ enum StatusSlot : int {
   kQueue2 = 4,       // second work-queue cursor
   kUnsorted = 5,     // build from an in-CSR: 1 when a row is not strictly increasing
   kInMismatch = 6,   // build from an in-CSR: 1 when an in-arc was not found among the out-arcs
+  kBeside = 7,       // as kStatus, for an in-CSR check that runs beside the censuses: kStatus never changes while
+                     // one of their kernels starts, so the waves of a workgroup agree on it
   kStatusWords = 16,
 };
 
@@ -206,8 +208,8 @@ struct InCheck {
 DevGraph enqueue_build(Pipeline& p, const BuildInput& in, hipStream_t s, hipEvent_t graph_ready = nullptr,
                        bool* ready_ok = nullptr, InCheck* deferred = nullptr);
 // The in-CSR check of a build (nothing when no in-CSR was given); its outcome
-// lands in the status word.  background: a bounded grid, for a stream that
-// runs beside a census.
+// lands in the status word.  background: a bounded grid, and the outcome in
+// kBeside, for a stream that runs beside a census.
 void enqueue_check_in(const BuildInput& in, const DevGraph& g, const InCheck& c, int32_t* status, hipStream_t s,
                       bool background);
 
