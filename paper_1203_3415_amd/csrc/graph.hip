@@ -171,8 +171,13 @@ __device__ __forceinline__ void block_rows(const int32_t* off, int32_t n, int64_
 __global__ __launch_bounds__(kArcB) void k_count_in(const int32_t* off, const int32_t* idx, int32_t n, int64_t m,
                                                  int32_t* in_cnt, int32_t* st, const int32_t* skip) {
   __shared__ uint32_t akey[kAggSlots];
-  __shared__ int32_t acnt[kAggSlots], row[kArcsPerBlock], wmax[kArcB / 64];
-  if (st[kStatus] != 0) return;
+  __shared__ int32_t acnt[kAggSlots], row[kArcsPerBlock], wmax[kArcB / 64], stop;
+  // One decision for the workgroup: another one may set the status at this
+  // moment, and waves that went on without the rest would compare their arcs
+  // with rows that only part of the workgroup wrote.
+  if (threadIdx.x == 0) stop = st[kStatus];
+  __syncthreads();
+  if (stop != 0) return;
   if (skip && *skip == 0) {
     // every row was in order: the in-CSR lookups of the placement stand
     if (blockIdx.x == 0 && threadIdx.x == 0 && st[kInMismatch]) set_status(st, MOTIF_ETRANSPOSE);

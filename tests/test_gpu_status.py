@@ -61,3 +61,22 @@ def test_in_csr_checked_beside_the_censuses(pm, n, ks, schemes):
                     assert np.array_equal(got, w)
     finally:
         pm.set_tuning(4, **saved)
+
+
+@pytest.mark.parametrize("bad,name", [(10 ** 6, "EINDEX"), (-1, "EINDEX"), ("self", "ESELFLOOP")])
+def test_wrong_arc_is_named(pm, bad, name):
+    # one wrong arc, met while most workgroups of the check are still to start
+    g = gg.chung_lu(100000, 1000000, 2.1, 2.1, 0.2, seed=3)
+    rng = np.random.default_rng(5)
+    idx = g.out_idx.copy()
+    for v in np.flatnonzero(np.diff(g.out_off) > 200):
+        idx[g.out_off[v]:g.out_off[v + 1]] = rng.permutation(idx[g.out_off[v]:g.out_off[v + 1]])
+    for place in (0, 5000, g.m - 1):
+        wrong = idx.copy()
+        wrong[place] = int(np.searchsorted(g.out_off, place, side="right")) - 1 if bad == "self" else bad
+        off_t, idx_t = pm.to_device(g.out_off, wrong)
+        for rep in range(8):
+            print(f"[case] wrong arc {bad} at {place} round {rep}", flush=True)
+            with pytest.raises(pm.MotifError) as e:
+                pm.census(off_t, idx_t, g.n, 3)
+            assert e.value.name == name
