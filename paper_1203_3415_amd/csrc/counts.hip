@@ -180,9 +180,10 @@ __device__ __forceinline__ void for_listed(const DevGraph& G, const int32_t* lis
 // Sorts the vertices into the lists: higher neighbours for the triangles,
 // lower neighbours and visits for the wedges (k = 4).  Eight lanes per vertex;
 // one counter update per list and workgroup.
+// big: higher neighbours from which a vertex has a workgroup to itself.
 constexpr int kClassify = 2048;  // most vertices of a workgroup (places fit in 12 bits)
 template <bool K4>
-__global__ __launch_bounds__(256) void k_classify(DevGraph G, Lists L, int32_t* __restrict__ nlist,
+__global__ __launch_bounds__(256) void k_classify(DevGraph G, Lists L, int32_t* __restrict__ nlist, int32_t big,
                                                   const int32_t* st) {
   __shared__ int32_t cnt[kLists], base[kLists];
   __shared__ uint32_t where[kClassify];
@@ -196,7 +197,7 @@ __global__ __launch_bounds__(256) void k_classify(DevGraph G, Lists L, int32_t* 
   for (int64_t v = v0 + (threadIdx.x >> 3); v < v1; v += 32) {
     int lt = 15, lw = 15;
     const int32_t pa = G.np_off[v], pb = G.np_off[v + 1], d = pb - pa;
-    if (d >= 2) lt = d <= 16 ? kTri16 : d <= 64 ? kTri64 : d <= 128 ? kTri128 : kTriBig;
+    if (d >= 2) lt = d <= 16 ? kTri16 : d >= big ? kTriBig : d <= 64 ? kTri64 : kTri128;
     if (K4) {
       const int32_t ma = G.gs_off[v] - pa, dm = G.gs_off[v + 1] - pb - ma;
       if (dm > 127) {
@@ -437,6 +438,9 @@ __global__ __launch_bounds__(256) void k_tri(DevGraph G, const uint16_t* __restr
 constexpr int kBigHB = 13;
 constexpr int kBigH = 1 << kBigHB;
 constexpr int kPlaneD = 256;
+// Common bits of a word up to which they are taken one by one (n = 800 with 15 %
+// of the arcs: 1,247 us a call, 1,390 with 4; n = 400 with 75 %: 9.2 and 7.5 ms).
+constexpr int kFewBits = 8;
 
 template <bool K4>
 __global__ __launch_bounds__(512) void k_tri_big(DevGraph G, const uint16_t* __restrict__ lut3,
@@ -449,6 +453,7 @@ __global__ __launch_bounds__(512) void k_tri_big(DevGraph G, const uint16_t* __r
   __shared__ u64 s_tri[27], s_paw[K4 ? 243 : 1], s_kh[K4 ? 199 : 1], s_h3[13];
   __shared__ uint32_t key[kBigH];
   __shared__ uint16_t at[kBigH];
+  __shared__ u64 xt1[K4 ? kBigH / 128 : 1], xt2[K4 ? kBigH / 128 : 1];  // types of N+(x), a bit plane per arc
   __shared__ u64 lplane[K4 ? 2 * kPlaneD * kPlaneD / 64 : 1];
   __shared__ uint16_t lut[K4 ? 4096 : 1];
   if (st[kStatus] != 0) return;
@@ -482,6 +487,15 @@ __global__ __launch_bounds__(512) void k_tri_big(DevGraph G, const uint16_t* __r
         uint32_t h = hash_mul(y, kBigHB);
         while (atomicCAS(&key[h], kNone, y) != kNone) h = (h + 1) & (kBigH - 1);
         at[h] = (uint16_t)i;
+      }
+    if (K4 && hashed)
+      for (int32_t i = threadIdx.x; i < W * 64; i += NT) {
+        const uint32_t t = i < d ? G.np_idx[xa + i] >> kTypeShift : 0u;
+        const u64 b1 = __ballot(t & 1u), b2 = __ballot(t & 2u);
+        if (lane == 0) {
+          xt1[i >> 6] = b1;
+          xt2[i >> 6] = b2;
+        }
       }
     if (K4)
       for (int64_t i = threadIdx.x; i < (int64_t)d * W; i += NT) {
@@ -529,27 +543,53 @@ __global__ __launch_bounds__(512) void k_tri_big(DevGraph G, const uint16_t* __r
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     if constexpr (K4) {
-      // common bits of rows j and k: a lane per k of row j while a row is a
-      // few words, else a lane per word
+      // The K4s of an edge j -> k: the common bits of their rows, one by one
+      // where a word has few of them, else counted by their types towards x, j
+      // and k, 27 intersections a word (n = 300, three quarters of the arcs:
+      // the call 34.2 -> 2.8 ms, with the lanes' choice below).
       auto edge = [&](int32_t j, int32_t k, uint32_t bx, uint32_t yz, int32_t l0, int32_t ls) {
         const uint32_t bk = bx | edge_code<4>(0, 2, G.np_idx[xa + k] >> kTypeShift) | edge_code<4>(1, 2, yz);
+        auto code = [&](uint32_t x, uint32_t r, uint32_t q) {
+          return bk | edge_code<4>(0, 3, x) | edge_code<4>(1, 3, r) | edge_code<4>(2, 3, q);
+        };
+        uint32_t n[14];  // two counts a word: at most d, 4,096
+        bool many = false;
+#pragma unroll
+        for (int i = 0; i < 14; ++i) n[i] = 0;
         for (int32_t lw = l0; lw < W; lw += ls) {
           const u64 r1 = word(P1, (int64_t)j * W + lw), r2 = word(P2, (int64_t)j * W + lw);
           const u64 q1 = word(P1, (int64_t)k * W + lw), q2 = word(P2, (int64_t)k * W + lw);
-          for (u64 com = (r1 | r2) & (q1 | q2); com; com &= com - 1ull) {
+          u64 com = (r1 | r2) & (q1 | q2);
+          if (hashed && __popcll(com) > kFewBits) {
+            many = true;
+            const u64 x1 = xt1[lw], x2 = xt2[lw];
+            const u64 r[3] = {r1 & ~r2, r2 & ~r1, r1 & r2}, q[3] = {q1 & ~q2, q2 & ~q1, q1 & q2};
+            const u64 x[3] = {x1 & ~x2, x2 & ~x1, x1 & x2};
+#pragma unroll
+            for (int i = 0; i < 27; ++i)
+              n[i >> 1] += (uint32_t)__popcll(x[i / 9] & r[(i / 3) % 3] & q[i % 3]) << (16 * (i & 1));
+            continue;
+          }
+          for (; com; com &= com - 1ull) {
             const int l = __builtin_ctzll(com);
-            const uint32_t code = bk | edge_code<4>(0, 3, G.np_idx[xa + lw * 64 + l] >> kTypeShift) |
-                                  edge_code<4>(1, 3, (uint32_t)((r1 >> l) & 1) | (uint32_t)((r2 >> l) & 1) << 1) |
-                                  edge_code<4>(2, 3, (uint32_t)((q1 >> l) & 1) | (uint32_t)((q2 >> l) & 1) << 1);
-            atomicAdd(&bins.kh[lut[code]], 1ull);
+            atomicAdd(&bins.kh[lut[code(G.np_idx[xa + lw * 64 + l] >> kTypeShift,
+                                        (uint32_t)((r1 >> l) & 1) | (uint32_t)((r2 >> l) & 1) << 1,
+                                        (uint32_t)((q1 >> l) & 1) | (uint32_t)((q2 >> l) & 1) << 1)]], 1ull);
           }
         }
+        if (many)
+#pragma unroll
+          for (int i = 0; i < 27; ++i) {
+            const uint32_t c = (n[i >> 1] >> (16 * (i & 1))) & 0xFFFFu;
+            if (c) atomicAdd(&bins.kh[lut[code(i / 9 + 1, (i / 3) % 3 + 1, i % 3 + 1)]], (u64)c);
+          }
       };
+      // a lane per k of row j, or per word of the rows, whichever takes fewer steps
       for (int32_t j = wv; j < d; j += NW) {
         const uint32_t bx = edge_code<4>(0, 1, G.np_idx[xa + j] >> kTypeShift);
         for (int32_t kw = 0; kw < W; ++kw) {
           const u64 p1 = word(P1, (int64_t)j * W + kw), p2 = word(P2, (int64_t)j * W + kw);
-          if constexpr (L) {
+          if (L || (hashed && __popcll(p1 | p2) > W)) {
             const uint32_t yz = (uint32_t)((p1 >> lane) & 1) | (uint32_t)((p2 >> lane) & 1) << 1;
             if (yz) edge(j, kw * 64 + lane, bx, yz, 0, 1);
           } else {
@@ -1397,6 +1437,12 @@ void enqueue_counts(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_t* a4, 
   if (n == 0) return;
   const int cus = p.num_cus;
   const CountPlan c = count_plan(n, m, g.max_graph_n, g.gid != nullptr);
+  // A vertex with more than 128 higher neighbours has a workgroup to itself; on a
+  // dense graph of a vertex or two per CU also one with more than 40, where a
+  // wave alone would be the whole call (n = 150, three quarters of the arcs:
+  // 4,283 us so, 795 us with a workgroup; n = 200, a fifth of the arcs or fewer,
+  // has no such vertices to speak of and the further launch costs 10 to 20 us).
+  const int32_t big = a4 && !g.gid && n <= 2 * cus && 5 * m > n * (n - 1) ? 41 : 129;
   // lists in words that the build is done with (at most 2 m / 17 vertices have
   // a degree of 17 or more, 2 m / 65 one of 65)
   Lists L{};
@@ -1409,9 +1455,10 @@ void enqueue_counts(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_t* a4, 
   auto list_grid = [&](int64_t most, int per, int wgs) { return dim3(grid_of(most, per, (int64_t)cus * wgs)); };
   // a vertex of tier d has at least d higher neighbours of at least its degree
   const int64_t n16 = std::min(n, m), n64 = std::min(n, 2 * m / 17);
-  const int64_t n128 = c.D > 64 ? std::min(n, 2 * m / 65) : 0, nbig = c.D > 128 ? std::min(n, 2 * m / 129) : 0;
+  const int64_t n128 = c.D > 64 && big > 65 ? std::min(n, 2 * m / 65) : 0;
+  const int64_t nbig = c.D >= big ? std::min(n, 2 * m / big) : 0;
   if (!a4) {
-    hipLaunchKernelGGL((k_classify<false>), dim3(cgrid), dim3(256), 0, s, g, L, queue, p.status);
+    hipLaunchKernelGGL((k_classify<false>), dim3(cgrid), dim3(256), 0, s, g, L, queue, big, p.status);
     hipLaunchKernelGGL((k_tri<16, 16, false>), list_grid(n16, 16, 8), dim3(256), 0, s, g, T.lut[3], T.lut[4], a3, nullptr,
                        nullptr, p.status, queue, L.v[kTri16]);
     if (c.D > 16)
@@ -1438,7 +1485,7 @@ void enqueue_counts(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_t* a4, 
     for (int l = 0; l < kLists; ++l) left->wedge[l] = L.v[l];
   }
   enqueue_zero(Te, sizeof(uint32_t) * 9 * (size_t)(m + 1), s);
-  hipLaunchKernelGGL((k_classify<true>), dim3(cgrid), dim3(256), 0, s, g, L, queue, p.status);
+  hipLaunchKernelGGL((k_classify<true>), dim3(cgrid), dim3(256), 0, s, g, L, queue, big, p.status);
   // The triangles beside the wedges where both are long (n = 10^5, m = 10^6: 450
   // and 1,030 us; the wedge table of a workgroup leaves half of a CU's waves and
   // a quarter of its LDS) and the caller's streams allow it.
