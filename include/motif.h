@@ -367,20 +367,25 @@ typedef struct motif_tuning {
   int32_t block;        /* threads per workgroup for the anchor kernels (64..1024)  */
   int32_t grid_per_cu;  /* persistent workgroups per compute unit (1..16)           */
   int32_t tile;         /* work-queue granularity (1..4096): G* entries per tile,
-                           except for the k = 5 core-reuse scheme, where the
-                           queue is cut by estimated cost into about `tile`
-                           tiles per workgroup (fewer on small graphs: a tile
-                           holds at least 512 cost units)                      */
-  int32_t heavy;        /* census scheme for k = 4, 5: 1 = subgraph copies (k = 4,
-                           and k = 5 of one graph where it fits) and core reuse
-                           (the other k = 5 calls), 2 = per-anchor scan;
-                           0 = keep                                               */
-  /* Kept for callers, checked and stored, without effect on the copies. */
-  int32_t solo_deg;     /* k = 4 (1..64)                                        */
-  int32_t light_deg;    /* k = 4 (1..256)                                       */
-  int32_t light5;       /* k = 5 core reuse: a triple whose lighter side has at most
-                           this degree takes the factored wave path (1..767);
-                           moves work, never changes the result                 */
+                           except for the core-reuse scheme, where the queue is
+                           cut by estimated cost into about `tile` tiles per
+                           workgroup (fewer on small graphs: a tile holds at
+                           least 128 (k = 4) or 512 (k = 5) cost units)         */
+  int32_t heavy;        /* census scheme for k = 4, 5: 1 = subgraph copies (k = 4
+                           of more than a few thousand arcs or beside other
+                           sizes, and k = 5 of one graph where it fits) and core
+                           reuse (the other k = 4 and 5 calls: neighbourhood of
+                           the highest-ranked anchor vertex scanned once per work
+                           unit), 2 = per-anchor scan; 0 = keep                   */
+  /* Work placement of the core-reuse scheme (degrees in the undirected graph
+   * G*); they move work between waves and workgroups, never change the result. */
+  int32_t solo_deg;     /* k = 4: a core (higher-ranked anchor end) of at most this
+                           degree runs whole anchors on one wave (1..64)        */
+  int32_t light_deg;    /* k = 4: an anchor whose other end has at most this
+                           degree runs on one wave, else on the workgroup
+                           (1..256)                                             */
+  int32_t light5;       /* k = 5: a triple whose lighter side has at most this
+                           degree takes the factored wave path (1..767)         */
 } motif_tuning_t;
 
 /* Read / override the default parameters for k (0 in a field = keep).

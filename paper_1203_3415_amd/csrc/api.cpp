@@ -58,18 +58,20 @@ int32_t g_init_err = 0;
 TuningSet g_tuning = {{
     {256, 4, 16, 1}, {256, 4, 16, 1}, {256, 4, 16, 1},
     {256, 4, 16, 1},    // k = 3: tile*16 vertices per tile (at most 1024)
-    // k = 4: copies, which have no parameters; block, grid and tile are the
-    // per-anchor scheme's
+    // k = 4: core reuse where the copies, which have no parameters, don't pay
+    // (tile = cost tiles per workgroup)
     {1024, 1, 4, 1, 48, 224, 512},
     // k = 5: core reuse, light-partner limit from a sweep on the n = 2e4 workload
     {1024, 1, 128, 1, 64, 192, 384},
 }};
 // Batches of small graphs (one fused census of many graphs of at most
-// kBatchSmallN vertices): the per-anchor scheme's parameters for k = 4 (many
-// small anchors, so smaller workgroups, two per CU, finer tiles).  Used while
-// k's tuning has not been set explicitly.
+// kBatchSmallN vertices): for k = 4 smaller workgroups, two per CU, and finer
+// tiles (many small cores).  Used while k's tuning has not been set explicitly.
 const Tuning kBatchTuning4 = {512, 2, 16, 1, 32, 256, 512};
 constexpr int64_t kBatchSmallN = 16384;
+// Arcs, of one graph or of a batch, up to which k = 4 reuses the cores, and
+// vertices of a graph (whose labels and W rows then fit; see copies4_pays).
+constexpr int64_t kReuse4Arcs = 5120, kReuse4BatchArcs = 14336, kReuse4N = 5120;
 bool g_batch_default[6] = {false, false, false, false, true, false};
 
 int32_t current_device(int* dev) {
@@ -265,6 +267,17 @@ TuningSet tuning_snapshot() {
   return g_tuning;
 }
 
+// The copies are ten and more launches, one after another, where kr_kernel<4> is
+// one, so small inputs keep the latter (us a call, core reuse and copies: n = 40
+// with 480 arcs 171 and 247, n = 400 with 3,200 262 and 290, n = 800 with 6,400
+// 280 and 281; batches of 8 graphs of n = 60 with 480 arcs 264 and 365, of n =
+// 200 with 1,600 311 and 348, of n = 400 with 3,200 420 and 383).  With other
+// sizes asked for as well the copies share their triangles (k = 3 and 4 of n =
+// 60 with 480 arcs: 282 and 258).
+bool copies4_pays(int32_t nk, bool batch, int64_t arcs, int64_t max_n) {
+  return nk > 1 || max_n > kReuse4N || arcs > (batch ? kReuse4BatchArcs : kReuse4Arcs);
+}
+
 namespace {
 int32_t size_bucket(int64_t arcs) { return arcs > 1 ? 63 - __builtin_clzll((unsigned long long)arcs) : 0; }
 }  // namespace
@@ -272,12 +285,13 @@ int32_t size_bucket(int64_t arcs) { return arcs > 1 ? 63 - __builtin_clzll((unsi
 TuningSet tuning_for_call(int dev, int32_t nk, const int32_t* ks, bool batch, int64_t arcs, int64_t max_n) {
   std::lock_guard<std::mutex> lk(g_mu);
   TuningSet t = g_tuning;
-  if (batch && max_n >= 0 && max_n <= kBatchSmallN && g_batch_default[4]) t.k[4] = kBatchTuning4;
+  if (batch && max_n <= kBatchSmallN && g_batch_default[4]) t.k[4] = kBatchTuning4;
   const DeviceState& d = g_dev[dev];
   for (int32_t i = 0; i < nk; ++i) {
     auto it = d.tuned.find(TuneKey{ks[i], batch ? 1 : 0, size_bucket(arcs)});
     if (it != d.tuned.end()) t.k[ks[i]] = it->second;
   }
+  t.k[4].copies = copies4_pays(nk, batch, arcs, max_n);
   return t;
 }
 
@@ -349,7 +363,9 @@ std::vector<TuneAxis> tune_axes(int k) {
     return {{&Tuning::heavy, {1, 0}, false},
             {&Tuning::block, {512, 1024}, false},
             {&Tuning::grid_per_cu, {1, 2}, false},
-            {&Tuning::tile, {2, 3, 4, 8, 16}, false}};
+            {&Tuning::tile, {2, 3, 4, 8, 16}, false},
+            {&Tuning::solo_deg, {16, 32, 48, 64}, true},
+            {&Tuning::light_deg, {96, 128, 160, 192, 224, 256}, true}};
   return {{&Tuning::block, {512, 1024}, false},
           {&Tuning::tile, {16, 32, 64, 128, 256}, false},
           {&Tuning::light5, {128, 256, 384, 512, 640, 767}, true}};
@@ -569,7 +585,7 @@ int32_t run_census(const BuildInput& in, int32_t k, uint64_t* hist, hipStream_t 
   int dev;
   int32_t rc = ensure_init(&dev);
   if (rc) return rc;
-  const TuningSet tune = tuning_for_call(dev, 1, &k, false, in.m);
+  const TuningSet tune = tuning_for_call(dev, 1, &k, false, in.m, in.n);
   Pipeline* p = nullptr;
   rc = get_pipeline(dev, s, std::max(pipeline_bytes(in.n, in.m, in.ngraphs, false, k, device_cus(dev), in.n, tune.k[k]),
                                      k == 5 ? copies5_need(in) : 0), &p);
@@ -906,7 +922,7 @@ int32_t motif_census_async(const int32_t* out_off, const int32_t* out_idx, const
   int dev;
   int32_t rc = ensure_init(&dev);
   if (rc) return rc;
-  const TuningSet tune = tuning_for_call(dev, 1, &k, false, m);
+  const TuningSet tune = tuning_for_call(dev, 1, &k, false, m, n);
   Pipeline* p = nullptr;
   rc = get_pipeline(dev, s, pipeline_bytes(n, m, 1, false, k, device_cus(dev), n, tune.k[k]), &p);
   if (rc) return rc;
@@ -963,7 +979,7 @@ int32_t motif_census_noalloc(const int32_t* out_off, const int32_t* out_idx, con
   // only after its work has finished, so two calls never overlap in it.
   static std::mutex scratch_mu;
   std::lock_guard<std::mutex> lk(scratch_mu);
-  TuningSet tune = tuning_for_call(dev, 1, &k, false, m);
+  TuningSet tune = tuning_for_call(dev, 1, &k, false, m, n);
   const size_t room = kScratchBytes - kScratchHead;
   size_t need = pipeline_bytes(n, m, 1, false, k, cus, n, tune.k[k]);
   if (need > room && (k == 4 || k == 5) && tune.k[k].heavy == 1) {
@@ -1012,7 +1028,7 @@ int32_t motif_census_undirected(const int32_t* out_off, const int32_t* out_idx, 
     enqueue_zero(hist, sizeof(uint64_t) * U, s);
     return hipStreamSynchronize(s) == hipSuccess ? 0 : MOTIF_EDEVICE;
   }
-  const TuningSet tune = tuning_for_call(dev, 1, &k, false, m);
+  const TuningSet tune = tuning_for_call(dev, 1, &k, false, m, n);
   Pipeline* p = nullptr;
   BuildInput in{};
   in.out_off = out_off;
@@ -1075,7 +1091,7 @@ int32_t motif_census_multi(const motif_graph_t* g, int32_t nk, const int32_t* ks
   in.n = g->n;
   in.m = g->m;
   // one build plus the workspace of every size (the censuses may run at once)
-  const TuningSet tune = tuning_for_call(dev, nk, ks, false, in.m);
+  const TuningSet tune = tuning_for_call(dev, nk, ks, false, in.m, in.n);
   const size_t build = build_bytes(in.n, in.m, 1, false);
   size_t bytes = build;
   for (int32_t i = 0; i < nk; ++i)
@@ -1152,8 +1168,11 @@ int32_t motif_autotune(const motif_graph_t* graphs, int32_t count, int32_t k, ui
   if (int32_t rc = ensure_init(&dev)) return rc;
   const int C = motif_num_classes(k);
   hipStream_t s = (hipStream_t)stream;
-  int64_t arcs = 0;
-  for (int32_t g = 0; g < count; ++g) arcs += std::max<int64_t>(0, graphs[g].m);
+  int64_t arcs = 0, max_n = 0;
+  for (int32_t g = 0; g < count; ++g) {
+    arcs += std::max<int64_t>(0, graphs[g].m);
+    max_n = std::max<int64_t>(max_n, graphs[g].n);
+  }
   const bool batch = count > 1;
   const TuneKey key{k, batch ? 1 : 0, size_bucket(arcs)};
   TuningSet base = tuning_snapshot();
@@ -1162,6 +1181,7 @@ int32_t motif_autotune(const motif_graph_t* graphs, int32_t count, int32_t k, ui
     auto it = g_dev[dev].tuned.find(key);
     if (it != g_dev[dev].tuned.end()) base.k[k] = it->second;
   }
+  base.k[4].copies = copies4_pays(1, batch, arcs, max_n);
   std::vector<uint64_t> ref((size_t)count * C), cur((size_t)count * C);
   bool have_ref = false;
   // One candidate: warm-up, then the median wall time of kTuneReps runs; its

@@ -1,8 +1,9 @@
 // Census kernels by anchors for k = 4 and 5 (gfx950, wave64), the exact final
-// division, and the launch of every census.  k = 3 and the default k = 4 count
-// subgraph copies (counts.hip), as k = 5 of one graph does where it fits
-// (copies5.hip); the kernels here take the other k = 5 calls (batches, calls
-// without a host wait, large or very dense graphs) and the per-anchor scheme.
+// division, and the launch of every census.  k = 3, k = 4 of all but small
+// inputs and k = 5 of one graph where it fits count subgraph copies (counts.hip,
+// copies5.hip); the kernels here take k = 4 of small inputs, the other k = 5
+// calls (batches, calls without a host wait, large or very dense graphs) and the
+// per-anchor scheme.
 //
 // Every k-set S is charged to the anchors that see it -- an undirected edge of
 // G* (k = 4, e-Patterns), a connected triple (k = 5, Delta-Patterns) -- and each
@@ -32,10 +33,11 @@
 // schedule.  Counters wrap modulo 2^64; the intermediate "negative" values of
 // the edge moves cancel exactly.
 //
-// k4_kernel and k5_kernel follow this per anchor.  kr_kernel computes the k = 5
-// sums with the neighbourhood of a triple's centre scanned once for all of its
-// triples: those of one centre and one heavier side share that side's sums and
-// are corrected per lighter side.
+// k4_kernel and k5_kernel follow this per anchor.  kr_kernel computes the same
+// sums with the neighbourhood of the highest-ranked anchor vertex scanned once
+// for all of its anchors; for k = 4 small anchors run on single waves with their
+// labels in LDS hashes, for k = 5 the triples of one centre and one heavier side
+// share that side's sums and are corrected per lighter side.
 #include <hip/hip_runtime.h>
 
 #include "codes.h"
@@ -55,6 +57,14 @@ __device__ __forceinline__ uint64_t lut_quad(const uint16_t* lut, uint32_t c0) {
 }
 __device__ __forceinline__ uint32_t quad_at(uint64_t q, uint32_t r) { return (uint32_t)(q >> (16u * r)) & 0xFFFFu; }
 
+// k = 4: slot of the label pair (a, b), 1 <= a <= b <= 15, among the 120 such
+// pairs (row-major upper triangle).
+constexpr int kPairs4 = 120;
+__device__ __forceinline__ uint32_t pair_slot4(uint32_t a, uint32_t b) {
+  const uint32_t a0 = a - 1u;
+  return a0 * 15u - (a0 * (a0 - 1u)) / 2u + (b - a);
+}
+
 constexpr int kMaxHubs = 512;  // rows of the per-core W table in LDS
 constexpr int kMaxBig = 64;          // cores whose W / M tables are built once per call
 constexpr int kBigMinDeg = 256;      // ... among vertices of at least this degree
@@ -63,11 +73,15 @@ constexpr int kBigRow = 12;          // words per W row (9 used, 16-byte aligned
 constexpr int kUnroll = 4;
 // Smallest cost of a work-queue tile of the core-reuse kernels: on small
 // graphs `tile` tiles per workgroup would cut below one core's units, and
-// every tile sets its cores up again (measured best tile costs: 370-850 on
-// graphs of 10^3-10^5 arcs).
+// every tile sets its cores up again (measured best tile costs: about 135
+// for k = 4 and 370-850 for k = 5 on graphs of 10^3-10^5 arcs).
+constexpr int32_t kMinTileCost4 = 128;
 constexpr int32_t kMinTileCost5 = 512;
 constexpr int kBucketShift = 6;     // the row-scan layout records the row at every 64th entry ...
 constexpr int kBuckets = 1024;      // ... for layouts of up to 64 K entries (else plain binary search)         // N+ entries per lane and pass of the flattened scans
+constexpr int kLightDegMax = 256;  // cap of the k = 4 light-side limit (wave hash load <= 1/2)
+constexpr int kWaveHashBits = 9;
+constexpr int kWaveHash = 1 << kWaveHashBits;  // slots of the wave-private hash of N(side): load <= 1/2
 constexpr uint32_t kEmptySlot = ~0u;
 constexpr int kLight5Max = 767;     // cap of the k = 5 light-partner limit (a partner must fit the table alone)
 constexpr int kNP5 = 32;            // light partners c per sub-chunk of a k = 5 unit (2 type bits each in 64)
@@ -77,12 +91,19 @@ constexpr int kT5Load = 768;        // ... holding at most this many keys (sum o
 static_assert(kLight5Max + 1 <= kT5Load, "a light partner must fit the table alone");
 constexpr uint32_t kInT5 = 64u;     // label bit 6: the vertex is a key of that table
 constexpr int kU5 = 16 * 48;        // per-unit move counters: (x label, y label, r), labels of 4 bits
+constexpr int kSoloDegMax = 64;     // cap of the k = 4 solo-core limit (one lane per core neighbour)
+constexpr int kSoloHashBits = 8;
+constexpr int kSoloHash = 1 << kSoloHashBits;  // keys of the solo hash of N(c) u N(s): load < 1/2
 
-// Work-placement limit of the core-reuse kernel, from the tuning (clamped to
-// its cap above).
+// Work-placement limits of the core-reuse kernels, from the tuning (each
+// clamped to its cap above).
 struct Limits {
-  int32_t light5;
+  int32_t solo, light, light5;
 };
+
+__device__ __forceinline__ uint32_t hash_slot(int32_t y) {
+  return ((uint32_t)y * 2654435761u) >> (32 - kWaveHashBits);  // Fibonacci hashing
+}
 
 constexpr u64 kMinusOne = ~0ull;
 
@@ -427,10 +448,11 @@ __global__ __launch_bounds__(BLOCK) void k5_kernel(DevGraph G, const uint16_t* _
 
 // ======================================================= core reuse ==
 //
-// The same sums as k5_kernel, reorganised so that the neighbourhood of the
-// anchor's centre is scanned once per work unit instead of once per anchor.
-// Core kappa = the centre b of the connected triple; the other anchor vertices
-// are the "sides".  Per core, once:
+// The same sums as k4_kernel / k5_kernel, reorganised so that the
+// neighbourhood of the highest-ranked anchor vertex is scanned once per work
+// unit instead of once per anchor.  Core kappa = the higher-rank endpoint of
+// the anchor edge (k = 4) or the centre b of the connected triple (k = 5);
+// the other anchor vertices are the "sides".  Per core, once:
 //   M[tx][ty][r] = edges x -> y (N+ orientation) with both ends in N(kappa),
 //                  by the types of x, y towards kappa and the edge type r;
 //   W[q][tp][r]  = edges p -> q (N+ orientation, p in N(kappa)) for every q.
@@ -453,8 +475,8 @@ __global__ __launch_bounds__(BLOCK) void k5_kernel(DevGraph G, const uint16_t* _
 // listed vertices are laid end to end and dealt out one entry per thread, so
 // the work of an anchor is spread over the whole workgroup whatever the row
 // lengths.
-template <int BLOCK, int LCAP>
-__global__ __launch_bounds__(BLOCK) void kr_kernel(DevGraph G, const uint16_t* __restrict__ lut,
+template <int K, int BLOCK, int LCAP>
+__global__ __launch_bounds__(BLOCK) void kr_kernel(DevGraph G, const uint16_t* __restrict__ lut_g,
                                                    uint64_t* __restrict__ acc, const int32_t* st,
                                                    int32_t* __restrict__ queue, uint32_t* __restrict__ glabels,
                                                    int64_t label_words, const int32_t* __restrict__ hub_id,
@@ -463,12 +485,13 @@ __global__ __launch_bounds__(BLOCK) void kr_kernel(DevGraph G, const uint16_t* _
                                                    const int32_t* __restrict__ big_id,
                                                    const uint32_t* __restrict__ wbig, int64_t wbig_stride,
                                                    const uint32_t* __restrict__ mbig, Limits lim) {
-  constexpr int K = 5, C = 9364, NL = 64, LB = 8;
+  constexpr int C = K == 4 ? 199 : 9364, NL = K == 4 ? 16 : 64, LB = K == 4 ? 4 : 8;
   constexpr int S1 = K - 2, S2 = K - 1;  // member slots
-  // LDS rows of W: fewer where the counters and labels leave no room
-  constexpr int HUBS = LCAP == 32768 ? 80 : kMaxHubs;
+  // LDS rows of W: fewer where the k = 5 counters and labels leave no room
+  constexpr int HUBS = (K == 5 && LCAP == 32768) ? 80 : (K == 4 && LCAP == 65536) ? 384 : kMaxHubs;
   constexpr bool GL = LCAP == 0;
   __shared__ u64 hist[C];
+  __shared__ uint16_t lut_lds[K == 4 ? 4096 : 1];
   __shared__ int32_t cnt[NL], nzl[NL], nz_count;
   __shared__ uint32_t Mc[27];
   __shared__ uint32_t W[HUBS * 9];
@@ -476,58 +499,89 @@ __global__ __launch_bounds__(BLOCK) void kr_kernel(DevGraph G, const uint16_t* _
   __shared__ int32_t sh_j0, sh_j1;
   __shared__ u64 seg_ctr[2];  // (rows << 32) | entries of the chunk being laid out
   constexpr int NW = BLOCK / 64;
+  // k = 4: per anchor, the inner-edge moves counted per label pair (a <= b)
+  // and arc type, 32-bit wrapping (per anchor they stay far inside int32);
+  // the classes and the no-edge halves are added once, in the closed form.
+  // The wave paths' tables share the row-scan layout's words: the two are
+  // never in use at the same time (workgroup phases are barrier-separated).
+  constexpr int TW = K == 4 ? kPairs4 * 3 : 0;
   constexpr int SEGW = 4 * BLOCK + kBuckets;  // with one word of row information per row
-  __shared__ __align__(16) int32_t seg_pool[SEGW];
+  constexpr int POOLW = NW * TW > SEGW ? NW * TW : SEGW;
+  __shared__ __align__(16) int32_t seg_pool[POOLW];
   int32_t* const seg_v = seg_pool;
   int32_t* const seg_start = seg_pool + BLOCK;
   int32_t* const seg_base = seg_pool + 2 * BLOCK;
   int32_t* const seg_at = seg_pool + 3 * BLOCK;
   int32_t* const seg_lab = seg_pool + 3 * BLOCK + kBuckets;  // rowinfo of each laid-out row
-  __shared__ int32_t wcnt[kNP5 * NL];  // set sizes, a row per light partner
-  // light partners of one unit: merged table of their neighbourhoods
+  uint32_t* const wT = reinterpret_cast<uint32_t*>(seg_pool);
+  constexpr int WH = K == 4 ? kWaveHash : 0;  // per-wave hash words
+  constexpr int NCN = K == 4 ? NW : kNP5;     // set-size rows: one per wave (k = 4), per light partner (k = 5)
+  __shared__ uint32_t wh[K == 4 ? NW * WH : 1];  // light anchors: per-wave hashes of the sides' neighbourhoods
+  __shared__ int32_t wcnt[NCN * NL];
+  // k = 5 light partners of one unit: merged table of their neighbourhoods
   // (vertex -> 2 type bits per partner, partner index + 1 of the vertex
   // itself), per-unit move counters, the a-part set sizes, the partners
-  constexpr int T5 = kT5, P5 = kNP5;
+  constexpr int T5 = K == 5 ? kT5 : 1, P5 = K == 5 ? kNP5 : 1;
   __shared__ uint32_t tkey[T5];
   __shared__ u64 ttyp[T5];
   __shared__ uint8_t tpid[T5];
-  __shared__ uint32_t U5[kU5];
+  __shared__ uint32_t U5[K == 5 ? kU5 : 1];
   // two buffers: the partner set of the next sub-chunk is chosen while the
   // current one finishes; sb is the buffer of the current sub-chunk
   __shared__ int32_t cnUb[2][16];
   __shared__ int32_t p5_vb[2][P5], p5_rowb[2][P5], p5_offb[2][P5], p5_ctlb[2][5], p5_dc[P5];
-  __shared__ uint16_t tlist[kT5Load];  // slots of the table's keys
+  __shared__ uint16_t tlist[K == 5 ? kT5Load : 1];  // slots of the table's keys
   __shared__ uint32_t p5_baseb[2][P5], p5_db[P5];
+  // k = 4: the workgroup path's move table (kept zero between anchors), and
+  // the label pair (a, b) of each table slot
+  __shared__ __align__(16) uint32_t bT[K == 4 ? TW : 1];
+  __shared__ uint8_t pair_a[K == 4 ? kPairs4 : 1], pair_b[K == 4 ? kPairs4 : 1];
   __shared__ int32_t unit_list[BLOCK], unit_ctr[3];
+  __shared__ int32_t lbk[K == 4 ? 32 : 1];  // k = 4 light units: counts and fills per log2 degree bucket
   __shared__ uint32_t lds_labels[LCAP > 0 ? LCAP / 4 : 1];
   if (st[kStatus] != 0) return;
   Labels<LB, GL> lab{LCAP > 0 ? lds_labels : glabels + (int64_t)blockIdx.x * label_words};
   uint32_t* WG = wg + (int64_t)blockIdx.x * w_stride;
+  const uint16_t* lut = K == 4 ? lut_lds : lut_g;
+  if (K == 4)
+    for (int i = threadIdx.x; i < 4096; i += BLOCK) lut_lds[i] = lut_g[i];
   for (int i = threadIdx.x; i < C; i += BLOCK) hist[i] = 0;
   if (threadIdx.x < NL) cnt[threadIdx.x] = 0;
   if (threadIdx.x < 27) Mc[threadIdx.x] = 0;
   if (threadIdx.x < 4) ncore[threadIdx.x] = 0;
   if (threadIdx.x < 2) seg_ctr[threadIdx.x] = 0;
   for (int i = threadIdx.x; i < HUBS * 9; i += BLOCK) W[i] = 0u;
-  for (int i = threadIdx.x; i < kNP5 * NL; i += BLOCK) wcnt[i] = 0;
-  for (int i = threadIdx.x; i < T5; i += BLOCK) {
-    tkey[i] = kEmptySlot;
-    ttyp[i] = 0ull;
-    tpid[i] = 0;
+  for (int i = threadIdx.x; i < NW * WH; i += BLOCK) wh[i] = kEmptySlot;
+  for (int i = threadIdx.x; i < NCN * NL; i += BLOCK) wcnt[i] = 0;
+  if (K == 5) {
+    for (int i = threadIdx.x; i < T5; i += BLOCK) {
+      tkey[i] = kEmptySlot;
+      ttyp[i] = 0ull;
+      tpid[i] = 0;
+    }
+    for (int i = threadIdx.x; i < kU5; i += BLOCK) U5[i] = 0u;
+    if (threadIdx.x < 32) cnUb[threadIdx.x >> 4][threadIdx.x & 15] = 0;
   }
-  for (int i = threadIdx.x; i < kU5; i += BLOCK) U5[i] = 0u;
-  if (threadIdx.x < 32) cnUb[threadIdx.x >> 4][threadIdx.x & 15] = 0;
+  if (K == 4) {
+    for (int i = threadIdx.x; i < TW; i += BLOCK) bT[i] = 0u;
+    if (threadIdx.x < 15)  // pairs (a, b), 1 <= a <= b <= 15, row a from slot pair_slot4(a, a)
+      for (uint32_t b = threadIdx.x + 1u; b <= 15u; ++b) {
+        const uint32_t t = pair_slot4(threadIdx.x + 1u, b);
+        pair_a[t] = (uint8_t)(threadIdx.x + 1u);
+        pair_b[t] = (uint8_t)b;
+      }
+  }
   if (LCAP > 0)
     for (int i = threadIdx.x; i < LCAP / 4; i += BLOCK) lds_labels[i] = 0u;
   __syncthreads();
 
   const int32_t n = G.n;
   const int32_t total = G.gs_off[n];
-  // the per-unit move counters of the light path are 32-bit and stay
+  // the per-unit move counters of the k = 5 light path are 32-bit and stay
   // within 3 |E*| in magnitude: exact while |E*| < 2^29
   const bool fact5 = total < (1 << 30);
   int32_t cur_g = -1, row = 0, core = -1, par = 0;
-  int32_t sb = 0;  // buffer of the current light sub-chunk
+  int32_t sb = 0;  // k = 5: buffer of the current light sub-chunk
   int32_t cbig = -1;  // slot of the current core among the precomputed big cores, or -1
   int64_t wbase = 0;  // first vertex of the core's graph
   auto wrow = [&](int32_t q) { return WG + (int64_t)(q - wbase) * kBigRow; };
@@ -558,9 +612,43 @@ __global__ __launch_bounds__(BLOCK) void kr_kernel(DevGraph G, const uint16_t* _
   // contribution of one edge between slots S1 (x) and S2 (y) of weight w
   auto edge = [&](uint32_t base, uint32_t Lx, uint32_t Ly, uint32_t r, u64 w) {
     const uint32_t c0 = base | slot_code<K, S1>(Lx) | slot_code<K, S2>(Ly);
-    const uint64_t q = lut_quad(lut, c0);
-    atomicAdd(&hist[quad_at(q, r)], w);
-    atomicAdd(&hist[quad_at(q, 0)], (u64)0 - w);
+    if constexpr (K == 5) {
+      const uint64_t q = lut_quad(lut, c0);
+      atomicAdd(&hist[quad_at(q, r)], w);
+      atomicAdd(&hist[quad_at(q, 0)], (u64)0 - w);
+    } else {
+      atomicAdd(&hist[lut[c0 | rel_code<K>(r)]], w);
+      atomicAdd(&hist[lut[c0]], (u64)0 - w);
+    }
+  };
+  // k = 4: the same move counted in the anchor's table T at (min label, max
+  // label, arc type seen from the smaller label's member): swapping the two
+  // members flips the arc type and keeps the class.  The no-edge half is the
+  // negated sum of a pair's three counts (the class of a member pair without
+  // an edge does not depend on which member is in which slot).
+  auto edge4 = [&](uint32_t* T, uint32_t, uint32_t Lx, uint32_t Ly, uint32_t r, u64 w) {
+    const bool sw = Lx > Ly;
+    const uint32_t a = sw ? Ly : Lx, b = sw ? Lx : Ly, rr = sw ? flip(r) : r;
+    atomicAdd(&T[pair_slot4(a, b) * 3u + rr - 1u], (uint32_t)w);
+  };
+  // Closed form of label pair slot t with the anchor's moves: the pair's
+  // member pairs go to its no-edge class, then each counted move takes one
+  // from there to the class with the edge.  zero: clear the pair's counts.
+  auto t_close = [&](const int32_t* cntv, uint32_t* T, uint32_t base, int32_t t, bool zero) {
+    const uint32_t La = pair_a[t], Lb = pair_b[t];
+    const u64 na = (u64)cntv[La], nb = (u64)cntv[Lb];
+    const int32_t s1 = (int32_t)T[3 * t], s2 = (int32_t)T[3 * t + 1], s3 = (int32_t)T[3 * t + 2];
+    if (zero) {
+      T[3 * t] = 0u;
+      T[3 * t + 1] = 0u;
+      T[3 * t + 2] = 0u;
+    }
+    const u64 w0 = (La == Lb ? na * (na - (na > 0)) / 2 : na * nb) - (u64)((int64_t)s1 + s2 + s3);
+    const uint32_t c0 = base | slot_code<K, S1>(La) | slot_code<K, S2>(Lb);
+    if (w0) atomicAdd(&hist[lut[c0]], w0);
+    if (s1) atomicAdd(&hist[lut[c0 | rel_code<K>(1u)]], (u64)(int64_t)s1);
+    if (s2) atomicAdd(&hist[lut[c0 | rel_code<K>(2u)]], (u64)(int64_t)s2);
+    if (s3) atomicAdd(&hist[lut[c0 | rel_code<K>(3u)]], (u64)(int64_t)s3);
   };
   // Flattened scan of the N+ rows of the vertices pick(0 .. items-1): pick
   // returns a vertex (or -1) and does the per-vertex work, visit(v, f, info)
@@ -637,7 +725,7 @@ __global__ __launch_bounds__(BLOCK) void kr_kernel(DevGraph G, const uint16_t* _
     }
   };
   auto flat_rows = [&](int32_t items, auto&& pick, auto&& visit) {
-    flat_rows_pre(items, [] {}, pick, visit, [](int32_t) { return 0u; });
+    flat_rows_pre(items, [] {}, pick, visit, [&](int32_t v) { return K == 4 ? lab.get((uint32_t)v) : 0u; });
   };
   // per-core set-up (labels of N(core), type counts, M, W) and tear-down
   auto core_setup = [&](int32_t c) {
@@ -656,10 +744,10 @@ __global__ __launch_bounds__(BLOCK) void kr_kernel(DevGraph G, const uint16_t* _
     bar<GL>();
     flat_rows(
         dcn, [&](int32_t i) { return (int32_t)(G.gs_idx[ca + i] & kIdMask); },
-        [&](int32_t y, uint32_t f, uint32_t) {
+        [&](int32_t y, uint32_t f, uint32_t Ly) {
           const int32_t x = (int32_t)(f & kIdMask);
           if (x == c) return;
-          const uint32_t r = f >> kTypeShift, ty = lab.get((uint32_t)y) & 3u;
+          const uint32_t r = f >> kTypeShift, ty = (K == 4 ? Ly : lab.get((uint32_t)y)) & 3u;
           const int32_t h = hub(x);
           if (h >= 0) atomicAdd(&W[h * 9 + (ty - 1) * 3 + (r - 1)], 1u);
           else atomicAdd(&wrow(x)[(ty - 1) * 3 + (r - 1)], 1u);
@@ -704,15 +792,16 @@ __global__ __launch_bounds__(BLOCK) void kr_kernel(DevGraph G, const uint16_t* _
     bar<GL>();
   };
 
-  // One anchor: core c, sides s0 and s1 whose labels are set.
+  // One anchor: core c, sides s0 (and s1 for k = 5) whose labels are set.
   auto anchor = [&](int32_t c, int32_t s0, int32_t s1, uint32_t base) {
     auto EDGE = [&](uint32_t bs, uint32_t Lx, uint32_t Ly, uint32_t r, u64 w) {
-      edge(bs, Lx, Ly, r, w);
+      if constexpr (K == 4) edge4(bT, bs, Lx, Ly, r, w);
+      else edge(bs, Lx, Ly, r, w);
     };
     const int32_t a0 = G.gs_off[s0], d0 = G.gs_off[s0 + 1] - a0;
-    const int32_t a1 = G.gs_off[s1], d1 = G.gs_off[s1 + 1] - a1;
-    const int32_t nsides = 2;
-    auto is_side = [&](int32_t y) { return y == s0 || y == s1; };
+    const int32_t a1 = K == 5 ? G.gs_off[s1] : 0, d1 = K == 5 ? G.gs_off[s1 + 1] - a1 : 0;
+    const int32_t nsides = K == 5 ? 2 : 1;
+    auto is_side = [&](int32_t y) { return y == s0 || (K == 5 && y == s1); };
     // list position -> vertex q of R' (each once); the O(1) part per q:
     // set sizes and the edges p -> q counted in W[q]
     auto pick = [&](int32_t i) -> int32_t {
@@ -743,13 +832,13 @@ __global__ __launch_bounds__(BLOCK) void kr_kernel(DevGraph G, const uint16_t* _
       return q;
     };
     // one edge q -> y of N+(q) with q in R'
-    auto visit = [&](int32_t q, uint32_t f, uint32_t) {
+    auto visit = [&](int32_t q, uint32_t f, uint32_t Lrow) {
       const int32_t y = (int32_t)(f & kIdMask);
       if (y == c) return;
       const uint32_t Ly = lab.get((uint32_t)y);
       const bool sy = is_side(y);
       if (!Ly && !sy) return;
-      const uint32_t Lq = lab.get((uint32_t)q);
+      const uint32_t Lq = K == 4 ? Lrow : lab.get((uint32_t)q);
       const bool mq = !is_side(q), my = !sy;
       const uint32_t r = f >> kTypeShift, cq = Lq & 3u, cy = Ly & 3u;
       // (cq, cy) takes -1, and +1 back when p = q is also counted in W[y]
@@ -775,16 +864,246 @@ __global__ __launch_bounds__(BLOCK) void kr_kernel(DevGraph G, const uint16_t* _
       for (int L = 4 + a; L < NL; L += 4) v -= cnt[L];
       // the type of each side towards the core sits in its own label
       const uint32_t t0 = lab.get((uint32_t)s0) & 3u;
-      const uint32_t t1 = lab.get((uint32_t)s1) & 3u;
-      v -= (t0 == (uint32_t)a) + (t1 == (uint32_t)a);
+      const uint32_t t1 = K == 5 ? lab.get((uint32_t)s1) & 3u : 0u;
+      v -= (t0 == (uint32_t)a) + (K == 5 && t1 == (uint32_t)a);
       cnt[a] = v;
     }
     bar<GL>();
-    closed_form<K, NL, BLOCK>(hist, lut, cnt, nzl, &nz_count, base);
+    if constexpr (K == 4) {  // every pair once: some moves sit on empty sets
+      for (int32_t t = threadIdx.x; t < kPairs4; t += BLOCK) t_close(cnt, bT, base, t, true);
+    } else {
+      closed_form<K, NL, BLOCK>(hist, lut, cnt, nzl, &nz_count, base);
+    }
     bar<GL>();
     if (threadIdx.x < NL) cnt[threadIdx.x] = 0;
   };
 
+  // Light k = 4 anchor {c, s} (d*(s) <= lim.light) on one wave.  The types
+  // of N(s) towards s sit in a wave-private hash table instead of the dense
+  // labels (which then hold only the core's types), so the waves of the
+  // workgroup take different anchors of the same core at the same time with
+  // no workgroup barrier.  Entry i of s's row stands for R' member i, the
+  // entry of c standing for s itself, and R' is taken 64 members at a time:
+  // one lane per member, their N+ rows laid end to end over the wave.  Same
+  // sums as anchor().
+  auto wave_anchor4 = [&](int32_t c, int32_t s, uint32_t base) {
+    const int32_t lane = (int32_t)(threadIdx.x & 63u);
+    uint32_t* H = wh + (threadIdx.x >> 6) * WH;
+    int32_t* cn = wcnt + (threadIdx.x >> 6) * NL;
+    uint32_t* E = wT + (threadIdx.x >> 6) * TW;
+    for (int32_t i = lane; i < TW / 4; i += 64) reinterpret_cast<uint4*>(E)[i] = make_uint4(0u, 0u, 0u, 0u);
+    const int32_t a0 = G.gs_off[s], d0 = G.gs_off[s + 1] - a0;
+    const uint32_t Ls = lab.get((uint32_t)s) & 3u;
+    for (int32_t i = lane; i < d0; i += 64) {
+      const uint32_t e = G.gs_idx[a0 + i];
+      const int32_t q = (int32_t)(e & kIdMask);
+      if (q == c) continue;
+      uint32_t h = hash_slot(q);
+      const uint32_t ent = ((uint32_t)q << 2) | (e >> kTypeShift);  // q < 2^30 - 1: never kEmptySlot
+      while (atomicCAS(&H[h], kEmptySlot, ent) != kEmptySlot) h = (h + 1) & (kWaveHash - 1);
+    }
+    wave_sync();  // hash table complete
+    for (int32_t i0 = 0; i0 < d0; i0 += 64) {
+      const int32_t i = i0 + lane;
+      int32_t q = -1;
+      uint32_t Lq = 0;
+      int32_t len = 0, rb = 0;
+      if (i < d0) {
+        const uint32_t e = G.gs_idx[a0 + i];
+        q = (int32_t)(e & kIdMask);
+        bool mq = true;
+        if (q == c) {
+          q = s;
+          Lq = Ls;
+          mq = false;
+        } else {
+          Lq = (lab.get((uint32_t)q) & 3u) | ((e >> kTypeShift) << 2);
+          atomicAdd(&cn[Lq], 1);
+        }
+        const uint32_t cq = Lq & 3u;
+        const Row9 wq = load_w(q);
+#pragma unroll
+        for (int tr = 0; tr < 9; ++tr) {
+          const uint32_t w = wq.v[tr];
+          if (!w) continue;
+          const uint32_t tp = (uint32_t)(tr / 3) + 1u, r = (uint32_t)(tr % 3) + 1u;
+          if (cq) edge4(E, base, tp, cq, r, (u64)0 - (u64)w);
+          if (mq) edge4(E, base, tp, Lq, r, (u64)w);
+        }
+        rb = G.np_off[q];
+        len = G.np_off[q + 1] - rb;
+      }
+      int32_t inc = len;
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) {
+        const int32_t t = __shfl_up(inc, d);
+        if (lane >= d) inc += t;
+      }
+      const int32_t tot = __shfl(inc, 63);
+      const int32_t rs = rb - (inc - len);  // flat entry j of this lane's row is np_idx[rs + j]
+      for (int32_t jb = 0; jb < tot; jb += 64 * kUnroll) {
+        int32_t sqs[kUnroll];
+        uint32_t sLs[kUnroll], fs[kUnroll];
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+          const int32_t j = jb + u * 64 + lane;
+          int32_t sl = 0;  // number of lanes whose rows end at or before j
+#pragma unroll
+          for (int st2 = 32; st2; st2 >>= 1)
+            if (__shfl(inc, sl + st2 - 1) <= j) sl += st2;
+          sqs[u] = __shfl(q, sl);
+          sLs[u] = (uint32_t)__shfl((int32_t)Lq, sl);
+          const int32_t srs = __shfl(rs, sl);
+          fs[u] = j < tot ? G.np_idx[srs + j] : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+          const int32_t j = jb + u * 64 + lane;
+          if (j >= tot) continue;
+          const int32_t sq = sqs[u];
+          const uint32_t sL = sLs[u], f = fs[u];
+          const int32_t y = (int32_t)(f & kIdMask);
+          if (y != c) {
+            const bool sy = y == s;
+            uint32_t Ly = lab.get((uint32_t)y) & 3u;
+            if (!sy) {
+              uint32_t h = hash_slot(y);
+              for (;;) {
+                const uint32_t e = H[h];
+                if (e == kEmptySlot) break;
+                if ((e >> 2) == (uint32_t)y) {
+                  Ly |= (e & 3u) << 2;
+                  break;
+                }
+                h = (h + 1) & (kWaveHash - 1);
+              }
+            }
+            if (Ly || sy) {
+              const bool mq = sq != s, my = !sy;
+              const uint32_t r = f >> kTypeShift, cq = sL & 3u, cy = Ly & 3u;
+              // (cq, cy) takes -1, and +1 back when p = sq is also counted in
+              // W[y] (y a side neighbour or the side): only the net is added
+              const bool inw = sy || (Ly >> 2);
+              if (cq && cy && !inw) edge4(E, base, cq, cy, r, kMinusOne);
+              if (mq && my) edge4(E, base, sL, Ly, r, 1ull);
+              if (cq && my && inw) edge4(E, base, cq, Ly, r, kMinusOne);
+            }
+          }
+        }
+      }
+    }
+    // edges inside N(core) with core-only labels
+    if (lane < 27) {
+      const uint32_t w = Mc[lane];
+      if (w) edge4(E, base, (uint32_t)lane / 9 + 1, ((uint32_t)lane / 3) % 3 + 1, (uint32_t)lane % 3 + 1, (u64)w);
+    }
+    wave_sync();
+    // sizes of the core-only sets: N(core) minus s minus R'
+    if (lane >= 1 && lane <= 3) {
+      int32_t v = ncore[lane];
+      for (int L = 4 + lane; L < NL; L += 4) v -= cn[L];
+      v -= (int32_t)(Ls == (uint32_t)lane);
+      cn[lane] = v;
+    }
+    wave_sync();
+    for (int32_t t = lane; t < kPairs4; t += 64) t_close(cn, E, base, t, false);
+    wave_sync();
+    if (lane < NL) cn[lane] = 0;
+    for (int32_t i = lane; i < WH; i += 64) H[i] = kEmptySlot;
+    wave_sync();
+  };
+  // Solo k = 4 anchor {c, s} with d*(c) <= lim.solo on one wave: the plain
+  // per-anchor method (as in k4_kernel) with the labels of N(c) u N(s) in a
+  // wave-private hash (keys, then complemented label bits, in the wave's
+  // table), so small cores need no workgroup set-up at all.  Members are the
+  // hash entries; each member's N+ row is scanned and every labelled
+  // neighbour is an inner edge; then the closed form over the 15 sets.
+  auto wave_solo4 = [&](int32_t c, int32_t s, uint32_t base) {
+    const int32_t lane = (int32_t)(threadIdx.x & 63u);
+    uint32_t* key = wh + (threadIdx.x >> 6) * WH;
+    uint32_t* nlab = key + kSoloHash;
+    int32_t* cn = wcnt + (threadIdx.x >> 6) * NL;
+    uint32_t* E = wT + (threadIdx.x >> 6) * TW;
+    for (int32_t i = lane; i < TW / 4; i += 64) reinterpret_cast<uint4*>(E)[i] = make_uint4(0u, 0u, 0u, 0u);
+    auto slot = [](uint32_t x) { return (x * 2654435761u) >> (32 - kSoloHashBits); };
+    auto insert = [&](uint32_t x, uint32_t bits) {
+      uint32_t h = slot(x);
+      for (;;) {
+        const uint32_t old = atomicCAS(&key[h], kEmptySlot, x);
+        if (old == kEmptySlot || old == x) {
+          atomicAnd(&nlab[h], ~bits);
+          return;
+        }
+        h = (h + 1) & (kSoloHash - 1);
+      }
+    };
+    const int32_t ca = G.gs_off[c], dc = G.gs_off[c + 1] - ca;  // dc <= lim.solo <= 64
+    if (lane < dc) {
+      const uint32_t e = G.gs_idx[ca + lane];
+      if ((int32_t)(e & kIdMask) != s) insert(e & kIdMask, e >> kTypeShift);
+    }
+    wave_sync();
+    const int32_t sa = G.gs_off[s], ds = G.gs_off[s + 1] - sa;  // ds <= dc
+    if (lane < ds) {
+      const uint32_t e = G.gs_idx[sa + lane];
+      if ((int32_t)(e & kIdMask) != c) insert(e & kIdMask, (e >> kTypeShift) << 2);
+    }
+    wave_sync();
+    for (int32_t i0 = 0; i0 < kSoloHash; i0 += 64) {
+      const uint32_t xk = key[i0 + lane];
+      uint32_t Lx = 0;
+      int32_t len = 0, rb = 0;
+      if (xk != kEmptySlot) {
+        Lx = ~nlab[i0 + lane];
+        atomicAdd(&cn[Lx], 1);
+        rb = G.np_off[xk];
+        len = G.np_off[xk + 1] - rb;
+      }
+      int32_t inc = len;
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) {
+        const int32_t t = __shfl_up(inc, d);
+        if (lane >= d) inc += t;
+      }
+      const int32_t tot = __shfl(inc, 63);
+      const int32_t rs = rb - (inc - len);
+      for (int32_t jb = 0; jb < tot; jb += 64 * kUnroll) {
+        uint32_t sLs[kUnroll], fs[kUnroll];
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+          const int32_t j = jb + u * 64 + lane;
+          int32_t sl = 0;
+#pragma unroll
+          for (int st2 = 32; st2; st2 >>= 1)
+            if (__shfl(inc, sl + st2 - 1) <= j) sl += st2;
+          sLs[u] = (uint32_t)__shfl((int32_t)Lx, sl);
+          const int32_t srs = __shfl(rs, sl);
+          fs[u] = j < tot ? G.np_idx[srs + j] : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+          if (jb + u * 64 + lane >= tot) continue;
+          const uint32_t f = fs[u], y = f & kIdMask;
+          uint32_t h = slot(y);
+          for (;;) {
+            const uint32_t kk = key[h];
+            if (kk == kEmptySlot) break;
+            if (kk == y) {
+              edge4(E, base, sLs[u], ~nlab[h], f >> kTypeShift, 1ull);
+              break;
+            }
+            h = (h + 1) & (kSoloHash - 1);
+          }
+        }
+      }
+    }
+    wave_sync();
+    for (int32_t t = lane; t < kPairs4; t += 64) t_close(cn, E, base, t, false);
+    wave_sync();
+    if (lane < NL) cn[lane] = 0;
+    for (int32_t i = lane; i < WH; i += 64) key[i] = kEmptySlot;
+    wave_sync();
+  };
   // ---- k = 5, light partners: the side-a part shared by a unit's triples --
   //
   // For a unit (b = core, a) the triples (b; a, c) with a light partner c
@@ -1046,6 +1365,24 @@ __global__ __launch_bounds__(BLOCK) void kr_kernel(DevGraph G, const uint16_t* _
     cn[lane] = 0;
     wave_sync();
   };
+  // A unit of a new core: flush the histogram on a graph change and set up
+  // the core's tables (the previous core's are torn down first).  The graph
+  // is checked even for the current core: the small-core pass of a tile may
+  // have moved the histogram to another graph in between.
+  auto enter_core = [&](int32_t c) {
+    const int32_t g = G.gid ? G.gid[c] : 0;
+    if (g != cur_g) {
+      hist_flush<C, BLOCK>(hist, acc, cur_g);
+      cur_g = g;
+      bar<GL>();
+    }
+    if (c == core) return;
+    if (core >= 0) core_teardown(core);
+    wbase = G.voff ? G.voff[g] : 0;
+    lab.base = (uint32_t)wbase;  // the previous core's labels are cleared
+    core = c;
+    core_setup(c);
+  };
 
   // One pull of the cost-cut work queue by wave 0: [sh_j0, sh_j1) are the
   // entries whose cost prefix lies in the pulled interval (sh_j0 = -1 once
@@ -1095,7 +1432,149 @@ __global__ __launch_bounds__(BLOCK) void kr_kernel(DevGraph G, const uint16_t* _
     }
   };
 
-  // Tiles of units cut by estimated cost (UnitCost5), about
+  if constexpr (K == 4) {
+    // Tiles of G* entries cut by estimated cost: cpre is the exclusive prefix
+    // sum of a per-entry cost (UnitCost4), and a tile is the run of
+    // entries whose prefix falls in one cost interval of the queue, about
+    // `tile` tiles per workgroup.  Within a tile, the entries of one core
+    // row are sorted into heavy units (whole workgroup, one after another)
+    // and light units (one wave each).
+    const int32_t tot_cost = cpre[total];
+    const int64_t parts = (int64_t)gridDim.x * (tile > 0 ? tile : 1);
+    const int32_t tc = (int32_t)max((int64_t)kMinTileCost4, ((int64_t)tot_cost + parts - 1) / parts);
+    // The last quarter of the cost is cut four times finer (second counter),
+    // so the tiles still running at the end are small.
+    const int32_t split = tot_cost - tot_cost / 4, tc_end = max(1, tc / 4);
+    for (;;) {
+      pull_tile(tot_cost, tc, split, tc_end);
+      bar<GL>();
+      const int32_t j0 = sh_j0, j1 = sh_j1;
+      bar<GL>();
+      if (j0 < 0) break;
+      if (j0 >= j1) continue;
+      // units of small cores: one wave each, no core set-up, in chunks of
+      // BLOCK entries of one graph
+      for (int32_t jc = j0; jc < j1;) {
+        int32_t jce = min(j1, jc + BLOCK);
+        const int32_t g = G.gid ? G.gid[G.gs_row[jc]] : 0;
+        if (G.gid) jce = min(jce, G.gs_off[(int32_t)G.voff[g + 1]]);
+        if (g != cur_g) {
+          hist_flush<C, BLOCK>(hist, acc, cur_g);
+          cur_g = g;
+        }
+        if (threadIdx.x < 2) unit_ctr[threadIdx.x] = 0;
+        bar<GL>();
+        {
+          const int32_t j = jc + (int32_t)threadIdx.x;
+          if (j < jce) {
+            const int32_t c = G.gs_row[j];
+            const int32_t dc = G.gs_off[c + 1] - G.gs_off[c];
+            if (dc <= lim.solo) {
+              const int32_t x = (int32_t)(G.gs_idx[j] & kIdMask), dx = G.gs_off[x + 1] - G.gs_off[x];
+              if (dx < dc || (dx == dc && x < c)) unit_list[atomicAdd(&unit_ctr[0], 1)] = j;
+            }
+          }
+        }
+        bar<GL>();
+        const int32_t nsolo = unit_ctr[0];
+        for (;;) {
+          int32_t u = 0;
+          if ((threadIdx.x & 63u) == 0) u = atomicAdd(&unit_ctr[1], 1);
+          u = __shfl(u, 0);
+          if (u >= nsolo) break;
+          const int32_t j = unit_list[u];
+          const uint32_t ej = G.gs_idx[j];
+          const uint32_t tcx = ej >> kTypeShift;
+          wave_solo4(G.gs_row[j], (int32_t)(ej & kIdMask),
+                     ((tcx & 1u) ? 1u << cbit<K>(0, 1) : 0u) | ((tcx & 2u) ? 1u << cbit<K>(1, 0) : 0u));
+        }
+        bar<GL>();
+        jc = jce;
+      }
+      // units of the other cores, one core row at a time
+      row = G.gs_row[j0];
+      for (int32_t js = j0; js < j1;) {
+        while (G.gs_off[row + 1] <= js) ++row;
+        const int32_t c = row;
+        const int32_t rowa = G.gs_off[c], rowb = G.gs_off[c + 1];
+        if (rowb - rowa <= lim.solo) {  // taken above
+          js = min(j1, rowb);
+          continue;
+        }
+        const int32_t je = min(min(j1, rowb), js + BLOCK);
+        if (threadIdx.x < 3) unit_ctr[threadIdx.x] = 0;
+        if (threadIdx.x < 32) lbk[threadIdx.x] = 0;
+        bar<GL>();
+        {
+          // heavy units to the front of the list; light units to the back,
+          // counted per log2 of the side's degree and then placed largest
+          // bucket first, so the waves take the long anchors first
+          const int32_t j = js + (int32_t)threadIdx.x;
+          int32_t bk = -1;
+          if (j < je) {
+            const int32_t x = (int32_t)(G.gs_idx[j] & kIdMask);
+            const int32_t dc = rowb - rowa, dx = G.gs_off[x + 1] - G.gs_off[x];
+            if (dx < dc || (dx == dc && x < c)) {  // anchor edge {c, x} owned by its higher-rank end
+              if (dx > lim.light) {
+                unit_list[atomicAdd(&unit_ctr[0], 1)] = j;
+              } else {
+                bk = 31 - __clz(max(dx, 1));  // 0 .. 8
+                atomicAdd(&unit_ctr[1], 1);
+                atomicAdd(&lbk[bk], 1);
+              }
+            }
+          }
+          bar<GL>();
+          if (bk >= 0) {
+            int32_t pos = 0;
+            for (int32_t b2 = bk + 1; b2 < 16; ++b2) pos += lbk[b2];
+            pos += atomicAdd(&lbk[16 + bk], 1);
+            unit_list[BLOCK - 1 - pos] = j;
+          }
+        }
+        bar<GL>();
+        const int32_t nheavy = unit_ctr[0], nlight = unit_ctr[1];
+        if (nheavy + nlight > 0) {
+          enter_core(c);
+          for (int32_t u = 0; u < nheavy; ++u) {
+            const int32_t j = unit_list[u];
+            const uint32_t ej = G.gs_idx[j];
+            const int32_t x = (int32_t)(ej & kIdMask);
+            const uint32_t tcx = ej >> kTypeShift;
+            const int32_t xa = G.gs_off[x], xb = G.gs_off[x + 1];
+            for (int32_t i = xa + threadIdx.x; i < xb; i += BLOCK) {
+              const uint32_t e = G.gs_idx[i];
+              if ((int32_t)(e & kIdMask) != c) lab.set_bits(e & kIdMask, (e >> kTypeShift) << 2);
+            }
+            bar<GL>();
+            anchor(c, x, -1, ((tcx & 1u) ? 1u << cbit<K>(0, 1) : 0u) | ((tcx & 2u) ? 1u << cbit<K>(1, 0) : 0u));
+            for (int32_t i = xa + threadIdx.x; i < xb; i += BLOCK) {
+              const uint32_t e = G.gs_idx[i];
+              if ((int32_t)(e & kIdMask) != c) lab.clear_bits(e & kIdMask, 3u << 2);
+            }
+            bar<GL>();
+          }
+          for (;;) {  // light units are handed to the waves one at a time
+            int32_t u = 0;
+            if ((threadIdx.x & 63u) == 0) u = atomicAdd(&unit_ctr[2], 1);
+            u = __shfl(u, 0);
+            if (u >= nlight) break;
+            const uint32_t ej = G.gs_idx[unit_list[BLOCK - 1 - u]];
+            const uint32_t tcx = ej >> kTypeShift;
+            wave_anchor4(c, (int32_t)(ej & kIdMask),
+                         ((tcx & 1u) ? 1u << cbit<K>(0, 1) : 0u) | ((tcx & 2u) ? 1u << cbit<K>(1, 0) : 0u));
+          }
+          bar<GL>();
+        }
+        js = je;
+      }
+    }
+    if (core >= 0) core_teardown(core);
+    hist_flush<C, BLOCK>(hist, acc, cur_g);
+    return;
+  }
+
+  // Tiles of units cut by estimated cost (UnitCost5) as for k = 4, about
   // `tile` per workgroup, the last quarter four times finer: the units of a
   // light core stay together (one core set-up), a heavy core's are spread.
   const int32_t tot_cost = cpre[total];
@@ -1116,8 +1595,14 @@ __global__ __launch_bounds__(BLOCK) void kr_kernel(DevGraph G, const uint16_t* _
       const int32_t rowa = G.gs_off[c], rowb = G.gs_off[c + 1];
       const uint32_t ej = G.gs_idx[j];
       const int32_t x = (int32_t)(ej & kIdMask);
-      // unit (b = c, a = x) with the neighbours of b of lower rank than x as partners
-      if (rowb - rowa < 2) continue;
+      bool unit;
+      if (K == 4) {  // anchor edge {c, x} owned by its higher-rank end
+        const int32_t dc = rowb - rowa, dx = G.gs_off[x + 1] - G.gs_off[x];
+        unit = dx < dc || (dx == dc && x < c);
+      } else {  // unit (b = c, a = x) with the neighbours of b of lower rank than x as partners
+        unit = rowb - rowa >= 2;
+      }
+      if (!unit) continue;
       if (c != core) {
         if (core >= 0) core_teardown(core);
         const int32_t g = G.gid ? G.gid[c] : 0;
@@ -1139,7 +1624,10 @@ __global__ __launch_bounds__(BLOCK) void kr_kernel(DevGraph G, const uint16_t* _
         if ((int32_t)(e & kIdMask) != c) lab.set_bits(e & kIdMask, (e >> kTypeShift) << 2);
       }
       bar<GL>();
-      {
+      if (K == 4) {
+        const uint32_t base = ((tcx & 1u) ? 1u << cbit<K>(0, 1) : 0u) | ((tcx & 2u) ? 1u << cbit<K>(1, 0) : 0u);
+        anchor(c, x, -1, base);
+      } else {
         // partners: the neighbours c2 of b of lower rank (d*, id) than x, so
         // that of the two sides of a triple the heavier one is shared by the
         // unit and the lighter one is done per triple.  Scanned BLOCK at a
@@ -1375,10 +1863,25 @@ __global__ __launch_bounds__(BLOCK) void kr_kernel(DevGraph G, const uint16_t* _
   hist_flush<C, BLOCK>(hist, acc, cur_g);
 }
 
-// Per-entry cost estimate of the core-reuse kernel, for cutting its work queue
-// into tiles of similar cost; 0 past the last entry.  Clamped to cmax so that
-// the prefix sum stays below 2^31; any positive costs give a correct tiling.
-// The values are scanned as they are computed.  Every G* entry (b, a) is a unit
+// Per-entry cost estimate of the k = 4 core-reuse kernel, for cutting its
+// work queue into tiles of similar cost: 1 for an entry that is not a unit,
+// else a fixed part (larger for a heavy unit, which takes the whole
+// workgroup) plus a quarter of the side's degree; 0 past the last entry.
+// Clamped to cmax so that the prefix sum stays below 2^31; any positive costs
+// give a correct tiling.  The values are scanned as they are computed.
+struct UnitCost4 {
+  DevGraph G;
+  int32_t cmax, light_deg;
+  __device__ int32_t operator()(int64_t j) const {
+    if (j >= G.gs_off[G.n]) return 0;
+    const int32_t r = G.gs_row[j], x = (int32_t)(G.gs_idx[j] & kIdMask);
+    const int32_t dr = G.gs_off[r + 1] - G.gs_off[r], dx = G.gs_off[x + 1] - G.gs_off[x];
+    if (dx < dr || (dx == dr && x < r)) return min(cmax, (dx > light_deg ? 40 : 4) + (dx >> 2));
+    return 1;
+  }
+};
+
+// The same for the k = 5 core-reuse kernel: every G* entry (b, a) is a unit
 // whose partners are about half of b's row, taken in sub-chunks, so its cost
 // grows with d*(b); the fixed part covers the unit's labels and barriers.
 struct UnitCost5 {
@@ -1583,7 +2086,7 @@ size_t pipeline_bytes(int64_t N, int64_t M, int32_t G, bool batch, int k, int nu
                       const Tuning& t) {
   auto al = [](size_t b) { return (b + 255) & ~size_t(255); };
   size_t b = build_bytes(N, M, G, batch);
-  const bool reuse = k == 5 && t.heavy == 1;
+  const bool reuse = by_reuse(k, t);
   if (by_copies(k, t)) b += count_bytes(N, M, maxn > 0 ? maxn : N, batch, k == 4);
   if (reuse)
     b += al(sizeof(int32_t) * (N + 1)) + al(64 * sizeof(int32_t)) +
@@ -1611,21 +2114,21 @@ size_t pipeline_bytes(int64_t N, int64_t M, int32_t G, bool batch, int k, int nu
 #define LAUNCH_K4(BLOCK, CAP)                                                                                   \
   hipLaunchKernelGGL((k4_kernel<BLOCK, CAP>), dim3(grid), dim3(BLOCK), 0, s, g, T.lut[4], acc, p.status, queue, \
                      glabels, lw, t.tile)
-#define LAUNCH_KR(BLOCK, CAP)                                                                           \
-  hipLaunchKernelGGL((kr_kernel<BLOCK, CAP>), dim3(grid), dim3(BLOCK), 0, s, g, T.lut[5], acc, p.status, queue, \
+#define LAUNCH_KR(K, BLOCK, CAP)                                                                        \
+  hipLaunchKernelGGL((kr_kernel<K, BLOCK, CAP>), dim3(grid), dim3(BLOCK), 0, s, g, T.lut[K], acc, p.status, queue, \
                      glabels, lw, hub_id, wg, ws, t.tile, cpre, big_id, wbig, wbig_stride, mbig, lim)
 #define LAUNCH_K5(BLOCK, CAP)                                                                                   \
   hipLaunchKernelGGL((k5_kernel<BLOCK, CAP>), dim3(grid), dim3(BLOCK), 0, s, g, T.lut[5], acc, p.status, queue, \
                      glabels, lw, t.tile)
 
 size_t w_slice_bytes(int k, int64_t maxn, const Tuning& t, int num_cus) {
-  if (!(k == 5 && t.heavy == 1)) return 0;
+  if (!by_reuse(k, t)) return 0;
   return sizeof(uint32_t) * kBigRow * (size_t)(maxn > 0 ? maxn : 1) * (size_t)grid_size(t, num_cus);
 }
 
 BigTables take_big_tables(Pipeline& p, int k, int32_t n, int64_t maxn, const Tuning& t, ZeroBatch& z) {
   BigTables b;
-  const bool reuse = k == 5 && t.heavy == 1;
+  const bool reuse = by_reuse(k, t);
   b.nbig = reuse && n > 0 ? big_slots(maxn) : 0;
   if (b.nbig == 0) return b;
   const int64_t lstride = big_label_words(maxn), wstride = (int64_t)kBigRow * maxn;
@@ -1649,7 +2152,6 @@ void enqueue_census(Pipeline& p, const DevGraph& g, int k, uint64_t* acc, uint64
     *side_ok = hipEventRecord(side_start, s) == hipSuccess;
   };
   const DevTables& T = dev_tables();
-  const int C = num_classes(k);
   // every region the set-up needs cleared goes into one batch, launched
   // before the first kernel that reads any of them
   ZeroBatch z;
@@ -1658,7 +2160,8 @@ void enqueue_census(Pipeline& p, const DevGraph& g, int k, uint64_t* acc, uint64
   z.add(queue, 64 * sizeof(int32_t));
   const Tuning& t = p.tune.k[k];
   const int grid = grid_size(t, p.num_cus);
-  const Limits lim{std::min(t.light5, kLight5Max)};
+  const Limits lim{std::min(t.solo_deg, kSoloDegMax), std::min(t.light_deg, kLightDegMax),
+                   std::min(t.light5, kLight5Max)};
   bool marked = false;  // the profiling events bracket the main census kernel only
   if (g.n > 0) {
     if (by_copies(k, t)) {
@@ -1671,7 +2174,7 @@ void enqueue_census(Pipeline& p, const DevGraph& g, int k, uint64_t* acc, uint64
       enqueue_counts(p, g, k == 3 ? acc : acc3, k == 4 ? acc : nullptr, queue, s);
       if (acc3) profile_mark(3, 1, false, s);
     } else {
-      const bool reuse = k == 5 && t.heavy == 1;
+      const bool reuse = by_reuse(k, t);
       // labels are indexed within one graph (Labels::base): room for the largest
       const int32_t ln = g.max_graph_n > 0 ? g.max_graph_n : g.n;
       const int cap = k == 4 ? label_cap_k4(ln) : label_cap_k5(ln);
@@ -1713,7 +2216,10 @@ void enqueue_census(Pipeline& p, const DevGraph& g, int k, uint64_t* acc, uint64
         hipLaunchKernelGGL(k_assign_hubs, dim3(blocks_for(g.n, 256)), dim3(256), 0, s, g.gs_off, g.n, hs, hub_id,
                            nbig, big_id, big_list, p.status);
         const int32_t cmax = cost_cap(g.gs_cap);
-        enqueue_scan1(sc_cost, cost, UnitCost5{g, cmax}, p.status, s);
+        if (k == 4)
+          enqueue_scan1(sc_cost, cost, UnitCost4{g, cmax, lim.light}, p.status, s);
+        else
+          enqueue_scan1(sc_cost, cost, UnitCost5{g, cmax}, p.status, s);
         if (nbig > 0)
           hipLaunchKernelGGL(k_big_labels, dim3(16, nbig), dim3(256), 0, s, g, hs, big_list, lbig, lstride, p.status);
         fork_side();
@@ -1726,7 +2232,12 @@ void enqueue_census(Pipeline& p, const DevGraph& g, int k, uint64_t* acc, uint64
       fork_side();
       profile_mark(k, 1, true, s);
       marked = true;
-      if (k == 4) {
+      if (k == 4 && reuse) {
+        if (cap != 8192) throw WorkspaceError();  // (never: graphs of at most kReuse4N vertices come here)
+        if (t.block == 512) LAUNCH_KR(4, 512, 8192);
+        else if (t.block == 1024) LAUNCH_KR(4, 1024, 8192);
+        else LAUNCH_KR(4, 256, 8192);
+      } else if (k == 4) {
         if (t.block == 512) {
           if (cap == 8192) LAUNCH_K4(512, 8192); else if (cap == 65536) LAUNCH_K4(512, 65536); else LAUNCH_K4(512, 0);
         } else if (t.block == 1024) {
@@ -1736,9 +2247,9 @@ void enqueue_census(Pipeline& p, const DevGraph& g, int k, uint64_t* acc, uint64
         }
       } else if (reuse) {
         if (t.block == 512) {
-          if (cap == 16384) LAUNCH_KR(512, 16384); else if (cap == 32768) LAUNCH_KR(512, 32768); else LAUNCH_KR(512, 0);
+          if (cap == 16384) LAUNCH_KR(5, 512, 16384); else if (cap == 32768) LAUNCH_KR(5, 512, 32768); else LAUNCH_KR(5, 512, 0);
         } else {
-          if (cap == 16384) LAUNCH_KR(1024, 16384); else if (cap == 32768) LAUNCH_KR(1024, 32768); else LAUNCH_KR(1024, 0);
+          if (cap == 16384) LAUNCH_KR(5, 1024, 16384); else if (cap == 32768) LAUNCH_KR(5, 1024, 32768); else LAUNCH_KR(5, 1024, 0);
         }
       } else {
         if (t.block == 512) {

@@ -116,10 +116,12 @@ struct Tuning {
   int grid_per_cu = 4;
   int tile = 16;
   int heavy = 1;  // census scheme for k = 4, 5: 1 = subgraph copies or core reuse, 0 = per-anchor scan
-  int solo_deg = 64;    // k = 4: kept for callers and tuning files, no effect (1..64)
-  int light_deg = 192;  // the same (1..256)
-  // Work-placement limit of the core-reuse kernel (degree in G*):
+  // Work-placement limits of the core-reuse kernels (degrees in G*):
+  int solo_deg = 64;    // k = 4: cores of at most this degree run whole anchors on one wave (<= 64)
+  int light_deg = 192;  // k = 4: sides of at most this degree run on one wave (<= 256)
   int light5 = 512;     // k = 5: lighter sides of at most this degree take the factored path (<= 767)
+  // k = 4 with heavy = 1: subgraph copies, else core reuse; set for each call from its sizes
+  bool copies = true;
 };
 // The tuning of every k, copied once per call so that a concurrent
 // motif_set_tuning() or autotune never changes a call between the sizing of
@@ -128,11 +130,15 @@ struct TuningSet {
   Tuning k[6];
 };
 TuningSet tuning_snapshot();
-// The tuning a call uses on device `dev`: the defaults (for a batch whose
-// graphs have at most max_n >= 0 vertices, the small-graph batch default of
-// k = 4 where it applies), with the autotuner's cached entry for (k, batch,
-// floor(log2 arcs)) in place of k's when there is one, for each of ks[0..nk).
-TuningSet tuning_for_call(int dev, int32_t nk, const int32_t* ks, bool batch, int64_t arcs, int64_t max_n = -1);
+// The tuning a call uses on device `dev` for graphs of at most max_n vertices
+// and `arcs` arcs in all: the defaults (for a batch the small-graph batch
+// default of k = 4 where it applies), with the autotuner's cached entry for (k,
+// batch, floor(log2 arcs)) in place of k's when there is one, for each of
+// ks[0..nk); and whether k = 4 is counted by copies.
+TuningSet tuning_for_call(int dev, int32_t nk, const int32_t* ks, bool batch, int64_t arcs, int64_t max_n);
+// Whether a k = 4 census (nk sizes in all) counts subgraph copies (counts.hip)
+// or reuses the cores (kr_kernel<4>).
+bool copies4_pays(int32_t nk, bool batch, int64_t arcs, int64_t max_n);
 
 // Buffers of one census pipeline (one stream).
 struct Pipeline {
@@ -152,7 +158,7 @@ struct Pipeline {
   bool may_fork = true;   // false: nothing may be allocated, those stay unmade
   bool fork_now = false;  // this call waits on the host and is not captured: its kernels may use them
   TuningSet tune;  // the tuning this call was sized with (set before any enqueue)
-  // Per-workgroup W rows of the k = 5 core-reuse kernel for the census
+  // Per-workgroup W rows of the k = 4, 5 core-reuse kernels for the census
   // on this pipeline's own stream: zeroed once when allocated, and left zero
   // by every census (each core's tear-down clears the rows it touched), so
   // no call has to clear them.  Null where the W rows come from the arena.
@@ -219,7 +225,7 @@ void enqueue_check_in(const BuildInput& in, const DevGraph& g, const InCheck& c,
 // p.wpool (only for work on the pipeline's own stream, one census at a time).
 struct ZeroBatch;
 
-// Big-core tables of a k = 5 core-reuse census (nbig = 0: none).
+// Big-core tables of a k = 4, 5 core-reuse census (nbig = 0: none).
 struct BigTables {
   int nbig = 0;
   int32_t* big_id = nullptr;    // [n + 1]
@@ -271,8 +277,10 @@ size_t copies5_bytes(int64_t n, int64_t m, bool lean);
 void enqueue_copies5_start(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_t* a4, Copies5Run* R, hipStream_t s);
 bool copies5_go(const Pipeline& p, int64_t m);
 void enqueue_copies5_finish(Pipeline& p, const DevGraph& g, const Copies5Run& R, uint64_t* out, hipStream_t s);
-// Whether k's census under tuning t counts subgraph copies.
-inline bool by_copies(int k, const Tuning& t) { return k == 3 || (k == 4 && t.heavy == 1); }
+// Whether k's census under tuning t counts subgraph copies, or reuses the cores
+// (k = 5 here: the calls that copies5 leaves out).
+inline bool by_copies(int k, const Tuning& t) { return k == 3 || (k == 4 && t.heavy == 1 && t.copies); }
+inline bool by_reuse(int k, const Tuning& t) { return t.heavy == 1 && (k == 5 || (k == 4 && !t.copies)); }
 // Copies of a single graph's totals (a workgroup adds to one of them).
 constexpr int kRep3 = 16, kRep4 = 64;
 // Words of the accumulators of a census of k over ngraphs graphs.
@@ -310,7 +318,7 @@ int32_t enqueue_anchors6(const DevGraph& g, int4* out, unsigned long long* ctr, 
 // `grid` zeroed slices of label_words words).
 void enqueue_census6(const DevGraph& g, const int4* anchors, int64_t nanchors, const Tables6& T, uint64_t* acc,
                      uint32_t* labels, int64_t label_words, int grid, int32_t* status, hipStream_t s);
-// Bytes of the per-workgroup W rows of a k = 5 core-reuse census (0 otherwise).
+// Bytes of the per-workgroup W rows of a k = 4, 5 core-reuse census (0 otherwise).
 size_t w_slice_bytes(int k, int64_t maxn, const Tuning& t, int num_cus);
 
 // Pack `count` device graphs into one union CSR inside the arena.

@@ -198,7 +198,7 @@ int64_t motif_request_footprint(int32_t n, int64_t m, int32_t k) {
   if (n < 0 || m < 0 || n >= kMaxN || m >= kMaxN) return MOTIF_EINVAL_SHAPE;
   int dev = 0;
   if (ensure_init(&dev)) return MOTIF_EDEVICE;
-  return (int64_t)request_bytes(n, m, k, device_cus(dev), tuning_for_call(dev, 1, &k, false, m).k[k]);
+  return (int64_t)request_bytes(n, m, k, device_cus(dev), tuning_for_call(dev, 1, &k, false, m, n).k[k]);
 }
 
 motif_server_t* motif_server_create(size_t hbm_budget_bytes, int32_t max_inflight) {
@@ -231,7 +231,7 @@ int32_t motif_server_submit(motif_server_t* s, const motif_graph_t* g, int32_t k
   r->n = g->n;
   r->m = g->m;
   r->hist_out = hist_out_host;
-  r->tune = tuning_for_call(s->device, 1, &k, false, g->m);
+  r->tune = tuning_for_call(s->device, 1, &k, false, g->m, g->n);
   r->footprint = request_bytes(g->n, g->m, k, s->cus, r->tune.k[k]);
   if (r->footprint > s->budget) {
     delete r;
