@@ -416,10 +416,12 @@ size_t copies5_need(const BuildInput& in, bool lean = false) {
 }
 
 // The sizes ks (5 among them) of one graph by subgraph copies, with a host wait
-// in the middle.  kNotTaken: not by this way (other scheme asked for, no room
-// in the workspace, or more triangles than the links have room for); no output
-// is written then and the caller starts over.  und: 5 alone, hists[0] receives
-// the undirected census.
+// in the middle.  Where the graph has more triangles than the links have room
+// for, the other sizes are done all the same and k = 5 reuses the cores of the
+// graph that is built (n = 100 with 3,286 arcs: 2,060 us by the cores alone, 2,263
+// so, 2,456 when everything started over).  kNotTaken: not by this way (other
+// scheme asked for, or no room in the workspace); nothing is enqueued then.
+// und: 5 alone, hists[0] receives the undirected census.
 constexpr int32_t kNotTaken = 1;
 int32_t run_copies5(Pipeline& p, const BuildInput& in, int32_t nk, const int32_t* ks, uint64_t* const* hists, bool und,
                     hipStream_t s) {
@@ -435,6 +437,7 @@ int32_t run_copies5(Pipeline& p, const BuildInput& in, int32_t nk, const int32_t
     DevGraph g = enqueue_build(p, in, s);
     if (und) enqueue_all_bidirected(g, s, p.status);
     for (int32_t i = 0; i < nk; ++i) profile_mark(ks[i], 0, false, s);
+    const size_t built = p.arena.mark();
     uint64_t* tmp = p.arena.take<uint64_t>((size_t)motif_num_classes(5));
     uint64_t* a3 = p.arena.take<uint64_t>((size_t)13 * kRep3);
     uint64_t* a4 = p.arena.take<uint64_t>((size_t)199 * kRep4);
@@ -444,16 +447,25 @@ int32_t run_copies5(Pipeline& p, const BuildInput& in, int32_t nk, const int32_t
     enqueue_copies5_start(p, g, a3, a4, &run, s);
     const int32_t rc = read_status(p, s);
     if (rc) return rc;
-    if (!copies5_go(p, in.m)) return kNotTaken;
+    const bool go = copies5_go(p, in.m);
+    if (run.counts.later && (go || nk > 1)) enqueue_counts_rest(p, g, a3, a4, run.queue, run.counts, s);
+    uint64_t* five = hists[0];
     for (int32_t i = 0; i < nk; ++i) {
-      if (ks[i] == 5) continue;
+      if (ks[i] == 5) {
+        five = hists[i];
+        continue;
+      }
       enqueue_solve(ks[i], ks[i] == 3 ? a3 : a4, nullptr, hists[i], 1, p.status, s);
       profile_mark(ks[i], 1, false, s);
     }
-    for (int32_t i = 0; i < nk; ++i) {
-      if (ks[i] != 5) continue;
-      enqueue_copies5_finish(p, g, run, und ? tmp : hists[i], s);
+    if (go) {
+      enqueue_copies5_finish(p, g, run, und ? tmp : five, s);
       profile_mark(5, 1, false, s);
+    } else {  // (what was taken since is given back to work that comes after it on the stream)
+      p.arena.rewind(built);
+      tmp = p.arena.take<uint64_t>((size_t)motif_num_classes(5));
+      uint64_t* acc = p.arena.take<uint64_t>(acc_words(5, 1, p.tune.k[5]));
+      enqueue_census(p, g, 5, acc, und ? tmp : five, s, true);
     }
     if (und)
       enqueue_project_undirected(tmp, dev_tables().und_of[5], motif_num_classes(5),

@@ -1665,6 +1665,8 @@ size_t copies5_bytes(int64_t n, int64_t m, bool lean) {
 }
 
 constexpr int64_t kFewUnits = 512;
+// Arcs below which the wedges of k = 4 wait until the triangles are known to fit.
+constexpr int64_t kFewArcs = 32768;
 
 void enqueue_copies5_start(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_t* a4, Copies5Run* R, hipStream_t s) {
   const int64_t n = g.n, m = (g.gs_cap - 1) / 2;
@@ -1687,6 +1689,8 @@ void enqueue_copies5_start(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_
   z.add(R->acc, sizeof(uint64_t) * kC5 * (size_t)shared_copies(m));
   z.add(R->tri, sizeof(uint32_t) * 27 * (size_t)n);
   enqueue_zero_batch(z, s);
+  // (above, the triangles run beside the wedges)
+  R->counts.later = m < kFewArcs;
   enqueue_counts(p, g, a3, a4, R->queue, s, &R->counts);
   hipLaunchKernelGGL(k_edges5, dim3((unsigned)std::min<int64_t>(4096, (m + 255) / 256 + 1)), dim3(256), 0, s, g,
                      R->counts.T, R->emap, R->cnt, R->epos, R->hi, R->queue, p.status);

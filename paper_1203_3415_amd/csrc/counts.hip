@@ -1429,6 +1429,45 @@ size_t count_bytes(int64_t n, int64_t m, int64_t maxn, bool batch, bool k4) {
   return b;
 }
 
+// The wedges, and (k_local) the vertices and edges, of a k = 4 pass: the latter
+// on ts, behind the triangles that they need.
+static void enqueue_wedges(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_t* a4, const int32_t* queue,
+                           const CountsOut& o, hipStream_t s, hipStream_t ts) {
+  const DevTables& T = dev_tables();
+  const int64_t n = g.n, m = (g.gs_cap - 1) / 2;
+  const int cus = p.num_cus;
+  const CountPlan c = count_plan(n, m, g.max_graph_n, g.gid != nullptr);
+  const int64_t n16 = std::min(n, m);
+  auto list_grid = [&](int64_t most, int per, int wgs) { return dim3(grid_of(most, per, (int64_t)cus * wgs)); };
+  // (the diamonds need the triangles only)
+  const dim3 lgrid(grid_of(n + m, 256, cus * 4));
+  if (a3)
+    hipLaunchKernelGGL((k_local<true, true>), lgrid, dim3(256), 0, ts, g, T.lut[3], T.lut[4], a3, a4, o.T, p.status);
+  else
+    hipLaunchKernelGGL((k_local<false, true>), lgrid, dim3(256), 0, ts, g, T.lut[3], T.lut[4], a3, a4, o.T, p.status);
+  hipLaunchKernelGGL((k_wedge<16, 7>), list_grid(n16, 16, 6), dim3(256), 0, s, g, T.lut[4], a4, p.status, queue,
+                     o.wedge[kWedge16]);
+  if (2 * m > kCap16)
+    hipLaunchKernelGGL((k_wedge<64, 9>), list_grid(n16, 4, 6), dim3(256), 0, s, g, T.lut[4], a4, p.status, queue,
+                       o.wedge[kWedge64]);
+  if (2 * m > kCap64)
+    hipLaunchKernelGGL((k_wedge<256, 12>), list_grid(n16, 1, 3), dim3(256), 0, s, g, T.lut[4], a4, p.status, queue,
+                       o.wedge[kWedge256]);
+  if (m > 127) {  // over 127 lower neighbours, or over kCap256 visits
+    if (o.bnd) hipLaunchKernelGGL(k_bounds, dim3(1), dim3(64), 0, s, g, c.nblk, o.bnd, p.status);
+    if (o.split)
+      hipLaunchKernelGGL(k_split, dim3(grid_of(n * (c.nfine + 1), 256, 65536)), dim3(256), 0, s, g, c.nfine, o.bnd, o.split,
+                         p.status);
+    const dim3 tg = list_grid(n * c.nfine, 1, 1);
+    auto launch_top = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, tg, dim3(kTopThreads), 0, s, g, T.lut[4], a4, p.status, queue, o.wedge[kWedgeTop],
+                         o.wedge[kWedgeHuge], o.split, c.nblk, c.nfine, o.bnd);
+    };
+    if (c.wide) launch_top(o.split ? k_wedge_top<5, true> : k_wedge_top<5, false>);
+    else launch_top(o.split ? k_wedge_top<3, true> : k_wedge_top<3, false>);
+  }
+}
+
 void enqueue_counts(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_t* a4, int32_t* queue, hipStream_t s,
                     CountsOut* left) {
   // (the accumulators and the queue words are zeroed by the caller)
@@ -1480,17 +1519,19 @@ void enqueue_counts(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_t* a4, 
   int32_t* bnd = p.arena.take<int32_t>((size_t)(c.nfine + c.nblk + 2));
   if (c.nfine == c.nblk) bnd = nullptr;  // the multiples of kBlock alone
   u64* planes = p.arena.take<u64>((size_t)c.slices * (size_t)c.D * (size_t)c.words * 2 + 1);
-  if (left) {
-    left->T = Te;
-    for (int l = 0; l < kLists; ++l) left->wedge[l] = L.v[l];
-  }
+  CountsOut own;
+  CountsOut* const out = left ? left : &own;
+  out->T = Te;
+  out->split = split;
+  out->bnd = bnd;
+  for (int l = 0; l < kLists; ++l) out->wedge[l] = L.v[l];
   enqueue_zero(Te, sizeof(uint32_t) * 9 * (size_t)(m + 1), s);
   hipLaunchKernelGGL((k_classify<true>), dim3(cgrid), dim3(256), 0, s, g, L, queue, big, p.status);
   // The triangles beside the wedges where both are long (n = 10^5, m = 10^6: 450
   // and 1,030 us; the wedge table of a workgroup leaves half of a CU's waves and
   // a quarter of its LDS) and the caller's streams allow it.
   Chains ch(p, s);
-  if (p.fork_now && m >= kCutsM) ch.fork(0);
+  if (p.fork_now && m >= kCutsM && !out->later) ch.fork(0);
   const hipStream_t ts = ch.on(0);
   hipLaunchKernelGGL((k_tri<16, 16, true>), list_grid(n16, 16, 6), dim3(256), 0, ts, g, T.lut[3], T.lut[4], a3, a4, Te,
                      p.status, queue, L.v[kTri16]);
@@ -1504,34 +1545,14 @@ void enqueue_counts(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_t* a4, 
     hipLaunchKernelGGL((k_tri_big<true>), dim3(std::min<unsigned>(c.slices ? c.slices : 512, grid_of(nbig, 1, cus * 2))),
                        dim3(512), 0, ts, g, T.lut[3], T.lut[4], a3, a4, Te, p.status, queue, L.v[kTriBig], planes, c.D,
                        c.words);
-  // (the diamonds need the triangles only)
-  const dim3 lgrid(grid_of(n + m, 256, cus * 4));
-  if (a3)
-    hipLaunchKernelGGL((k_local<true, true>), lgrid, dim3(256), 0, ts, g, T.lut[3], T.lut[4], a3, a4, Te, p.status);
-  else
-    hipLaunchKernelGGL((k_local<false, true>), lgrid, dim3(256), 0, ts, g, T.lut[3], T.lut[4], a3, a4, Te, p.status);
-  hipLaunchKernelGGL((k_wedge<16, 7>), list_grid(n16, 16, 6), dim3(256), 0, s, g, T.lut[4], a4, p.status, queue,
-                     L.v[kWedge16]);
-  if (2 * m > kCap16)
-    hipLaunchKernelGGL((k_wedge<64, 9>), list_grid(n16, 4, 6), dim3(256), 0, s, g, T.lut[4], a4, p.status, queue,
-                       L.v[kWedge64]);
-  if (2 * m > kCap64)
-    hipLaunchKernelGGL((k_wedge<256, 12>), list_grid(n16, 1, 3), dim3(256), 0, s, g, T.lut[4], a4, p.status, queue,
-                       L.v[kWedge256]);
-  if (m > 127) {  // over 127 lower neighbours, or over kCap256 visits
-    if (bnd) hipLaunchKernelGGL(k_bounds, dim3(1), dim3(64), 0, s, g, c.nblk, bnd, p.status);
-    if (split)
-      hipLaunchKernelGGL(k_split, dim3(grid_of(n * (c.nfine + 1), 256, 65536)), dim3(256), 0, s, g, c.nfine, bnd, split,
-                         p.status);
-    const dim3 tg = list_grid(n * c.nfine, 1, 1);
-    auto launch_top = [&](auto kernel) {
-      hipLaunchKernelGGL(kernel, tg, dim3(kTopThreads), 0, s, g, T.lut[4], a4, p.status, queue, L.v[kWedgeTop],
-                         L.v[kWedgeHuge], split, c.nblk, c.nfine, bnd);
-    };
-    if (c.wide) launch_top(split ? k_wedge_top<5, true> : k_wedge_top<5, false>);
-    else launch_top(split ? k_wedge_top<3, true> : k_wedge_top<3, false>);
-  }
+  if (out->later) return;  // (not forked)
+  enqueue_wedges(p, g, a3, a4, queue, *out, s, ts);
   ch.join();
+}
+
+void enqueue_counts_rest(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_t* a4, const int32_t* queue,
+                         const CountsOut& left, hipStream_t s) {
+  enqueue_wedges(p, g, a3, a4, queue, left, s, s);
 }
 
 void enqueue_solve(int k, const uint64_t* acc, uint64_t* tmp, uint64_t* out, int64_t ngraphs, int32_t* status,

@@ -254,17 +254,24 @@ void enqueue_census(Pipeline& p, const DevGraph& g, int k, uint64_t* acc, uint64
 // through tmp (same size), written only if none is negative.
 size_t count_bytes(int64_t n, int64_t m, int64_t maxn, bool batch, bool k4);
 struct CountsOut {  // what a k = 4 pass leaves behind
+  bool later = false;                  // in: the wedges are left to enqueue_counts_rest
   const uint32_t* T = nullptr;         // typed triangle counts per N+ entry, nine each
   const int32_t* wedge[9] = {};        // lists of vertices (ListId in counts.h)
+  int32_t *split = nullptr, *bnd = nullptr;  // tables of k_wedge_top, or null
 };
 void enqueue_counts(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_t* a4, int32_t* queue, hipStream_t s,
                     CountsOut* left = nullptr);
+// The wedges, vertices and edges of a pass whose CountsOut said later.
+void enqueue_counts_rest(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_t* a4, const int32_t* queue,
+                         const CountsOut& left, hipStream_t s);
 void enqueue_solve(int k, const uint64_t* acc, uint64_t* tmp, uint64_t* out, int64_t ngraphs, int32_t* status,
                    hipStream_t s);
 // The k = 5 census of one graph by subgraph copies (copies5.hip): start
 // enqueues the k = 3, 4 totals (a3, a4: acc_words of a single graph, zeroed
-// here) and counts what the rest takes room for; once the status words are
-// read back, copies5_go says whether it fits, and finish enqueues the rest.
+// here; on small graphs without the wedges, which enqueue_counts_rest adds when
+// the totals are needed) and counts what the rest takes room for; once the
+// status words are read back, copies5_go says whether it fits, and finish
+// enqueues the rest.
 struct Copies5Run {
   bool lean = false;  // in: the workspace has copies5_bytes(.., true) only
   uint64_t *a3 = nullptr, *a4 = nullptr, *acc = nullptr;
