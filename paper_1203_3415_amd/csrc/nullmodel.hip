@@ -115,38 +115,43 @@ __device__ __forceinline__ bool row_has(const typename T::Word* idx, int32_t p, 
   return hit;
 }
 
-// Does the lane's row [p0, e0) hold x0, or its row [p1, e1) x1 (both rows
-// non-empty where act)?  Called by whole waves.  A round of the switch waits
-// for its slowest proposal, and a lane alone on a hub row of a few hundred
-// targets was that proposal: rows of more than kShortRow targets are scanned
-// by the whole wave, one row after another (each row is held by one proposal
-// only, so a wave meets few of them), the others by their own lanes, both rows
-// of a lane at once.  1,000 copies of n = 2,000, m = 8,000 with their census
-// and z-scores: 40.0 -> 33.0 ms; 256 graphs of n = 500 to 5,000, m = 4n, with
-// reciprocated pairs kept: 51.9 -> 34.0 ms.
+// Does the lane's row [p0, e0) hold x0, or its row [p1, e1) x1?  Called by whole
+// waves.  A round of the switch waits for its slowest proposal, and a lane alone
+// on a hub row of a few hundred targets was that proposal: rows of more than
+// kShortRow targets are scanned by the whole wave, one row after another (each
+// row is held by one proposal only, so a wave meets few of them), the others by
+// their own lanes, eight targets in two loads (m = 10^6 uniform arcs of n =
+// 40,000: 33 ms an attempt an arc so, 59 with rows of more than 16 by the wave and
+// single, clamped loads; n = 30,000, m = 200,000, power law: 10.1 and 11.0, by
+// the lanes alone 28.2).
 constexpr int32_t kTarget = 0x7FFFFFFF;
-constexpr int32_t kShortRow = 16;
+constexpr int32_t kShortRow = 64;
 __device__ __forceinline__ bool pair_has(const int32_t* idx, bool act, int32_t p0, int32_t e0, int32_t x0, int32_t p1,
                                          int32_t e1, int32_t x1) {
   const int32_t lane = (int32_t)(threadIdx.x & 63u);
   const int32_t n0 = act ? e0 - p0 : 0, n1 = act ? e1 - p1 : 0;
   const bool l0 = n0 > kShortRow, l1 = n1 > kShortRow;
   const int32_t s0 = l0 ? 0 : n0, s1 = l1 ? 0 : n1;
-  const int32_t q0 = s0 ? p0 : 0, q1 = s1 ? p1 : 0;            // rows to read; slot 0 when there is none
-  const int32_t t0 = q0 + max(s0, 1) - 1, t1 = q1 + max(s1, 1) - 1;  // last slot of each
   bool hit = false;
-  for (int32_t s = 0; s < kShortRow; s += 4) {
-    if (!__ballot(s < s0 || s < s1)) break;
-    int32_t v[4], w[4];
+  auto own = [&](int32_t n, int32_t p, int32_t x) {
+    for (int32_t s = 0; __ballot(s < n && n >= 8) != 0ull; s += 8) {
+      if (s >= n || n < 8) continue;
+      const int32_t q = p + min(s, n - 8);  // (the last eight overlap those before)
+      int32_t v[8];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      v[u] = idx[min(q0 + s + u, t0)];  // past the end: the last target again
-      w[u] = idx[min(q1 + s + u, t1)];
+      for (int u = 0; u < 8; ++u) v[u] = idx[q + u];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) hit |= (v[u] & kTarget) == x;
     }
+    if (n >= 8) return;
+    int32_t v[7];
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
-      hit |= (s0 > 0 && (v[u] & kTarget) == x0) || (s1 > 0 && (w[u] & kTarget) == x1);
-  }
+    for (int u = 0; u < 7; ++u) v[u] = u < n ? idx[p + u] : ~x;
+#pragma unroll
+    for (int u = 0; u < 7; ++u) hit |= (v[u] & kTarget) == x;
+  };
+  own(s0, p0, x0);
+  own(s1, p1, x1);
   for (int side = 0; side < 2; ++side) {
     for (uint64_t m = __ballot(side ? l1 : l0); m; m &= m - 1ull) {
       const int src = __builtin_ctzll(m);
@@ -550,10 +555,10 @@ __global__ __launch_bounds__(kSwB, PER_CU * kSwB / 256) void k_switch(const Swit
                      !held_by_other(d) && a != d && c != b && b != d;
           if (__ballot(run)) {
             run = run & !pair(run, off[a], off[a + 1], d, off[c], off[c + 1], b);
-            // rows b and d may be empty: then they hold nothing
-            const int32_t nb = off[b + 1] - off[b], nd = off[d + 1] - off[d];
-            const int32_t pb = nb ? off[b] : off[a], eb = nb ? off[b + 1] : off[a + 1];
-            const int32_t pd = nd ? off[d] : off[c], ed = nd ? off[d + 1] : off[c + 1];
+            // rows b and d may be empty: then they hold nothing (in LDS another row is looked over for nobody)
+            const bool nb = !LDS || off[b + 1] > off[b], nd = !LDS || off[d + 1] > off[d];
+            const int32_t pb = off[nb ? b : a], eb = off[(nb ? b : a) + 1];
+            const int32_t pd = off[nd ? d : c], ed = off[(nd ? d : c) + 1];
             run = run & !pair(run, pb, eb, nb ? c : -1, pd, ed, nd ? a : -1);
             // the reverse arcs of a reciprocated pair: b->a becomes b->c, d->c becomes d->a
             const int32_t kind = wi & T::mutual;
