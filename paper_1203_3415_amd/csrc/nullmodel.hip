@@ -164,13 +164,16 @@ __device__ __forceinline__ bool pair_has(const int32_t* idx, bool act, int32_t p
   return hit;
 }
 
-// The same on 16-bit targets in LDS, two to a word: rows of up to kShortWords
-// words by their lanes, both halves compared at once (the smaller of each pair
-// of differences is kept), the last word apart, whose upper half may be the next
-// row's; the longer rows by the wave, their bounds read from their lane's
-// registers.  With two workgroups on a CU a round is bound by its vector
-// instructions, and most of them are here.
-constexpr int32_t kShortWords = 8;
+// The same on 16-bit targets in LDS, two to a word, the rows non-empty where act:
+// rows of up to kShortWords words by their lanes, both halves compared at once
+// (the smaller of each pair of differences is kept), the last word apart, whose
+// upper half may be the next row's; the longer rows by the wave, their bounds
+// read from their lane's registers, unless more than kFewRows of the wave's are
+// longer: then their lanes go on, up to kLongWords (300 graphs of n = 1,000 with
+// 30,000 uniform arcs, ten attempts an arc: 2.7 ms so, 12.5 with all of them by
+// the wave, 4.1 by the lanes alone).  With two workgroups on a CU a round is bound
+// by its vector instructions, and most of them are here.
+constexpr int32_t kShortWords = 8, kLongWords = 32, kFewRows = 10;
 typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t min_halves(uint32_t a, uint32_t b) {
   return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(ushort2v, a), __builtin_bit_cast(ushort2v, b)));
@@ -185,8 +188,10 @@ __device__ __forceinline__ bool pair_has16(const uint16_t* idx, bool act, int32_
   const uint32_t y0 = (uint32_t)x0 * 0x10001u, y1 = (uint32_t)x1 * 0x10001u;
   const int32_t b0 = p0 >> 1, t0 = (e0 - 1) >> 1, b1 = p1 >> 1, t1 = (e1 - 1) >> 1;  // first and last words
   const int32_t n0 = act ? t0 - b0 + 1 : 0, n1 = act ? t1 - b1 + 1 : 0;
-  const uint64_t l0 = __ballot(n0 > kShortWords), l1 = __ballot(n1 > kShortWords);
-  const int32_t s0 = n0 > kShortWords ? 0 : n0, s1 = n1 > kShortWords ? 0 : n1;
+  const uint64_t o0 = __ballot(n0 > kShortWords), o1 = __ballot(n1 > kShortWords);
+  const int32_t cap = __popcll(o0) + __popcll(o1) > kFewRows ? kLongWords : kShortWords;  // the same on every lane
+  const uint64_t l0 = __ballot(n0 > cap), l1 = __ballot(n1 > cap);
+  const int32_t s0 = n0 > cap ? 0 : n0, s1 = n1 > cap ? 0 : n1;
   const int32_t q0 = s0 ? b0 : 0, q1 = s1 ? b1 : 0, z0 = s0 ? t0 : 0, z1 = s1 ? t1 : 0;
   // the last words; halves outside the row are made to differ
   const uint32_t d0 = ((words[z0] ^ y0) & M) | ((uint32_t)e0 & 1u) << 16 | (n0 == 1 ? (uint32_t)p0 & 1u : 0u);
@@ -194,9 +199,7 @@ __device__ __forceinline__ bool pair_has16(const uint16_t* idx, bool act, int32_
   bool hit = (s0 > 0 && zero_half(d0)) || (s1 > 0 && zero_half(d1));
   uint32_t m0 = 0xFFFFFFFFu, m1 = 0xFFFFFFFFu;
   const int32_t i0 = max(z0 - 1, q0), i1 = max(z1 - 1, q1);  // (past the end: the last of these again)
-#pragma unroll
-  for (int32_t s = 0; s < kShortWords; s += 4) {
-    if (!__ballot(s < s0 - 1 || s < s1 - 1)) break;
+  auto step = [&](int32_t s) {
     uint32_t v[4], w[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
@@ -217,6 +220,15 @@ __device__ __forceinline__ bool pair_has16(const uint16_t* idx, bool act, int32_
       m0 = min_halves(m0, v[u]);
       m1 = min_halves(m1, w[u]);
     }
+  };
+#pragma unroll
+  for (int32_t s = 0; s < kShortWords; s += 4) {
+    if (!__ballot(s < s0 - 1 || s < s1 - 1)) break;
+    step(s);
+  }
+  for (int32_t s = kShortWords; s < cap; s += 4) {
+    if (!__ballot(s < s0 - 1 || s < s1 - 1)) break;
+    step(s);
   }
   hit |= (s0 > 1 && zero_half(m0)) || (s1 > 1 && zero_half(m1));
   auto whole = [&](uint64_t mask, int32_t p_, int32_t e_, uint32_t y_) {

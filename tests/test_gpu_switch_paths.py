@@ -1,8 +1,48 @@
-"""Arc-switch randomisation of ensembles through every launch of its kernels."""
+"""Arc-switch rounds against the host rendering of the chain, target by target, on
+every instance of the switch kernel: two workgroups per CU (more graphs than CUs),
+one per CU with and without the second set of reservations, and global memory;
+for graphs with a few long rows (scanned by the wave), with many rows of middling
+length (scanned by their lanes) and with rows on both sides of where the scans
+change hands."""
 import numpy as np
 import pytest
 
+import graphgen as gg
+from test_gpu_switch_rounds import _graph, _switch
+
 pytestmark = pytest.mark.gpu
+
+SHAPES = {
+    "hubs": (200, [1, 15, 16, 17, 18, 63, 64, 65, 127, 128, 129, 180]),
+    "middling": (110, [17 + (7 * i) % 15 for i in range(110)]),
+    "edges": (160, [w for w in (1, 7, 8, 9, 14, 15, 16, 17, 18, 62, 63, 64, 65, 66, 67) for _ in range(9)]),
+}
+
+
+@pytest.mark.parametrize("mutual", [False, True])
+@pytest.mark.parametrize("shape", sorted(SHAPES))
+@pytest.mark.parametrize("place", ["two_per_cu", "one_per_cu", "one_set", "global"])
+def test_paths_equal_host(place, shape, mutual):
+    import torch
+    import paper_1203_3415_amd as pm
+    n, lens = SHAPES[shape]
+    g = _graph(n, lens, 0.3, len(lens))
+    if place in ("one_set", "global"):  # among isolated vertices: no room for a second set of n words, or for any
+        n = {"one_set": 12000 if mutual else 15000, "global": 40000}[place]
+        g = gg.from_arcs(n, g.arcs())
+    lds, half = 38 * 1024, (g.m + 1) // 2
+    words = n + 1 + half + (2 if mutual else 1) * n
+    if place == "one_set":
+        assert words <= lds < words + half + n
+    assert (words > lds) == (place == "global")
+    count = torch.cuda.get_device_properties(0).multi_processor_count + 40 if place == "two_per_cu" else 2
+    off, idx = pm.to_device(g.out_off, g.out_idx)
+    devs = [(off, idx.clone(), n) for _ in range(count)]
+    print(f"[case] switch paths {place} {shape} mutual={mutual} m={g.m} graphs={count}", flush=True)
+    pm.null_randomize(devs, 5, seed=11, mutual=mutual)
+    torch.cuda.synchronize()
+    for i in {0, 1, count // 2, count - 1}:
+        assert devs[i][1].cpu().tolist() == _switch(g, 5, 11, i, mutual), i
 
 
 def test_uneven_ensemble_is_checked():
