@@ -256,12 +256,13 @@ __device__ __forceinline__ bool pair_has16(const uint16_t* idx, bool act, int32_
 // construction), for every lane with act, the rows one after another by the
 // whole wave: few lanes of a wave move reciprocated pairs, and one alone on a
 // hub's row held the round up (256 graphs of n = 500 to 5,000, m = 4n,
-// pairs kept, 100 attempts an arc: 17.8 -> 15.2 ms a call).
+// pairs kept, 100 attempts an arc: 17.8 -> 15.2 ms a call).  Where repeated arcs
+// left none, the row's last, as row_find.
 template <int32_t MASK>
 __device__ __forceinline__ int32_t wave_find16(const uint16_t* idx, bool act, int32_t p_, int32_t e_, int32_t x_) {
   const uint32_t* words = reinterpret_cast<const uint32_t*>(idx);
   const int32_t lane = (int32_t)(threadIdx.x & 63u);
-  int32_t found = p_;
+  int32_t found = e_ - 1;
   for (uint64_t mask = __ballot(act); mask; mask &= mask - 1ull) {
     const int src = __builtin_ctzll(mask);
     const int32_t p = __builtin_amdgcn_readlane(p_, src), e = __builtin_amdgcn_readlane(e_, src);

@@ -66,3 +66,23 @@ def test_uneven_ensemble_is_checked():
             with pytest.raises(pm.MotifError) as e:
                 pm.null_randomize(devs, 1, seed=1)
             assert e.value.name == name and np.array_equal(x.cpu().numpy(), idx)
+
+
+@pytest.mark.parametrize("seed", range(4))
+def test_repeated_arcs_alike_in_lds_and_memory(seed):
+    # repeated arcs are not refused; the reverse of one may then be gone from its row
+    import torch
+    import paper_1203_3415_amd as pm
+    rng = np.random.default_rng(seed)
+    pairs = [(int(a), int(b)) for a, b in rng.integers(0, 30, (150, 2)) if a != b]
+    arcs = sorted(pairs + [(b, a) for a, b in pairs[::2]] + pairs[::3])
+    off = np.searchsorted([a for a, _ in arcs], np.arange(31)).astype(np.int32)
+    idx = np.asarray([b for _, b in arcs], np.int32)
+    far = np.concatenate([off, np.full(40000 - 30, len(arcs), np.int32)])
+    o, x = pm.to_device(off, idx)
+    fo, fx = pm.to_device(far, idx)
+    print(f"[case] repeated arcs seed={seed} m={len(arcs)}", flush=True)
+    pm.null_randomize([(o, x, 30)], 40, seed=seed, mutual=True)
+    pm.null_randomize([(fo, fx, 40000)], 40, seed=seed, mutual=True)
+    torch.cuda.synchronize()
+    assert torch.equal(x, fx)
