@@ -15,11 +15,14 @@ constexpr uint32_t kNone = 0xFFFFFFFFu;
 // counter: a pull is an atomic on one address, about 25 ns each however many
 // waves wait for it, which was most of these kernels' time on 10^4 vertices.
 enum ListId : int { kTri16 = 0, kTri64 = 1, kTri128 = 2, kTriBig = 3, kWedge16 = 4, kWedge64 = 5, kWedge256 = 6,
-                    kWedgeTop = 7, kWedgeHuge = 8, kLists = 9 };
+                    kWedgeTop = 7, kWedgeHuge = 8, kWedgeFar7 = 9, kWedgeFar11 = 10, kLists = 11 };
 struct Lists {
   int32_t* v[kLists];
 };
 constexpr int kHugeD = 1000;  // lower neighbours from which a vertex's wedges are cut by row entries too
+// On graphs of many ids (kFarBlocks): visits and lower neighbours up to which a
+// vertex's wedges are hashed in parts instead of counted block by block.
+constexpr int kFarVisits = 65536, kFarD = 1024, kFarBlocks = 32;
 constexpr int kCap16 = 96, kCap64 = 384, kCap256 = 3072;  // visits of a vertex in the three wedge hashes
 
 __device__ __forceinline__ uint32_t hash_mul(uint32_t x, int bits) { return (x * 2654435761u) >> (32 - bits); }

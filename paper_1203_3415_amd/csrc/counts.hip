@@ -180,11 +180,12 @@ __device__ __forceinline__ void for_listed(const DevGraph& G, const int32_t* lis
 // Sorts the vertices into the lists: higher neighbours for the triangles,
 // lower neighbours and visits for the wedges (k = 4).  Eight lanes per vertex;
 // one counter update per list and workgroup.
-// big: higher neighbours from which a vertex has a workgroup to itself.
+// big: higher neighbours from which a vertex has a workgroup to itself; far: the
+// graph has many ids.
 constexpr int kClassify = 2048;  // most vertices of a workgroup (places fit in 12 bits)
 template <bool K4>
 __global__ __launch_bounds__(256) void k_classify(DevGraph G, Lists L, int32_t* __restrict__ nlist, int32_t big,
-                                                  const int32_t* st) {
+                                                  int32_t far, const int32_t* st) {
   __shared__ int32_t cnt[kLists], base[kLists];
   __shared__ uint32_t where[kClassify];
   if (st[kStatus] != 0) return;
@@ -200,23 +201,26 @@ __global__ __launch_bounds__(256) void k_classify(DevGraph G, Lists L, int32_t* 
     if (d >= 2) lt = d <= 16 ? kTri16 : d >= big ? kTriBig : d <= 64 ? kTri64 : kTri128;
     if (K4) {
       const int32_t ma = G.gs_off[v] - pa, dm = G.gs_off[v + 1] - pb - ma;
-      if (dm > 127) {
+      if (dm > (far ? kFarD : 127)) {
         lw = dm > kHugeD ? kWedgeHuge : kWedgeTop;
       } else if (dm >= 2) {
         int32_t vis = 0;
+        const int32_t cap = far ? kFarVisits + 1 : kCap256 + 1;
         for (int32_t i = l8; i < dm; i += 32) {  // (past the end: the last one, not counted)
           uint32_t w[4];
 #pragma unroll
           for (int k = 0; k < 4; ++k) w[k] = G.nm_idx[ma + min(i + 8 * k, dm - 1)] & kIdMask;
 #pragma unroll
           for (int k = 0; k < 4; ++k) {
-            const int32_t dw = min(G.deg[w[k]], kCap256 + 1);
+            const int32_t dw = min(G.deg[w[k]], cap);
             vis += i + 8 * k < dm ? dw : 0;
           }
         }
 #pragma unroll
         for (int o = 4; o; o >>= 1) vis += __shfl_xor(vis, o);
-        lw = vis <= kCap16 ? kWedge16 : vis <= kCap64 ? kWedge64 : vis <= kCap256 ? kWedge256 : kWedgeTop;
+        if (dm > 127) lw = vis <= kFarVisits ? kWedgeFar11 : dm > kHugeD ? kWedgeHuge : kWedgeTop;
+        else lw = vis <= kCap16 ? kWedge16 : vis <= kCap64 ? kWedge64 : vis <= kCap256 ? kWedge256 : kWedgeTop;
+        if (far && lw == kWedgeTop && dm <= 127 && vis <= kFarVisits) lw = kWedgeFar7;
       }
     }
     if (l8 == 0) {  // lists of v (15: none) and its places in this workgroup's parts of them
@@ -741,6 +745,121 @@ __global__ __launch_bounds__(256) void k_wedge(DevGraph G, const uint16_t* __res
     c4_flush(bins, lut4, totals<199, kRep4>(G, a4, g), threadIdx.x, 256);
     __syncthreads();
     if (threadIdx.x < 81) bins[threadIdx.x] = 0;
+  });
+}
+
+// Vertices of k_wedge_top on graphs of many ids, where nearly every block would
+// have a handful of a vertex's entries: the w of u in parts by their mixed ids,
+// as many as keep a part within the hash (H / 2 vertices; a part with more is
+// halved until it fits), one workgroup per u.  Rows in pieces of 64 entries,
+// sixteen lanes each, listed once.  FB bits per count: 7 in one word for u with
+// at most 127 lower neighbours, 11 in two.  k = 4 of power laws, m = 6 * 10^6
+// arcs: n = 3 * 10^6 (exponent 2.5) 65.7 ms by blocks and 10.5 so, n = 6 * 10^6
+// (2.2) 244 and 65; n = 10^6 of 10^7 arcs 53.4 and 26.9.
+__device__ __forceinline__ uint32_t mix32(uint32_t h) {  // finaliser of MurmurHash3 (A. Appleby), a bijection
+  h ^= h >> 16;
+  h *= 0x85EBCA6Bu;
+  h ^= h >> 13;
+  h *= 0xC2B2AE35u;
+  return h ^ h >> 16;
+}
+template <int HB, int FB>
+__global__ __launch_bounds__(1024) void k_wedge_far(DevGraph G, const uint16_t* __restrict__ lut4,
+                                                    uint64_t* __restrict__ a4, const int32_t* st,
+                                                    const int32_t* __restrict__ nlist, const int32_t* __restrict__ vlist) {
+  constexpr int NT = 1024, H = 1 << HB, NWORD = FB == 7 ? 1 : 2, MAXP = kFarVisits / 64 + kFarD;
+  static_assert(H / 2 + NT < H, "probes end: a part stops at H / 2 vertices, with one more per thread on the way");
+  static_assert(FB == 7 || kFarD < 2048, "11-bit counts");
+  __shared__ uint32_t key[H], piece[MAXP];  // piece: row << 16 | place in it
+  __shared__ u64 cnt[NWORD][H], bins[81];
+  __shared__ int32_t row[kFarD], len[kFarD];  // len: entries << 2 | type less one
+  __shared__ int32_t npiece, visits, used, over;
+  if (st[kStatus] != 0) return;
+  const int32_t count = nlist[FB == 7 ? kWedgeFar7 : kWedgeFar11];
+  if ((int32_t)blockIdx.x >= count) return;
+  const int t = threadIdx.x;
+  for (int i = t; i < H; i += NT) {
+    key[i] = kNone;
+    for (int w = 0; w < NWORD; ++w) cnt[w][i] = 0;
+  }
+  if (t < 81) bins[t] = 0;
+  if (t == 0) npiece = visits = used = over = 0;
+  __syncthreads();
+  auto one = [&](int32_t u) {  // the same u on every thread
+    const int32_t ua = G.gs_off[u], ub = G.gs_off[u + 1];
+    const int32_t ma = ua - G.np_off[u], dm = ub - G.np_off[u + 1] - ma;  // dm <= kFarD
+    const uint32_t du = (uint32_t)(ub - ua);
+    if (t < dm) {
+      const uint32_t ev = G.nm_idx[ma + t], v = ev & kIdMask;
+      const int32_t ra = G.gs_off[v], m = G.gs_off[v + 1] - ra, q = (m + 63) >> 6;
+      row[t] = ra;
+      len[t] = m << 2 | (int32_t)((ev >> kTypeShift) - 1u);
+      atomicAdd(&visits, m);
+      const int32_t at = atomicAdd(&npiece, q);
+      for (int32_t j = 0; j < q; ++j) piece[at + j] = (uint32_t)t << 16 | (uint32_t)j;
+    }
+    __syncthreads();
+    const int32_t np = npiece, vis = visits;
+    uint32_t parts = 1;
+    while ((uint32_t)vis > parts * (H * 3 / 8)) parts *= 2;
+    __syncthreads();
+    if (t == 0) npiece = visits = 0;
+    for (uint32_t first = 0; first < parts; ++first)
+      for (uint32_t mod = parts, res = first;;) {  // w with mix32(w) = res modulo mod, a power of two
+        for (int32_t x = t >> 4; x < np; x += NT / 16) {
+          const uint32_t pc = piece[x];
+          const int32_t i = (int32_t)(pc >> 16), off = (int32_t)(pc & 0xFFFFu) * 64, p = len[i] & 3;
+          each4(G.gs_idx + row[i] + off, t & 15, 16, min(64, (len[i] >> 2) - off), [&](int32_t, uint32_t f) {
+            const uint32_t w = f & kIdMask;
+            if ((mix32(w) & (mod - 1u)) != res || (int32_t)w == u) return;
+            if (__hip_atomic_load(&over, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) return;
+            uint32_t h = hash_mul(w, HB);
+            for (;;) {
+              const uint32_t old = atomicCAS(&key[h], kNone, w);
+              if (old == kNone && atomicAdd(&used, 1) >= H / 2) over = 1;
+              if (old == kNone || old == w) break;
+              h = (h + 1) & (H - 1);
+            }
+            const int k = 3 * p + (int)(f >> kTypeShift) - 1;
+            if constexpr (NWORD == 1) atomicAdd(&cnt[0][h], 1ull << (7 * k));
+            else atomicAdd(&cnt[k / 5][h], 1ull << (11 * (k % 5)));
+          });
+        }
+        __syncthreads();
+        const bool full = over != 0;
+        for (int i = t; i < H; i += NT) {
+          const uint32_t w = key[i];
+          if (w == kNone) continue;
+          uint32_t c[9], sum = 0;
+#pragma unroll
+          for (int k = 0; k < 9; ++k) {
+            c[k] = NWORD == 1 ? (uint32_t)(cnt[0][i] >> (7 * k)) & 127u
+                              : (uint32_t)(cnt[NWORD == 1 ? 0 : k / 5][i] >> (11 * (k % 5))) & 2047u;
+            sum += c[k];
+          }
+          if (!full && sum > 1 && ranked_below(G, (uint32_t)G.deg[w], (int32_t)w, du, u)) c4_pairs(c, bins);
+          key[i] = kNone;
+          for (int k = 0; k < NWORD; ++k) cnt[k][i] = 0;
+        }
+        __syncthreads();
+        if (t == 0) used = over = 0;
+        __syncthreads();
+        if (full) {  // the same on every thread
+          mod *= 2;
+          continue;
+        }
+        while (mod > parts && res >= mod / 2) {  // both halves of the part above are done
+          mod /= 2;
+          res -= mod;
+        }
+        if (mod == parts) break;
+        res += mod / 2;
+      }
+  };
+  for_listed<NT, false>(G, vlist, count, 1, 0, one, [&](int32_t g) {
+    c4_flush(bins, lut4, totals<199, kRep4>(G, a4, g), t, NT);
+    __syncthreads();
+    if (t < 81) bins[t] = 0;
   });
 }
 
@@ -1394,7 +1513,7 @@ constexpr size_t kPlaneBytes = size_t(64) << 20;  // adjacency slices of k_tri_b
 struct CountPlan {
   bool wide;                 // degrees may reach 2^21
   int32_t nblk, nfine;       // blocks of ids of k_wedge_top, and with the shares of entries
-  bool split;
+  bool split, far;
   int64_t D, words;          // bound on d+ and the words of an adjacency row
   int slices;                // adjacency slices of k_tri_big in global memory (0: none can be needed)
 };
@@ -1406,6 +1525,7 @@ CountPlan count_plan(int64_t n, int64_t m, int64_t maxn, bool batch) {
   c.nblk = (int32_t)std::max<int64_t>(1, (mg + kBlock - 1) / kBlock);
   c.nfine = c.nblk + (!batch && m >= kCutsM ? kCuts - 1 : 0);
   c.split = n * (c.nfine + 1) <= kSplitCap;
+  c.far = c.nblk > kFarBlocks;
   // N+(x) has at most sqrt(2 m*) entries: its members all have degree d(x) or more
   int64_t r = 1;
   while (r * r <= 2 * m) ++r;
@@ -1422,7 +1542,7 @@ size_t count_bytes(int64_t n, int64_t m, int64_t maxn, bool batch, bool k4) {
   auto al = [](size_t b) { return (b + 255) & ~size_t(255); };
   if (!k4) return 0;
   const CountPlan c = count_plan(n, m, maxn, batch);
-  size_t b = al(sizeof(uint32_t) * 9 * (size_t)(m + 1)) + 5 * al(sizeof(int32_t) * (size_t)(n + 1));
+  size_t b = al(sizeof(uint32_t) * 9 * (size_t)(m + 1)) + (c.far ? 7 : 5) * al(sizeof(int32_t) * (size_t)(n + 1));
   if (c.split) b += al(sizeof(int32_t) * (size_t)n * (c.nfine + 1));
   b += al(sizeof(int32_t) * (size_t)(c.nfine + c.nblk + 2));
   b += al((size_t)c.slices * (size_t)c.D * (size_t)c.words * 16 + 16);
@@ -1453,6 +1573,12 @@ static void enqueue_wedges(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_
   if (2 * m > kCap64)
     hipLaunchKernelGGL((k_wedge<256, 12>), list_grid(n16, 1, 3), dim3(256), 0, s, g, T.lut[4], a4, p.status, queue,
                        o.wedge[kWedge256]);
+  if (c.far) {
+    hipLaunchKernelGGL((k_wedge_far<13, 7>), list_grid(n16, 1, 1), dim3(1024), 0, s, g, T.lut[4], a4, p.status, queue,
+                       o.wedge[kWedgeFar7]);
+    hipLaunchKernelGGL((k_wedge_far<12, 11>), list_grid(n16, 1, 1), dim3(1024), 0, s, g, T.lut[4], a4, p.status, queue,
+                       o.wedge[kWedgeFar11]);
+  }
   if (m > 127) {  // over 127 lower neighbours, or over kCap256 visits
     if (o.bnd) hipLaunchKernelGGL(k_bounds, dim3(1), dim3(64), 0, s, g, c.nblk, o.bnd, p.status);
     if (o.split)
@@ -1497,7 +1623,7 @@ void enqueue_counts(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_t* a4, 
   const int64_t n128 = c.D > 64 && big > 65 ? std::min(n, 2 * m / 65) : 0;
   const int64_t nbig = c.D >= big ? std::min(n, 2 * m / big) : 0;
   if (!a4) {
-    hipLaunchKernelGGL((k_classify<false>), dim3(cgrid), dim3(256), 0, s, g, L, queue, big, p.status);
+    hipLaunchKernelGGL((k_classify<false>), dim3(cgrid), dim3(256), 0, s, g, L, queue, big, (int32_t)c.far, p.status);
     hipLaunchKernelGGL((k_tri<16, 16, false>), list_grid(n16, 16, 8), dim3(256), 0, s, g, T.lut[3], T.lut[4], a3, nullptr,
                        nullptr, p.status, queue, L.v[kTri16]);
     if (c.D > 16)
@@ -1514,7 +1640,7 @@ void enqueue_counts(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_t* a4, 
     return;
   }
   uint32_t* Te = p.arena.take<uint32_t>(9 * (size_t)(m + 1));
-  for (int l : {kWedge16, kWedge64, kWedge256, kWedgeTop, kWedgeHuge}) L.v[l] = p.arena.take<int32_t>((size_t)n + 1);
+  for (int l = kWedge16; l <= (c.far ? kWedgeFar11 : kWedgeHuge); ++l) L.v[l] = p.arena.take<int32_t>((size_t)n + 1);
   int32_t* split = c.split ? p.arena.take<int32_t>((size_t)n * (c.nfine + 1)) : nullptr;
   int32_t* bnd = p.arena.take<int32_t>((size_t)(c.nfine + c.nblk + 2));
   if (c.nfine == c.nblk) bnd = nullptr;  // the multiples of kBlock alone
@@ -1526,7 +1652,7 @@ void enqueue_counts(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_t* a4, 
   out->bnd = bnd;
   for (int l = 0; l < kLists; ++l) out->wedge[l] = L.v[l];
   enqueue_zero(Te, sizeof(uint32_t) * 9 * (size_t)(m + 1), s);
-  hipLaunchKernelGGL((k_classify<true>), dim3(cgrid), dim3(256), 0, s, g, L, queue, big, p.status);
+  hipLaunchKernelGGL((k_classify<true>), dim3(cgrid), dim3(256), 0, s, g, L, queue, big, (int32_t)c.far, p.status);
   // The triangles beside the wedges where both are long (n = 10^5, m = 10^6: 450
   // and 1,030 us; the wedge table of a workgroup leaves half of a CU's waves and
   // a quarter of its LDS) and the caller's streams allow it.

@@ -256,7 +256,7 @@ size_t count_bytes(int64_t n, int64_t m, int64_t maxn, bool batch, bool k4);
 struct CountsOut {  // what a k = 4 pass leaves behind
   bool later = false;                  // in: the wedges are left to enqueue_counts_rest
   const uint32_t* T = nullptr;         // typed triangle counts per N+ entry, nine each
-  const int32_t* wedge[9] = {};        // lists of vertices (ListId in counts.h)
+  const int32_t* wedge[11] = {};       // lists of vertices (ListId in counts.h)
   int32_t *split = nullptr, *bnd = nullptr;  // tables of k_wedge_top, or null
 };
 void enqueue_counts(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_t* a4, int32_t* queue, hipStream_t s,
