@@ -46,7 +46,8 @@ def _pole(mids, each, ends, rng, high=0, n=N):
 
 
 @pytest.mark.parametrize("mids,each,high", [(127, 40, -60), (128, 40, 60), (100, 30, -40), (100, 29, -40), (1024, 20, 0),
-                                            (1025, 20, 0), (600, 108, 0), (600, 109, 0)])
+                                            (1025, 20, 0), (600, 108, 0), (600, 109, 0), (127, 40, 0),
+                                            (128, 40, 0)])
 def test_pole(pm, mids, each, high):
     # far ends: 3,000 vertices spread over the ids, so that many are met twice
     rng = np.random.default_rng(mids * each)
