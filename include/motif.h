@@ -446,7 +446,9 @@ typedef struct motif_server motif_server_t;
 /* Returns NULL on failure (no device, bad arguments). */
 motif_server_t* motif_server_create(size_t hbm_budget_bytes, int32_t max_inflight);
 
-/* Device bytes a request for this graph and k would hold while admitted. */
+/* Device bytes a request for this graph and k would hold while admitted, at
+ * most (a server of several requests in flight counts small k = 4 requests so
+ * that they hold less). */
 int64_t motif_request_footprint(int32_t n, int64_t m, int32_t k);
 
 /* Queue one request.  `g` holds HOST pointers; they are copied before this
