@@ -448,13 +448,14 @@ motif_server_t* motif_server_create(size_t hbm_budget_bytes, int32_t max_infligh
 
 /* Device bytes a request for this graph and k would hold while admitted, at
  * most (a server of several requests in flight counts small k = 4 requests so
- * that they hold less). */
+ * that they hold less, and a k = 4 request of at most 5,120 vertices that is
+ * beyond the server's budget is counted by the reuse of cores if that fits). */
 int64_t motif_request_footprint(int32_t n, int64_t m, int32_t k);
 
 /* Queue one request.  `g` holds HOST pointers; they are copied before this
  * call returns, so the caller may reuse them.  hist_out_host must stay valid
  * until the request completes (motif_server_wait returns) or is cancelled.
- * Returns MOTIF_ETOOBIG if the footprint exceeds the budget, MOTIF_EAGAIN if
+ * Returns MOTIF_ETOOBIG if no way to count it fits the budget, MOTIF_EAGAIN if
  * the pending queue is full.  *ticket identifies the request. */
 int32_t motif_server_submit(motif_server_t* s, const motif_graph_t* g, int32_t k,
                             uint64_t* hist_out_host, uint64_t* ticket);

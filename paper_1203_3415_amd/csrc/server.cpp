@@ -237,6 +237,12 @@ int32_t motif_server_submit(motif_server_t* s, const motif_graph_t* g, int32_t k
   // 834; by one worker 3,277 and 2,686).
   if (s->max_inflight > 1) r->tune.k[4].copies = true;
   r->footprint = request_bytes(g->n, g->m, k, s->cus, r->tune.k[k]);
+  if (r->footprint > s->budget && k == 4 && r->tune.k[4].copies && !copies4_pays(1, false, 0, g->n)) {
+    // The copies' tables don't fit (n = 1,000 with 562,341 arcs: 108 MB), core
+    // reuse, which takes any graph of so few vertices, may (45 MB).
+    r->tune.k[4].copies = false;
+    r->footprint = request_bytes(g->n, g->m, k, s->cus, r->tune.k[k]);
+  }
   if (r->footprint > s->budget) {
     delete r;
     return MOTIF_ETOOBIG;
