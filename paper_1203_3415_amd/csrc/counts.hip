@@ -436,8 +436,8 @@ __global__ __launch_bounds__(256) void k_tri(DevGraph G, const uint16_t* __restr
 // LDS hash of up to kBigH / 2 members (beyond that a binary search in the
 // id-sorted row), T by global atomics, and for k = 4 the two adjacency bit
 // planes of N+(x), in LDS up to kPlaneD members and else in the workgroup's
-// slice of global memory (2 D rows of `words` words, D >= any d+).  d+ is at
-// most sqrt(2 m), so only large dense graphs have any (98 at most on the n =
+// slice of global memory (2 D rows of `words` words, D >= any d+).  A launch
+// takes the x of above < d+ <= most.  d+ is at most sqrt(2 m), so only large dense graphs have any (98 at most on the n =
 // 10^5, m = 10^6 graph).
 constexpr int kBigHB = 13;
 constexpr int kBigH = 1 << kBigHB;
@@ -452,7 +452,7 @@ __global__ __launch_bounds__(512) void k_tri_big(DevGraph G, const uint16_t* __r
                                                  uint64_t* __restrict__ a4, uint32_t* __restrict__ T,
                                                  const int32_t* st, const int32_t* __restrict__ nlist,
                                                  const int32_t* __restrict__ vlist, u64* __restrict__ planes, int64_t D,
-                                                 int64_t words) {
+                                                 int64_t words, int32_t above, int32_t most) {
   constexpr int NT = 512, NW = NT / 64;
   __shared__ u64 s_tri[27], s_paw[K4 ? 243 : 1], s_kh[K4 ? 199 : 1], s_h3[13];
   __shared__ uint32_t key[kBigH];
@@ -615,6 +615,7 @@ __global__ __launch_bounds__(512) void k_tri_big(DevGraph G, const uint16_t* __r
       G, vlist, count, 1, 0,
       [&](int32_t x) {
         const int32_t d = G.np_off[x + 1] - G.np_off[x];
+        if (d <= above || d > most) return;  // another launch's
         if (!K4 || d <= kPlaneD) work(x, std::true_type{}, lplane, lplane + kPlaneD * kPlaneD / 64);
         else work(x, std::false_type{}, gp, gp + D * words);
       },
@@ -1508,7 +1509,9 @@ unsigned grid_of(int64_t items, int per, int64_t most) {
 // ------------------------------------------------------------------ sizes --
 
 constexpr int64_t kSplitCap = int64_t(64) << 20;  // entries of the row-split table (256 MB), beyond that binary searches
-constexpr size_t kPlaneBytes = size_t(64) << 20;  // adjacency slices of k_tri_big
+// Adjacency slices of k_tri_big: 64 MB, or 16 bytes an arc (a slice's room is for
+// the largest d+ that m allows, 520 KB at m = 10^6 and 5 MB at 10^7).
+constexpr size_t kPlaneBytes = size_t(64) << 20, kPlaneArc = 16;
 
 struct CountPlan {
   bool wide;                 // degrees may reach 2^21
@@ -1532,7 +1535,7 @@ CountPlan count_plan(int64_t n, int64_t m, int64_t maxn, bool batch) {
   c.D = std::max<int64_t>(1, std::min(mg, r));
   c.words = (c.D + 63) / 64;
   const size_t per = (size_t)c.D * (size_t)c.words * 16;
-  c.slices = c.D > kPlaneD ? (int)std::max<size_t>(1, std::min<size_t>(256, kPlaneBytes / per)) : 0;
+  c.slices = c.D > kPlaneD ? (int)std::max<size_t>(1, std::min<size_t>(256, std::max(kPlaneBytes, kPlaneArc * (size_t)m) / per)) : 0;
   return c;
 }
 
@@ -1634,7 +1637,7 @@ void enqueue_counts(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_t* a4, 
                          nullptr, nullptr, p.status, queue, L.v[kTri128]);
     if (nbig > 0)
       hipLaunchKernelGGL((k_tri_big<false>), list_grid(nbig, 1, 3), dim3(512), 0, s, g, T.lut[3], T.lut[4], a3,
-                         nullptr, nullptr, p.status, queue, L.v[kTriBig], nullptr, 0, 0);
+                         nullptr, nullptr, p.status, queue, L.v[kTriBig], nullptr, 0, 0, 0, INT32_MAX);
     hipLaunchKernelGGL((k_local<true, false>), dim3(grid_of(n, 256, cus * 4)), dim3(256), 0, s, g, T.lut[3], T.lut[4],
                        a3, nullptr, nullptr, p.status);
     return;
@@ -1667,10 +1670,20 @@ void enqueue_counts(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_t* a4, 
   if (n128 > 0)
     hipLaunchKernelGGL((k_tri<64, 128, true>), list_grid(n128, 4, 3), dim3(256), 0, ts, g, T.lut[3], T.lut[4], a3, a4,
                        Te, p.status, queue, L.v[kTri128]);
-  if (nbig > 0)  // a workgroup whose x need a global slice has its own
-    hipLaunchKernelGGL((k_tri_big<true>), dim3(std::min<unsigned>(c.slices ? c.slices : 512, grid_of(nbig, 1, cus * 2))),
-                       dim3(512), 0, ts, g, T.lut[3], T.lut[4], a3, a4, Te, p.status, queue, L.v[kTriBig], planes, c.D,
-                       c.words);
+  if (nbig > 0) {
+    // A workgroup whose x need a global slice has its own.  With slices for less
+    // than a quarter of the workgroups the x that need none are a launch of all of
+    // them (m = 10^7 of n = 5 * 10^4, up to 220 higher neighbours: 528 ms by the 12
+    // workgroups of the slices, 280 so; at 129 slices of 512 neither gains).
+    const unsigned all = grid_of(nbig, 1, cus * 2), few = c.slices ? std::min<unsigned>(c.slices, all) : all;
+    auto launch = [&](unsigned grid, int32_t above, int32_t most) {
+      hipLaunchKernelGGL((k_tri_big<true>), dim3(grid), dim3(512), 0, ts, g, T.lut[3], T.lut[4], a3, a4, Te, p.status,
+                         queue, L.v[kTriBig], planes, c.D, c.words, above, most);
+    };
+    const bool split = 4 * few < all;
+    if (split) launch(all, 0, kPlaneD);
+    launch(few, split ? kPlaneD : 0, INT32_MAX);
+  }
   if (out->later) return;  // (not forked)
   enqueue_wedges(p, g, a3, a4, queue, *out, s, ts);
   ch.join();
