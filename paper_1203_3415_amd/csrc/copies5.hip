@@ -1670,6 +1670,7 @@ constexpr int64_t kFewArcs = 32768;
 
 void enqueue_copies5_start(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_t* a4, Copies5Run* R, hipStream_t s) {
   const int64_t n = g.n, m = (g.gs_cap - 1) / 2;
+  if (!copies5_fits(n, m)) throw WorkspaceError();  // (never; the kernels' 16-bit words rest on it)
   Arena& A = p.arena;
   ZeroBatch z;
   R->a3 = a3;
