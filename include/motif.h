@@ -392,16 +392,19 @@ typedef struct motif_tuning {
  * Setting them also drops the autotuner's cached entries for k.  Fused
  * censuses of more than one graph at k = 4, each of at most 16,384 vertices,
  * start from their own default (block 512, grid 2 per CU, tile 16, solo 32,
- * light 256: many small cores) until k's parameters are set here;
+ * light 256: many small cores; read where they are counted by core reuse) until
+ * k's parameters are set here;
  * motif_get_tuning reads the single-graph defaults. */
 int32_t motif_get_tuning(int32_t k, motif_tuning_t* out);
 int32_t motif_set_tuning(int32_t k, const motif_tuning_t* in);
 
 /* Autotuner: times the fused batch census of `graphs` (device pointers, as for
- * motif_census_batch; count = 1 tunes the single-graph path) under candidate
- * tunings -- a coordinate descent, two passes, over block, grid, tile, the
- * census scheme and the work-placement limits -- each candidate timed as the
- * median of 3 runs after a warm-up.  The fastest is cached for (this device,
+ * motif_census_batch; count = 1 tunes the entries that single graphs use) under
+ * candidate tunings -- a coordinate descent, two passes, over block, grid, tile,
+ * the census scheme and the work-placement limits, as far as the counting of
+ * these graphs reads them (k = 3, and k = 4 by subgraph copies, read none but
+ * the scheme; at k = 5 they are those of the core-reuse kernel) -- each candidate
+ * timed as the median of 3 runs after a warm-up.  The fastest is cached for (this device,
  * k, batch or single graph, floor(log2(total arcs))) and used by every later
  * call that falls in that bucket; it is also written to *best.  `hists` is
  * scratch output (count * C uint64, device).  Every candidate's histograms

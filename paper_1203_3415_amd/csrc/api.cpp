@@ -357,8 +357,10 @@ struct TuneAxis {
   int& field(Tuning& t) const { return t.*mem; }
 };
 
+// (The counting of subgraph copies, k = 3 and k = 4 where it pays, has none of
+// them: only whether to count so is tried then.)
 std::vector<TuneAxis> tune_axes(int k) {
-  if (k == 3) return {{&Tuning::tile, {4, 8, 16, 32, 64}, false}, {&Tuning::grid_per_cu, {2, 4, 8}, false}};
+  if (k == 3) return {};
   if (k == 4)
     return {{&Tuning::heavy, {1, 0}, false},
             {&Tuning::block, {512, 1024}, false},
@@ -1229,7 +1231,7 @@ int32_t motif_autotune(const motif_graph_t* graphs, int32_t count, int32_t k, ui
   const std::vector<TuneAxis> axes = tune_axes(k);
   for (int pass = 0; pass < 2; ++pass) {
     for (const TuneAxis& ax : axes) {
-      if (ax.reuse_only && bt.heavy != 1) continue;
+      if ((ax.reuse_only && bt.heavy != 1) || (by_copies(k, bt) && ax.mem != &Tuning::heavy)) continue;
       for (int v : ax.values) {
         Tuning t = bt;
         if (ax.field(t) == v) continue;

@@ -135,3 +135,18 @@ def test_core_reuse_placement(pm):
                 assert np.array_equal(h[0], want[0]) and np.array_equal(h[1], want[1])
     finally:
         pm.set_tuning(4, **saved)
+
+
+def test_autotune_of_copies(pm):
+    # parameters that the counting of copies doesn't read stay as they are
+    g = gg.chung_lu(4000, 30000, 2.3, 2.4, 0.2, seed=4)
+    dev = [(*pm.to_device(g.out_off, g.out_idx), g.n)]
+    for k in (3, 4):
+        saved = pm.get_tuning(k)
+        try:
+            print(f"[case] autotune by copies k={k}", flush=True)
+            best = pm.autotune(dev, k)
+            assert {f: v for f, v in best.items() if f != "heavy"} == {f: v for f, v in saved.items() if f != "heavy"}
+            assert np.array_equal(pm.census(*dev[0], k), oracle.method_census(g, k))
+        finally:
+            pm.set_tuning(k, **saved)
