@@ -268,9 +268,10 @@ def bench_census(args):
 
     dominant = max(ks)
     kms = float(np.mean(kern_ms[dominant]))
-    kname = kernel_name(dominant, pm.get_tuning(dominant)["heavy"] if dominant > 3 else 0)
+    kname = kernel_name(dominant, pm.get_tuning(dominant)["heavy"] if dominant > 3 else 0, g.n, g.m, len(ks))
     kbytes = {"copies<3>": k3_kernel_bytes, "k4_kernel": k4_kernel_bytes, "copies<4>": copies4_bytes,
-              "copies<5>": copies5_bytes}.get(kname, lambda _: None)(st)
+              "kr_kernel<4>": kr4_kernel_bytes, "copies<5>": copies5_bytes,
+              "kr_kernel<5>": kr5_kernel_bytes}.get(kname, lambda _: None)(st)
     roofline = None
     if kbytes is not None:
         achieved = kbytes / (kms * 1e-3) / 1e9
@@ -278,10 +279,10 @@ def bench_census(args):
                     "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": stored_traffic(kname, args.workload),
                     "kernel": kname, "kernel_ms": round(kms, 3), "algorithmic_bytes": kbytes}
         # The per-anchor byte model (what the paper's method, one anchor at a
-        # time, must read).  The copies read far fewer
-        # bytes than that, from a working set that sits in the caches, so the
-        # model's rate can exceed the HBM peak: it is reported beside the
-        # kernel's own floor, and the counters below say what binds.
+        # time, must read).  The copies read far fewer bytes than that, from a
+        # working set that sits in the caches, so the model's rate can exceed the
+        # HBM peak: it is reported beside the kernel's own floor, and the counters
+        # below, where there are any of these kernels, say what binds.
         method = {4: k4_kernel_bytes, 5: k5_method_bytes, 3: k3_kernel_bytes}[dominant](st)
         roofline["method_model_bytes"] = method
         roofline["method_model_frac"] = round(method / (kms * 1e-3) / 1e9 / HBM_PEAK_GBS, 3)
@@ -321,10 +322,19 @@ def bench_census(args):
     print(json.dumps(line), flush=True)
 
 
-def kernel_name(k: int, scheme: int) -> str:
-    """The kernels between the census events: the subgraph copies (for k = 5
-    where the graph fits), or the per-anchor kernel."""
-    return f"copies<{k}>" if k == 3 or scheme == 1 else f"k{k}_kernel"
+def kernel_name(k: int, scheme: int, n: int, m: int, sizes: int) -> str:
+    """The kernels between the census events of the largest size k of `sizes`:
+    the subgraph copies, the reuse of cores (k = 4 alone on small inputs; k = 5
+    of graphs that the copies leave out by their size) or the per-anchor kernel.
+    Not told here: k = 5 of a graph with more triangles than the copies have room
+    for, counted by the reuse of cores too."""
+    if k > 3 and scheme != 1:
+        return f"k{k}_kernel"
+    if k == 4 and sizes == 1 and n <= 5120 and m <= 5120:
+        return "kr_kernel<4>"
+    if k == 5 and (n > 65536 or m > 1 << 20 or 3 * m > n * (n - 1)):
+        return "kr_kernel<5>"
+    return f"copies<{k}>"
 
 
 TRAFFIC_DIR = os.path.join(ROOT, "profiles")
