@@ -14,7 +14,11 @@
  * (Delta-Patterns, Lemma "lema5d") -- using closed forms for neighbour pairs
  * with no edge between them (Facts "base"/"basefive") and edge counts between
  * the neighbour sets for the rest; each class total is finally divided by the
- * number of anchors that see one occurrence (Fact "correction").
+ * number of anchors that see one occurrence (Fact "correction").  Most calls
+ * count from the same facts the other way round: the occurrences of each typed
+ * connected subgraph pattern, from degrees, wedges and triangles, of which the
+ * induced counts are a fixed integer combination (k = 3; k = 4 but for small
+ * inputs; k = 5 of one graph where its tables fit; motif_tuning_t.heavy).
  *
  * Class numbering.  The paper leaves positions arbitrary.  Here: for k
  * vertices the arc i->j (i != j) is bit  i*(k-1) + (j < i ? j : j-1)  of a
@@ -36,10 +40,11 @@
  *    workspaces and class tables (device memory), released by
  *    motif_shutdown().
  *  - `stream` is a hipStream_t (NULL = the default stream).  Work is enqueued
- *    on it.  motif_census(), motif_census_multi() and the batch calls then
- *    wait for that stream once, at the end, so that an invalid graph or a
- *    failed self-check is reported by the return code; the histogram is
- *    complete when they return.  motif_census_async() does not wait: it
+ *    on it.  motif_census(), motif_census_multi() and the batch calls
+ *    wait for that stream at the end, so that an invalid graph or a failed
+ *    self-check is reported by the return code; the histogram is complete
+ *    when they return.  (With k = 5 they may also wait in the middle, where
+ *    the number of triangles decides how the rest is counted.)  motif_census_async() does not wait: it
  *    reports the outcome through a device status word instead.
  *  - Thread safety: calls on different streams may run concurrently (each
  *    stream gets its own workspace); calls on the same stream are ordered.
@@ -71,7 +76,8 @@ extern "C" {
 #define MOTIF_ECANCELED (-12)    /* server: request was cancelled                      */
 #define MOTIF_EINVAL_ARG (-13)   /* other bad argument (NULL pointer, bad count...)   */
 #define MOTIF_EINTERNAL (-14)    /* self-check failed: a class total was not an exact
-                                    multiple of its anchor multiplicity               */
+                                    multiple of its anchor multiplicity or, counted
+                                    from subgraph patterns, came out negative          */
 #define MOTIF_EPARSE (-15)       /* network file: malformed line or id out of range    */
 #define MOTIF_EIO (-16)          /* network file: cannot be opened or read             */
 
@@ -235,19 +241,22 @@ int32_t motif_census_undirected(const int32_t* out_off, const int32_t* out_idx, 
  * exactly what motif_census(..., ks[i], hists[i], ...) would write.  The
  * validation and the G* / N+ build run once and are shared (the paper's
  * motif profiles use several sizes of one network, Section "Results and
- * Discussion").  The largest size runs on `stream`, the others on a second
- * stream owned by the library, forked after the build; both are joined
- * before the call returns, so on return the work on `stream` includes all
- * of it.  `g` holds device pointers; errors as for motif_census(): on any
+ * Discussion").  k = 3 shares the triangles of k = 4, and both are part of a
+ * k = 5 pass by subgraph patterns, all on `stream`; where k = 5 reuses cores,
+ * the smaller sizes run on a second stream owned by the library, forked after
+ * the build, as does the check of an in-CSR.  Streams that the library forks
+ * are joined before the call returns, so on return the work on `stream`
+ * includes all of it.  `g` holds device pointers; errors as for motif_census(): on any
  * validation error no histogram is written; a self-check failure
  * (MOTIF_EINTERNAL) of one size may leave the other sizes written. */
 int32_t motif_census_multi(const motif_graph_t* g, int32_t nk, const int32_t* ks, uint64_t* const* hists,
                            void* stream);
 
 /* Census of `count` graphs in one fused pass: the graphs are packed into one
- * disjoint union on the device, built once, and censused by one persistent
- * kernel that pulls anchor tiles from a device work queue; each tile's counts
- * are routed to its own graph's histogram.  hists: device, count *
+ * disjoint union on the device, built once, and censused by one set of kernels
+ * for all of them (k = 3, 4), or by one persistent kernel that pulls tiles of
+ * work from a device queue (k = 5, and k = 4 of small inputs); counts are
+ * routed to each graph's own histogram.  hists: device, count *
  * motif_num_classes(k) uint64 (graph g at offset g*C).  hists[g] equals
  * motif_census() on graph g alone, bit for bit.  `graphs` is a host array of
  * descriptors holding device pointers.  Used for null-model ensembles of

@@ -536,9 +536,10 @@ int32_t run_census_multi_enqueue(Pipeline& p, const BuildInput& in, int32_t nk, 
   int32_t top = 0;
   for (int32_t i = 1; i < nk; ++i)
     if (ks[i] > ks[top]) top = i;
-  // The largest census's big-core tables (307 MB on the n = 10^5 graph) are
-  // cleared on the second stream while the build runs: the build is a chain
-  // of latency-bound kernels that leaves the bandwidth free.  (The previous
+  // The big-core tables of a largest size that reuses cores (k = 5 of a graph
+  // that the copies leave out; some 300 MB) are cleared on the second stream
+  // while the build runs: the build is a chain of latency-bound kernels that
+  // leaves the bandwidth free.  (The previous
   // call on this pipeline has ended on both streams, so the region is idle.)
   auto device_error = [&] {
     (void)hipStreamSynchronize(s);  // best effort: the error is what the caller acts on

@@ -1657,8 +1657,10 @@ void enqueue_counts(Pipeline& p, const DevGraph& g, uint64_t* a3, uint64_t* a4, 
   enqueue_zero(Te, sizeof(uint32_t) * 9 * (size_t)(m + 1), s);
   hipLaunchKernelGGL((k_classify<true>), dim3(cgrid), dim3(256), 0, s, g, L, queue, big, (int32_t)c.far, p.status);
   // The triangles beside the wedges where both are long (n = 10^5, m = 10^6: 450
-  // and 1,030 us; the wedge table of a workgroup leaves half of a CU's waves and
-  // a quarter of its LDS) and the caller's streams allow it.
+  // and 1,030 us) and the caller's streams allow it.  Beside the hashed wedges,
+  // that is: a workgroup of k_wedge_top has a CU to itself (161,440 of 163,840
+  // bytes of LDS, 16 waves of 128 registers), and takes each as the triangles
+  // leave it.
   Chains ch(p, s);
   if (p.fork_now && m >= kCutsM && !out->later) ch.fork(0);
   const hipStream_t ts = ch.on(0);

@@ -58,7 +58,7 @@ namespace motif {
 namespace {
 
 constexpr int kSwB = kSwitchProposals;  // threads per workgroup = proposals per round
-constexpr int kSwLds = 38 * 1024;       // LDS words for one graph: n + 1 offsets, m targets, n locks
+constexpr int kSwLds = 38 * 1024;       // LDS words for one graph: n + 1 offsets, m targets of 16 bits, n locks
 constexpr int kSwPerCu = 2;             // switch workgroups per CU when their graphs fit in half the LDS
 constexpr uint32_t kFree = 0xFFFFFFFFu;
 // lock word index | kHeld: the row's winning proposal holds both its rows
@@ -326,13 +326,14 @@ __device__ __forceinline__ void round_barrier() {
 }
 
 // Randomise the graphs list[0..count) of gs, one workgroup per graph.  LDS:
-// the graph is held in LDS ((n + 1) + m + n words, + n target claims when
-// MUT), kSwLds / PER_CU words: with PER_CU = 2 two workgroups share a CU
-// (a round is a short chain of LDS reads between barriers, and a second
-// workgroup fills the gaps), for lists whose graphs all fit in half.  When
-// the words left over hold a 16-bit source row per arc slot (n <= 65,536),
-// the rows of a round's two slots are read from that table instead of a
-// binary search of the offsets (a switch moves targets, never slots).
+// the graph is held in LDS ((n + 1) + (m + 1) / 2 + n words, targets of 16 bits
+// as n < kSwLds / 2; + n target claims when MUT), kSwLds / PER_CU words: with
+// PER_CU = 2 two workgroups share a CU (a round is a short chain of LDS reads
+// between barriers, and a second workgroup fills the gaps), for lists of more
+// graphs than CUs, where they fit in half.  When the words left over hold a
+// 16-bit source row per arc slot, (m + 1) / 2 more, the rows of a round's two
+// slots are read from that table instead of a binary search of the offsets (a
+// switch moves targets, never slots).
 // Otherwise it is switched in place in global memory with this
 // workgroup's lock slice glock + blockIdx.x * lock_stride (lock_stride >= n,
 // or 2n when MUT, of every listed graph).  MUT: the slots ordered by kind go
