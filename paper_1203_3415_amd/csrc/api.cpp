@@ -171,8 +171,9 @@ int device_cus(int dev) {
 
 namespace {
 
-// Pipeline (workspace) of a stream on a device, with at least `bytes` of arena.
-int32_t get_pipeline(int dev, hipStream_t s, size_t bytes, Pipeline** out) {
+// Pipeline (workspace) of a stream on a device, with at least `least` bytes of
+// arena, and `wish` where the device has them.
+int32_t get_pipeline(int dev, hipStream_t s, size_t least, Pipeline** out, size_t wish = 0) {
   std::lock_guard<std::mutex> lk(g_mu);
   DeviceState& d = g_dev[dev];
   Pipeline*& p = d.pipes[s];
@@ -183,6 +184,7 @@ int32_t get_pipeline(int dev, hipStream_t s, size_t bytes, Pipeline** out) {
     if (hipHostMalloc(&p->host_status, kStatusWords * sizeof(int32_t), hipHostMallocDefault) != hipSuccess)
       return MOTIF_ENOMEM;
   }
+  const size_t bytes = std::max(least, wish);
   if (p->arena.cap < bytes) {
     if (p->arena.base) {  // a failure here shows up as a failed allocation below
       (void)hipStreamSynchronize(s);
@@ -195,11 +197,15 @@ int32_t get_pipeline(int dev, hipStream_t s, size_t bytes, Pipeline** out) {
     size_t want = std::max(bytes, p->arena.cap + p->arena.cap / 2);
     if (hipMalloc(&p->arena.base, want) != hipSuccess) {
       p->arena.base = nullptr;
-      if (hipMalloc(&p->arena.base, bytes) != hipSuccess) {
-        p->arena.base = nullptr;
-        return MOTIF_ENOMEM;
-      }
       want = bytes;
+      if (hipMalloc(&p->arena.base, want) != hipSuccess) {
+        p->arena.base = nullptr;
+        want = least;
+        if (least == bytes || hipMalloc(&p->arena.base, want) != hipSuccess) {
+          p->arena.base = nullptr;
+          return MOTIF_ENOMEM;
+        }
+      }
     }
     p->arena.cap = want;
   }
@@ -602,8 +608,8 @@ int32_t run_census(const BuildInput& in, int32_t k, uint64_t* hist, hipStream_t 
   if (rc) return rc;
   const TuningSet tune = tuning_for_call(dev, 1, &k, false, in.m, in.n);
   Pipeline* p = nullptr;
-  rc = get_pipeline(dev, s, std::max(pipeline_bytes(in.n, in.m, in.ngraphs, false, k, device_cus(dev), in.n, tune.k[k]),
-                                     k == 5 ? copies5_need(in) : 0), &p);
+  rc = get_pipeline(dev, s, pipeline_bytes(in.n, in.m, in.ngraphs, false, k, device_cus(dev), in.n, tune.k[k]), &p,
+                    k == 5 ? copies5_need(in) : 0);
   if (rc) return rc;
   p->tune = tune;
   ensure_wpool(p, s, w_slice_bytes(k, in.n, tune.k[k], device_cus(dev)));
@@ -1050,8 +1056,8 @@ int32_t motif_census_undirected(const int32_t* out_off, const int32_t* out_idx, 
   in.out_idx = out_idx;
   in.n = n;
   in.m = m;
-  rc = get_pipeline(dev, s, std::max(pipeline_bytes(n, m, 1, false, k, device_cus(dev), n, tune.k[k]),
-                                     k == 5 ? copies5_need(in) : 0), &p);
+  rc = get_pipeline(dev, s, pipeline_bytes(n, m, 1, false, k, device_cus(dev), n, tune.k[k]), &p,
+                    k == 5 ? copies5_need(in) : 0);
   if (rc) return rc;
   p->tune = tune;
   ensure_wpool(p, s, w_slice_bytes(k, n, tune.k[k], device_cus(dev)));
@@ -1108,13 +1114,13 @@ int32_t motif_census_multi(const motif_graph_t* g, int32_t nk, const int32_t* ks
   // one build plus the workspace of every size (the censuses may run at once)
   const TuningSet tune = tuning_for_call(dev, nk, ks, false, in.m, in.n);
   const size_t build = build_bytes(in.n, in.m, 1, false);
-  size_t bytes = build;
-  for (int32_t i = 0; i < nk; ++i)
+  size_t bytes = build, wish = 0;
+  for (int32_t i = 0; i < nk; ++i) {
     bytes += pipeline_bytes(in.n, in.m, 1, false, ks[i], device_cus(dev), in.n, tune.k[ks[i]]) - build;
-  for (int32_t i = 0; i < nk; ++i)
-    if (ks[i] == 5) bytes = std::max(bytes, copies5_need(in));
+    if (ks[i] == 5) wish = copies5_need(in);
+  }
   Pipeline* p = nullptr;
-  rc = get_pipeline(dev, s, bytes, &p);
+  rc = get_pipeline(dev, s, bytes, &p, wish);
   if (rc) return rc;
   p->tune = tune;
   int32_t top = 0;  // the largest size runs on `stream` and may use the pool
